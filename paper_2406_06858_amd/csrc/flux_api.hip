@@ -452,13 +452,7 @@ static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
   pl->k_per_split = kt_per * pl->bk;
   pl->split_tiles = split > 1 ? (int)split_tiles : (int)tiles;
   pl->full_tiles = (int)tiles - pl->split_tiles;
-  // 0: the tile divides the shape; 1: ragged (register-staged kernel); 2: only M is ragged and the
-  // configuration has the deep pipeline, which reads rows past M as zeros.  That relies on the
-  // buffer range check, so it is only used where a lane's row is entirely part of its own offset
-  // (32-row tiles: one load instruction per wave covers all rows), not added per instruction.
-  if ((p->N % pl->bn != 0) || (p->K % pl->bk != 0)) pl->edge = 1;
-  else if (p->M % pl->bm != 0) pl->edge = (g_cfgs[cfg].stages > 2 && pl->bm == 32) ? 2 : 1;   // (see below)
-  else pl->edge = 0;
+  pl->edge = p->M % pl->bm != 0 || p->N % pl->bn != 0 || p->K % pl->bk != 0;      // masked loads and stores
   pl->n_xcd = (p->flags & (FLUX_FLAG_NO_SWIZZLE | FLUX_FLAG_NO_XCD_REMAP)) ? 1 : N_XCD;
   // Reduce-scatter grids of many short tiles.  Workgroups that the hardware dispatches one per tile
   // run in lock step (a freed compute unit gets its next workgroup only when its turn comes in the

@@ -5,17 +5,18 @@
 // the peer partial tiles and writes each row into its owner's slice, paper Alg. 1).
 //
 // Mapping to the hardware:
-//   * bf16 inputs, v_mfma_f32_32x32x16_bf16, fp32 accumulators kept in registers;
+//   * bf16 inputs, v_mfma_f32_16x16x32_bf16, fp32 accumulators kept in registers;
 //   * A tile [BM][BK] and B tile [BK][BN] staged in LDS with XOR-swizzled 16-byte slots;
 //     A fragments are read with ds_read_b128, B fragments (B is [K,N] row-major, so a lane
 //     needs 8 consecutive k of one column) with the transposing ds_read_b64_tr_b16;
-//   * 128-bit global loads into registers for tile t+1 while tile t is multiplied;
+//   * direct global-to-LDS loads of the slabs ahead while this one is multiplied;
 //   * the accumulators go through LDS once in the epilogue so that every lane owns 8
 //     consecutive columns of a row: peer partials are read and outputs written 16 B (bf16)
 //     or 32 B (fp32) per lane, 128..512 B contiguous per row.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <utility>
 #include "flux.h"
 
 namespace flux {
@@ -24,7 +25,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 
@@ -271,126 +271,35 @@ struct TileCfg {
   static constexpr bool B_NK = B_NK_;
   static constexpr int NT = WAVES_M * WAVES_N * 64;
   static constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
-  static constexpr int MI = WTM / 32, NI = WTN / 32;
+  static constexpr int MI = WTM / 16, NI = WTN / 16;       // 16x16 blocks of a wave's tile
   static constexpr int A_SLOTS = BK / 8, B_SLOTS = BN / 8;
   static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BK * BN * 2;
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
-  static constexpr int A_VEC = BM * BK / 8 / NT, B_VEC = BK * BN / 8 / NT;
   static constexpr int EP_STRIDE = WTN + 8;                       // floats; 4 rows apart = 128 B off
   static constexpr int EP_BYTES = WAVES_M * WAVES_N * 32 * EP_STRIDE * 4;
-  static constexpr int ESTAGE = NSTAGE >= 2 ? 2 : 1;              // stages of the register-staged kernel
-  static constexpr int MAIN_BYTES = ESTAGE * STAGE_BYTES > EP_BYTES ? ESTAGE * STAGE_BYTES : EP_BYTES;
-  static constexpr int MISC_OFF = MAIN_BYTES;              // 16 B: one int shared by the workgroup
-  static constexpr int PTRS_OFF = MAIN_BYTES + 16;         // FLUX_MAX_RANKS output slice pointers
-  static constexpr int LDS_BYTES = PTRS_OFF + 8 * FLUX_MAX_RANKS;
-  static_assert(BM % (WAVES_M * 32) == 0 && BN % (WAVES_N * 32) == 0 && BK % 16 == 0, "tile shape");
-  static_assert((BM * BK / 8) % NT == 0 && (BK * BN / 8) % NT == 0, "loader shape");
+  static_assert(BM % (WAVES_M * 32) == 0 && BN % (WAVES_N * 32) == 0 && BK % 32 == 0, "tile shape");
   static_assert(B_SLOTS >= 8, "BN >= 64");
 };
 
-template <class C, bool EDGE>
-struct Loader {
-  // per-thread global pointers of the 16-byte vectors this thread stages, k offset 0
-  const __bf16* pa[C::A_VEC];
-  const __bf16* pb[C::B_VEC];
-  int lds_a[C::A_VEC], lds_b[C::B_VEC];
-  int ka[C::A_VEC];            // column (k) offset of each A vector inside the tile
-  int kb[C::B_VEC];            // row (k) offset of each B vector inside the tile
-  bool nb_ok[C::B_VEC];
-
-  __device__ __forceinline__ void init(const GemmArgs& a, int m0, int n0, int tid) {
+// MFMA shape: 16x16x32, the A fragment held over a row of MFMAs.  With random operands the chip runs at its power
+// limit, and this form takes less power than 32x32x16: MFMAs alone 2.0 against 1.75-1.8 PFLOP/s (2.4 for both on
+// zeros).  Holding B instead and changing A every time costs 25 % of the rate even on zeros.
+//
+// The instruction is written out with its accumulator tied to an accumulation register: left to itself the compiler
+// gives D and C different registers and shuffles hundreds of them around per slab.  It then does not know that
+// the result takes a while: whoever reads the accumulators waits for them (mfma_results_settle).
+__device__ __forceinline__ void mfma_in_place(f32x4& acc, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+// The results of all MFMAs issued so far can be read (18 wait states are the most any of them takes).  The
+// accumulators pass through, so that nothing that reads them can be moved in front.
+template <int MI, int NI>
+__device__ __forceinline__ void mfma_results_settle(f32x4 (&acc)[MI][NI]) {
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
 #pragma unroll
-    for (int p = 0; p < C::A_VEC; ++p) {
-      const int v = tid + C::NT * p;
-      const int row = v / C::A_SLOTS, slot = v % C::A_SLOTS;
-      int gr = m0 + row;
-      if (EDGE) gr = gr < a.M ? gr : a.M - 1;
-      pa[p] = a.A + (size_t)gr * a.lda + slot * 8;
-      ka[p] = slot * 8;
-      lds_a[p] = row * (C::BK * 2) + ((slot ^ swz_a<C::A_SLOTS>(row)) << 4);
-    }
+  for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-    for (int p = 0; p < C::B_VEC; ++p) {
-      const int v = tid + C::NT * p;
-      if constexpr (C::B_NK) {
-        const int n = v / C::A_SLOTS, slot = v % C::A_SLOTS;
-        int gn = n0 + n;
-        nb_ok[p] = !EDGE || gn < a.N;
-        if (EDGE && gn >= a.N) gn = 0;
-        pb[p] = a.B + (size_t)gn * a.ldb + slot * 8;
-        kb[p] = slot * 8;
-        lds_b[p] = C::A_BYTES + n * (C::BK * 2) + ((slot ^ swz_a<C::A_SLOTS>(n)) << 4);
-      } else {
-        const int k = v / C::B_SLOTS, s = v % C::B_SLOTS;
-        int gn = n0 + s * 8;
-        nb_ok[p] = !EDGE || gn < a.N;
-        if (EDGE && gn >= a.N) gn = 0;
-        pb[p] = a.B + (size_t)k * a.ldb + gn;
-        kb[p] = k;
-        lds_b[p] = C::A_BYTES + k * (C::BN * 2) + ((s ^ swz_b<C::B_SLOTS>(k)) << 4);
-      }
-    }
-  }
-
-  __device__ __forceinline__ void load(const GemmArgs& a, int k0, int k_end, uint4 (&ra)[C::A_VEC], uint4 (&rb)[C::B_VEC]) const {
-#pragma unroll
-    for (int p = 0; p < C::A_VEC; ++p) {
-      if (!EDGE || k0 + ka[p] < k_end) ra[p] = *reinterpret_cast<const uint4*>(pa[p] + k0);
-      else ra[p] = make_uint4(0, 0, 0, 0);
-    }
-#pragma unroll
-    for (int p = 0; p < C::B_VEC; ++p) {
-      if (!EDGE || (nb_ok[p] && k0 + kb[p] < k_end))
-        rb[p] = *reinterpret_cast<const uint4*>(pb[p] + (C::B_NK ? (size_t)k0 : (size_t)k0 * a.ldb));
-      else rb[p] = make_uint4(0, 0, 0, 0);
-    }
-  }
-
-  __device__ __forceinline__ void store(unsigned char* stage, const uint4 (&ra)[C::A_VEC], const uint4 (&rb)[C::B_VEC]) const {
-#pragma unroll
-    for (int p = 0; p < C::A_VEC; ++p) *reinterpret_cast<uint4*>(stage + lds_a[p]) = ra[p];
-#pragma unroll
-    for (int p = 0; p < C::B_VEC; ++p) *reinterpret_cast<uint4*>(stage + lds_b[p]) = rb[p];
-  }
-};
-
-// One BK-deep slab of MFMAs out of the LDS stage.
-template <class C>
-__device__ __forceinline__ void mma_stage(const unsigned char* stage, int wm, int wn, int lane,
-                                          f32x16 (&acc)[C::MI][C::NI]) {
-  const int g = lane >> 4, i = lane & 15;
-#pragma unroll
-  for (int ks = 0; ks < C::BK / 16; ++ks) {
-    bf16x8 af[C::MI], bfr[C::NI];
-#pragma unroll
-    for (int mi = 0; mi < C::MI; ++mi) {
-      const int row = wm * C::WTM + mi * 32 + (lane & 31);
-      const int q = ks * 2 + (lane >> 5);
-      af[mi] = *reinterpret_cast<const bf16x8*>(stage + row * (C::BK * 2) + ((q ^ swz_a<C::A_SLOTS>(row)) << 4));
-    }
-#pragma unroll
-    for (int ni = 0; ni < C::NI; ++ni) {
-      if constexpr (C::B_NK) {
-        const int row = wn * C::WTN + ni * 32 + (lane & 31);
-        const int q = ks * 2 + (lane >> 5);
-        bfr[ni] = *reinterpret_cast<const bf16x8*>(stage + C::A_BYTES + row * (C::BK * 2) + ((q ^ swz_a<C::A_SLOTS>(row)) << 4));
-      } else {
-        const int k = ks * 16 + 8 * (g >> 1) + (i >> 2);
-        const int n = wn * C::WTN + ni * 32 + 16 * (g & 1) + 4 * (i & 3);
-        const int off = C::A_BYTES + k * (C::BN * 2) + ((((n >> 3) ^ swz_b<C::B_SLOTS>(k))) << 4) + ((n >> 2) & 1) * 8;
-        typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-        s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(stage + off));
-        s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(stage + off + 4 * C::BN * 2));
-        s16x8 w = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        bfr[ni] = __builtin_bit_cast(bf16x8, w);
-      }
-    }
-#pragma unroll
-    for (int mi = 0; mi < C::MI; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < C::NI; ++ni)
-        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[mi], bfr[ni], acc[mi][ni], 0, 0, 0);
-  }
+    for (int ni = 0; ni < NI; ++ni) asm volatile("" : "+a"(acc[mi][ni]));
 }
 
 // Store 8 consecutive output columns of one row into the owner's slice (GetOutput of Alg. 1) or
@@ -499,23 +408,30 @@ __device__ __forceinline__ void epilogue_block(const GemmArgs& a, void* const* l
   }
 }
 
+// 32 rows of a wave's accumulators into its staging area (row-major): a lane of a 16x16 block holds four
+// consecutive rows of one column.
+template <class C>
+__device__ __forceinline__ void stage_rows32(float* ep, const f32x4 (&acc)[C::MI][C::NI], int mb, int lane) {
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int ni = 0; ni < C::NI; ++ni)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        ep[(16 * s + 4 * (lane >> 4) + e) * C::EP_STRIDE + ni * 16 + (lane & 15)] = acc[2 * mb + s][ni][e];
+  __builtin_amdgcn_wave_barrier();
+}
+
 // The whole epilogue of one wave: its accumulators pass through LDS 32 rows at a time.
 template <class C, int EPI, bool EDGE, bool PF32, int BATCH, int NP>
-__device__ __forceinline__ void epilogue_all(const GemmArgs& a, void* const* lds_outs, float* ep, f32x16 (&acc)[C::MI][C::NI],
+__device__ __forceinline__ void epilogue_all(const GemmArgs& a, void* const* lds_outs, float* ep, f32x4 (&acc)[C::MI][C::NI],
                                              int m0, int n0, int lane, int wm, int wn) {
   PeerBufs pb;
   if (EPI == EPI_RS) make_peer_bufs(a, m0, n0, pb);
 #pragma unroll
-  for (int mi = 0; mi < C::MI; ++mi) {
-#pragma unroll
-    for (int ni = 0; ni < C::NI; ++ni)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int r = 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-        ep[r * C::EP_STRIDE + ni * 32 + (lane & 31)] = acc[mi][ni][e];
-      }
-    __builtin_amdgcn_wave_barrier();
-    epilogue_block<C, EPI, EDGE, PF32, BATCH, NP>(a, lds_outs, ep, pb, wm * C::WTM + mi * 32, wn * C::WTN, m0, n0, lane);
+  for (int mb = 0; mb < C::WTM / 32; ++mb) {
+    stage_rows32<C>(ep, acc, mb, lane);
+    epilogue_block<C, EPI, EDGE, PF32, BATCH, NP>(a, lds_outs, ep, pb, wm * C::WTM + mb * 32, wn * C::WTN, m0, n0, lane);
     __builtin_amdgcn_wave_barrier();
   }
 }
@@ -1096,24 +1012,17 @@ __device__ __forceinline__ bool wait_signals(const GemmArgs& a, int m0, int m1, 
 // row, so that an instruction touches two whole cache lines and not sixteen partial ones (with the
 // eight-columns-per-lane layout of the other epilogues this form took five times as long).
 template <class C, bool EDGE>
-__device__ __forceinline__ void epilogue_all_atomic(const GemmArgs& a, void* const* lds_outs, float* ep, f32x16 (&acc)[C::MI][C::NI],
+__device__ __forceinline__ void epilogue_all_atomic(const GemmArgs& a, void* const* lds_outs, float* ep, f32x4 (&acc)[C::MI][C::NI],
                                                     int m0, int n0, int lane, int wm, int wn) {
   constexpr int W = C::WTN < 64 ? C::WTN : 64;   // columns per instruction
   constexpr int RPI = 64 / W;                    // rows per instruction
   const int c_in = lane % W, r_in = lane / W;
 #pragma unroll
-  for (int mi = 0; mi < C::MI; ++mi) {
-#pragma unroll
-    for (int ni = 0; ni < C::NI; ++ni)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int r = 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-        ep[r * C::EP_STRIDE + ni * 32 + (lane & 31)] = acc[mi][ni][e];
-      }
-    __builtin_amdgcn_wave_barrier();
+  for (int mb = 0; mb < C::WTM / 32; ++mb) {
+    stage_rows32<C>(ep, acc, mb, lane);
     for (int r0 = 0; r0 < 32; r0 += RPI) {
       const int r = r0 + r_in;
-      const int gm = m0 + wm * C::WTM + mi * 32 + r;
+      const int gm = m0 + wm * C::WTM + mb * 32 + r;
       const int owner = gm / a.S;
       float* row = static_cast<float*>(lds_outs[owner]) + (size_t)(gm - owner * a.S) * a.ldc + n0 + wn * C::WTN;
 #pragma unroll
@@ -1132,7 +1041,7 @@ __device__ __forceinline__ void epilogue_all_atomic(const GemmArgs& a, void* con
 // with 8 consecutive columns of one row.  `smem` must hold C::EP_BYTES and is free to reuse.
 template <class C, int EPI, bool EDGE>
 __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem, int* lds_misc, void* const* lds_outs,
-                                          f32x16 (&acc)[C::MI][C::NI], int tile, int split, bool is_split,
+                                          f32x4 (&acc)[C::MI][C::NI], int tile, int split, bool is_split,
                                           int m0, int n0, int tid, int lane, int wave, int wm, int wn, int vb = -1) {
   trace_stamp(a, TRACE_MAIN_END, vb);
   // ---- split-K: all but the last-arriving workgroup of a tile park their partial sums ----
@@ -1146,23 +1055,21 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
     float* mine = a.sk_partials + ((size_t)split * a.split_tiles + st) * (C::BM * C::BN);
     __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(mine, 0, BLOCK_BYTES, 0x00027000);
     // layout inside a tile's partial block: [vector index][thread] -> coalesced 16-byte columns.
-    // A vector holds four of eight consecutive rows; with a ragged M (a decode tile of 8 rows in a
+    // A vector holds four consecutive rows; with a ragged M (a decode tile of 8 rows in a
     // 32-row tile) the vectors that lie wholly past the last row are neither parked nor read back:
     // their offset is moved past the end of the block, where the range check of the buffer drops a
     // store and answers a load with zeros (a branch around them would make every load wait for
     // the one before).
-    const int rows_valid = EDGE ? a.M - m0 - wm * C::WTM : C::BM;
+    const int rows_valid = EDGE ? a.M - m0 - wm * C::WTM - 4 * (lane >> 4) : C::BM;
 #pragma unroll
     for (int mi = 0; mi < C::MI; ++mi)
 #pragma unroll
-      for (int ni = 0; ni < C::NI; ++ni)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const u32x4 v = {__float_as_uint(acc[mi][ni][4 * q]), __float_as_uint(acc[mi][ni][4 * q + 1]),
-                           __float_as_uint(acc[mi][ni][4 * q + 2]), __float_as_uint(acc[mi][ni][4 * q + 3])};
-          const bool past = EDGE && mi * 32 + 8 * q >= rows_valid;
-          __builtin_amdgcn_raw_buffer_store_b128(v, rm, past ? BLOCK_BYTES : (((mi * C::NI + ni) * 4 + q) * C::NT + tid) * 16, 0, SC1);
-        }
+      for (int ni = 0; ni < C::NI; ++ni) {
+        const u32x4 v = {__float_as_uint(acc[mi][ni][0]), __float_as_uint(acc[mi][ni][1]),
+                         __float_as_uint(acc[mi][ni][2]), __float_as_uint(acc[mi][ni][3])};
+        const bool past = EDGE && mi * 16 >= rows_valid;
+        __builtin_amdgcn_raw_buffer_store_b128(v, rm, past ? BLOCK_BYTES : ((mi * C::NI + ni) * C::NT + tid) * 16, 0, SC1);
+      }
     __builtin_amdgcn_s_waitcnt(0x0F70);                   // vmcnt(0): stores acknowledged
     __syncthreads();
     int* lds_last = lds_misc;
@@ -1183,13 +1090,13 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
 #pragma unroll
       for (int ni = 0; ni < C::NI; ++ni)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[mi][ni][e] = 0.f;
+        for (int e = 0; e < 4; ++e) acc[mi][ni][e] = 0.f;
     // Sixteen or thirty-two loads are issued before the first is used.  Left to itself the compiler waits for
     // every vector before it requests the next (a memory round trip each: 17 us for the 256 KB of
     // two parts of a 256x128 tile); a branch around a load has the same effect, so parts past the
     // end are read as zeros through the buffer's range check instead.  A large tile takes its
     // vectors a batch at a time, part by part; a small one takes all vectors of several parts.
-    constexpr int NVEC = C::MI * C::NI * 4;                 // 16-byte vectors per thread and part
+    constexpr int NVEC = C::MI * C::NI;                     // 16-byte vectors per thread and part
     constexpr int IN_FLIGHT = NVEC >= 32 ? 32 : 16;         // (32 is ahead for the large tiles, 16 for the small)
     constexpr int VB = NVEC < IN_FLIGHT ? NVEC : IN_FLIGHT; // vectors per batch within a part
     constexpr int PB = IN_FLIGHT / VB;                      // parts per batch
@@ -1206,8 +1113,8 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
           __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(other, 0, BLOCK_BYTES, 0x00027000);
 #pragma unroll
           for (int i = 0; i < VB; ++i) {
-            const int idx = b0 + i, mi = idx / (C::NI * 4), q = idx % 4;
-            const bool past = none || (EDGE && mi * 32 + 8 * q >= rows_valid);
+            const int idx = b0 + i, mi = idx / C::NI;
+            const bool past = none || (EDGE && mi * 16 >= rows_valid);
             v[g][i] = __builtin_amdgcn_raw_buffer_load_b128(ro, past ? BLOCK_BYTES : (idx * C::NT + tid) * 16, 0, SC1);
           }
         }
@@ -1216,11 +1123,9 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
         for (int g = 0; g < PB; ++g)
 #pragma unroll
           for (int i = 0; i < VB; ++i) {
-            const int idx = b0 + i, mi = idx / (C::NI * 4), ni = (idx / 4) % C::NI, q = idx % 4;
-            acc[mi][ni][4 * q] += __uint_as_float(v[g][i][0]);
-            acc[mi][ni][4 * q + 1] += __uint_as_float(v[g][i][1]);
-            acc[mi][ni][4 * q + 2] += __uint_as_float(v[g][i][2]);
-            acc[mi][ni][4 * q + 3] += __uint_as_float(v[g][i][3]);
+            const int idx = b0 + i, mi = idx / C::NI, ni = idx % C::NI;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[mi][ni][e] += __uint_as_float(v[g][i][e]);
           }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -1257,71 +1162,8 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
   trace_stamp(a, TRACE_END, vb);
 }
 
-template <class C, int EPI, bool WAIT, bool EDGE>
-__global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel(const GemmArgs a) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
-
-  int tile, split;
-  bool is_split;
-  map_block(a, (int)blockIdx.x, tile, split, is_split);
-  int mt, nt;
-  tile_coord(a.tm, tile, mt, nt);
-  const int m0 = mt * C::BM, n0 = nt * C::BN;
-  const int m1 = m0 + C::BM < a.M ? m0 + C::BM : a.M;
-  trace_begin(a, tile, mt, nt, split, is_split);
-
-  // output slices by rank (reduce-scatter) or chunk sources by rank (all-gather)
-  void** lds_outs = reinterpret_cast<void**>(smem + C::PTRS_OFF);
-  if (EPI == EPI_RS || WAIT) {
-    fill_lds_outs(a, lds_outs, tid);
-  }
-
-  if (WAIT) {
-    transfer_own_pieces(a, reinterpret_cast<int*>(smem + C::MISC_OFF), lds_outs);
-    if (!wait_signals(a, m0, m1, reinterpret_cast<int*>(smem + C::MISC_OFF), lds_outs)) { trace_stamp(a, TRACE_END); return; }
-    trace_stamp(a, TRACE_READY);
-  }
-
-  const int k_begin = is_split ? split * a.k_per_split : 0;
-  const int k_end = (is_split && k_begin + a.k_per_split < a.K) ? k_begin + a.k_per_split : a.K;
-  const int KT = (k_end - k_begin + C::BK - 1) / C::BK;
-
-  f32x16 acc[C::MI][C::NI];
-#pragma unroll
-  for (int mi = 0; mi < C::MI; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < C::NI; ++ni)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[mi][ni][e] = 0.f;
-
-  Loader<C, EDGE> ld;
-  ld.init(a, m0, n0, tid);
-  uint4 ra[C::A_VEC], rb[C::B_VEC];
-
-  if (KT > 0) {
-    ld.load(a, k_begin, k_end, ra, rb);
-    ld.store(smem, ra, rb);
-    __syncthreads();
-    for (int kt = 0; kt < KT; ++kt) {
-      unsigned char* cur = smem + (C::ESTAGE == 2 ? (kt & 1) * C::STAGE_BYTES : 0);
-      const bool more = kt + 1 < KT;
-      if (more) ld.load(a, k_begin + (kt + 1) * C::BK, k_end, ra, rb);
-      mma_stage<C>(cur, wm, wn, lane, acc);
-      if (C::ESTAGE == 1) __syncthreads();
-      if (more) ld.store(smem + (C::ESTAGE == 2 ? ((kt + 1) & 1) * C::STAGE_BYTES : 0), ra, rb);
-      __syncthreads();
-    }
-  }
-
-  gemm_tail<C, EPI, EDGE>(a, smem, reinterpret_cast<int*>(smem + C::MISC_OFF), lds_outs, acc, tile, split, is_split,
-                          m0, n0, tid, lane, wave, wm, wn);
-}
-
-
 // ---------------------------------------------------------------------------------------------
-// Fast path for shapes that the tile divides: global -> LDS without passing through registers.
+// Operand loads: global -> LDS without passing through registers.
 //
 // buffer_load_dwordx4 ... lds writes the 64 x 16 B a wave fetches to 1 KiB of consecutive LDS,
 // so the swizzled layouts above are produced by permuting which 16 B each lane FETCHES:
@@ -1330,12 +1172,18 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel(const GemmArgs a) {
 //   B: one instruction = 1 KiB / (2*BN) k-rows; lane i fills physical slot i%B_SLOTS and
 //      fetches logical slot (i%B_SLOTS) ^ swz_b(k).
 // Per K-slab only scalar offsets change (soffset), so the address arithmetic costs no vector
-// instructions.  The two LDS stages are separate arrays: the compiler's wait-count insertion can
-// then tell the stage being filled from the stage being read and does not serialise them.
+// instructions.
+//
+// EDGE (the tile does not divide the shape): a lane whose 16 bytes lie past the last row, past the last column of a
+// [K,N] matrix, or past the end of K asks for an offset outside the records, which loads zeros and touches no memory:
+// a compare and a select per load, between the MFMAs.  (The scalar offset takes no part in the hardware's range
+// check, so the check alone would not do.)  Rows and columns past the end would only reach results that are not
+// stored; K has to be padded with zeros on both sides.  Against a kernel that staged masked loads through
+// registers: 3000 x 3584 x 8192 268 -> 186 us, 1496 x 5112 x 3400 with 8 ranks 119 -> 88 us, 200 x 3584 x 8192 58 -> 50 us.
 // ---------------------------------------------------------------------------------------------
 typedef __attribute__((address_space(3))) void lds_void_t;
 
-template <class C>
+template <class C, bool EDGE>
 struct DmaLoader {
   static constexpr int NW = C::NT / 64;
   static constexpr int A_RPI = 8;                              // A rows per instruction (1 KiB of 128-byte rows)
@@ -1351,14 +1199,32 @@ struct DmaLoader {
   __amdgpu_buffer_rsrc_t ra, rb;
   uint32_t voff_a, voff_b;
   uint32_t K2, N2;               // row pitches in bytes
+  uint32_t bytes_a, bytes_b;     // extents
+  // EDGE: how many of this lane's loads of A (and of an [N,K] B) have a row, the k of its vector in a slab, and the k of
+  // its first vector of a [K,N] B (out of reach for a lane past the last column)
+  int lim_a, lim_b, k_vec, k_row;
+  static constexpr uint32_t OUTSIDE = 0xfffffff0u;      // a matrix has fewer than 2^31 elements
+
+  // The same loader, or one whose loads all lie outside its records: they touch no memory (a slab past the end).
+  __device__ __forceinline__ DmaLoader only_if(bool valid, const GemmArgs& a) const {
+    DmaLoader d = *this;
+    d.ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.A), 0, (int)(valid ? bytes_a : 0u), 0x00027000);
+    d.rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.B), 0, (int)(valid ? bytes_b : 0u), 0x00027000);
+    return d;
+  }
 
   __device__ __forceinline__ void init(const GemmArgs& a, int m0, int n0, int wave, int lane) {
-    ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.A), 0, (int)(((unsigned)(a.M - 1) * (unsigned)a.lda + (unsigned)a.K) * 2u), 0x00027000);
-    rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.B), 0,
-                                           (int)((C::B_NK ? (unsigned)(a.N - 1) * (unsigned)a.ldb + (unsigned)a.K
-                                                          : (unsigned)(a.K - 1) * (unsigned)a.ldb + (unsigned)a.N) * 2u), 0x00027000);
+    bytes_a = ((unsigned)(a.M - 1) * (unsigned)a.lda + (unsigned)a.K) * 2u;
+    bytes_b = (C::B_NK ? (unsigned)(a.N - 1) * (unsigned)a.ldb + (unsigned)a.K : (unsigned)(a.K - 1) * (unsigned)a.ldb + (unsigned)a.N) * 2u;
+    ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.A), 0, (int)bytes_a, 0x00027000);
+    rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.B), 0, (int)bytes_b, 0x00027000);
     const int r_in = lane / C::A_SLOTS, sp = lane % C::A_SLOTS;
     const int row = A_RPI * wave + r_in;
+    if (EDGE) {
+      k_vec = (sp ^ swz_a<C::A_SLOTS>(row)) * 8;
+      lim_a = (a.M - m0 - row + A_RPI * NW - 1) / (A_RPI * NW);           // (not positive: none)
+      if (C::B_NK) lim_b = (a.N - n0 - row + A_RPI * NW - 1) / (A_RPI * NW);
+    }
     K2 = (uint32_t)a.lda * 2u;
     N2 = (uint32_t)a.ldb * 2u;
     voff_a = (uint32_t)(m0 + row) * K2 + ((uint32_t)(sp ^ swz_a<C::A_SLOTS>(row)) << 4);
@@ -1368,37 +1234,36 @@ struct DmaLoader {
       const int k_in = lane / C::B_SLOTS, spb = lane % C::B_SLOTS;
       const int k = RPI * wave + k_in;
       voff_b = (uint32_t)k * N2 + (uint32_t)n0 * 2u + ((uint32_t)(spb ^ swz_b<C::B_SLOTS>(k)) << 4);
+      if (EDGE) k_row = n0 + (spb ^ swz_b<C::B_SLOTS>(k)) * 8 < a.N ? k : 0x40000000;
     }
   }
   static constexpr int N_INSTR = A_INSTR + B_INSTR;
 
-  // same with an index that is constant after loop unrolling
+  // load idx (constant after unrolling; A's first) of the slab that starts at k0, into LDS stage `stage`
   __device__ __forceinline__ void issue_dyn(int idx, const GemmArgs& a, unsigned char* stage, int k0, int wave) const {
     if (idx < A_INSTR) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void_t*)(stage + (idx * NW + wave) * 1024), 16, (int)voff_a,
+      const uint32_t v = !EDGE || idx < (k_vec < a.K - k0 ? lim_a : 0) ? voff_a : OUTSIDE;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void_t*)(stage + (idx * NW + wave) * 1024), 16, (int)v,
                                                (int)((uint32_t)k0 * 2u + (uint32_t)(idx * A_RPI * NW) * K2), 0, 0);
     } else {
       const int p = idx - A_INSTR;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void_t*)(stage + C::A_BYTES + (p * NW + wave) * 1024), 16, (int)voff_b,
+      const bool in = !EDGE || (C::B_NK ? p < (k_vec < a.K - k0 ? lim_b : 0) : k_row < a.K - k0 - p * RPI * NW);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void_t*)(stage + C::A_BYTES + (p * NW + wave) * 1024), 16, (int)(in ? voff_b : OUTSIDE),
                                                (int)(C::B_NK ? (uint32_t)k0 * 2u + (uint32_t)(p * RPI * NW) * N2 : (uint32_t)(k0 + p * RPI * NW) * N2), 0, 0);
     }
   }
 
-  // this wave's loads of the A part / the B part of one K-slab; `stage` is the base of the LDS stage being filled
+  // this wave's loads of the A part / the B part of one K-slab
   __device__ __forceinline__ void issue_a(const GemmArgs& a, unsigned char* stage, int k0, int wave) const {
 #pragma unroll
-    for (int p = 0; p < A_INSTR; ++p)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void_t*)(stage + (p * NW + wave) * 1024), 16, (int)voff_a,
-                                               (int)((uint32_t)k0 * 2u + (uint32_t)(p * A_RPI * NW) * K2), 0, 0);
+    for (int d = 0; d < A_INSTR; ++d) issue_dyn(d, a, stage, k0, wave);
+    // keep the loads where they are written: scheduled late they would be issued just before
+    // the wait for them, and nothing would overlap
     __builtin_amdgcn_sched_barrier(0);
   }
   __device__ __forceinline__ void issue_b(const GemmArgs& a, unsigned char* stage, int k0, int wave) const {
 #pragma unroll
-    for (int p = 0; p < B_INSTR; ++p)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void_t*)(stage + C::A_BYTES + (p * NW + wave) * 1024), 16, (int)voff_b,
-                                               (int)(C::B_NK ? (uint32_t)k0 * 2u + (uint32_t)(p * RPI * NW) * N2 : (uint32_t)(k0 + p * RPI * NW) * N2), 0, 0);
-    // keep the loads where they are written: scheduled late they would be issued just before
-    // the wait for them, and nothing would overlap
+    for (int d = A_INSTR; d < N_INSTR; ++d) issue_dyn(d, a, stage, k0, wave);
     __builtin_amdgcn_sched_barrier(0);
   }
   // all loads of one K-slab for this wave
@@ -1408,71 +1273,9 @@ struct DmaLoader {
   }
 };
 
-template <class C>
-__device__ __forceinline__ bf16x8 frag_a(const unsigned char* stage, int ks, int mi, int wm, int lane) {
-  const int row = wm * C::WTM + mi * 32 + (lane & 31);
-  const int q = ks * 2 + (lane >> 5);
-  return *reinterpret_cast<const bf16x8*>(stage + row * (C::BK * 2) + ((q ^ swz_a<C::A_SLOTS>(row)) << 4));
-}
-
-template <class C>
-__device__ __forceinline__ bf16x8 frag_b(const unsigned char* stage, int ks, int ni, int wn, int lane) {
-  if constexpr (C::B_NK) {
-    const int row = wn * C::WTN + ni * 32 + (lane & 31);
-    const int q = ks * 2 + (lane >> 5);
-    return *reinterpret_cast<const bf16x8*>(stage + C::A_BYTES + row * (C::BK * 2) + ((q ^ swz_a<C::A_SLOTS>(row)) << 4));
-  }
-  const int g = lane >> 4, i = lane & 15;
-  const int k = ks * 16 + 8 * (g >> 1) + (i >> 2);
-  const int n = wn * C::WTN + ni * 32 + 16 * (g & 1) + 4 * (i & 3);
-  const int off = C::A_BYTES + k * (C::BN * 2) + ((((n >> 3) ^ swz_b<C::B_SLOTS>(k))) << 4) + ((n >> 2) & 1) * 8;
-  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-  s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(stage + off));
-  s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(stage + off + 4 * C::BN * 2));
-  s16x8 w = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-  return __builtin_bit_cast(bf16x8, w);
-}
-
-// The same two fragment reads as instructions the compiler cannot look into.  For every LDS read
-// it can see, the compiler works out by itself how many of the direct-to-LDS loads still in flight
-// must land first; around a ring of more than two stages it gets that wrong on the safe side and
-// drains the pipeline.  With these reads the waits are the kernel's own: the counter wait before
-// the workgroup barrier for the loads, wait_lds_reads() for the fragments.
 typedef __attribute__((address_space(3))) unsigned char lds_byte_t;
 __device__ __forceinline__ uint32_t lds_address(const unsigned char* p) {
   return (uint32_t)reinterpret_cast<uintptr_t>((const lds_byte_t*)p);
-}
-
-template <class C>
-__device__ __forceinline__ bf16x8 frag_a_opaque(uint32_t stage, int ks, int mi, int wm, int lane) {
-  const int row = wm * C::WTM + mi * 32 + (lane & 31);
-  const int q = ks * 2 + (lane >> 5);
-  const uint32_t addr = stage + row * (C::BK * 2) + ((q ^ swz_a<C::A_SLOTS>(row)) << 4);
-  u32x4 v;
-  asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr) : "memory");
-  return __builtin_bit_cast(bf16x8, v);
-}
-
-template <class C>
-__device__ __forceinline__ bf16x8 frag_b_opaque(uint32_t stage, int ks, int ni, int wn, int lane) {
-  if constexpr (C::B_NK) {
-    const int row = wn * C::WTN + ni * 32 + (lane & 31);
-    const int q = ks * 2 + (lane >> 5);
-    const uint32_t addr = stage + C::A_BYTES + row * (C::BK * 2) + ((q ^ swz_a<C::A_SLOTS>(row)) << 4);
-    u32x4 v;
-    asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr) : "memory");
-    return __builtin_bit_cast(bf16x8, v);
-  }
-  const int g = lane >> 4, i = lane & 15;
-  const int k = ks * 16 + 8 * (g >> 1) + (i >> 2);
-  const int n = wn * C::WTN + ni * 32 + 16 * (g & 1) + 4 * (i & 3);
-  const uint32_t addr = stage + C::A_BYTES + k * (C::BN * 2) + ((((n >> 3) ^ swz_b<C::B_SLOTS>(k))) << 4) + ((n >> 2) & 1) * 8;
-  typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
-  u32x2 lo, hi;
-  asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(lo) : "v"(addr) : "memory");
-  asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(hi) : "v"(addr + 4 * C::BN * 2) : "memory");
-  const u32x4 w = {lo[0], lo[1], hi[0], hi[1]};
-  return __builtin_bit_cast(bf16x8, w);
 }
 
 // All LDS reads issued so far have returned.  The fragments pass through it so that nothing that
@@ -1484,122 +1287,6 @@ __device__ __forceinline__ void wait_lds_reads(bf16x8 (&af)[MI], bf16x8 (&bfr)[N
   for (int i = 0; i < MI; ++i) asm volatile("" : "+v"(af[i]));
 #pragma unroll
   for (int i = 0; i < NI; ++i) asm volatile("" : "+v"(bfr[i]));
-}
-
-// One K-slab out of LDS stage `cur`, software-pipelined by hand:
-//   * the MFMAs run in (ks, mi) groups of NI; the fragments of k-step ks+1 are fetched while the
-//     MFMAs of ks run (two register sets);
-//   * the wave's DMA loads for the NEXT slab (into `nxt`) are dealt out one group at a time.  A
-//     wave issues in order, and a burst of loads would hold it in the memory pipeline's queue
-//     for about as long as the slab's MFMAs take; spread out, the loads drain behind the MFMAs.
-// Loads are only placed in the first SPREAD_NUM/SPREAD_DEN of the groups so the last one has
-// time to land before the end-of-slab wait.
-template <class C, bool ISSUE>
-__device__ __forceinline__ void mma_stage_dma(const unsigned char* cur, unsigned char* nxt, const DmaLoader<C>& ld,
-                                              const GemmArgs& a, int k_next, int wave, int wm, int wn, int lane,
-                                              f32x16 (&acc)[C::MI][C::NI]) {
-  constexpr int KS = C::BK / 16;
-  constexpr int G = KS * C::MI;                       // MFMA groups in the slab
-  constexpr int L = DmaLoader<C>::N_INSTR;            // loads to place
-  constexpr int GS = (G * 3 + 3) / 4;                 // groups that carry loads
-  // (the slab's offset goes into the loads' scalar operand: should the compiler ever take the loop
-  // counter for a value that may differ between lanes, it would wrap every load into a loop over lanes)
-  k_next = __builtin_amdgcn_readfirstlane(k_next);
-  bf16x8 af[2][C::MI], bfr[2][C::NI];
-#pragma unroll
-  for (int mi = 0; mi < C::MI; ++mi) af[0][mi] = frag_a<C>(cur, 0, mi, wm, lane);
-#pragma unroll
-  for (int ni = 0; ni < C::NI; ++ni) bfr[0][ni] = frag_b<C>(cur, 0, ni, wn, lane);
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-#pragma unroll
-    for (int mi = 0; mi < C::MI; ++mi) {
-      const int g = ks * C::MI + mi;
-      // loads [g*L/GS, (g+1)*L/GS) go with group g (compile-time after unrolling)
-      if (ISSUE && g < GS) {
-        const int lo = g * L / GS, hi = (g + 1) * L / GS;
-#pragma unroll
-        for (int idx = 0; idx < L; ++idx)
-          if (idx >= lo && idx < hi) ld.issue_dyn(idx, a, nxt, k_next, wave);
-      }
-      if (mi == 0 && ks + 1 < KS) {
-#pragma unroll
-        for (int m2 = 0; m2 < C::MI; ++m2) af[(ks + 1) & 1][m2] = frag_a<C>(cur, ks + 1, m2, wm, lane);
-#pragma unroll
-        for (int ni = 0; ni < C::NI; ++ni) bfr[(ks + 1) & 1][ni] = frag_b<C>(cur, ks + 1, ni, wn, lane);
-      }
-#pragma unroll
-      for (int ni = 0; ni < C::NI; ++ni)
-        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks & 1][mi], bfr[ks & 1][ni], acc[mi][ni], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-}
-
-// mma_stage_dma with the opaque fragment reads: the fragments of k-step ks are waited for at the
-// top of the step, then those of ks+1 are requested, then the MFMAs of ks run.
-template <class C>
-__device__ __forceinline__ void mma_stage_dma_opaque(const unsigned char* cur_p, unsigned char* nxt, const DmaLoader<C>& ld,
-                                                     const GemmArgs& a, int k_next, int wave, int wm, int wn, int lane,
-                                                     f32x16 (&acc)[C::MI][C::NI]) {
-  constexpr int KS = C::BK / 16;
-  constexpr int G = KS * C::MI;
-  constexpr int L = DmaLoader<C>::N_INSTR;
-  constexpr int GS = (G * 3 + 3) / 4;
-  const uint32_t cur = lds_address(cur_p);
-  if constexpr (C::MI * C::NI <= 2) {
-    // One or two MFMAs per k-step (the 32x32 and 32x64 wave tiles of the few-row configurations):
-    // too little to hide a k-step's fragment reads behind, so reading step by step pays the LDS
-    // latency four times per slab.  Request the next slab first, fetch all fragments of this one in
-    // one go (48 registers at most), wait once.
-    ld.issue(a, nxt, k_next, wave);
-    bf16x8 af[KS * C::MI], bfr[KS * C::NI];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-#pragma unroll
-      for (int mi = 0; mi < C::MI; ++mi) af[ks * C::MI + mi] = frag_a_opaque<C>(cur, ks, mi, wm, lane);
-#pragma unroll
-      for (int ni = 0; ni < C::NI; ++ni) bfr[ks * C::NI + ni] = frag_b_opaque<C>(cur, ks, ni, wn, lane);
-    }
-    wait_lds_reads<KS * C::MI, KS * C::NI>(af, bfr);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-      for (int mi = 0; mi < C::MI; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < C::NI; ++ni)
-          acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks * C::MI + mi], bfr[ks * C::NI + ni], acc[mi][ni], 0, 0, 0);
-    return;
-  }
-  bf16x8 af[2][C::MI], bfr[2][C::NI];
-#pragma unroll
-  for (int mi = 0; mi < C::MI; ++mi) af[0][mi] = frag_a_opaque<C>(cur, 0, mi, wm, lane);
-#pragma unroll
-  for (int ni = 0; ni < C::NI; ++ni) bfr[0][ni] = frag_b_opaque<C>(cur, 0, ni, wn, lane);
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    wait_lds_reads<C::MI, C::NI>(af[ks & 1], bfr[ks & 1]);
-    if (ks + 1 < KS) {
-#pragma unroll
-      for (int m2 = 0; m2 < C::MI; ++m2) af[(ks + 1) & 1][m2] = frag_a_opaque<C>(cur, ks + 1, m2, wm, lane);
-#pragma unroll
-      for (int ni = 0; ni < C::NI; ++ni) bfr[(ks + 1) & 1][ni] = frag_b_opaque<C>(cur, ks + 1, ni, wn, lane);
-    }
-#pragma unroll
-    for (int mi = 0; mi < C::MI; ++mi) {
-      const int g = ks * C::MI + mi;
-      if (g < GS) {
-        const int lo = g * L / GS, hi = (g + 1) * L / GS;
-#pragma unroll
-        for (int idx = 0; idx < L; ++idx)
-          if (idx >= lo && idx < hi) ld.issue_dyn(idx, a, nxt, k_next, wave);
-      }
-#pragma unroll
-      for (int ni = 0; ni < C::NI; ++ni)
-        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks & 1][mi], bfr[ks & 1][ni], acc[mi][ni], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
 }
 
 template <int N>
@@ -1621,11 +1308,220 @@ __device__ __forceinline__ void wait_vm0_and_barrier() {
   __syncthreads();
 }
 
-template <class C, int EPI, bool WAIT>
+// f(0), f(1), ... f(N-1) with the index as a compile-time constant.
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
+// The main loop of every kernel: K-slabs out of an LDS ring of NSTAGE stages, every memory instruction placed
+// by hand between the MFMAs.  A wave issues in order and (with the large tile) has its SIMD to itself, so what it
+// issues in a burst or waits for is time its matrix core stands still:
+//   * a slab has two k-steps of 32; the fragments of the next k-step are read while the MFMAs of this one run,
+//     one read per few MFMAs, also across the slab's end: the last k-step reads the first fragments of the
+//     next stage;
+//   * the one barrier per slab therefore sits at the start of the last k-step: by then the next slab has landed
+//     (counter wait: loads land in issue order), and every wave has its last fragments of this stage in
+//     registers, so this stage is free for the slab NSTAGE ahead;
+//   * the wave's loads for that slab are dealt out from there on, over LOAD_SPAN MFMAs, and have the rest of the slab
+//     to land.
+// What bounds it: the chip's power limit for long K (8192^3, N(0,.) operands: 1.57 PFLOP/s, MFMAs alone 2.0).  Plain
+// GEMM kernels, us, against reading a k-step's fragments in one burst, waiting at the slab's end and 32x32x16 MFMAs:
+// 8192^3 699 against 799, 8192x12288x4608 611 against 691, 4096x3584x8192 171 against 195, 8192x12288x1536 233 against
+// 260.  Of that the placement gives 5-6 %, the MFMA shape 8-9 %.
+// The fragment reads are instructions the compiler cannot look into.  For every LDS read it can see, it works
+// out by itself which of the direct-to-LDS loads in flight must land first, and gets that wrong on the safe side.
+// Their addresses are a few registers per lane plus an immediate.  They are waited for in the k-step that issued
+// them, so no register is waiting for data where the compiler is free to move registers around.
+//
+// B_FIRST (signal wait): B, which does not depend on a gathered A, is requested before the wait for all of the first
+// slabs, A after it.  Without, the first slabs are requested one after the other, so that slab 0 does not have to
+// wait for the B of the others (64 x 8192 x 3584: 0.5 us of 23).
+template <class C, bool B_FIRST, bool EDGE>
+struct MmaPipe {
+  typedef DmaLoader<C, EDGE> Ld;
+  static constexpr int NS = C::NSTAGE;
+  static constexpr int KS = C::BK / 32;                              // k-steps per slab
+  static_assert(KS == 2, "two fragment sets, one per k-step");
+  static constexpr int G = C::MI * C::NI;                            // MFMAs per k-step
+  static constexpr int NF = C::MI + C::NI;                           // fragments per k-step
+  static constexpr int L = Ld::N_INSTR;                    // loads per slab and wave
+  static constexpr int LA = Ld::A_INSTR;
+  static constexpr int NBV = C::B_NK ? KS : C::NI;
+  static constexpr int NHI = (NS * C::STAGE_BYTES + 65535) / 65536;  // a read's immediate offset reaches 64 KB
+  // Placement, in MFMAs.  (8192^3, of G = 64: within 1 % for SPREAD 40 to 62, BAR_AT 1 to 12, SPAN 64 to 96; SPAN 118
+  // costs 3-6 %: the last loads have not landed at the wait.)
+  static constexpr int BAR_AT = G / 8;                               // MFMAs of the last k-step ahead of the barrier
+  static constexpr int SPREAD = (G * 15 + 15) / 16;                  // the reads go with the first SPREAD MFMAs of a k-step
+  static constexpr int SPAN = G * 11 / 8;                            // the loads with the first SPAN MFMAs from the last k-step on
+  static_assert(BAR_AT < SPREAD && SPREAD <= G && SPAN <= 2 * G, "placement");
+  // load d of a slab goes with slot load_slot(d), counted from the start of the last k-step of the slab NS before it
+  static constexpr int load_slot(int d) { return BAR_AT + d * (SPAN - BAR_AT) / L; }
+  static constexpr int loads_before(int slot) { int n = 0; while (n < L && load_slot(n) < slot) ++n; return n; }
+  static constexpr int reads_before(int slot, int from) { int n = 0; while (n < NF && from + n * (SPREAD - from) / NF < slot) ++n; return n; }
+  static constexpr int L0 = loads_before(G);                         // loads of a slab that go with that last k-step
+
+  uint32_t a[NHI][KS], b[NHI][NBV];
+  bf16x8 af[2][C::MI], bf[2][C::NI];
+
+  __device__ __forceinline__ void init(const unsigned char* pool, int wm, int wn, int lane) {
+    const uint32_t base = lds_address(pool);
+    const int g = lane >> 4, i = lane & 15;
+#pragma unroll
+    for (int h = 0; h < NHI; ++h) {
+      const uint32_t bh = base + h * 65536u;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const int row = wm * C::WTM + i, q = ks * 4 + g;
+        a[h][ks] = bh + row * (C::BK * 2) + ((q ^ swz_a<C::A_SLOTS>(row)) << 4);
+        if constexpr (C::B_NK) {
+          const int rn = wn * C::WTN + i;
+          b[h][ks] = bh + rn * (C::BK * 2) + ((q ^ swz_a<C::A_SLOTS>(rn)) << 4);
+        }
+      }
+      if constexpr (!C::B_NK) {
+#pragma unroll
+        for (int ni = 0; ni < C::NI; ++ni) {
+          const int k = 8 * g + (i >> 2);
+          const int n = wn * C::WTN + ni * 16 + 4 * (i & 3);
+          b[h][ni] = bh + k * (C::BN * 2) + (((n >> 3) ^ swz_b<C::B_SLOTS>(k)) << 4) + ((n >> 2) & 1) * 8;
+        }
+      }
+    }
+  }
+
+  template <int OFF>
+  static __device__ __forceinline__ bf16x8 read16(const uint32_t (&base)[NHI]) {
+    u32x4 v;
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(base[OFF / 65536]), "n"(OFF % 65536));
+    return __builtin_bit_cast(bf16x8, v);
+  }
+  template <int OFF>
+  static __device__ __forceinline__ bf16x8 read_tr(const uint32_t (&base)[NHI]) {
+    typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+    constexpr int O2 = OFF + 4 * C::BN * 2;
+    u32x2 lo, hi;
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo) : "v"(base[OFF / 65536]), "n"(OFF % 65536));
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(base[O2 / 65536]), "n"(O2 % 65536));
+    const u32x4 w = {lo[0], lo[1], hi[0], hi[1]};
+    return __builtin_bit_cast(bf16x8, w);
+  }
+  // fragment R (in the order the MFMAs want them) of k-step K out of stage S
+  template <int S, int K, int R>
+  __device__ __forceinline__ void fetch() {
+    constexpr bool IS_B = R >= 1 && R <= C::NI;
+    constexpr int I = R == 0 ? 0 : (IS_B ? R - 1 : R - C::NI);
+    uint32_t base[NHI];
+#pragma unroll
+    for (int h = 0; h < NHI; ++h) base[h] = IS_B ? b[h][C::B_NK ? K : I] : a[h][K];
+    if constexpr (!IS_B) af[K][I] = read16<S * C::STAGE_BYTES + I * 16 * C::BK * 2>(base);
+    else if constexpr (C::B_NK) bf[K][I] = read16<S * C::STAGE_BYTES + C::A_BYTES + I * 16 * C::BK * 2>(base);
+    else bf[K][I] = read_tr<S * C::STAGE_BYTES + C::A_BYTES + K * 32 * C::BN * 2>(base);
+  }
+
+  // Fills the pipeline: slabs 0 .. NS-2 and the first loads of slab NS-1 requested, the fragments of the first k-step
+  // read.  Slabs past the end are loads outside the records everywhere (no memory access): every step issues the same
+  // number of loads, which keeps the counter waits constants and the loop one shape.
+  __device__ __forceinline__ void request_b(const Ld& ld, const GemmArgs& ga, unsigned char* pool, int k_begin, int KT, int wave) {
+    static_assert(B_FIRST);
+#pragma unroll
+    for (int j = 0; j < NS - 1; ++j) ld.only_if(j < KT, ga).issue_b(ga, pool + j * C::STAGE_BYTES, k_begin + j * C::BK, wave);
+  }
+  __device__ __forceinline__ void start(const Ld& ld, const GemmArgs& ga, unsigned char* pool, int k_begin, int KT, int wave) {
+#pragma unroll
+    for (int j = 0; j < NS - 1; ++j) {
+      const Ld l = ld.only_if(j < KT, ga);
+      if constexpr (B_FIRST) l.issue_a(ga, pool + j * C::STAGE_BYTES, k_begin + j * C::BK, wave);
+      else l.issue(ga, pool + j * C::STAGE_BYTES, k_begin + j * C::BK, wave);
+    }
+    const Ld l = ld.only_if(NS - 1 < KT, ga);
+#pragma unroll
+    for (int d = 0; d < L0; ++d) l.issue_dyn(d, ga, pool + (NS - 1) * C::STAGE_BYTES, k_begin + (NS - 1) * C::BK, wave);
+    wait_vm_at_most<(NS - 2) * (B_FIRST ? LA : L) + L0>();        // slab 0 is there
+    barrier_keeping_loads_in_flight();
+    static_for<NF>([&](auto r) { fetch<0, 0, decltype(r)::value>(); });
+    wait_lds_reads<C::MI, C::NI>(af[0], bf[0]);
+  }
+
+  // Slab kt, which lies in stage S = kt % NS.  VM_EXTRA: that many younger memory operations, issued by before_wait(),
+  // may stay outstanding at the wait.
+  template <int S, int VM_EXTRA, class Hook>
+  __device__ __forceinline__ void step(const Ld& ld, const GemmArgs& ga, unsigned char* pool, int k_begin, int kt, int KT, int wave,
+                                       f32x4 (&acc)[C::MI][C::NI], Hook&& before_wait) {
+    unsigned char* const st_rest = pool + ((S + NS - 1) % NS) * C::STAGE_BYTES;
+    unsigned char* const st_cur = pool + S * C::STAGE_BYTES;
+    // (the slab's offset goes into the loads' scalar operand: should the compiler ever take the loop
+    // counter for a value that may differ between lanes, it would wrap every load into a loop over lanes)
+    kt = __builtin_amdgcn_readfirstlane(kt);
+    const Ld ld_rest = ld.only_if(kt + NS - 1 < KT, ga), ld_first = ld.only_if(kt + NS < KT, ga);
+    const int k_rest = k_begin + (kt + NS - 1) * C::BK, k_first = k_rest + C::BK;
+    static_for<KS>([&](auto ks_) {
+      constexpr int ks = decltype(ks_)::value;
+      constexpr bool LAST = ks == KS - 1;
+      if constexpr (LAST) before_wait();
+      static_for<G>([&](auto g_) {
+        constexpr int g = decltype(g_)::value;
+        constexpr int mi = g / C::NI, ni = g % C::NI;
+        if constexpr (LAST && g == BAR_AT) {
+          // slab kt+1 is there (this wave's part, then everyone's); stage S has been read by all
+          if constexpr (B_FIRST && S < NS - 2) {
+            // (slabs 0 .. NS-2 were requested as all of B, then all of A: behind slab kt+1's are the A parts of the
+            // later ones of those, and the slabs requested since)
+            if (kt == S) wait_vm_at_most<(NS - 3 - S) * LA + (S + 1) * L + VM_EXTRA>();
+            else wait_vm_at_most<(NS - 2) * L + VM_EXTRA>();
+          } else {
+            wait_vm_at_most<(NS - 2) * L + VM_EXTRA>();
+          }
+          barrier_keeping_loads_in_flight();
+        }
+        mfma_in_place(acc[mi][ni], af[ks][mi], bf[ks][ni]);
+        // this MFMA's loads [d0, d1) and fragment reads [r0, r1)
+        constexpr int d0 = loads_before(LAST ? g : G + g), d1 = loads_before((LAST ? g : G + g) + 1);
+#pragma unroll
+        for (int d = d0; d < d1; ++d) {
+          if constexpr (LAST) ld_first.issue_dyn(d, ga, st_cur, k_first, wave);
+          else ld_rest.issue_dyn(d, ga, st_rest, k_rest, wave);
+        }
+        constexpr int r0 = reads_before(g, LAST ? BAR_AT : 0), r1 = reads_before(g + 1, LAST ? BAR_AT : 0);
+        static_for<r1 - r0>([&](auto r_) {
+          constexpr int r = r0 + decltype(r_)::value;
+          if constexpr (LAST) fetch<(S + 1) % NS, 0, r>();
+          else fetch<S, ks + 1, r>();
+        });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      wait_lds_reads<C::MI, C::NI>(af[1 - ks], bf[1 - ks]);
+    });
+  }
+
+  // Slabs kt (a multiple of NS; 0 after start()) to the end.
+  __device__ __forceinline__ void run(const Ld& ld, const GemmArgs& ga, unsigned char* pool, int k_begin, int KT, int kt, int wave,
+                                      f32x4 (&acc)[C::MI][C::NI]) {
+    for (; kt + NS <= KT; kt += NS)
+      static_for<NS>([&](auto s_) {
+        constexpr int S = decltype(s_)::value;
+        step<S, 0>(ld, ga, pool, k_begin, kt + S, KT, wave, acc, [] {});
+      });
+    static_for<NS - 1>([&](auto s_) {
+      constexpr int S = decltype(s_)::value;
+      if (kt + S < KT) step<S, 0>(ld, ga, pool, k_begin, kt + S, KT, wave, acc, [] {});
+    });
+    mfma_results_settle<C::MI, C::NI>(acc);
+  }
+};
+
+// EDGE: the tile does not divide M, N or K (see DmaLoader; the epilogue leaves rows and columns past the end out).
+template <class C, int EPI, bool WAIT, bool EDGE>
 __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs a) {
-  constexpr int S0_BYTES = C::STAGE_BYTES > C::EP_BYTES ? C::STAGE_BYTES : C::EP_BYTES;
-  __shared__ __attribute__((aligned(1024))) unsigned char stage0[S0_BYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char stage1[C::STAGE_BYTES];
+  // the transfer inside the main loop (SideCopy) is asked of the two-stage kernel with one workgroup per unit
+  constexpr bool CARRY = WAIT && !EDGE && C::NSTAGE == 2 && C::OCC == 1;
+  // one pool: the stages, and over them (once the main loop is done) the epilogue's staging area
+  constexpr int POOL_BYTES = C::NSTAGE * C::STAGE_BYTES > C::EP_BYTES ? C::NSTAGE * C::STAGE_BYTES : C::EP_BYTES;
+  __shared__ __attribute__((aligned(1024))) unsigned char pool[POOL_BYTES];
   __shared__ int lds_misc[4];
   __shared__ void* lds_outs[FLUX_MAX_RANKS];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1643,102 +1539,102 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
   if (EPI == EPI_RS || WAIT) {      // output slices (reduce-scatter) or chunk sources (all-gather), by rank
     fill_lds_outs(a, lds_outs, tid);
   }
+  const int k_begin = is_split ? split * a.k_per_split : 0;
+  const int k_end = (is_split && k_begin + a.k_per_split < a.K) ? k_begin + a.k_per_split : a.K;
+  const int KT = (k_end - k_begin + C::BK - 1) / C::BK;
+
+  DmaLoader<C, EDGE> ld;
+  ld.init(a, m0, n0, wave, lane);
+  MmaPipe<C, WAIT, EDGE> pipe;
+  pipe.init(pool, wm, wn, lane);
   SideCopy side;
-  if (WAIT) {
+  if constexpr (WAIT) {
+    const int m1 = (!EDGE || m0 + C::BM < a.M) ? m0 + C::BM : a.M;
+    // First this workgroup's own pieces of the chunks: the whole grid waits for them.
     transfer_own_pieces(a, lds_misc, lds_outs);
-    side.begin(a, lds_misc + 2, lds_outs);     // (also orders fill_lds_outs before the reads of lds_outs below)
-    // A workgroup that has pieces to move and no data to compute on yet moves them in batches, and
-    // counts tiles in as they become due, until its own signals are there (the main loop then
-    // carries what is left) or its part of the transfer is done (then it waits like anybody else).
-    while (side.pending() && !signals_all_set(a, m0, m0 + C::BM, lds_misc + 2)) {
-      if (!side.all_stored()) side.pump(a, lds_outs);
-      else __builtin_amdgcn_s_sleep(16);
-      side.maybe_finish(a);
+    if constexpr (CARRY) {
+      side.begin(a, lds_misc + 2, lds_outs);     // (also orders fill_lds_outs before the reads of lds_outs below)
+      // A workgroup that has pieces to move and no data to compute on yet moves them in batches, and
+      // counts tiles in as they become due, until its own signals are there (the main loop then
+      // carries what is left) or its part of the transfer is done (then it waits like anybody else).
+      while (side.pending() && !signals_all_set(a, m0, m1, lds_misc + 2)) {
+        if (!side.all_stored()) side.pump(a, lds_outs);
+        else __builtin_amdgcn_s_sleep(16);
+        side.maybe_finish(a);
+      }
     }
-    if (!wait_signals(a, m0, m0 + C::BM, lds_misc, lds_outs)) {
+    // Then the weights, which do not depend on the gathered rows: their part of the first slabs is on its
+    // way while the workgroup waits for its signals.
+    pipe.request_b(ld, a, pool, k_begin, KT, wave);
+    if (!wait_signals(a, m0, m1, lds_misc, lds_outs)) {
       // given up (a workgroup only gets to its wait with pieces left if its signals were there, so this
       // is for safety): the pieces it claimed still have to be moved, or their tiles' signals never come
-      if (side.pending()) side.drain(a, lds_outs);
+      if constexpr (CARRY) {
+        if (side.pending()) side.drain(a, lds_outs);
+      }
+      wait_vm_at_most<0>();        // nothing of this workgroup is left in flight towards its LDS
       trace_stamp(a, TRACE_END);
       return;
     }
     trace_stamp(a, TRACE_READY);
   }
-  const int k_begin = is_split ? split * a.k_per_split : 0;
-  const int k_end = (is_split && k_begin + a.k_per_split < a.K) ? k_begin + a.k_per_split : a.K;
-  const int KT = (k_end - k_begin) / C::BK;
 
-  f32x16 acc[C::MI][C::NI];
+  f32x4 acc[C::MI][C::NI];
 #pragma unroll
   for (int mi = 0; mi < C::MI; ++mi)
 #pragma unroll
     for (int ni = 0; ni < C::NI; ++ni)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[mi][ni][e] = 0.f;
+      for (int e = 0; e < 4; ++e) acc[mi][ni][e] = 0.f;
 
-  DmaLoader<C> ld;
-  ld.init(a, m0, n0, wave, lane);
-  ld.issue(a, stage0, k_begin, wave);
-  wait_vm0_and_barrier();
-  // Every slab prefetches its successor; the last one fetches itself again (into the stage that
-  // is not being read), which keeps a single code shape for the loop instead of a prefetch-free
-  // copy of it that the register allocator handles badly.
-  const int k_last = k_begin + (KT - 1) * C::BK;
+  pipe.start(ld, a, pool, k_begin, KT, wave);
   int kt = 0;
-  if (WAIT && side.pending()) {
-    // With the transfer aboard (a workgroup of the first round with pieces to move; everybody else
-    // runs the plain loop below): per slab two stores (of the vectors loaded two slabs ago) ahead of
-    // the slab's operand loads and two loads behind them.  "All but the two youngest operations have
-    // completed" then means that the operand loads have landed (loads complete in order, and the
-    // stores are older than all of them), and the barrier must not make the compiler wait for those
-    // last loads.  Thread 0 looks at the clock once per two slabs and leaves word in LDS whether a
-    // tile is due to be counted in (a decision every wave must take alike: finish() has barriers).
-    // When the last tile is counted in, the plain loop takes over for the rest of K.
-    u32x4 dA0 = side.load(a, lds_outs), dA1 = side.load(a, lds_outs);
-    u32x4 dB0 = side.load(a, lds_outs), dB1 = side.load(a, lds_outs);
-    for (; kt + 2 <= KT && side.pending(); kt += 2) {
-      side.store(a, dA0);
-      side.store(a, dA1);
-      mma_stage_dma<C, true>(stage0, stage1, ld, a, k_begin + (kt + 1) * C::BK, wave, wm, wn, lane, acc);
-      dA0 = side.load(a, lds_outs);
-      dA1 = side.load(a, lds_outs);
-      wait_vm_at_most<2>();
-      barrier_keeping_loads_in_flight();
-      side.store(a, dB0);
-      side.store(a, dB1);
-      const int k2 = k_begin + (kt + 2) * C::BK;
-      mma_stage_dma<C, true>(stage1, stage0, ld, a, k2 < k_last ? k2 : k_last, wave, wm, wn, lane, acc);
-      dB0 = side.load(a, lds_outs);
-      dB1 = side.load(a, lds_outs);
-      const bool look = side.may_be_due();       // (uniform)
-      if (look && tid == 0) *side.slot = side.due() ? 1 : 0;
-      wait_vm_at_most<2>();
-      barrier_keeping_loads_in_flight();
-      if (look) {
-        const int go = __builtin_amdgcn_readfirstlane(*side.slot);
-        if (go) side.finish(a);           // (its barriers also keep the slot from being rewritten too early)
+  if constexpr (CARRY) {
+    if (side.pending()) {
+      // With the transfer aboard (a workgroup of the first round with pieces to move; everybody else
+      // runs the plain loop below): per slab two stores (of the vectors loaded two slabs ago) ahead of
+      // the slab's operand loads and two loads right before the slab's wait.  "All but the two youngest
+      // operations have completed" then means that the operand loads have landed (loads complete in
+      // order, and those two are the youngest loads).  Thread 0 looks at the clock once per two slabs and
+      // leaves word in LDS whether a tile is due to be counted in (a decision every wave must take
+      // alike: finish() has barriers).  When the last tile is counted in, the plain loop takes over for the rest of K.
+      u32x4 dA0 = side.load(a, lds_outs), dA1 = side.load(a, lds_outs);
+      u32x4 dB0 = side.load(a, lds_outs), dB1 = side.load(a, lds_outs);
+      for (; kt + 2 <= KT && side.pending(); kt += 2) {
+        side.store(a, dA0);
+        side.store(a, dA1);
+        pipe.template step<0, 2>(ld, a, pool, k_begin, kt, KT, wave, acc, [&] {
+          dA0 = side.load(a, lds_outs);
+          dA1 = side.load(a, lds_outs);
+        });
+        side.store(a, dB0);
+        side.store(a, dB1);
+        bool look = false;
+        pipe.template step<1, 2>(ld, a, pool, k_begin, kt + 1, KT, wave, acc, [&] {
+          look = side.may_be_due();       // (uniform)
+          if (look) {
+            if (tid == 0) *side.slot = side.due() ? 1 : 0;
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          }
+          dB0 = side.load(a, lds_outs);
+          dB1 = side.load(a, lds_outs);
+        });
+        if (look) {
+          const int go = __builtin_amdgcn_readfirstlane(*side.slot);
+          if (go) side.finish(a);           // (its barriers also keep the slot from being rewritten too early)
+        }
+      }
+      if (side.pending()) {          // K is over before the transfer is: the vectors in flight first, then the rest
+        side.store(a, dA0); side.store(a, dA1); side.store(a, dB0); side.store(a, dB1);
+        side.ld_t = side.st_t; side.ld_s = side.st_s; side.ld_off = side.st_off;     // the loads start again where the stores are
+        side.set_src(a, lds_outs, side.ld_t);
+        side.drain(a, lds_outs);
       }
     }
-    wait_vm0_and_barrier();
-    if (side.pending()) {          // K is over before the transfer is: the vectors in flight first, then the rest
-      side.store(a, dA0); side.store(a, dA1); side.store(a, dB0); side.store(a, dB1);
-      side.ld_t = side.st_t; side.ld_s = side.st_s; side.ld_off = side.st_off;     // the loads start again where the stores are
-      side.set_src(a, lds_outs, side.ld_t);
-      side.drain(a, lds_outs);
-    }
   }
-  for (; kt + 2 <= KT; kt += 2) {
-    mma_stage_dma<C, true>(stage0, stage1, ld, a, k_begin + (kt + 1) * C::BK, wave, wm, wn, lane, acc);
-    wait_vm0_and_barrier();
-    const int k2 = k_begin + (kt + 2) * C::BK;
-    mma_stage_dma<C, true>(stage1, stage0, ld, a, k2 < k_last ? k2 : k_last, wave, wm, wn, lane, acc);
-    wait_vm0_and_barrier();
-  }
-  if (kt < KT) {
-    mma_stage_dma<C, true>(stage0, stage1, ld, a, k_last, wave, wm, wn, lane, acc);
-    wait_vm0_and_barrier();
-  }
-  gemm_tail<C, EPI, false>(a, stage0, lds_misc, lds_outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn);
+  pipe.run(ld, a, pool, k_begin, KT, kt, wave, acc);
+  wait_vm0_and_barrier();        // the epilogue's staging area lies over stages other waves may still be reading
+  gemm_tail<C, EPI, EDGE>(a, pool, lds_misc, lds_outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn);
 }
 
 // The same kernel as a grid of resident workgroups, one per compute unit, each walking the block
@@ -1746,9 +1642,8 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
 // instead of in dispatch).
 template <class C, int EPI>
 __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma_resident(const GemmArgs a_) {
-  constexpr int S0_BYTES = C::STAGE_BYTES > C::EP_BYTES ? C::STAGE_BYTES : C::EP_BYTES;
-  __shared__ __attribute__((aligned(1024))) unsigned char stage0[S0_BYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char stage1[C::STAGE_BYTES];
+  constexpr int POOL_BYTES = 2 * C::STAGE_BYTES > C::EP_BYTES ? 2 * C::STAGE_BYTES : C::EP_BYTES;   // the stages; later the epilogue's staging area
+  __shared__ __attribute__((aligned(1024))) unsigned char pool[POOL_BYTES];
   __shared__ int lds_misc[4];
   __shared__ void* lds_outs[FLUX_MAX_RANKS];
   if (EPI == EPI_RS) fill_lds_outs(a_, lds_outs, (int)threadIdx.x);
@@ -1781,148 +1676,23 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma_resident(const 
     const int k_begin = is_split ? split * a.k_per_split : 0;
     const int k_end = (is_split && k_begin + a.k_per_split < a.K) ? k_begin + a.k_per_split : a.K;
     const int KT = (k_end - k_begin) / C::BK;
-    f32x16 acc[C::MI][C::NI];
+    f32x4 acc[C::MI][C::NI];
 #pragma unroll
     for (int mi = 0; mi < C::MI; ++mi)
 #pragma unroll
       for (int ni = 0; ni < C::NI; ++ni)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[mi][ni][e] = 0.f;
-    DmaLoader<C> ld;
+        for (int e = 0; e < 4; ++e) acc[mi][ni][e] = 0.f;
+    DmaLoader<C, false> ld;
     ld.init(a, m0, n0, wave, lane);
-    ld.issue(a, stage0, k_begin, wave);
+    MmaPipe<C, false, false> pipe;
+    pipe.init(pool, wm, wn, lane);
+    pipe.start(ld, a, pool, k_begin, KT, wave);
+    pipe.run(ld, a, pool, k_begin, KT, 0, wave, acc);
     wait_vm0_and_barrier();
-    const int k_last = k_begin + (KT - 1) * C::BK;
-    int kt = 0;
-    for (; kt + 2 <= KT; kt += 2) {
-      mma_stage_dma<C, true>(stage0, stage1, ld, a, k_begin + (kt + 1) * C::BK, wave, wm, wn, lane, acc);
-      wait_vm0_and_barrier();
-      const int k2 = k_begin + (kt + 2) * C::BK;
-      mma_stage_dma<C, true>(stage1, stage0, ld, a, k2 < k_last ? k2 : k_last, wave, wm, wn, lane, acc);
-      wait_vm0_and_barrier();
-    }
-    if (kt < KT) {
-      mma_stage_dma<C, true>(stage0, stage1, ld, a, k_last, wave, wm, wn, lane, acc);
-      wait_vm0_and_barrier();
-    }
-    gemm_tail<C, EPI, false>(a, stage0, lds_misc, lds_outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, vb);
+    gemm_tail<C, EPI, false>(a, pool, lds_misc, lds_outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, vb);
     __syncthreads();      // the staging area and lds_misc are the next block's
   }
-}
-
-// ---------------------------------------------------------------------------------------------
-// The same pipeline with NSTAGE >= 3 LDS stages, for tiles that have little arithmetic per byte
-// (few rows: decode).  Such a tile is bound by how many bytes its compute unit keeps in flight:
-// slab kt is computed while the loads of slabs kt+1 .. kt+NSTAGE-1 are outstanding.  Loads land in
-// issue order, so "all but the (NSTAGE-2) youngest slabs have landed" is a plain counter wait.
-// Stages are separate arrays (see above); the epilogue has its own staging area, so the tail of
-// the load pipeline need not drain before it starts.
-// ---------------------------------------------------------------------------------------------
-// MASK: M is not a multiple of the tile height.  Rows past M are read as zeros (they lie outside
-// the buffer resource of A) and the epilogue leaves them out.
-// Counter wait of the first pass of the deep pipeline when the weights' part of the first slabs
-// was issued ahead of everything else: before slab j is read, at most the A parts of the slabs
-// after it (up to slab NS-2) and the j whole slabs issued since may be outstanding.  `j` is a
-// constant after unrolling; the wait instruction needs its count as an immediate.
-template <int NS, int LA, int L, int J = 0>
-struct FirstPassWait {
-  static __device__ __forceinline__ void run(int j) {
-    if constexpr (J < NS - 1) {
-      if (j == J) wait_vm_at_most<(NS - 2 - J) * LA + J * L>();
-      else FirstPassWait<NS, LA, L, J + 1>::run(j);
-    }
-  }
-};
-
-template <class C, int EPI, bool WAIT, bool MASK>
-__global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma_deep(const GemmArgs a) {
-  constexpr int NS = C::NSTAGE;
-  static_assert(NS >= 3 && NS <= 9, "3 to 9 stages");
-  constexpr int L = DmaLoader<C>::N_INSTR;                  // loads per slab and wave
-  static_assert((NS - 2) * L < 64, "outstanding loads must fit the counter");
-  // One pool: the stages, and over them (once the main loop is done) the epilogue's staging area.
-  constexpr int POOL_BYTES = NS * C::STAGE_BYTES > C::EP_BYTES ? NS * C::STAGE_BYTES : C::EP_BYTES;
-  __shared__ __attribute__((aligned(1024))) unsigned char pool[POOL_BYTES];
-  __shared__ int lds_misc[4];
-  __shared__ void* lds_outs[FLUX_MAX_RANKS];
-  unsigned char* st[NS];
-#pragma unroll
-  for (int j = 0; j < NS; ++j) st[j] = pool + j * C::STAGE_BYTES;
-  unsigned char* const ep_stage = pool;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
-
-  int tile, split;
-  bool is_split;
-  map_block(a, (int)blockIdx.x, tile, split, is_split);
-  int mt, nt;
-  tile_coord(a.tm, tile, mt, nt);
-  const int m0 = mt * C::BM, n0 = nt * C::BN;
-  trace_begin(a, tile, mt, nt, split, is_split);
-
-  if (EPI == EPI_RS || WAIT) {
-    fill_lds_outs(a, lds_outs, tid);
-  }
-  const int k_begin = is_split ? split * a.k_per_split : 0;
-  const int k_end = (is_split && k_begin + a.k_per_split < a.K) ? k_begin + a.k_per_split : a.K;
-  const int KT = (k_end - k_begin) / C::BK;
-
-  DmaLoader<C> ld;
-  ld.init(a, m0, n0, wave, lane);
-  // Slabs past the end are replaced by the last one: every step issues the same number of loads,
-  // which keeps the counter wait a constant and the loop one shape.  Such a repeat lands in a
-  // stage whose slab has been consumed, never in the one the last slab is read from.
-  const int last = KT - 1;
-  constexpr int LA = DmaLoader<C>::A_INSTR;
-  if (WAIT) {
-    // First this workgroup's own pieces of the chunks: the whole grid waits for them.  Then the
-    // weights, which do not depend on the gathered rows: their part of the first slabs is on its
-    // way while the workgroup waits for its signals.  In the first pass of the loop the order of
-    // issue is then [B of slabs 0..NS-2][A of slabs 0..NS-2][slab NS-1]..., and "slab j has landed"
-    // means that at most the A parts after it and j whole slabs are out.
-    transfer_own_pieces(a, lds_misc, lds_outs);
-#pragma unroll
-    for (int j = 0; j < NS - 1; ++j) ld.issue_b(a, st[j], k_begin + (j < last ? j : last) * C::BK, wave);
-    const int m1 = (!MASK || m0 + C::BM < a.M) ? m0 + C::BM : a.M;
-    if (!wait_signals(a, m0, m1, lds_misc, lds_outs)) {
-      wait_vm_at_most<0>();        // nothing of this workgroup is left in flight towards its LDS
-      trace_stamp(a, TRACE_END);
-      return;
-    }
-    trace_stamp(a, TRACE_READY);
-#pragma unroll
-    for (int j = 0; j < NS - 1; ++j) ld.issue_a(a, st[j], k_begin + (j < last ? j : last) * C::BK, wave);
-  } else {
-#pragma unroll
-    for (int j = 0; j < NS - 1; ++j) ld.issue(a, st[j], k_begin + (j < last ? j : last) * C::BK, wave);
-  }
-
-  f32x16 acc[C::MI][C::NI];
-#pragma unroll
-  for (int mi = 0; mi < C::MI; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < C::NI; ++ni)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[mi][ni][e] = 0.f;
-
-  for (int kt0 = 0; kt0 < KT; kt0 += NS) {
-#pragma unroll
-    for (int j = 0; j < NS; ++j) {
-      const int kt = kt0 + j;
-      if (kt < KT) {
-        // slab kt has landed (this wave's part of it)
-        if (WAIT && j < NS - 1 && kt0 == 0) FirstPassWait<NS, LA, L>::run(j);
-        else wait_vm_at_most<(NS - 2) * L>();
-        barrier_keeping_loads_in_flight();   // ... everyone's part; and slab kt-1 has been read by all
-        const int kn = kt + NS - 1 < last ? kt + NS - 1 : last;
-        mma_stage_dma_opaque<C>(st[j], st[(j + NS - 1) % NS], ld, a, k_begin + kn * C::BK, wave, wm, wn, lane, acc);
-      }
-    }
-  }
-  wait_vm_at_most<0>();
-  __syncthreads();       // the epilogue's staging area lies over stages other waves may still be reading
-  gemm_tail<C, EPI, MASK>(a, ep_stage, lds_misc, lds_outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn);
 }
 
 }  // namespace flux

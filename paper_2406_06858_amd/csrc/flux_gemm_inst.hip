@@ -30,53 +30,25 @@ namespace flux {
 typedef TileCfg<FLUX_CFG_PARAMS> Cfg;            // B as [K,N]
 typedef TileCfg<FLUX_CFG_PARAMS, true> CfgNK;    // B as [N,K]
 
-// Shapes the tile divides take a direct-to-LDS kernel (two stages, or the deep pipeline for
-// configurations with more); ragged shapes the register-staged one, which masks rows, columns
-// and the K tail.  The deep pipeline also takes shapes where only M is ragged (edge = 2).
-enum : int { EDGE_NONE = 0, EDGE_ANY = 1, EDGE_ROWS = 2 };
-
-template <class Cfg, int EPI, bool WAIT, int EDGE>
-static hipError_t launch_one(const GemmArgs& a, int grid, hipStream_t s) {
-  if constexpr (EDGE == EDGE_NONE && Cfg::NSTAGE == 2) {
-    if constexpr (!WAIT && Cfg::OCC == 1) {
-      if (a.persist_blocks > 0) {
-        hipLaunchKernelGGL((gemm_kernel_dma_resident<Cfg, EPI>), dim3(grid), dim3(Cfg::NT), 0, s, a);
-        return hipGetLastError();
-      }
-    }
-    hipLaunchKernelGGL((gemm_kernel_dma<Cfg, EPI, WAIT>), dim3(grid), dim3(Cfg::NT), 0, s, a);
-    return hipGetLastError();
-  } else if constexpr (EDGE != EDGE_ANY && Cfg::NSTAGE >= 3) {
-    hipLaunchKernelGGL((gemm_kernel_dma_deep<Cfg, EPI, WAIT, EDGE == EDGE_ROWS>), dim3(grid), dim3(Cfg::NT), 0, s, a);
-    return hipGetLastError();
-  } else if constexpr (EDGE == EDGE_ROWS) {
-    return hipErrorInvalidValue;     // only asked of the deep pipeline
-  } else {
-    auto k = gemm_kernel<Cfg, EPI, WAIT, EDGE == EDGE_ANY>;
-    static bool attr_set = false;
-    if (!attr_set) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS_BYTES);
-      if (e != hipSuccess) return e;
-      attr_set = true;
-    }
-    hipLaunchKernelGGL(k, dim3(grid), dim3(Cfg::NT), Cfg::LDS_BYTES, s, a);
-    return hipGetLastError();
-  }
-}
-
+// `edge`: the tile does not divide the shape (masked loads and stores).
 template <class Cfg, int EPI, bool WAIT>
-static hipError_t launch_edge(int edge, const GemmArgs& a, int grid, hipStream_t s) {
-  if (edge == EDGE_ANY) return launch_one<Cfg, EPI, WAIT, EDGE_ANY>(a, grid, s);
-  if (edge == EDGE_ROWS) return launch_one<Cfg, EPI, WAIT, EDGE_ROWS>(a, grid, s);
-  return launch_one<Cfg, EPI, WAIT, EDGE_NONE>(a, grid, s);
+static hipError_t launch_one(int edge, const GemmArgs& a, int grid, hipStream_t s) {
+  if constexpr (!WAIT && Cfg::NSTAGE == 2 && Cfg::OCC == 1) {
+    if (a.persist_blocks > 0) {          // (only planned for shapes the tile divides)
+      hipLaunchKernelGGL((gemm_kernel_dma_resident<Cfg, EPI>), dim3(grid), dim3(Cfg::NT), 0, s, a);
+      return hipGetLastError();
+    }
+  }
+  if (edge) hipLaunchKernelGGL((gemm_kernel_dma<Cfg, EPI, WAIT, true>), dim3(grid), dim3(Cfg::NT), 0, s, a);
+  else hipLaunchKernelGGL((gemm_kernel_dma<Cfg, EPI, WAIT, false>), dim3(grid), dim3(Cfg::NT), 0, s, a);
+  return hipGetLastError();
 }
 
 template <class Cfg>
 static hipError_t launch_layout(int epi, int wait, int edge, const GemmArgs& a, int grid, hipStream_t s) {
-  if (epi == EPI_RS) return launch_edge<Cfg, EPI_RS, false>(edge, a, grid, s);
-  if (wait) return launch_edge<Cfg, EPI_PLAIN, true>(edge, a, grid, s);
-  return launch_edge<Cfg, EPI_PLAIN, false>(edge, a, grid, s);
+  if (epi == EPI_RS) return launch_one<Cfg, EPI_RS, false>(edge, a, grid, s);
+  if (wait) return launch_one<Cfg, EPI_PLAIN, true>(edge, a, grid, s);
+  return launch_one<Cfg, EPI_PLAIN, false>(edge, a, grid, s);
 }
 
 #define FLUX_CAT2(a, b) a##b
