@@ -681,16 +681,26 @@ static int take_trace(const Plan& pl, flux_trace_record_t** out) {
   return FLUX_OK;
 }
 
-static int launch_gemm(const Plan& pl, int epi, int wait, const GemmArgs& a, hipStream_t s) {
+// Fills in what depends on how the grid is launched.
+static int launch_gemm(const Plan& pl, int epi, int wait, GemmArgs& a, hipStream_t s) {
   const int grid = pl.full_tiles + pl.split_tiles * pl.split_k;
   hipEvent_t e0 = g_prof_start, e1 = g_prof_stop;
   g_prof_start = g_prof_stop = nullptr;
+  // The parts of a K-cut tile wait for each other and finish it together where they all fit the chip at the same time
+  // (they are the whole grid, or its last round).  Parts that give up waiting leave their share to the last one, so a
+  // chip that is busy with other kernels costs time, not results.  A tile added by atomic additions, or one that is to be
+  // counted in as ready by whoever writes it, stays with the part that arrives last.  So does a large tile in two parts:
+  // eight or more 16x32 blocks per wave, a round trip each, are slower than the last part's batches (512 x 8192 x 3584 with 7
+  // peers 62 against 57 us, three parts of 256 x 8192 x 8192 65 against 67, two of a 64x128 tile of 128 x 8192 x 4096 with
+  // 15 fp32 peers 38 against 45).
+  const bool share = pl.split_k > (pl.bm * pl.bn > 64 * 128 ? 2 : 1) && pl.split_k <= SK_SHARE_MAX && a.write_only != 2 && a.tile_ready == nullptr &&
+                     (long long)pl.split_tiles * pl.split_k <= (long long)N_CU * g_cfgs[pl.cfg].occupancy;
+  a.sk_share = share;
   if (e0) FLUX_HIP(hipEventRecord(e0, s));
   if (pl.resident && epi == EPI_RS && !wait && a.write_only == 0) {
-    GemmArgs b = a;
-    b.persist_blocks = grid;
-    b.persist_delay_ticks = pl.resident_delay_ticks;
-    FLUX_HIP(g_cfgs[pl.cfg].launch(epi, wait, pl.edge, b, N_CU, s));
+    a.persist_blocks = grid;
+    a.persist_delay_ticks = pl.resident_delay_ticks;
+    FLUX_HIP(g_cfgs[pl.cfg].launch(epi, wait, pl.edge, a, N_CU, s));
   } else {
     FLUX_HIP(g_cfgs[pl.cfg].launch(epi, wait, pl.edge, a, grid, s));
   }

@@ -37,6 +37,9 @@ constexpr size_t WS_COUNTER_OFF = 256;     // uint32 per communication tile (cop
 constexpr int MAX_COMM_TILES = 1024;
 constexpr size_t WS_TILECNT_OFF = WS_COUNTER_OFF + 4 * MAX_COMM_TILES;   // split-K arrival counters
 constexpr int MAX_SPLITK_TILES = 4096;
+// Counter of the st-th K-cut tile.  Neighbouring tiles' counters lie 256 bytes apart: atomics on one memory channel queue
+// up behind each other, tens of nanoseconds each, and the parts of all tiles arrive at about the same time.
+__host__ __device__ constexpr int sk_counter_index(int st) { return (st % 64) * (MAX_SPLITK_TILES / 64) + st / 64; }
 // Workgroups past their signal wait are counted in two levels: workgroup b adds to leaf b mod
 // DONE_LEAVES, whoever completes a leaf adds to the root (WS_DONE_OFF).  Hundreds of additions to one
 // address queue up behind each other (tens of nanoseconds each), and every workgroup waits for its
@@ -139,6 +142,7 @@ struct GemmArgs {
                              // 2: no peers are read, the tile is added to the slice with atomic additions
   float* sk_partials;             // [split_k][split_tiles][BM*BN] fp32
   uint32_t* sk_counters;          // [tiles]
+  int32_t sk_share;               // the parts of a tile share its final sum out among themselves (see finish_shared)
   int32_t partial_f32, out_f32;
   flux_trace_record_t* trace;     // tile trace, one record per workgroup; null: none
   uint32_t* tile_ready;           // reduce-scatter, Write branch: per output tile, producers that have written it; null: not kept
@@ -1035,6 +1039,161 @@ __device__ __forceinline__ void epilogue_all_atomic(const GemmArgs& a, void* con
   }
 }
 
+// ---- a K-cut tile finished by all of its parts --------------------------------------------------
+// Left to the part that arrives last, the end of a K-cut tile is a chain of round trips of ONE workgroup (all parts' sums
+// read back, then the peers' rows, batch after batch) at what one compute unit can pull, while the others are gone:
+// 4-8 us of an 18 us kernel (64 x 8192 x 3584, 4 parts, 7 peers), 15 us of 38 (200 x 3584 x 8192, 9 parts).  Where all parts
+// surely run at the same time (sk_share, decided on the host), each parks its sums, asks for the peers' rows of its
+// share of the tile, waits for the other parts, and finishes that share: one round trip for the
+// parts' sums, with the peers' rows already there.
+// A share is a range of 16x32 blocks of the tile, numbered wave tile by wave tile; a wave takes one block at a time.
+// The sum runs in split order, then peers in rank order, as ever: results do not depend on timing.
+// us per call, last part -> shared: rs 64 x 8192 x 3584 24.0 -> 21.5, ag 200 x 3584 x 8192 49.8 -> 40.1, rs 1080 x 408 x 6144
+// 48 -> 25, ag 8192 x 4608 x 12288 (its last round's 64 tiles in 4 parts) 754 -> 743.  (Asking for the next block's sums while
+// a block is finished made the small calls 0.5-1 us slower: the code of a tail runs once, and every line of it is fetched.)
+//
+// The tile's counter word: parts that have arrived in bits [6:0], parts that have seen all arrive in bits [13:7], parts
+// that gave up waiting (bounded: they may be kept from running) in bits [31:16].  Who gives up leaves its share to the
+// last to arrive, who reads in its own arrival whose those are.  The last to see the tile complete clears the word.
+constexpr uint32_t SK_SEEN = 1u << 7, SK_GAVE_UP = 1u << 16;
+constexpr int SK_SHARE_MAX = 16;                      // parts of a tile whose shares fit the word
+constexpr unsigned long long SK_WAIT_TICKS = 10000;   // 100 us
+
+template <class C, int EPI, bool EDGE, bool PF32, int NP>
+struct SharedFinish {
+  static constexpr int LPP = PF32 ? 2 : 1;            // 16-byte loads per peer and lane
+  static constexpr int NPA = NP > 0 ? NP : 1;
+  static constexpr int BLOCKS_W = C::MI * (C::NI / 2);          // 16x32 blocks of a wave tile
+  static constexpr int BLOCKS = (C::NT / 64) * BLOCKS_W;
+  static constexpr int STRIDE = 36;                   // floats per staged row: rows stay 16-byte aligned
+  static_assert(C::NI % 2 == 0 && 16 * STRIDE <= 32 * C::EP_STRIDE, "a block is staged in a wave's part of the staging area");
+
+  // where this lane's eight columns of block u lie (row and column within the tile)
+  static __device__ __forceinline__ void place(int u, int lane, int& row, int& col) {
+    const int w = u / BLOCKS_W, v = u % BLOCKS_W;
+    row = (w / C::WAVES_N) * C::WTM + (v / (C::NI / 2)) * 16 + lane / 4;
+    col = (w % C::WAVES_N) * C::WTN + (v % (C::NI / 2)) * 32 + (lane % 4) * 8;
+  }
+  static __device__ __forceinline__ void load_peers(const GemmArgs& a, const PeerBufs& pb, int u, int m0, int n0, int lane, u32x4 (&w)[NPA][LPP]) {
+    int row, col;
+    place(u, lane, row, col);
+    const bool ok = !EDGE || (m0 + row < a.M && n0 + col < a.N);
+    const int voff = ok ? (int)(((uint32_t)row * (uint32_t)a.N + (uint32_t)col) * (PF32 ? 4u : 2u)) : (int)0x80000000;
+#pragma unroll
+    for (int j = 0; j < NP; ++j)
+#pragma unroll
+      for (int l = 0; l < LPP; ++l) w[j][l] = __builtin_amdgcn_raw_buffer_load_b128(pb.r[j], voff + 16 * l, 0, 2);
+  }
+  static __device__ __forceinline__ void block(const GemmArgs& a, void* const* lds_outs, float* ep, int u, int st, int m0, int n0, int lane,
+                                               const u32x4 (&w)[NPA][LPP]) {
+    constexpr int SC1 = 16;
+    constexpr int BLOCK_BYTES = C::BM * C::BN * 4;
+    const int wv = u / BLOCKS_W, v = u % BLOCKS_W;
+    const int mi = v / (C::NI / 2), ni = v % (C::NI / 2) * 2;
+    const int off = ((mi * C::NI + ni) * C::NT + wv * 64 + lane) * 16;
+    const bool past = EDGE && m0 + (wv / C::WAVES_N) * C::WTM + mi * 16 + 4 * (lane >> 4) >= a.M;    // (never parked)
+    f32x4 sum[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    constexpr int PB = 8;                             // parts whose loads are out together
+    for (int s0 = 0; s0 < a.split_k; s0 += PB) {
+      u32x4 x[PB][2];
+#pragma unroll
+      for (int g = 0; g < PB; ++g) {
+        const int s = s0 + g;
+        const bool none = s >= a.split_k;
+        float* part = a.sk_partials + ((size_t)(none ? 0 : s) * a.split_tiles + st) * (C::BM * C::BN);
+        __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(part, 0, BLOCK_BYTES, 0x00027000);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) x[g][i] = __builtin_amdgcn_raw_buffer_load_b128(r, none || past ? BLOCK_BYTES : off + i * C::NT * 16, 0, SC1);
+      }
+      __builtin_amdgcn_sched_barrier(0);              // all of them before the first is waited for
+#pragma unroll
+      for (int g = 0; g < PB; ++g)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sum[i][e] += __uint_as_float(x[g][i][e]);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ep[(4 * (lane >> 4) + e) * STRIDE + i * 16 + (lane & 15)] = sum[i][e];
+    __builtin_amdgcn_wave_barrier();
+    const float4 y = *reinterpret_cast<const float4*>(ep + (lane / 4) * STRIDE + (lane % 4) * 8);
+    const float4 z = *reinterpret_cast<const float4*>(ep + (lane / 4) * STRIDE + (lane % 4) * 8 + 4);
+    __builtin_amdgcn_wave_barrier();
+    float o[8] = {y.x, y.y, y.z, y.w, z.x, z.y, z.z, z.w};
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+      if (PF32) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { o[e] += __uint_as_float(w[j][0][e]); o[4 + e] += __uint_as_float(w[j][LPP - 1][e]); }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { o[2 * e] += bf16_lo(w[j][0][e]); o[2 * e + 1] += bf16_hi(w[j][0][e]); }
+      }
+    }
+    int row, col;
+    place(u, lane, row, col);
+    if (!EDGE || (m0 + row < a.M && n0 + col < a.N)) store_row8<EPI>(a, lds_outs, m0 + row, n0 + col, o);
+  }
+
+  // Called by every part once its sums are parked and acknowledged.  `lds_misc`: two ints of the workgroup.
+  static __device__ __forceinline__ void run(const GemmArgs& a, int* lds_misc, void* const* lds_outs, float* ep, int tile, int split,
+                                             int m0, int n0, int tid, int lane, int wave) {
+    const int st = tile - a.full_tiles, S = a.split_k;
+    uint32_t* const word = a.sk_counters + sk_counter_index(st);
+    constexpr int NW = C::NT / 64;
+    PeerBufs pb;
+    if (NP > 0) make_peer_bufs(a, m0, n0, pb);
+    int u = BLOCKS * split / S + wave;
+    const int u_end = BLOCKS * (split + 1) / S;
+    u32x4 w[NPA][LPP];
+    if (NP > 0 && u < u_end) load_peers(a, pb, u, m0, n0, lane, w);       // on their way during the wait
+    if (tid == 0) {
+      uint32_t extra = 0u;                            // parts whose shares fall to this one
+      int mine = 1;
+      const uint32_t prev = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if ((prev & 127u) + 1u == (uint32_t)S) {
+        extra = prev >> 16;
+      } else {
+        const unsigned long long t0 = wall_clock64();
+        const unsigned long long limit = a.timeout_ticks < SK_WAIT_TICKS ? a.timeout_ticks : SK_WAIT_TICKS;
+        while ((__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 127u) != (uint32_t)S) {
+          if (wall_clock64() - t0 > limit) {
+            const uint32_t old = __hip_atomic_fetch_or(word, SK_GAVE_UP << split, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            mine = (old & 127u) == (uint32_t)S;       // (all there after all: the last one did not see this part give up)
+            break;
+          }
+          __builtin_amdgcn_s_sleep(1);
+        }
+      }
+      lds_misc[0] = mine;
+      lds_misc[1] = (int)extra;
+    }
+    __syncthreads();
+    const int mine = __builtin_amdgcn_readfirstlane(lds_misc[0]);
+    uint32_t extra = (uint32_t)__builtin_amdgcn_readfirstlane(lds_misc[1]);
+    if (tid == 0) {
+      // seen; whoever completes that clears the word for the next launch.  (A part that gave up counts too.)
+      const uint32_t prev = __hip_atomic_fetch_add(word, SK_SEEN, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (((prev >> 7) & 127u) + 1u == (uint32_t)S) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (!mine) return;
+    for (; u < u_end;) {
+      block(a, lds_outs, ep, u, st, m0, n0, lane, w);
+      u += NW;
+      if (NP > 0 && u < u_end) load_peers(a, pb, u, m0, n0, lane, w);
+    }
+    for (; extra != 0u; extra &= extra - 1u) {
+      const int s = __builtin_ctz(extra);
+      for (int x = BLOCKS * s / S + wave; x < BLOCKS * (s + 1) / S; x += NW) {
+        if (NP > 0) load_peers(a, pb, x, m0, n0, lane, w);
+        block(a, lds_outs, ep, x, st, m0, n0, lane, w);
+      }
+    }
+  }
+};
+
 // Everything after the main loop: the split-K hand-over (all but the last-arriving workgroup of
 // a tile park their partial sums, the last one adds them up) and the epilogue, in which the
 // accumulators pass through LDS once (per wave, 32 rows at a time) so that every lane ends up
@@ -1072,11 +1231,25 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
       }
     __builtin_amdgcn_s_waitcnt(0x0F70);                   // vmcnt(0): stores acknowledged
     __syncthreads();
+    if (a.sk_share) {                                     // (uniform)
+      float* const ep = reinterpret_cast<float*>(smem) + wave * (32 * C::EP_STRIDE);
+      if (EPI != EPI_RS || a.write_only) SharedFinish<C, EPI, EDGE, false, 0>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
+      else if (a.R <= 8) {
+        if (a.partial_f32) SharedFinish<C, EPI, EDGE, true, 7>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
+        else SharedFinish<C, EPI, EDGE, false, 7>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
+      } else {
+        if (a.partial_f32) SharedFinish<C, EPI, EDGE, true, 15>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
+        else SharedFinish<C, EPI, EDGE, false, 15>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
+      }
+      trace_stamp(a, TRACE_END, vb);
+      return;
+    }
     int* lds_last = lds_misc;
     if (tid == 0) {
-      const uint32_t prev = __hip_atomic_fetch_add(a.sk_counters + st, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      uint32_t* const word = a.sk_counters + sk_counter_index(st);
+      const uint32_t prev = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const int last = prev == (uint32_t)(a.split_k - 1);
-      if (last) __hip_atomic_store(a.sk_counters + st, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
+      if (last) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
       *lds_last = last;
     }
     __syncthreads();

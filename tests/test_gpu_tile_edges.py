@@ -45,3 +45,32 @@ def test_all_gather_of_a_ragged_shape(M, N, K):
     assert status == (fb.FLUX_OK, 0)
     assert torch.equal(A_agg.cpu(), torch.cat(chunks))
     gh.assert_bits_equal(C, want, f"{(M, N, K)}")
+
+
+@pytest.mark.parametrize("R,pd", [(1, "bf16"), (8, "bf16"), (8, "f32"), (16, "bf16"), (16, "f32")])
+@pytest.mark.parametrize("cfg,M,N,K,split", [(9, 64, 256, 1024, 4), (8, 16, 256, 1024, 9), (9, 48, 264, 1000, 2), (2, 208, 264, 640, 3),
+                                             (1, 256, 256, 1024, 16), (10, 128, 136, 520, 5), (9, 64, 128, 1088, 17)])
+def test_k_cut_tile_finished_by_its_parts(cfg, M, N, K, split, R, pd):
+    """All parts of a tile finish it together (up to 16 of them; 17 leave it to the last), also where every part but the
+    last gives up waiting at once (a spin limit of one tick: its share falls to the last); the counters must be
+    clear again after each call."""
+    w = fi.Workload("parts", "rs", M, N, K, R, partial_dtype=pd, out_dtype=pd, a_dist=("int", 2), b_dist=("int", 2),
+                    peer_dist=("int", 8), seed=M + K + R)
+    rank = R - 1
+    A, B, peers = fi.make_rs_inputs(w, rank)
+    _, want = gh.oracle_rs(w, rank, A, B, peers)
+    dA, dB = A.to(gh.DEV), B.to(gh.DEV)
+    dpeers = [None if t is None else t.to(gh.DEV) for t in peers]
+    ws = None
+    for ticks in (0, 1, 0, 1):
+        p = fb.problem(M, N, K, R, rank, pd, pd, cfg, split, spin_timeout_ticks=ticks)
+        if ws is None:
+            ws = gh.workspace_for(fb.FLUX_OP_RS, p)
+            ws.fill_(-1)
+            fb.flux_init_buffers(fb.FLUX_OP_RS, p, ws)
+        outs = [torch.full((w.S, N), float("nan"), dtype=torch.bfloat16 if pd == "bf16" else torch.float32, device=gh.DEV) for _ in range(R)]
+        _say("parts cfg", cfg, (M, N, K), "split", split, "R", R, pd, "ticks", ticks)
+        fb.flux_gemm_rs(p, dA, dB, dpeers, outs, ws)
+        torch.cuda.synchronize()
+        for r in range(R):
+            gh.assert_bits_equal(outs[r], want[r], f"ticks {ticks} slice {r}")
