@@ -1112,6 +1112,12 @@ int flux_ag_gemm(const flux_problem_t* p, const void* const* A_chunks, void* A_a
   // communication tile
   a.acquire_l2 = (reinterpret_cast<uintptr_t>(A_agg) % 128 != 0) || (((size_t)pitch_a(p) * 2) % 128 != 0);
   const uint32_t call_id = next_call_id();
+  // A local chunk that is not in place yet is moved by the grid like the remote ones, ahead of them, where the grid moves
+  // everything; a grid that keeps a link's schedule (whose tiles are counted from the first remote one), a driver, or R = 1
+  // has it copied by a kernel of its own ahead of the grid.
+  const __bf16* local_dst = static_cast<const __bf16*>(A_agg) + (size_t)p->rank * (p->M / p->R) * pitch_a(p);
+  const bool local_away = A_chunks[p->rank] != static_cast<const void*>(local_dst);
+  const bool local_in_grid = local_away && pl.copy_self && pl.pace_ticks == 0 && p->R > 1;
   if (pl.copy_help && p->R > 1) {
     a.copy_pieces = pl.copy_pieces;
     a.copy_driver_wgs = pl.copy_self ? 0 : pl.copy_wgs;
@@ -1124,12 +1130,14 @@ int flux_ag_gemm(const flux_problem_t* p, const void* const* A_chunks, void* A_a
     for (int r = 0; r < p->R; ++r) a.outs[r] = const_cast<void*>(A_chunks[r]);   // chunk sources by rank
     if (pl.copy_self) {
       a.copy_owner_wgs = pl.copy_owners;
-      a.copy_n_tiles = (p->R - 1) * pl.ctpc;
+      a.copy_local = local_in_grid;
+      a.copy_n_tiles = (p->R - 1 + (local_in_grid ? 1 : 0)) * pl.ctpc;
       a.copy_defer_tiles = pl.defer_tiles;
       a.copy_defer_steps = pl.defer_steps;
       a.copy_pace_ticks = pl.pace_ticks;
       static_assert(FLUX_MAX_RANKS <= 16, "chunk indices are packed four bits each");
-      for (int i = 0; i < p->R - 1; ++i) a.copy_order4 |= (unsigned long long)order[i] << (4 * i);
+      if (local_in_grid) a.copy_order4 = (unsigned long long)p->rank;
+      for (int i = 0; i < p->R - 1; ++i) a.copy_order4 |= (unsigned long long)order[i] << (4 * (i + (local_in_grid ? 1 : 0)));
     }
   }
   if ((p->flags & FLUX_FLAG_COPY_MEMCPY) && p->R > 1) {
@@ -1153,8 +1161,7 @@ int flux_ag_gemm(const flux_problem_t* p, const void* const* A_chunks, void* A_a
   }
 
   // local chunk (its signal is preset, so it must be in place before the kernel starts)
-  const __bf16* local_dst = static_cast<const __bf16*>(A_agg) + (size_t)p->rank * (p->M / p->R) * pitch_a(p);
-  if (A_chunks[p->rank] != static_cast<const void*>(local_dst)) {
+  if (local_away && !local_in_grid) {
     int self = p->rank;
     st = launch_copy(p, pl, A_chunks, A_agg, &self, 1, false, nullptr, nullptr, 0, cs);
     if (st != FLUX_OK) return st;

@@ -129,6 +129,10 @@ struct GemmArgs {
   uint32_t copy_call_id;     // 0: take the id from copy_call_seq (calls without a copy kernel)
   int32_t copy_driver_wgs;   // workgroups of the copy kernel launched beside this grid (0: none)
   int32_t copy_n_tiles;
+  // The rank's own chunk lies in a buffer of its own and is moved by the grid too, ahead of the remote ones (copy_n_tiles
+  // counts it, its tiles come first).  Its signals are preset, so a tile of it has arrived when its word in copy_counters
+  // reads copy_pieces.  (See tile_arrived.)
+  int32_t copy_local;
   // The last copy_defer_tiles remote communication tiles of the transfer order are not moved before
   // the signal wait: the workgroups of the first round carry them inside their main loops (piece w
   // of each such tile by workgroup w, copy_defer_steps 16-byte vectors per thread and tile).
@@ -525,23 +529,40 @@ __device__ __forceinline__ bool claim_piece(uint32_t* claim, uint32_t call_id) {
   return __hip_atomic_exchange(claim, call_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != call_id;
 }
 
-// After the stores of `n` pieces of one tile: wait until they are acknowledged, count the pieces
-// in, set the signal if they were the tile's last.  All threads of the workgroup call this.
-__device__ __forceinline__ void finish_pieces(uint32_t* counter, uint32_t* signal, int pieces, int n) {
-  __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0): this wave's write-through stores are acknowledged
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    if (n == pieces) {
-      // the whole tile was this workgroup's (a small transfer: one piece per tile): nobody else counts, no round trip
+// Communication tile f has arrived: its signal is set, or, for a tile of a local chunk that the grid moves (its signal is
+// preset to 1 throughout), all of its pieces have been counted in.  The last workgroup past its wait clears those counts.
+//
+// The local chunk used to be put in place by a kernel of its own ahead of the grid: a launch, its drain and 400 KB..6 MB of
+// copy that nothing overlapped with (ag 200 x 3584 x 8192 with the chunk in a buffer of its own: 39.5 us per call with it, 37.1
+// with the grid moving it; 3000 x 3584 x 8192 185 -> 175 us).
+__device__ __forceinline__ bool moved_local(const GemmArgs& a, int f) { return a.copy_local && f >= a.sig_local_lo && f < a.sig_local_hi; }
+__device__ __forceinline__ bool tile_arrived(const GemmArgs& a, int f) {
+  const bool local = moved_local(a, f);
+  const uint32_t v = __hip_atomic_load(local ? a.copy_counters + f : a.signals + f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  return local ? v == (uint32_t)a.copy_pieces : v != 0u;
+}
+// `n` of the `pieces` pieces of tile f are in place (their stores acknowledged): count them in, set the signal if they were the
+// tile's last.  One thread calls this.
+__device__ __forceinline__ void count_pieces_in(uint32_t* counter, uint32_t* signal, int pieces, int n, bool local) {
+  if (n == pieces) {
+    // the whole tile was this workgroup's (a small transfer: one piece per tile): nobody else counts, no round trip
+    if (local) __hip_atomic_store(counter, (uint32_t)pieces, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else __hip_atomic_store(signal, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  } else {
+    const uint32_t prev = __hip_atomic_fetch_add(counter, (uint32_t)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!local && prev + (uint32_t)n == (uint32_t)pieces) {
+      __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
       __hip_atomic_store(signal, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    } else {
-      const uint32_t prev = __hip_atomic_fetch_add(counter, (uint32_t)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (prev + (uint32_t)n == (uint32_t)pieces) {
-        __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
-        __hip_atomic_store(signal, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      }
     }
   }
+}
+
+// After the stores of `n` pieces of one tile: wait until they are acknowledged, then count the pieces in.
+// All threads of the workgroup call this.
+__device__ __forceinline__ void finish_pieces(uint32_t* counter, uint32_t* signal, int pieces, int n, bool local = false) {
+  __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0): this wave's write-through stores are acknowledged
+  __syncthreads();
+  if (threadIdx.x == 0) count_pieces_in(counter, signal, pieces, n, local);
   // Callers loop: without a barrier here, this one-thread block and the one-thread block that
   // opens the caller's next iteration (a claim, a counter fetch) are adjacent across the back
   // edge, and the compiler has been seen to merge them into one divergent region that the other
@@ -604,7 +625,7 @@ __device__ __forceinline__ void transfer_own_pieces(const GemmArgs& a, int* lds,
     __syncthreads();
     if (lds[2]) {
       store_piece(dst, a.copy_tile_vec, piece, a.copy_pieces, tid, v, agg_pitch(a));
-      finish_pieces(a.copy_counters + f, a.signals + f, a.copy_pieces, 1);
+      finish_pieces(a.copy_counters + f, a.signals + f, a.copy_pieces, 1, moved_local(a, f));
     }
     return;
   }
@@ -638,11 +659,7 @@ __device__ __forceinline__ void transfer_own_pieces(const GemmArgs& a, int* lds,
       const int g = base + tid * G;
       const int j = g / a.copy_pieces;
       const int f = (int)((a.copy_order4 >> (4 * (j / ctpc))) & 15) * ctpc + j % ctpc;
-      const uint32_t prev = __hip_atomic_fetch_add(a.copy_counters + f, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (prev + 1u == (uint32_t)a.copy_pieces) {
-        __hip_atomic_store(a.copy_counters + f, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
-        __hip_atomic_store(a.signals + f, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      }
+      count_pieces_in(a.copy_counters + f, a.signals + f, a.copy_pieces, 1, moved_local(a, f));
     }
     __syncthreads();
   }
@@ -772,11 +789,7 @@ struct SideCopy {
         if (!((mine >> t) & 1u)) continue;
         int f, chunk, sub;
         locate(a, t, f, chunk, sub);
-        const uint32_t prev = __hip_atomic_fetch_add(a.copy_counters + f, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (prev + 1u == (uint32_t)a.copy_pieces) {
-          __hip_atomic_store(a.copy_counters + f, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
-          __hip_atomic_store(a.signals + f, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        }
+        count_pieces_in(a.copy_counters + f, a.signals + f, a.copy_pieces, 1, false);      // (deferred tiles are remote)
       }
       *slot = upto;
     }
@@ -823,8 +836,7 @@ __device__ __forceinline__ bool signals_all_set(const GemmArgs& a, int m0, int m
   if (threadIdx.x < 64) {
     bool any = false;
     for (int base = 0; base < nf; base += 64) {
-      const bool unset = base + (int)threadIdx.x < nf &&
-                         __hip_atomic_load(a.signals + f0 + base + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == 0u;
+      const bool unset = base + (int)threadIdx.x < nf && !tile_arrived(a, f0 + base + (int)threadIdx.x);
       any = any || __ballot(unset) != 0ull;
     }
     if (threadIdx.x == 0) *slot = any ? 0 : 1;
@@ -871,8 +883,7 @@ __device__ __forceinline__ bool wait_signals(const GemmArgs& a, int m0, int m1, 
       for (int polls = 0;; ++polls) {
         first_missing = -1;
         for (int base = 0; base < nf && first_missing < 0; base += 64) {
-          const bool unset = base + tid < nf &&
-                             __hip_atomic_load(a.signals + f0 + base + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == 0u;
+          const bool unset = base + tid < nf && !tile_arrived(a, f0 + base + tid);
           const unsigned long long missing = __ballot(unset);
           if (missing != 0) first_missing = f0 + base + __builtin_ctzll(missing);
         }
@@ -941,15 +952,15 @@ __device__ __forceinline__ bool wait_signals(const GemmArgs& a, int m0, int m1, 
     }
     // One of the unclaimed pieces among the tiles of the window, picked by a hash that differs per
     // workgroup and attempt: workgroups that wait for the same tiles then rarely go for the same
-    // piece (taking "the first free one" would make them queue up behind each other).  The local
-    // chunk's tiles are never copied by anyone, their signals are preset.
+    // piece (taking "the first free one" would make them queue up behind each other).  A local
+    // chunk that is in place already is not copied by anyone, its signals are preset.
     if (!have_call_id) { call_id = transfer_call_id(a); have_call_id = true; }
     const int wt = f1 - w0 + 1 < window_tiles ? f1 - w0 + 1 : window_tiles;
     const int total = wt * a.copy_pieces;
     salt = salt * 1664525u + 1013904223u;
     for (int i = tid; i < total; i += blockDim.x) {
       const int f = w0 + i / a.copy_pieces;
-      if (f >= a.sig_local_lo && f < a.sig_local_hi) continue;
+      if (!a.copy_local && f >= a.sig_local_lo && f < a.sig_local_hi) continue;
       if (__hip_atomic_load(a.copy_claims + (size_t)f * a.copy_pieces + i % a.copy_pieces, __ATOMIC_RELAXED,
                             __HIP_MEMORY_SCOPE_AGENT) != call_id) {
         const uint32_t h = ((uint32_t)i * 2654435761u) ^ salt;
@@ -967,7 +978,7 @@ __device__ __forceinline__ bool wait_signals(const GemmArgs& a, int m0, int m1, 
         const int ctpc = a.n_signals / a.R;
         const uint4* src = static_cast<const uint4*>(lds_srcs[f / ctpc]) + (unsigned long long)(f % ctpc) * a.copy_tile_vec;
         copy_piece(src, agg_tile(a, f), a.copy_tile_vec, piece, a.copy_pieces, tid, agg_pitch(a));
-        finish_pieces(a.copy_counters + f, a.signals + f, a.copy_pieces, 1);
+        finish_pieces(a.copy_counters + f, a.signals + f, a.copy_pieces, 1, moved_local(a, f));
       }
     } else {
       dead_w0 = w0;                     // every piece of this window is in the hands of a workgroup that is running
@@ -999,6 +1010,9 @@ __device__ __forceinline__ bool wait_signals(const GemmArgs& a, int m0, int m1, 
       for (int i = 0; i < a.n_signals; ++i)
         __hip_atomic_store(a.signals + i, (i >= a.sig_local_lo && i < a.sig_local_hi) ? 1u : 0u, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_SYSTEM);
+      if (a.copy_local)
+        for (int i = a.sig_local_lo; i < a.sig_local_hi; ++i)
+          __hip_atomic_store(a.copy_counters + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (a.copy_pieces > 0 && a.copy_call_id == 0u)
         __hip_atomic_fetch_add(a.copy_call_seq, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (a.copy_driver_wgs > 0)
