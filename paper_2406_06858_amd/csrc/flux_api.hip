@@ -359,7 +359,7 @@ static void plan_split(const flux_problem_t* p, int cfg, long long tiles, int kt
 // Estimated time of the GEMM under configuration `cfg`, in arbitrary units: rounds of the grid
 // over the chip's workgroup slots, times the tile's area, over the configuration's rate per slot
 // (from measurements of full grids: 256x256 = 1, 256x128 on three stages 0.84, 128x128 two per
-// CU 0.8 per CU; a ragged shape runs the register-staged kernel at about 0.7 of that).
+// CU 0.8 per CU; a shape the tile does not divide 0.7 of that, so that of two near ones the tile that divides it is taken).
 static double plan_cost(const flux_problem_t* p, int cfg) {
   const int bm = g_cfgs[cfg].bm, bn = g_cfgs[cfg].bn, bk = g_cfgs[cfg].bk;
   const long long tiles = (long long)((p->M + bm - 1) / bm) * ((p->N + bn - 1) / bn);
@@ -384,9 +384,11 @@ static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
   if (p->tile_config > 0) {
     cfg = p->tile_config - 1;
   } else {
-    // few rows: the tile is bound by memory, so take the deep load pipeline if the shape allows its
-    // direct-to-LDS loads (whole tiles along N and K; M may be ragged), else the two-stage twin
+    // few rows: the tile is bound by memory, so take the deep load pipeline
     const bool deep_ok = p->K % 64 == 0;
+    const long long weights = (long long)p->N * p->K;
+    // 64x128 tiles on four stages, for any rows, columns and K (masked loads): tiles of one round of the chip
+    const bool one_round = (long long)((p->M + 63) / 64) * ((p->N + 127) / 128) <= N_CU;
     if (p->M <= 32) cfg = (deep_ok && p->N % 128 == 0) ? 7 : 5;          // 32x128
     else if (p->M == 64 && deep_ok && p->N % 128 == 0 && p->N / 128 <= N_CU &&
              std::min<long long>(N_CU / (p->N / 128), p->K / 64 / 8) <= 5) {
@@ -395,8 +397,18 @@ static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
       // whose grid leaves a quarter of the chip idle there; no difference on 8192x3584 and 8192x8192)
       cfg = 8;
     }
-    else if (p->M <= 64) cfg = (deep_ok && p->N % 64 == 0 && p->M == 64) ? 6 : 4;   // 64x64 deep, else 64x128
-    else if ((long long)p->M * p->N <= 256ll * 1024) cfg = 3;            // 64x64, small problems
+    else if (p->M <= 64) {
+      // 64x64 on six stages, else 64x128: on four stages where K is long enough to fill them (us, four against two stages:
+      // 48 rows 12288x6144 41 / 57, 6144x4608 20 / 27, 3584x6144 19.2 / 21.6, 1536x4608 12.4 / 12.6), on two stages with
+      // their finer K cut below (1536x1536 12.9 / 10.7, 3584x1536 13.7 / 12.2, 40 rows 1000x2008 15.7 / 14.7)
+      cfg = (deep_ok && p->N % 64 == 0 && p->M == 64) ? 6 : p->K > 2048 ? 8 : 4;
+    }
+    else if ((long long)p->M * p->N <= 256ll * 1024 && weights <= 4ll * 1024 * 1024) {
+      // 64x64, small problems, up to weights of 4M values (us, 64x64 on two against 64x128 on four stages: 72x1536x1536 9.9 /
+      // 13.5, 136x1536x1536 12.1 / 14.1, 128x2048x2048 10.2 / 10.8, 128x1024x4096 15.7 / 16.0; above 72x3584x1536 18.3 / 14.5,
+      // 72x3000x4096 27.0 / 13.6, 136x1536x4608 22.1 / 14.9)
+      cfg = 3;
+    }
     else if (p->M == 128 && deep_ok && p->N % 128 == 0 && p->K > 8192 && 2ll * (p->N / 128) <= N_CU / 2) {
       // Two m-tiles, a long K and few columns: the two-per-CU 64x128 tile, whose finer K cut fills
       // its 512 slots (6144x12288: 55 against 66 us for 64x128 on four stages, weights from HBM).
@@ -419,6 +431,16 @@ static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
       cfg = 9;
     }
     else if (p->M <= 256 && p->M % 64 == 0 && deep_ok && p->N % 128 == 0) cfg = 8;   // 64x128 deep
+    else if (one_round && (p->M < 128 ? p->K <= 8192 : p->M <= 512 && (p->K <= 4096 || weights <= 20ll * 1000 * 1000))) {
+      // Rows that no case above takes, whose 64x128 tiles fit the chip at once.  They read the weights once per 64
+      // rows, 256x128 tiles once per 256, but with fewer K parts, and smaller ones to hand over, each.  Up to 127 rows
+      // that wins up to K = 8192 (us, 256x128 or what was taken / 64x128: 72 rows 3584x8192 39 / 28, 8192x3584 24.3 / 21.3,
+      // 12288x6144 70 / 54; 4608x12288 41 / 48), up to 512 rows with a short K or few weights (200 rows 8192x3584 34.9 / 27.6,
+      // 1536x1536 28.5 / 14.4, 3584x4608 25.9 / 24.1, 1536x6144 23.8 / 21.2; 512 rows 3584x1536 34.0 / 18.2; the other side:
+      // 136, 200 and 320 rows 3584x6144 25.2 / 27.3, 28.1 / 29.3, 36.3 / 40.8, 200 rows 6144x6144 40 / 52, 512 rows
+      // 6144x1536, 384 tiles, 28.2 / 28.9).
+      cfg = 8;
+    }
     else {
       // Large tiles: 256x256 moves the least operand data per flop but needs a grid that fills the
       // chip round by round; 256x128 and 128x128 give two and four times the tiles.  Take the one

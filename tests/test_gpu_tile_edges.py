@@ -47,6 +47,30 @@ def test_all_gather_of_a_ragged_shape(M, N, K):
     gh.assert_bits_equal(C, want, f"{(M, N, K)}")
 
 
+@pytest.mark.parametrize("op", ["ag", "rs"])
+@pytest.mark.parametrize("M,N,K,tile", [(40, 1544, 2056, (64, 128)), (40, 1544, 2048, (64, 128)), (72, 1544, 2760, (64, 128)), (72, 1544, 2712, (64, 64)),
+                                        (200, 4200, 1000, (64, 128)), (512, 584, 2056, (64, 128)), (328, 1032, 4104, (64, 128)), (520, 584, 2056, None)])
+def test_tile_of_few_ragged_rows(op, M, N, K, tile):
+    """The configuration the library takes to either side of its lines for few rows: K, size of the weights, rows."""
+    p = fb.problem(M, N, K, 8, 5)
+    got = fb.flux_tile_shape(fb.FLUX_OP_AG if op == "ag" else fb.FLUX_OP_RS, p)
+    assert tile is None or (got.tile_m, got.tile_n) == tile
+    w = fi.Workload("few_rows", op, M, N, K, 8, a_dist=("int", 2), b_dist=("int", 2), peer_dist=("int", 8), seed=M + K)
+    _say("few rows", op, (M, N, K))
+    if op == "ag":
+        chunks, B, arrival = fi.make_ag_inputs(w, 5)
+        _, want = gh.oracle_ag(w, chunks, B)
+        C, _, _, status = gh.run_ag(w, 5, chunks, B, arrival, repeat=2)
+        assert status == (fb.FLUX_OK, 0)
+        gh.assert_bits_equal(C, want, f"{(M, N, K)}")
+    else:
+        A, B, peers = fi.make_rs_inputs(w, 5)
+        _, want = gh.oracle_rs(w, 5, A, B, peers)
+        _, outs = _rs_call(w, 5, A, B, peers, (8, 16, 8))
+        for r in range(w.R):
+            gh.assert_bits_equal(outs[r][1], want[r], f"{(M, N, K)} slice {r}")
+
+
 @pytest.mark.parametrize("R,pd", [(1, "bf16"), (8, "bf16"), (8, "f32"), (16, "bf16"), (16, "f32")])
 @pytest.mark.parametrize("cfg,M,N,K,split", [(9, 64, 256, 1024, 4), (8, 16, 256, 1024, 9), (9, 48, 264, 1000, 2), (2, 208, 264, 640, 3),
                                              (1, 256, 256, 1024, 16), (10, 128, 136, 520, 5), (9, 64, 128, 1088, 17)])
