@@ -322,6 +322,9 @@ static int validate_problem(int op, const flux_problem_t* p) {
   return FLUX_OK;
 }
 
+constexpr long long MAX_AUTO_PARTS = 16;   // SK_SHARE_MAX: with more parts the last one to arrive sums them all (us, up to 24 parts
+// against 16: rs 48x1536x12288 23.4 / 16.0, rs 64x512x12288 17.4 / 12.5, ag 40x1536x12288 23.5 / 19.3, rs 8x1536x12288 17.0 / 14.4)
+
 // How K is cut for configuration `cfg`: `split` parts for the last `split_tiles` tiles of the grid
 // (all of them for a uniform split), none for the others.
 static void plan_split(const flux_problem_t* p, int cfg, long long tiles, int kt, int* split_out, long long* split_tiles_out) {
@@ -331,8 +334,8 @@ static void plan_split(const flux_problem_t* p, int cfg, long long tiles, int kt
     split = 1;
     if (g_cfgs[cfg].stages > 2) {
       // deep pipeline, one workgroup per CU: as many K parts as still give a single round, each
-      // long enough for the pipeline to fill
-      if (tiles < slots) split = (int)std::max<long long>(1, std::min<long long>(slots / tiles, kt / 8));
+      // long enough for the pipeline to fill, and no more than can finish the tile together
+      if (tiles < slots) split = (int)std::max<long long>(1, std::min<long long>({slots / tiles, kt / 8, MAX_AUTO_PARTS}));
     } else if (tiles < 256) {                   // too few tiles to fill the chip: cut K as well
       split = (int)std::min<long long>((512 + tiles - 1) / tiles, 16);
       split = std::max(1, std::min(split, kt / 4));
