@@ -282,6 +282,12 @@ struct Plan {
 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// Do the `na` bytes at a and the `nb` bytes at b share any?
+static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + nb && y < x + na;
+}
+
 // Row pitches in elements (0 in the problem: packed).
 static inline long long pitch_a(const flux_problem_t* p) { return p->lda ? p->lda : p->K; }
 static inline long long pitch_b(const flux_problem_t* p) { return p->ldb ? p->ldb : (p->b_is_nk ? p->K : p->N); }
@@ -1139,10 +1145,15 @@ int flux_ag_gemm(const flux_problem_t* p, const void* const* A_chunks, void* A_a
   const uint32_t call_id = next_call_id();
   // A local chunk that is not in place yet is moved by the grid like the remote ones, ahead of them, where the grid moves
   // everything; a grid that keeps a link's schedule (whose tiles are counted from the first remote one), a driver, or R = 1
-  // has it copied by a kernel of its own ahead of the grid.
+  // has it copied by a kernel of its own ahead of the grid.  So does a chunk handed over inside the gathered matrix (in
+  // another chunk's rows, say) or inside C: the grid writes both while it would still be reading the chunk.
   const __bf16* local_dst = static_cast<const __bf16*>(A_agg) + (size_t)p->rank * (p->M / p->R) * pitch_a(p);
   const bool local_away = A_chunks[p->rank] != static_cast<const void*>(local_dst);
-  const bool local_in_grid = local_away && pl.copy_self && pl.pace_ticks == 0 && p->R > 1;
+  const size_t agg_bytes = ((size_t)(p->M - 1) * pitch_a(p) + p->K) * 2;
+  const size_t c_bytes = ((size_t)(p->M - 1) * pitch_c(p) + p->N) * (p->out_dtype == FLUX_F32 ? 4 : 2);
+  const bool local_in_grid = local_away && pl.copy_self && pl.pace_ticks == 0 && p->R > 1 &&
+                             !overlap(A_chunks[p->rank], chunk_elems * 2, A_agg, agg_bytes) &&
+                             !overlap(A_chunks[p->rank], chunk_elems * 2, C, c_bytes);
   if (pl.copy_help && p->R > 1) {
     a.copy_pieces = pl.copy_pieces;
     a.copy_driver_wgs = pl.copy_self ? 0 : pl.copy_wgs;

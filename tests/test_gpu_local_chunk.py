@@ -57,6 +57,38 @@ def test_local_chunk_moved_by_the_grid(M, N, K, R, ctpc, cfg, pitch):
         assert torch.equal(C, want), f"call {call}"
 
 
+@pytest.mark.parametrize("where", ["agg", "agg_across", "c"])
+@pytest.mark.parametrize("M,N,K,R,cfg", [(64, 512, 512, 8, 0), (1024, 1024, 1024, 4, 3), (2048, 2560, 1536, 8, 1)])
+def test_local_chunk_inside_what_the_call_writes(M, N, K, R, cfg, where):
+    """The local chunk handed over in another chunk's rows of the gathered matrix, across two chunks' rows, or in the first
+    rows of C: the call reads all of it before it writes there."""
+    w = fi.Workload("local_inside", "ag", M, N, K, R, a_dist=("int", 2), b_dist=("int", 2), seed=M + K + R)
+    rank = R - 1
+    chunks, B, arrival = fi.make_ag_inputs(w, rank)
+    dB = B.to(gh.DEV)
+    dchunks = [c.to(gh.DEV) for c in chunks]
+    gathered = torch.cat(dchunks)
+    want = (gathered.float() @ dB.float()).to(torch.bfloat16)           # exact in fp32: integers below 2^24
+    A_agg = torch.empty((M, K), dtype=torch.bfloat16, device=gh.DEV)
+    C = torch.empty((M, N), dtype=torch.bfloat16, device=gh.DEV)
+    at = {"agg": A_agg.flatten(), "agg_across": A_agg.flatten()[w.S // 2 * K:], "c": C.flatten()}[where][:w.S * K].view(w.S, K)
+    p = fb.problem(M, N, K, R, rank, "bf16", "bf16", cfg, spin_timeout_ticks=gh.TEST_TIMEOUT_TICKS)
+    signals = torch.zeros(R, dtype=torch.int32, device=gh.DEV)
+    ws = gh.workspace_for(fb.FLUX_OP_AG, p)
+    fb.flux_init_buffers(fb.FLUX_OP_AG, p, ws, signals)
+    copy = torch.cuda.Stream()
+    for call in range(3):
+        _say("local inside", where, (M, N, K), "R", R, "call", call)
+        A_agg.fill_(float("nan"))
+        C.fill_(float("nan"))
+        at.copy_(dchunks[rank])
+        fb.flux_ag_gemm(p, dchunks[:rank] + [at] + dchunks[rank + 1:], A_agg, dB, C, signals, arrival, ws, torch.cuda.current_stream(), copy)
+        torch.cuda.synchronize()
+        assert fb.flux_query_status(ws) == (fb.FLUX_OK, 0)
+        assert torch.equal(A_agg, gathered)
+        assert torch.equal(C, want), f"call {call}"
+
+
 @pytest.mark.parametrize("dt", ["bf16", "f32"])
 @pytest.mark.parametrize("R", range(1, 17))
 def test_slice_reduce_of_every_rank_count(R, dt):
