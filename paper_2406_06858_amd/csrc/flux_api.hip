@@ -328,8 +328,9 @@ static int validate_problem(int op, const flux_problem_t* p) {
   return FLUX_OK;
 }
 
-constexpr long long MAX_AUTO_PARTS = 16;   // SK_SHARE_MAX: with more parts the last one to arrive sums them all (us, up to 24 parts
-// against 16: rs 48x1536x12288 23.4 / 16.0, rs 64x512x12288 17.4 / 12.5, ag 40x1536x12288 23.5 / 19.3, rs 8x1536x12288 17.0 / 14.4)
+// With more parts the last one to arrive sums them all (us, up to 24 parts against 16: rs 48x1536x12288 23.4 / 16.0,
+// rs 64x512x12288 17.4 / 12.5, ag 40x1536x12288 23.5 / 19.3, rs 8x1536x12288 17.0 / 14.4).
+constexpr long long MAX_AUTO_PARTS = SK_SHARE_MAX;
 
 // How K is cut for configuration `cfg`: `split` parts for the last `split_tiles` tiles of the grid
 // (all of them for a uniform split), none for the others.

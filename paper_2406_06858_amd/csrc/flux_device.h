@@ -23,8 +23,6 @@ namespace flux {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 
@@ -1071,6 +1069,8 @@ __device__ __forceinline__ void epilogue_all_atomic(const GemmArgs& a, void* con
 // last to arrive, who reads in its own arrival whose those are.  The last to see the tile complete clears the word.
 constexpr uint32_t SK_SEEN = 1u << 7, SK_GAVE_UP = 1u << 16;
 constexpr int SK_SHARE_MAX = 16;                      // parts of a tile whose shares fit the word
+static_assert(((unsigned long long)SK_GAVE_UP << (SK_SHARE_MAX - 1)) <= 0x80000000ull && SK_SHARE_MAX < 128,
+              "every part has a give-up bit, and the counts below them can hold all parts");
 constexpr unsigned long long SK_WAIT_TICKS = 10000;   // 100 us
 
 template <class C, int EPI, bool EDGE, bool PF32, int NP>
