@@ -611,23 +611,23 @@ static int check_arrival(const flux_problem_t* p, const int32_t* arrival, int* o
 // (key, index).  ReduceScatter: key = position of the owner of the tile's first row in the
 // ring that starts after the local rank and ends on it.  AllGather: key = latest position, in
 // [local chunk, arrival order...], among the chunks the tile's rows touch.
-static void pack_order(TileMap* tm) {
+static void pack_order(TileMap* tm, const uint16_t* m_order) {
   tm->packed = tm->tiles_m <= 16;
   tm->pad_ = 0;
   tm->order4 = 0;
   if (tm->packed)
-    for (int t = 0; t < tm->tiles_m; ++t) tm->order4 |= (uint64_t)tm->m_order[t] << (4 * t);
+    for (int t = 0; t < tm->tiles_m; ++t) tm->order4 |= (uint64_t)m_order[t] << (4 * t);
 }
 
-static void build_tile_map(int op, const flux_problem_t* p, const Plan& pl, const int* arrival, TileMap* tm) {
+static void build_tile_map(int op, const flux_problem_t* p, const Plan& pl, const int* arrival, TileMap* tm, uint16_t* m_order) {
   tm->tiles_m = pl.tiles_m;
   tm->tiles_n = pl.tiles_n;
   tm->n_xcd = pl.n_xcd;
   const int S = p->M / p->R;
   if (p->flags & FLUX_FLAG_NO_SWIZZLE) {
     tm->band_h = 1;
-    for (int t = 0; t < pl.tiles_m; ++t) tm->m_order[t] = (uint16_t)t;
-    pack_order(tm);
+    for (int t = 0; t < pl.tiles_m; ++t) m_order[t] = (uint16_t)t;
+    pack_order(tm, m_order);
     return;
   }
   // a band = the m-tiles that wait for the same signal (one communication tile, Sec. 4.3), if whole
@@ -656,8 +656,8 @@ static void build_tile_map(int op, const flux_problem_t* p, const Plan& pl, cons
     keyed[t] = {key, t};
   }
   std::sort(keyed.begin(), keyed.end());
-  for (int t = 0; t < pl.tiles_m; ++t) tm->m_order[t] = (uint16_t)keyed[t].second;
-  pack_order(tm);
+  for (int t = 0; t < pl.tiles_m; ++t) m_order[t] = (uint16_t)keyed[t].second;
+  pack_order(tm, m_order);
 }
 
 static size_t workspace_need(const Plan& pl) {
@@ -967,10 +967,11 @@ int flux_tile_coord(int op, const flux_problem_t* p, const int32_t* arrival_orde
     st = check_arrival(p, arrival_order, order);
     if (st != FLUX_OK) return st;
   }
-  static thread_local TileMap tm;
-  build_tile_map(op, p, pl, order, &tm);
+  TileMap tm;
+  static thread_local uint16_t m_order[FLUX_MAX_M_TILES];
+  build_tile_map(op, p, pl, order, &tm, m_order);
   int mt, nt;
-  tile_coord(tm, block, mt, nt);
+  tile_coord(tm, m_order, block, mt, nt);
   *m_tile = mt; *n_tile = nt;
   return FLUX_OK;
 }
@@ -1046,7 +1047,7 @@ int gemm_rs_planned(const flux_problem_t* p, const Plan& pl, const void* A, cons
     a.outs[r] = out_slices[r];
     if (!write_only && r != p->rank) a.peers[j++] = peer_partials[r];
   }
-  build_tile_map(FLUX_OP_RS, p, pl, nullptr, &a.tm);
+  build_tile_map(FLUX_OP_RS, p, pl, nullptr, &a.tm, a.m_order);
   return launch_gemm(pl, EPI_RS, 0, a, s);
 }
 
@@ -1183,7 +1184,7 @@ int flux_ag_gemm(const flux_problem_t* p, const void* const* A_chunks, void* A_a
     for (int r = 0; r < p->R; ++r) a.outs[r] = const_cast<void*>(A_chunks[r]);   // chunk sources by rank
     a.self_serve_ticks = 10000u;
   }
-  build_tile_map(FLUX_OP_AG, p, pl, order, &a.tm);
+  build_tile_map(FLUX_OP_AG, p, pl, order, &a.tm, a.m_order);
 
   const bool driver_form = !(pl.copy_self || p->R == 1);
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -1274,7 +1275,7 @@ int flux_gemm_ref_unfused(int op, int phases, const flux_problem_t* p, const voi
   flux_problem_t q = *p;
   q.flags |= FLUX_FLAG_NO_SWIZZLE;
   Plan plq = pl;
-  build_tile_map(op, &q, plq, nullptr, &a.tm);
+  build_tile_map(op, &q, plq, nullptr, &a.tm, a.m_order);
   a.tm.n_xcd = pl.n_xcd;
   a.tm.band_h = 1;
 
@@ -1396,7 +1397,7 @@ int flux_gemm_ref_chunked(int op, const flux_problem_t* p, const void* A, const 
   GemmArgs g;
   fill_common(&g, &q, plq, plq.split_k > 1 ? workspace : nullptr);
   g.B = static_cast<const __bf16*>(B);
-  build_tile_map(FLUX_OP_RS, &q, plq, nullptr, &g.tm);
+  build_tile_map(FLUX_OP_RS, &q, plq, nullptr, &g.tm, g.m_order);
   g.tm.n_xcd = plq.n_xcd;
   g.tm.band_h = 1;
 

@@ -15,6 +15,7 @@
 //     or 32 B (fp32) per lane, 128..512 B contiguous per row.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 #include <utility>
 #include "flux.h"
@@ -63,17 +64,17 @@ struct TileMap {
   int32_t tiles_m, tiles_n, band_h, n_xcd;
   int32_t packed, pad_;
   uint64_t order4;
-  uint16_t m_order[FLUX_MAX_M_TILES];
 };
 
-__host__ __device__ inline void tile_coord(const TileMap& tm, int block, int& mt, int& nt) {
+// `m_order`: the table, read where the order is not packed.
+__host__ __device__ inline void tile_coord(const TileMap& tm, const uint16_t* m_order, int block, int& mt, int& nt) {
   const int band_sz = tm.band_h * tm.tiles_n;
   const int band = block / band_sz;
   int q = block - band * band_sz;
   if (tm.n_xcd > 1 && band_sz % tm.n_xcd == 0) q = (q % tm.n_xcd) * (band_sz / tm.n_xcd) + q / tm.n_xcd;
   const int i = band * tm.band_h + q % tm.band_h;
   nt = q / tm.band_h;
-  mt = tm.packed ? (int)((tm.order4 >> (4 * i)) & 15) : (int)tm.m_order[i];
+  mt = tm.packed ? (int)((tm.order4 >> (4 * i)) & 15) : (int)m_order[i];
 }
 
 enum : int { EPI_PLAIN = 0, EPI_RS = 1 };
@@ -81,9 +82,12 @@ enum : int { EPI_PLAIN = 0, EPI_RS = 1 };
 // Kernel arguments.  A workgroup's first fetches from the argument block miss the scalar cache one
 // 64-byte line after the other, a quarter of a microsecond each, before its first load can be
 // issued: the scalars sit together at the front, grouped by who needs them (every kernel; the signal
-// wait; the transfer; split-K and the reduce-scatter epilogue), and the arrays come last.
+// wait; the transfer; split-K and the reduce-scatter epilogue), and the arrays come last.  What every workgroup reads
+// ahead of its first operand load fills the first two lines exactly (asserted below).  With the tile map behind the arrays
+// a field added anywhere pushed it across one more line; us per launched call, map in a line behind the arrays / across
+// two / here: rs 128 x 256 x 256 fp32, 2 ranks, 7.04 / 7.22 / 6.29, rs 64 x 8192 x 3584, 8 ranks, - / 19.7 / 18.9.
 struct GemmArgs {
-  // ---- every kernel ----
+  // ---- every kernel: two lines ----
   const __bf16* A;           // [M,K]
   const __bf16* B;           // [K,N]
   void* C;                   // [M,N] of out dtype (plain epilogue)
@@ -97,6 +101,11 @@ struct GemmArgs {
   // partly filled round of the grid keeps all CUs busy to the end.
   int32_t full_tiles, split_tiles;
   int32_t split_k, k_per_split;   // k_per_split is a multiple of BK
+  TileMap tm;
+  flux_trace_record_t* trace;     // tile trace, one record per workgroup; null: none
+  int32_t write_only;        // 1: reduce-scatter epilogue without the reduction (Write branch of Alg. 1);
+                             // 2: no peers are read, the tile is added to the slice with atomic additions
+  int32_t partial_f32;
   // ---- all-gather prologue: the signal wait ----
   uint32_t* signals;
   uint32_t* done_counter;
@@ -140,21 +149,19 @@ struct GemmArgs {
   // counted in no earlier than (i + 1) * copy_pace_ticks (100 MHz ticks) after the kernel started
   unsigned long long copy_pace_ticks;
   // ---- split-K hand-over, reduce-scatter epilogue ----
-  int32_t write_only;        // 1: reduce-scatter epilogue without the reduction (Write branch of Alg. 1);
-                             // 2: no peers are read, the tile is added to the slice with atomic additions
   float* sk_partials;             // [split_k][split_tiles][BM*BN] fp32
   uint32_t* sk_counters;          // [tiles]
   int32_t sk_share;               // the parts of a tile share its final sum out among themselves (see finish_shared)
-  int32_t partial_f32, out_f32;
-  flux_trace_record_t* trace;     // tile trace, one record per workgroup; null: none
+  int32_t out_f32;
   uint32_t* tile_ready;           // reduce-scatter, Write branch: per output tile, producers that have written it; null: not kept
   int32_t persist_blocks;         // > 0: a grid of resident workgroups, workgroup b takes the blocks b, b + grid, ... below this
   uint32_t persist_delay_ticks;   // ... and every second group of eight starts this late (100 MHz ticks)
   // ---- arrays ----
-  void* outs[FLUX_MAX_RANKS];
+  alignas(64) void* outs[FLUX_MAX_RANKS];
   const void* peers[FLUX_MAX_RANKS];   // the R-1 peer partials packed in ascending rank order
-  TileMap tm;
+  uint16_t m_order[FLUX_MAX_M_TILES];  // order of the m-tiles, where it does not fit tm.order4
 };
+static_assert(alignof(GemmArgs) == 64 && offsetof(GemmArgs, partial_f32) + sizeof(int32_t) == 128, "every workgroup's arguments: the first two lines");
 
 // The rank-indexed pointers (output slices, or chunk sources) go to LDS for dynamic indexing.  The
 // second half of the array lies in another line of the argument block and is only touched when
@@ -1719,7 +1726,7 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
   bool is_split;
   map_block(a, (int)blockIdx.x, tile, split, is_split);
   int mt, nt;
-  tile_coord(a.tm, tile, mt, nt);
+  tile_coord(a.tm, a.m_order, tile, mt, nt);
   const int m0 = mt * C::BM, n0 = nt * C::BN;
   trace_begin(a, tile, mt, nt, split, is_split);
 
@@ -1857,7 +1864,7 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma_resident(const 
     bool is_split;
     map_block(a, vb, tile, split, is_split);
     int mt, nt;
-    tile_coord(a.tm, tile, mt, nt);
+    tile_coord(a.tm, a.m_order, tile, mt, nt);
     const int m0 = mt * C::BM, n0 = nt * C::BN;
     trace_begin(a, tile, mt, nt, split, is_split, vb);
     const int k_begin = is_split ? split * a.k_per_split : 0;
