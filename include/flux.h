@@ -126,8 +126,12 @@ typedef struct flux_problem {
                                not signalled before (i+1)*tile_bytes/link_gbps after the
                                transfer started (its data may move earlier)                      */
   int32_t reserved;         /* must be 0                                                          */
-  uint64_t spin_timeout_ticks;  /* AG: bound on one signal wait, in 100 MHz wall-clock ticks;
-                                   0 = library default (10 s).  The paper spins without bound.   */
+  uint64_t spin_timeout_ticks;  /* bound on one signal wait (AG) or wait for a tile's ready count
+                                   (flux_rs_reduce_slice_ready), in 100 MHz wall-clock ticks;
+                                   0 = library default (10 s).  The paper spins without bound.
+                                   Also bounds, below the library's own 100 us, how long a K part
+                                   of a tile waits for the tile's others before it leaves its
+                                   share of the sum to the last of them: never an error.         */
   int64_t lda, ldb, ldc;    /* row pitches in elements, 0 = packed (K, N, N).  Multiples of 8, at
                                least a row long, below FLUX_MAX_N (ldc), the last element's index
                                below 2^31.
@@ -218,7 +222,7 @@ int flux_gemm_rs_static(const flux_problem_t* p, const void* A, const void* B,
  *   A_chunks        host array [R] of device pointers, chunk r = [M/R,K] bf16 ("A_list").
  *   A_agg           device [M,K] bf16 (row pitch lda), written by the call.  If A_chunks[rank] already points
  *                   at A_agg + rank*(M/R)*lda the local chunk is not copied.  The local chunk may lie elsewhere
-                   inside A_agg or inside C: it is read before either is written.  16-byte alignment is
+ *                   inside A_agg or inside C: it is read before either is written.  16-byte alignment is
  *                   required; with 128-byte alignment and a row pitch that is a multiple of 64 no cache line holds
  *                   rows of two communication tiles, and a workgroup leaves its signal wait without
  *                   invalidating its die's L2 (one to two microseconds per workgroup otherwise).

@@ -719,8 +719,8 @@ static int launch_gemm(const Plan& pl, int epi, int wait, GemmArgs& a, hipStream
   hipEvent_t e0 = g_prof_start, e1 = g_prof_stop;
   g_prof_start = g_prof_stop = nullptr;
   // The parts of a K-cut tile wait for each other and finish it together where they all fit the chip at the same time
-  // (they are the whole grid, or its last round).  Parts that give up waiting leave their share to the last one, so a
-  // chip that is busy with other kernels costs time, not results.  A tile added by atomic additions, or one that is to be
+  // (they are the whole grid, or its last round).  On a chip that is busy with other kernels, parts whose tile-mates have not
+  // started leave their share to the last one.  A tile added by atomic additions, or one that is to be
   // counted in as ready by whoever writes it, stays with the part that arrives last.  So does a large tile in two parts:
   // eight or more 16x32 blocks per wave, a round trip each, are slower than the last part's batches (512 x 8192 x 3584 with 7
   // peers 62 against 57 us, three parts of 256 x 8192 x 8192 65 against 67, two of a 64x128 tile of 128 x 8192 x 4096 with

@@ -1071,14 +1071,30 @@ __device__ __forceinline__ void epilogue_all_atomic(const GemmArgs& a, void* con
 // 48 -> 25, ag 8192 x 4608 x 12288 (its last round's 64 tiles in 4 parts) 754 -> 743.  (Asking for the next block's sums while
 // a block is finished made the small calls 0.5-1 us slower: the code of a tail runs once, and every line of it is fetched.)
 //
-// The tile's counter word: parts that have arrived in bits [6:0], parts that have seen all arrive in bits [13:7], parts
-// that gave up waiting (bounded: they may be kept from running) in bits [31:16].  Who gives up leaves its share to the
-// last to arrive, who reads in its own arrival whose those are.  The last to see the tile complete clears the word.
-constexpr uint32_t SK_SEEN = 1u << 7, SK_GAVE_UP = 1u << 16;
+// A part that has not been given a compute unit yet (another kernel holds some) may be waiting for one of these.  So a part
+// waits for the others only where all of them have started, and for those that have not an eighth of its own time (at least
+// 0.5 us: a grid is not dispatched at once); a part that all others gave up on sums the tile alone, as if nothing were
+// shared.  Waiting for every part up to the bound stalled calls beside a kernel that holds compute units for as long (us per
+// call beside one that holds 4 / 32 / 128 units, every part waited for -> only started ones -> none ever: rs 64 x 2048 x 8192
+// 54 / 54 / 72 -> 26 / 26 / 29 -> 23 / 24 / 28, ag 8 x 3584 x 8192 30 / 59 / 73 -> 31 / 31 / 36 -> 28 / 29 / 34).  The start is
+// counted after the first slab is there: ahead of it, the addition's round trip comes first (+0.25 us).
+//
+// The tile's counter word: parts that have arrived in bits [4:0], parts that have seen all arrive in bits [9:5], parts
+// that have started their main loop in bits [14:10], parts that gave up waiting in bits [31:16].  Who gives up leaves its
+// share to the last to arrive, who reads in its own arrival whose those are.  The last to see the tile complete clears the
+// word; every part's start has been counted by then (acknowledged ahead of its arrival).
+constexpr uint32_t SK_COUNT = 31u, SK_SEEN_AT = 5, SK_STARTED_AT = 10, SK_GAVE_UP = 1u << 16;
 constexpr int SK_SHARE_MAX = 16;                      // parts of a tile whose shares fit the word
-static_assert(((unsigned long long)SK_GAVE_UP << (SK_SHARE_MAX - 1)) <= 0x80000000ull && SK_SHARE_MAX < 128,
-              "every part has a give-up bit, and the counts below them can hold all parts");
-constexpr unsigned long long SK_WAIT_TICKS = 10000;   // 100 us
+static_assert(SK_SHARE_MAX <= 16, "a give-up bit per part, counts of up to 31");
+constexpr uint32_t SK_WAIT_TICKS = 10000;             // 100 us: longest wait for a part that has started
+constexpr uint32_t SK_START_TICKS = 50;               // 0.5 us: shortest wait for one that has not (a grid is being dispatched)
+
+// This part has its first operands and enters its main loop: counted in, and the time taken.
+__device__ __forceinline__ uint32_t part_started(const GemmArgs& a, int tile, int tid) {
+  if (tid == 0)
+    __hip_atomic_fetch_add(a.sk_counters + sk_counter_index(tile - a.full_tiles), 1u << SK_STARTED_AT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return (uint32_t)wall_clock64();
+}
 
 template <class C, int EPI, bool EDGE, bool PF32, int NP>
 struct SharedFinish {
@@ -1158,9 +1174,10 @@ struct SharedFinish {
     if (!EDGE || (m0 + row < a.M && n0 + col < a.N)) store_row8<EPI>(a, lds_outs, m0 + row, n0 + col, o);
   }
 
-  // Called by every part once its sums are parked and acknowledged.  `lds_misc`: two ints of the workgroup.
-  static __device__ __forceinline__ void run(const GemmArgs& a, int* lds_misc, void* const* lds_outs, float* ep, int tile, int split,
-                                             int m0, int n0, int tid, int lane, int wave) {
+  // Called by every part once its sums are parked and acknowledged.  `lds_misc`: two ints of the workgroup; `t_started`: what
+  // part_started returned.  False: all others gave up, the tile is this part's alone (the caller sums it up).
+  static __device__ __forceinline__ bool run(const GemmArgs& a, int* lds_misc, void* const* lds_outs, float* ep, int tile, int split,
+                                             int m0, int n0, int tid, int lane, int wave, uint32_t t_started) {
     const int st = tile - a.full_tiles, S = a.split_k;
     uint32_t* const word = a.sk_counters + sk_counter_index(st);
     constexpr int NW = C::NT / 64;
@@ -1170,19 +1187,32 @@ struct SharedFinish {
     const int u_end = BLOCKS * (split + 1) / S;
     u32x4 w[NPA][LPP];
     if (NP > 0 && u < u_end) load_peers(a, pb, u, m0, n0, lane, w);       // on their way during the wait
+    // seen; whoever completes that clears the word for the next launch.  (A part that gives up counts too, in the same addition.)
+    auto seen = [&](uint32_t and_gave_up) {
+      const uint32_t prev = __hip_atomic_fetch_add(word, (1u << SK_SEEN_AT) + and_gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (((prev >> SK_SEEN_AT) & SK_COUNT) + 1u == (uint32_t)S) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return prev;
+    };
+    bool gave_up = false;
     if (tid == 0) {
       uint32_t extra = 0u;                            // parts whose shares fall to this one
       int mine = 1;
       const uint32_t prev = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if ((prev & 127u) + 1u == (uint32_t)S) {
+      if ((prev & SK_COUNT) + 1u == (uint32_t)S) {
         extra = prev >> 16;
       } else {
-        const unsigned long long t0 = wall_clock64();
-        const unsigned long long limit = a.timeout_ticks < SK_WAIT_TICKS ? a.timeout_ticks : SK_WAIT_TICKS;
-        while ((__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 127u) != (uint32_t)S) {
-          if (wall_clock64() - t0 > limit) {
-            const uint32_t old = __hip_atomic_fetch_or(word, SK_GAVE_UP << split, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            mine = (old & 127u) == (uint32_t)S;       // (all there after all: the last one did not see this part give up)
+        const uint32_t t0 = (uint32_t)wall_clock64();
+        const uint32_t longest = a.timeout_ticks < SK_WAIT_TICKS ? (uint32_t)a.timeout_ticks : SK_WAIT_TICKS;
+        uint32_t unstarted = (t0 - t_started) / 8;
+        if (unstarted < SK_START_TICKS) unstarted = SK_START_TICKS;
+        if (unstarted > longest) unstarted = longest;
+        for (;;) {
+          const uint32_t now = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if ((now & SK_COUNT) == (uint32_t)S) break;
+          const bool all_started = ((now >> SK_STARTED_AT) & SK_COUNT) == (uint32_t)S;
+          if ((uint32_t)wall_clock64() - t0 > (all_started ? longest : unstarted)) {
+            gave_up = true;
+            mine = (seen(SK_GAVE_UP << split) & SK_COUNT) == (uint32_t)S;   // (all there after all: the last one did not see this part give up)
             break;
           }
           __builtin_amdgcn_s_sleep(1);
@@ -1193,25 +1223,23 @@ struct SharedFinish {
     }
     __syncthreads();
     const int mine = __builtin_amdgcn_readfirstlane(lds_misc[0]);
-    uint32_t extra = (uint32_t)__builtin_amdgcn_readfirstlane(lds_misc[1]);
-    if (tid == 0) {
-      // seen; whoever completes that clears the word for the next launch.  (A part that gave up counts too.)
-      const uint32_t prev = __hip_atomic_fetch_add(word, SK_SEEN, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (((prev >> 7) & 127u) + 1u == (uint32_t)S) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (!mine) return;
+    const uint32_t extra = (uint32_t)__builtin_amdgcn_readfirstlane(lds_misc[1]);
+    if (tid == 0 && !gave_up) seen(0u);
+    if (!mine) return true;
+    if (extra == ((1u << S) - 1u - (1u << split))) return false;
     for (; u < u_end;) {
       block(a, lds_outs, ep, u, st, m0, n0, lane, w);
       u += NW;
       if (NP > 0 && u < u_end) load_peers(a, pb, u, m0, n0, lane, w);
     }
-    for (; extra != 0u; extra &= extra - 1u) {
-      const int s = __builtin_ctz(extra);
-      for (int x = BLOCKS * s / S + wave; x < BLOCKS * (s + 1) / S; x += NW) {
+    if (extra != 0u)                                  // (all waves over all of the tile's blocks: a share may be less than one a wave)
+      for (int x = wave; x < BLOCKS; x += NW) {
+        const int owner = (S * (x + 1) - 1) / BLOCKS; // BLOCKS * owner / S <= x < BLOCKS * (owner + 1) / S
+        if (((extra >> owner) & 1u) == 0u) continue;
         if (NP > 0) load_peers(a, pb, x, m0, n0, lane, w);
         block(a, lds_outs, ep, x, st, m0, n0, lane, w);
       }
-    }
+    return true;
   }
 };
 
@@ -1222,7 +1250,7 @@ struct SharedFinish {
 template <class C, int EPI, bool EDGE>
 __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem, int* lds_misc, void* const* lds_outs,
                                           f32x4 (&acc)[C::MI][C::NI], int tile, int split, bool is_split,
-                                          int m0, int n0, int tid, int lane, int wave, int wm, int wn, int vb = -1) {
+                                          int m0, int n0, int tid, int lane, int wave, int wm, int wn, uint32_t t_started, int vb = -1) {
   trace_stamp(a, TRACE_MAIN_END, vb);
   // ---- split-K: all but the last-arriving workgroup of a tile park their partial sums ----
   if (is_split) {
@@ -1254,28 +1282,32 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
     __syncthreads();
     if (a.sk_share) {                                     // (uniform)
       float* const ep = reinterpret_cast<float*>(smem) + wave * (32 * C::EP_STRIDE);
-      if (EPI != EPI_RS || a.write_only) SharedFinish<C, EPI, EDGE, false, 0>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
+      bool finished;
+      if (EPI != EPI_RS || a.write_only) finished = SharedFinish<C, EPI, EDGE, false, 0>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave, t_started);
       else if (a.R <= 8) {
-        if (a.partial_f32) SharedFinish<C, EPI, EDGE, true, 7>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
-        else SharedFinish<C, EPI, EDGE, false, 7>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
+        if (a.partial_f32) finished = SharedFinish<C, EPI, EDGE, true, 7>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave, t_started);
+        else finished = SharedFinish<C, EPI, EDGE, false, 7>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave, t_started);
       } else {
-        if (a.partial_f32) SharedFinish<C, EPI, EDGE, true, 15>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
-        else SharedFinish<C, EPI, EDGE, false, 15>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
+        if (a.partial_f32) finished = SharedFinish<C, EPI, EDGE, true, 15>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave, t_started);
+        else finished = SharedFinish<C, EPI, EDGE, false, 15>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave, t_started);
       }
-      trace_stamp(a, TRACE_END, vb);
-      return;
+      if (finished) {
+        trace_stamp(a, TRACE_END, vb);
+        return;
+      }
+    } else {
+      int* lds_last = lds_misc;
+      if (tid == 0) {
+        uint32_t* const word = a.sk_counters + sk_counter_index(st);
+        const uint32_t prev = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int last = prev == (uint32_t)(a.split_k - 1);
+        if (last) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
+        *lds_last = last;
+      }
+      __syncthreads();
+      trace_stamp(a, TRACE_END, vb);    // a workgroup that is not the tile's last ends here
+      if (!*lds_last) return;
     }
-    int* lds_last = lds_misc;
-    if (tid == 0) {
-      uint32_t* const word = a.sk_counters + sk_counter_index(st);
-      const uint32_t prev = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const int last = prev == (uint32_t)(a.split_k - 1);
-      if (last) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
-      *lds_last = last;
-    }
-    __syncthreads();
-    trace_stamp(a, TRACE_END, vb);    // a workgroup that is not the tile's last ends here
-    if (!*lds_last) return;
     // The sum always runs over the parked partials in split order, whichever workgroup happens
     // to be last, so results do not depend on arrival timing.  (Keeping the own part in registers
     // and skipping its load was tried: no gain for 64x64 tiles, a loss for 64x128.)
@@ -1782,6 +1814,7 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
       for (int e = 0; e < 4; ++e) acc[mi][ni][e] = 0.f;
 
   pipe.start(ld, a, pool, k_begin, KT, wave);
+  const uint32_t t_started = is_split && a.sk_share ? part_started(a, tile, tid) : 0u;
   int kt = 0;
   if constexpr (CARRY) {
     if (side.pending()) {
@@ -1828,7 +1861,7 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
   }
   pipe.run(ld, a, pool, k_begin, KT, kt, wave, acc);
   wait_vm0_and_barrier();        // the epilogue's staging area lies over stages other waves may still be reading
-  gemm_tail<C, EPI, EDGE>(a, pool, lds_misc, lds_outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn);
+  gemm_tail<C, EPI, EDGE>(a, pool, lds_misc, lds_outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, t_started);
 }
 
 // The same kernel as a grid of resident workgroups, one per compute unit, each walking the block
@@ -1882,9 +1915,10 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma_resident(const 
     MmaPipe<C, false, false> pipe;
     pipe.init(pool, wm, wn, lane);
     pipe.start(ld, a, pool, k_begin, KT, wave);
+    const uint32_t t_started = is_split && a.sk_share ? part_started(a, tile, tid) : 0u;
     pipe.run(ld, a, pool, k_begin, KT, 0, wave, acc);
     wait_vm0_and_barrier();
-    gemm_tail<C, EPI, false>(a, pool, lds_misc, lds_outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, vb);
+    gemm_tail<C, EPI, false>(a, pool, lds_misc, lds_outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, t_started, vb);
     __syncthreads();      // the staging area and lds_misc are the next block's
   }
 }

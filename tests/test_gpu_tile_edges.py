@@ -98,3 +98,52 @@ def test_k_cut_tile_finished_by_its_parts(cfg, M, N, K, split, R, pd):
         torch.cuda.synchronize()
         for r in range(R):
             gh.assert_bits_equal(outs[r], want[r], f"ticks {ticks} slice {r}")
+
+
+@pytest.mark.parametrize("M,N,K,cfg,split,R", [(64, 2048, 8192, 9, 16, 8), (64, 8192, 4096, 9, 4, 8), (256, 4096, 4096, 2, 8, 1), (64, 4096, 4096, 10, 16, 16)])
+def test_k_parts_beside_a_kernel_that_holds_compute_units(M, N, K, cfg, split, R):
+    """Half of the compute units belong to another stream's GEMM for longer than the K-cut call takes, so half of its parts
+    start only when others leave: nobody may sit out the bound (100 us) waiting for them, and the sums are the same bit for
+    bit, whoever takes over whose share.  Then two K-cut calls side by side."""
+    held = fb.problem(4096, 2048, 32768, 1, 0, tile_config=1, split_k=1)               # 128 tiles, one per compute unit
+    hA, hB = (torch.zeros(s, dtype=torch.bfloat16, device=gh.DEV) for s in ((4096, 32768), (32768, 2048)))
+    hC = torch.empty((4096, 2048), dtype=torch.bfloat16, device=gh.DEV)
+    w = fi.Workload("beside", "rs", M, N, K, R, a_dist=("int", 2), b_dist=("int", 2), peer_dist=("int", 8), seed=M + K + R)
+    A, B, peers = fi.make_rs_inputs(w, 0)
+    dA, dB = A.to(gh.DEV), B.to(gh.DEV)
+    dpeers = [None if t is None else t.to(gh.DEV) for t in peers]
+    total = dA.float() @ dB.float()                     # exact: integers whose sums stay below 2^24
+    for t in dpeers[1:]:
+        total += t.float()
+    want = total.to(torch.bfloat16)
+    p = fb.problem(M, N, K, R, 0, tile_config=cfg, split_k=split)
+    grid = fb.flux_split_plan(fb.FLUX_OP_RS, p)[1] * split
+    sides = []
+    for _ in range(2):
+        ws = gh.workspace_for(fb.FLUX_OP_RS, p)
+        fb.flux_init_buffers(fb.FLUX_OP_RS, p, ws)
+        sides.append((ws, [torch.empty((w.S, N), dtype=torch.bfloat16, device=gh.DEV) for _ in range(R)], torch.cuda.Stream()))
+    rec = torch.zeros((grid, 8), dtype=torch.int64, device=gh.DEV)
+    overlapped = False
+    for attempt in range(6):
+        _say("beside a kernel that holds units", (M, N, K), "cfg", cfg, "split", split, "R", R, "attempt", attempt)
+        for _, outs, _ in sides:
+            for o in outs:
+                o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        holder = torch.cuda.Stream()
+        if attempt < 5:
+            fb.flux_gemm_rs(held, hA, hB, [None], [hC], None, holder)
+            fb.flux_trace_next_call(rec)
+        for ws, outs, stream in sides[:1 if attempt < 5 else 2]:
+            fb.flux_gemm_rs(p, dA, dB, dpeers, outs, ws, stream)
+        torch.cuda.synchronize()
+        for _, outs, _ in sides[:1 if attempt < 5 else 2]:
+            assert torch.equal(torch.cat(outs), want)
+        if attempt < 5:
+            start, end_main, end = (rec[:, i].cpu() for i in (4, 6, 7))
+            overlapped = overlapped or bool(start.max() > end_main.min())
+            # (finishing a tile alone takes some tens of us; a part that sat out the bound is past it)
+            assert int((end - end_main).max()) < 9000, f"a part waited {int((end - end_main).max()) / 100} us"
+    if not overlapped:
+        pytest.skip("the two kernels never ran at the same time")
