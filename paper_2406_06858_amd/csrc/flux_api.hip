@@ -724,7 +724,8 @@ static int launch_gemm(const Plan& pl, int epi, int wait, GemmArgs& a, hipStream
   // counted in as ready by whoever writes it, stays with the part that arrives last.  So does a large tile in two parts:
   // eight or more 16x32 blocks per wave, a round trip each, are slower than the last part's batches (512 x 8192 x 3584 with 7
   // peers 62 against 57 us, three parts of 256 x 8192 x 8192 65 against 67, two of a 64x128 tile of 128 x 8192 x 4096 with
-  // 15 fp32 peers 38 against 45).
+  // 15 fp32 peers 38 against 45), and any tile in two parts without peers to fetch during the wait (ag 64 x 3584 x 1024 16.6
+  // against 15.9, ag 256 x 3584 x 1536 18.4 / 17.8, write-only 512 x 1024 x 1024 10.3 / 9.5, one rank 64 x 3584 x 1024 12.8 / 12.6).
   const bool no_peers = epi != EPI_RS || a.write_only != 0 || a.R == 1;
   const bool share = pl.split_k > (pl.bm * pl.bn > 64 * 128 || no_peers ? 2 : 1) && pl.split_k <= SK_SHARE_MAX && a.write_only != 2 && a.tile_ready == nullptr &&
                      (long long)pl.split_tiles * pl.split_k <= (long long)N_CU * g_cfgs[pl.cfg].occupancy;
