@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
+#include <type_traits>
 #include <utility>
 #include "flux.h"
 
@@ -1504,15 +1505,27 @@ __device__ __forceinline__ uint32_t lds_address(const unsigned char* p) {
   return (uint32_t)reinterpret_cast<uintptr_t>((const lds_byte_t*)p);
 }
 
+// A fragment as its LDS reads leave it: one 16-byte read, or the two halves of a transposing read.  The halves are two
+// values until their wait is over: joining them means whatever the register allocator makes of it, a copy included.
+typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+struct FragHalves { u32x2 lo, hi; };
+__device__ __forceinline__ void frag_settle(bf16x8& f) { asm volatile("" : "+v"(f)); }
+__device__ __forceinline__ void frag_settle(FragHalves& f) { asm volatile("" : "+v"(f.lo), "+v"(f.hi)); }
+__device__ __forceinline__ bf16x8 frag_value(const bf16x8& f) { return f; }
+__device__ __forceinline__ bf16x8 frag_value(const FragHalves& f) {
+  const u32x4 w = {f.lo[0], f.lo[1], f.hi[0], f.hi[1]};
+  return __builtin_bit_cast(bf16x8, w);
+}
+
 // All LDS reads issued so far have returned.  The fragments pass through it so that nothing that
 // uses them can be moved in front of the wait.
-template <int MI, int NI>
-__device__ __forceinline__ void wait_lds_reads(bf16x8 (&af)[MI], bf16x8 (&bfr)[NI]) {
+template <int NA, int NB, class FA, class FB>
+__device__ __forceinline__ void wait_lds_reads(FA (&af)[NA], FB (&bfr)[NB]) {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-  for (int i = 0; i < MI; ++i) asm volatile("" : "+v"(af[i]));
+  for (int i = 0; i < NA; ++i) frag_settle(af[i]);
 #pragma unroll
-  for (int i = 0; i < NI; ++i) asm volatile("" : "+v"(bfr[i]));
+  for (int i = 0; i < NB; ++i) frag_settle(bfr[i]);
 }
 
 template <int N>
@@ -1592,7 +1605,9 @@ struct MmaPipe {
   static constexpr int L0 = loads_before(G);                         // loads of a slab that go with that last k-step
 
   uint32_t a[NHI][KS], b[NHI][NBV];
-  bf16x8 af[2][C::MI], bf[2][C::NI];
+  typedef std::conditional_t<C::B_NK, bf16x8, FragHalves> FragB;
+  bf16x8 af[2][C::MI];
+  FragB bf[2][C::NI];
 
   __device__ __forceinline__ void init(const unsigned char* pool, int wm, int wn, int lane) {
     const uint32_t base = lds_address(pool);
@@ -1627,14 +1642,12 @@ struct MmaPipe {
     return __builtin_bit_cast(bf16x8, v);
   }
   template <int OFF>
-  static __device__ __forceinline__ bf16x8 read_tr(const uint32_t (&base)[NHI]) {
-    typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+  static __device__ __forceinline__ FragHalves read_tr(const uint32_t (&base)[NHI]) {
     constexpr int O2 = OFF + 4 * C::BN * 2;
-    u32x2 lo, hi;
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo) : "v"(base[OFF / 65536]), "n"(OFF % 65536));
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(base[O2 / 65536]), "n"(O2 % 65536));
-    const u32x4 w = {lo[0], lo[1], hi[0], hi[1]};
-    return __builtin_bit_cast(bf16x8, w);
+    FragHalves f;
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.lo) : "v"(base[OFF / 65536]), "n"(OFF % 65536));
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.hi) : "v"(base[O2 / 65536]), "n"(O2 % 65536));
+    return f;
   }
   // fragment R (in the order the MFMAs want them) of k-step K out of stage S
   template <int S, int K, int R>
@@ -1670,7 +1683,7 @@ struct MmaPipe {
     wait_vm_at_most<(NS - 2) * (B_FIRST ? LA : L) + L0>();        // slab 0 is there
     barrier_keeping_loads_in_flight();
     static_for<NF>([&](auto r) { fetch<0, 0, decltype(r)::value>(); });
-    wait_lds_reads<C::MI, C::NI>(af[0], bf[0]);
+    wait_lds_reads(af[0], bf[0]);
   }
 
   // Slab kt, which lies in stage S = kt % NS.  VM_EXTRA: that many younger memory operations, issued by before_wait(),
@@ -1704,7 +1717,7 @@ struct MmaPipe {
           }
           barrier_keeping_loads_in_flight();
         }
-        mfma_in_place(acc[mi][ni], af[ks][mi], bf[ks][ni]);
+        mfma_in_place(acc[mi][ni], af[ks][mi], frag_value(bf[ks][ni]));
         // this MFMA's loads [d0, d1) and fragment reads [r0, r1)
         constexpr int d0 = loads_before(LAST ? g : G + g), d1 = loads_before((LAST ? g : G + g) + 1);
 #pragma unroll
@@ -1720,7 +1733,7 @@ struct MmaPipe {
         });
         __builtin_amdgcn_sched_barrier(0);
       });
-      wait_lds_reads<C::MI, C::NI>(af[1 - ks], bf[1 - ks]);
+      wait_lds_reads(af[1 - ks], bf[1 - ks]);
     });
   }
 
