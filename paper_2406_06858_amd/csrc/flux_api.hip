@@ -334,7 +334,8 @@ constexpr long long MAX_AUTO_PARTS = SK_SHARE_MAX;
 
 // How K is cut for configuration `cfg`: `split` parts for the last `split_tiles` tiles of the grid
 // (all of them for a uniform split), none for the others.
-static void plan_split(const flux_problem_t* p, int cfg, long long tiles, int kt, int* split_out, long long* split_tiles_out) {
+static void plan_split(const flux_problem_t* p, int cfg, long long tiles, int kt, int* split_out, long long* split_tiles_out,
+                       bool estimate = false) {
   int split = p->split_k;
   const long long slots = (long long)N_CU * g_cfgs[cfg].occupancy;
   if (split <= 0) {
@@ -343,8 +344,17 @@ static void plan_split(const flux_problem_t* p, int cfg, long long tiles, int kt
       // deep pipeline, one workgroup per CU: as many K parts as still give a single round, each
       // long enough for the pipeline to fill, and no more than can finish the tile together
       if (tiles < slots) split = (int)std::max<long long>(1, std::min<long long>({slots / tiles, kt / 8, MAX_AUTO_PARTS}));
-    } else if (tiles < 256) {                   // too few tiles to fill the chip: cut K as well
-      split = (int)std::min<long long>((512 + tiles - 1) / tiles, 16);
+    } else if (tiles < 256) {
+      // Too few tiles to fill the chip: cut K as well, into no more parts than the chip has slots.  A part too many is a second
+      // round (us, one more part / as many as fit: rs 976x264x12288 48 / 33, 48x12288x1536 27 / 19, 1040x1416x6144 61 / 48,
+      // 1496x408x8192 51 / 36, ag 736x264x6144 28 / 24).
+      // plan_cost's estimate counts the part too many where slots are left over: without it, it favours 128x128 tiles too much (128x128 against 256x128 on three stages, us: 340x3424x12288 67.6 / 61.1, 366x3584x12288 fp32 63.4 / 58.4, ag
+      // 352x6120x5784 65.9 / 61.9, ag 320x3888x8192 53.3 / 50.5, 256x256 in two parts against 256x128, ag 960x8192x12288 188 /
+      // 171; the other side: 128x4560x8192 32.3 / 33.4, ag 264x5592x4608 43.1 / 44.5).
+      // One workgroup per compute unit and 129 to 170 tiles: three parts in two rounds, 0.72 of a round of whole tiles
+      // (1024x9512x12288 293 against 317 us).
+      const long long parts = slots / tiles == 1 && 2 * slots / tiles == 3 ? 3 : slots / tiles;
+      split = (int)std::min<long long>(estimate ? (512 + tiles - 1) / tiles : parts, 16);
       split = std::max(1, std::min(split, kt / 4));
       // parked fp32 partials (written and re-read) should not outweigh the operands themselves
       const long long operands = (long long)p->M * p->K + (long long)p->K * p->N;
@@ -377,7 +387,7 @@ static double plan_cost(const flux_problem_t* p, int cfg) {
   const long long slots = (long long)N_CU * g_cfgs[cfg].occupancy;
   int split;
   long long split_tiles;
-  plan_split(p, cfg, tiles, kt, &split, &split_tiles);
+  plan_split(p, cfg, tiles, kt, &split, &split_tiles, true);
   const double part = (1.0 + 0.04 * (split - 1)) / split;          // a K part, with its hand-over
   double rounds;
   if (split > 1 && split_tiles < tiles) rounds = (double)((tiles - split_tiles) / slots) + part * (double)((split_tiles * split + slots - 1) / slots);

@@ -348,3 +348,18 @@ def test_deferred_transfer_is_planned_for_grids_of_several_rounds():
     assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 512, 8, 2)) == 0          # K too short to carry the vectors
     assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 12288, 8, 2, tile_config=2)) == 0   # other kernel
     assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 12288, 1, 0)) == 0
+
+
+@pytest.mark.parametrize("op,M,N,K,cfg", [("rs", 976, 264, 12288, 4), ("rs", 48, 12288, 1536, 5), ("rs", 8, 12288, 1648, 6), ("rs", 1040, 1416, 6144, 3),
+                                          ("ag", 736, 264, 6144, 4), ("ag", 1496, 408, 8192, 3), ("rs", 776, 8192, 12288, 1), ("rs", 64, 1024, 1024, 5)])
+def test_a_uniform_k_cut_is_one_round(op, M, N, K, cfg):
+    """Two-stage tiles cut into as many K parts as the chip has slots for (two workgroups per compute unit; one for 256x256),
+    not into one more."""
+    opc = fb.FLUX_OP_RS if op == "rs" else fb.FLUX_OP_AG
+    full, cut, parts = fb.flux_split_plan(opc, fb.problem(M, N, K, 8, 0, tile_config=cfg))
+    assert full == 0 and parts > 1 and cut * parts <= (256 if cfg == 1 else 512)
+
+
+def test_three_parts_in_two_rounds_of_large_tiles():
+    for N, plan in ((8192, (0, 128, 2)), (8448, (0, 132, 3)), (10752, (0, 168, 3)), (11008, (0, 172, 1)), (12288, (0, 192, 1))):
+        assert fb.flux_split_plan(fb.FLUX_OP_RS, fb.problem(1024, N, 12288, 8, 0, tile_config=1)) == plan
