@@ -409,7 +409,16 @@ static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
     const long long weights = (long long)p->N * p->K;
     // 64x128 tiles on four stages, for any rows, columns and K (masked loads): tiles of one round of the chip
     const bool one_round = (long long)((p->M + 63) / 64) * ((p->N + 127) / 128) <= N_CU;
-    if (p->M <= 32) cfg = (deep_ok && p->N % 128 == 0) ? 7 : 5;          // 32x128
+    if (p->M <= 32) {
+      // 32x128.  Whole tiles: on six stages, but on two, whose K is cut finer, where six stages would cut K into a few parts
+      // of small weights (us, six / two: 8x1024x1024 10.0 / 9.0, 32x3584x1536 11.6 / 10.7, ag 20x4608x1536 16.0 / 14.9,
+      // 32x6144x1024 12.2 / 10.8; the other side: 8x3584x3072 11.8 / 13.6, 8x8192x1536 12.2 / 13.4, 8x1536x512 7.8 / 9.1).
+      // Else on two stages.  (Six are 3-8 % ahead where their parts fill the chip, 16x10448x11424 54.0 / 52.3, 32x9048x4328 26.1 /
+      // 24.8, or 9 % behind, 8x5320x12288 32.1 / 35.1, and behind where they do not, 24x12288x9736 68.8 / 74.4.)
+      const long long slabs = p->K / 64;
+      const bool six = deep_ok && p->N % 128 == 0 && (slabs < 16 || slabs > 32 || weights > 8ll * 1024 * 1024);
+      cfg = six ? 7 : 5;
+    }
     else if (p->M == 64 && deep_ok && p->N % 128 == 0 && p->N / 128 <= N_CU &&
              std::min<long long>(N_CU / (p->N / 128), p->K / 64 / 8) <= 5) {
       // 64 rows over a large weight matrix: 64x128 tiles on four stages where at most five K parts

@@ -363,3 +363,14 @@ def test_a_uniform_k_cut_is_one_round(op, M, N, K, cfg):
 def test_three_parts_in_two_rounds_of_large_tiles():
     for N, plan in ((8192, (0, 128, 2)), (8448, (0, 132, 3)), (10752, (0, 168, 3)), (11008, (0, 172, 1)), (12288, (0, 192, 1))):
         assert fb.flux_split_plan(fb.FLUX_OP_RS, fb.problem(1024, N, 12288, 8, 0, tile_config=1)) == plan
+
+
+@pytest.mark.parametrize("M,N,K,parts", [
+    (8, 1024, 1024, 4), (32, 3584, 1536, 6), (32, 4096, 2048, 8), (32, 4096, 2112, 4), (32, 4224, 2048, 4), (8, 8192, 512, 1), (8, 1536, 960, 1),   # whole tiles
+    (16, 10448, 11424, 6), (24, 5320, 8192, 12), (32, 12288, 10168, 5), (32, 2808, 2088, 7), (16, 552, 896, 3), (16, 16392, 4104, 3)])
+def test_k_parts_of_up_to_32_rows(M, N, K, parts):
+    """Six stages (at least eight slabs a part, one workgroup per compute unit) or two (four slabs, two workgroups), on either
+    side of the lines between them; two where the tile does not divide the shape."""
+    p = fb.problem(M, N, K, 1, 0)
+    assert fb.flux_tile_shape(fb.FLUX_OP_RS, p).tile_m == 32
+    assert fb.flux_split_plan(fb.FLUX_OP_RS, p) == (0, -(-N // 128), parts)
