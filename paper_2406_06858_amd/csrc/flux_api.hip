@@ -460,11 +460,13 @@ static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
       cfg = 9;
     }
     else if (p->M <= 256 && p->M % 64 == 0 && deep_ok && p->N % 128 == 0) cfg = 8;   // 64x128 deep
-    else if (one_round && (p->M < 128 ? p->K <= 8192 : p->M <= 512 && (p->K <= 4096 || weights <= 20ll * 1000 * 1000))) {
+    else if (one_round && (p->M < 128 ? p->K <= 8192 || weights <= 25ll * 1024 * 1024 : p->M <= 512 && (p->K <= 4096 || weights <= 20ll * 1000 * 1000))) {
       // Rows that no case above takes, whose 64x128 tiles fit the chip at once.  They read the weights once per 64
       // rows, 256x128 tiles once per 256, but with fewer K parts, and smaller ones to hand over, each.  Up to 127 rows
       // that wins up to K = 8192 (us, 256x128 or what was taken / 64x128: 72 rows 3584x8192 39 / 28, 8192x3584 24.3 / 21.3,
-      // 12288x6144 70 / 54; 4608x12288 41 / 48), up to 512 rows with a short K or few weights (200 rows 8192x3584 34.9 / 27.6,
+      // 12288x6144 70 / 54; 4608x12288 41 / 48), and beyond it for weights of up to 25M values, of which larger tiles leave
+      // the chip half empty (72 rows 1000x12288 20.7 / 16.8, 2048x12288 22.3 / 20.5, 120 rows 1536x12288 24.7 / 24.2, ag 72
+      // rows 1000x8200 24.0 / 20.5; the other side: 72 rows 2600x10000 28.3 / 31.5, 3584x8200 27.5 / 28.3), up to 512 rows with a short K or few weights (200 rows 8192x3584 34.9 / 27.6,
       // 1536x1536 28.5 / 14.4, 3584x4608 25.9 / 24.1, 1536x6144 23.8 / 21.2; 512 rows 3584x1536 34.0 / 18.2; the other side:
       // 136, 200 and 320 rows 3584x6144 25.2 / 27.3, 28.1 / 29.3, 36.3 / 40.8, 200 rows 6144x6144 40 / 52, 512 rows
       // 6144x1536, 384 tiles, 28.2 / 28.9).

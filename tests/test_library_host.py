@@ -374,3 +374,11 @@ def test_k_parts_of_up_to_32_rows(M, N, K, parts):
     p = fb.problem(M, N, K, 1, 0)
     assert fb.flux_tile_shape(fb.FLUX_OP_RS, p).tile_m == 32
     assert fb.flux_split_plan(fb.FLUX_OP_RS, p) == (0, -(-N // 128), parts)
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(72, 1000, 12288, (64, 128)), (104, 1536, 12288, (64, 128)), (120, 2048, 12288, (64, 128)), (72, 4608, 8192, (64, 128)),
+                                        (72, 2600, 10088, (128, 128)), (72, 3200, 12288, (128, 128))])
+def test_tile_of_65_to_127_rows_over_a_long_k(M, N, K, tile):
+    for op in (fb.FLUX_OP_RS, fb.FLUX_OP_AG):
+        got = fb.flux_tile_shape(op, fb.problem(M, N, K, 8, 0))
+        assert (got.tile_m, got.tile_n) == tile
