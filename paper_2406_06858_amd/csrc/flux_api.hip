@@ -407,6 +407,9 @@ static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
     // few rows: the tile is bound by memory, so take the deep load pipeline
     const bool deep_ok = p->K % 64 == 0;
     const long long weights = (long long)p->N * p->K;
+    // Few results: 64x128 tiles cut for one workgroup per CU have parts enough, and fewer to hand over, than for two (us, two /
+    // one: 128x1536x12288 27.4 / 24.5, 256x1024x8192 20.6 / 17.9, 256x1024x12288 24.2 / 22.1, ag 256x1024x8192 27.1 / 24.3)
+    const bool narrow = (long long)p->M * p->N <= 256ll * 1024;
     // 64x128 tiles on four stages, for any rows, columns and K (masked loads): tiles of one round of the chip
     const bool one_round = (long long)((p->M + 63) / 64) * ((p->N + 127) / 128) <= N_CU;
     if (p->M <= 32) {
@@ -432,13 +435,13 @@ static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
       // their finer K cut below (1536x1536 12.9 / 10.7, 3584x1536 13.7 / 12.2, 40 rows 1000x2008 15.7 / 14.7)
       cfg = (deep_ok && p->N % 64 == 0 && p->M == 64) ? 6 : p->K > 2048 ? 8 : 4;
     }
-    else if ((long long)p->M * p->N <= 256ll * 1024 && weights <= 4ll * 1024 * 1024) {
+    else if (narrow && weights <= 4ll * 1024 * 1024) {
       // 64x64, small problems, up to weights of 4M values (us, 64x64 on two against 64x128 on four stages: 72x1536x1536 9.9 /
       // 13.5, 136x1536x1536 12.1 / 14.1, 128x2048x2048 10.2 / 10.8, 128x1024x4096 15.7 / 16.0; above 72x3584x1536 18.3 / 14.5,
       // 72x3000x4096 27.0 / 13.6, 136x1536x4608 22.1 / 14.9)
       cfg = 3;
     }
-    else if (p->M == 128 && deep_ok && p->N % 128 == 0 && p->K > 8192 && 2ll * (p->N / 128) <= N_CU / 2) {
+    else if (p->M == 128 && deep_ok && p->N % 128 == 0 && p->K > 8192 && !narrow && 2ll * (p->N / 128) <= N_CU / 2) {
       // Two m-tiles, a long K and few columns: the two-per-CU 64x128 tile, whose finer K cut fills
       // its 512 slots (6144x12288: 55 against 66 us for 64x128 on four stages, weights from HBM).
       // (64x64 tiles on six stages are 11-19 % ahead on 3584x8192 and 8192x3584 while the weights
@@ -453,7 +456,7 @@ static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
       // 68-72 against 88-91 us.
       cfg = 1;
     }
-    else if (p->M == 256 && deep_ok && p->N % 128 == 0 && p->K >= 8192 && 4ll * (p->N / 128) <= N_CU) {
+    else if (p->M == 256 && deep_ok && p->N % 128 == 0 && p->K >= 8192 && !narrow && 4ll * (p->N / 128) <= N_CU) {
       // ... and where that takes more parts, over a long K: 64x128 tiles, two workgroups per CU, K
       // cut so that every slot has a part (3584x8192, weights from HBM: 36-41 us against 40-44 us
       // for the same tile on four stages, one per CU).

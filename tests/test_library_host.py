@@ -382,3 +382,10 @@ def test_tile_of_65_to_127_rows_over_a_long_k(M, N, K, tile):
     for op in (fb.FLUX_OP_RS, fb.FLUX_OP_AG):
         got = fb.flux_tile_shape(op, fb.problem(M, N, K, 8, 0))
         assert (got.tile_m, got.tile_n) == tile
+
+
+@pytest.mark.parametrize("M,N,K,parts", [(128, 1536, 12288, 10), (128, 2048, 12288, 8), (256, 1024, 8192, 8), (256, 1024, 12288, 8),       # one workgroup per CU
+                                         (128, 2176, 12288, 15), (256, 1152, 8192, 13)])                                                   # two
+def test_k_parts_of_few_rows_and_columns(M, N, K, parts):
+    p = fb.problem(M, N, K, 8, 0)
+    assert fb.flux_split_plan(fb.FLUX_OP_RS, p) == (0, M // 64 * (N // 128), parts)
