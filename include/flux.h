@@ -215,10 +215,11 @@ int flux_gemm_rs_static(const flux_problem_t* p, const void* A, const void* B,
  * that waits takes over unclaimed pieces of the tiles it waits for, so a mover that has not been
  * given a compute unit yet cannot stall the grid.
  * Stream capture: in the default form the call is one kernel launch on compute_stream, which also
- * moves a local chunk that is not in place yet (R = 1, or a local chunk that lies inside A_agg or
- * C: a copy ahead of it), and everything that changes from call to call lives in the workspace, so
- * it may be recorded in a HIP graph and replayed.  The forms with a driver take a fresh claim id from the host on every call: under
- * stream capture they return FLUX_ERR_UNSUPPORTED.
+ * moves a local chunk that is not in place yet (R = 1, a local chunk that lies inside A_agg or C, or
+ * one above 6 MiB where all tiles are cut along K: a copy ahead of it), and everything that changes
+ * from call to call lives in the workspace, so it may be recorded in a HIP graph and replayed.  The
+ * forms with a driver take a fresh claim id from the host on every call: under stream capture they
+ * return FLUX_ERR_UNSUPPORTED.
  *   A_chunks        host array [R] of device pointers, chunk r = [M/R,K] bf16 ("A_list").
  *   A_agg           device [M,K] bf16 (row pitch lda), written by the call.  If A_chunks[rank] already points
  *                   at A_agg + rank*(M/R)*lda the local chunk is not copied.  The local chunk may lie elsewhere

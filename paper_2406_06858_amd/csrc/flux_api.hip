@@ -1174,12 +1174,17 @@ int flux_ag_gemm(const flux_problem_t* p, const void* const* A_chunks, void* A_a
   // A local chunk that is not in place yet is moved by the grid like the remote ones, ahead of them, where the grid moves
   // everything; a grid that keeps a link's schedule (whose tiles are counted from the first remote one), a driver, or R = 1
   // has it copied by a kernel of its own ahead of the grid.  So does a chunk handed over inside the gathered matrix (in
-  // another chunk's rows, say) or inside C: the grid writes both while it would still be reading the chunk.
+  // another chunk's rows, say) or inside C: the grid writes both while it would still be reading the chunk.  And so does a large
+  // chunk of a grid whose every tile is cut along K: no part can start before the grid has moved everything, and the copy
+  // kernel moves it faster (us, grid / copy ahead: 2 ranks 1088x1408x12288, 13 MB, 113 / 98, 1352x2800x10608 148 / 143, 4 ranks
+  // 7 MB 141 / 137, 2 ranks 2000x1536x6144 71.9 / 70.2; the other side: 2 ranks 512x3584x8192, 4 MB, 52.4 / 54.0, 8 ranks
+  // 200x3584x8192 35.2 / 37.1, whole tiles: 2 ranks 4096x3584x8192, 34 MB, 196 / 202, 8192x2560x1536 94.8 / 99.3).
   const __bf16* local_dst = static_cast<const __bf16*>(A_agg) + (size_t)p->rank * (p->M / p->R) * pitch_a(p);
   const bool local_away = A_chunks[p->rank] != static_cast<const void*>(local_dst);
   const size_t agg_bytes = ((size_t)(p->M - 1) * pitch_a(p) + p->K) * 2;
   const size_t c_bytes = ((size_t)(p->M - 1) * pitch_c(p) + p->N) * (p->out_dtype == FLUX_F32 ? 4 : 2);
-  const bool local_in_grid = local_away && pl.copy_self && pl.pace_ticks == 0 && p->R > 1 &&
+  const bool all_cut = pl.split_k > 1 && pl.full_tiles == 0;
+  const bool local_in_grid = local_away && pl.copy_self && pl.pace_ticks == 0 && p->R > 1 && !(all_cut && chunk_elems * 2 > (6u << 20)) &&
                              !overlap(A_chunks[p->rank], chunk_elems * 2, A_agg, agg_bytes) &&
                              !overlap(A_chunks[p->rank], chunk_elems * 2, C, c_bytes);
   if (pl.copy_help && p->R > 1) {

@@ -1,5 +1,5 @@
-"""A local chunk in a buffer of its own is moved by the GEMM grid, ahead of the remote chunks; and the slice reduction for
-every number of partials.  Integer inputs whose sums stay below 2^24: bit for bit."""
+"""A local chunk in a buffer of its own is moved by the GEMM grid, ahead of the remote chunks, or copied ahead of it; and the
+slice reduction for every number of partials.  Integer inputs whose sums stay below 2^24: bit for bit."""
 import pytest
 import torch
 
@@ -21,6 +21,8 @@ pytestmark = pytest.mark.gpu
     (64, 128, 256, 2, 1, 7, 0),
     (4096, 1280, 4096, 8, 1, 3, 0),       # several rounds of tiles, many pieces per owner
     (8192, 2560, 1536, 8, 1, 1, 0),       # the last chunks carried inside the main loops
+    (768, 384, 8192, 2, 1, 3, 0),         # K-cut tiles, a chunk of 6 MiB: by the grid ...
+    (770, 384, 8192, 2, 1, 3, 8),         # ... and above: a copy ahead of the grid
 ])
 def test_local_chunk_moved_by_the_grid(M, N, K, R, ctpc, cfg, pitch):
     w = fi.Workload("local", "ag", M, N, K, R, a_dist=("int", 2), b_dist=("int", 2), seed=M + K + R)
@@ -92,7 +94,7 @@ def test_local_chunk_inside_what_the_call_writes(M, N, K, R, cfg, where):
 @pytest.mark.parametrize("dt", ["bf16", "f32"])
 @pytest.mark.parametrize("R", range(1, 17))
 def test_slice_reduce_of_every_rank_count(R, dt):
-    """Partials padded to 1, 3, 7 or 15 peers; one row of one vector, and a row count no workgroup divides."""
+    """Every number of partials from one to sixteen; one row of one vector, and a row count no workgroup divides."""
     td = torch.bfloat16 if dt == "bf16" else torch.float32
     for S, N in ((1, 8), (37, 136)):
         g = torch.Generator().manual_seed(R + S)
