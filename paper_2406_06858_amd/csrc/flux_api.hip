@@ -379,7 +379,11 @@ static void plan_split(const flux_problem_t* p, int cfg, long long tiles, int kt
 // Estimated time of the GEMM under configuration `cfg`, in arbitrary units: rounds of the grid
 // over the chip's workgroup slots, times the tile's area, over the configuration's rate per slot
 // (from measurements of full grids: 256x256 = 1, 256x128 on three stages 0.84, 128x128 two per
-// CU 0.8 per CU; a shape the tile does not divide 0.7 of that, so that of two near ones the tile that divides it is taken).
+// CU 0.8 per CU).  A shape that the tile does not divide counts 0.7 of that.  Masked loads cost less (ag 4096x3584x8192 with 8
+// rows, columns or K values less: 256x256 5 %, 256x128 7-15 %, 128x128 4-16 %), but with 0.93 in its place five of twelve drawn
+// shapes whose tile then changes are slower (1920x12288x3584 209 -> 237 us, 3456x6144x3584 204 -> 217) and four faster
+// (3968x8192x4608 263 -> 237, ag 5248x8192x1536 158 -> 143, ag 4224x3584x8192 246 -> 215): it stands in for what the
+// estimate leaves out, the epilogues of a last round among it.
 static double plan_cost(const flux_problem_t* p, int cfg) {
   const int bm = g_cfgs[cfg].bm, bn = g_cfgs[cfg].bn, bk = g_cfgs[cfg].bk;
   const long long tiles = (long long)((p->M + bm - 1) / bm) * ((p->N + bn - 1) / bn);

@@ -23,7 +23,7 @@ namespace flux {
 #elif FLUX_CFG_ID == 9
 #define FLUX_CFG_PARAMS 64, 128, 64, 2, 2, 4, 1    // M <= 256: four LDS stages
 #elif FLUX_CFG_ID == 10
-#define FLUX_CFG_PARAMS 64, 128, 64, 2, 2, 3, 2    // EXPERIMENT: 64x128, three stages, two workgroups per CU
+#define FLUX_CFG_PARAMS 64, 128, 64, 2, 2, 3, 2    // few rows over a long K: 64x128, three stages, two workgroups per CU
 #else
 #error "FLUX_CFG_ID must be 1..10"
 #endif
