@@ -25,7 +25,7 @@ if ROOT not in sys.path:
 
 MFMA_BF16_PEAK_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
 # bytes per launch behind the L2 of the two kernels of the timed step (rocprofv3 FETCH_SIZE + WRITE_SIZE)
-TRAFFIC_BYTES = {"rs": 2170.7e6 + 205.8e6, "ag": 2619.6e6 + 319.2e6}     # profiles/bench_c4_pmc_traffic.txt
+TRAFFIC_BYTES = {"rs": 2220.0e6 + 223.6e6, "ag": 2710.7e6 + 325.1e6}     # profiles/bench_c4_pmc_traffic.txt
 HBM_PEAK_GBS = 8000.0
 TIMEOUT_TICKS = 500_000_000        # 5 s: a lost signal ends the run with an error, not a hang
 
