@@ -757,7 +757,9 @@ static int launch_gemm(const Plan& pl, int epi, int wait, GemmArgs& a, hipStream
   const bool no_peers = epi != EPI_RS || a.write_only != 0 || a.R == 1;
   const bool share = pl.split_k > (pl.bm * pl.bn > 64 * 128 || no_peers ? 2 : 1) && pl.split_k <= SK_SHARE_MAX && a.write_only != 2 && a.tile_ready == nullptr &&
                      (long long)pl.split_tiles * pl.split_k <= (long long)N_CU * g_cfgs[pl.cfg].occupancy;
-  a.sk_share = share;
+  // (an eighth of a main loop: about 0.4 us per slab of a 64x128 tile; the parts of a last round start one by one)
+  const long long eighth = (long long)(pl.k_per_split / pl.bk) * pl.bm * pl.bn * 5 / (64 * 128);
+  a.sk_share = !share ? 0 : pl.full_tiles > 0 ? (int32_t)SK_WAIT_TICKS : (int32_t)std::min<long long>(std::max<long long>(eighth, SK_START_TICKS), SK_WAIT_TICKS);
   if (e0) FLUX_HIP(hipEventRecord(e0, s));
   if (pl.resident && epi == EPI_RS && !wait && a.write_only == 0) {
     a.persist_blocks = grid;

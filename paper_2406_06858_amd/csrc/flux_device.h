@@ -152,7 +152,8 @@ struct GemmArgs {
   // ---- split-K hand-over, reduce-scatter epilogue ----
   float* sk_partials;             // [split_k][split_tiles][BM*BN] fp32
   uint32_t* sk_counters;          // [tiles]
-  int32_t sk_share;               // the parts of a tile share its final sum out among themselves (see finish_shared)
+  int32_t sk_share;               // not 0: the parts of a tile share its final sum out among themselves (see SharedFinish), and wait so many
+                                  // 100 MHz ticks for parts that have not started
   int32_t out_f32;
   uint32_t* tile_ready;           // reduce-scatter, Write branch: per output tile, producers that have written it; null: not kept
   int32_t persist_blocks;         // > 0: a grid of resident workgroups, workgroup b takes the blocks b, b + grid, ... below this
@@ -1073,8 +1074,8 @@ __device__ __forceinline__ void epilogue_all_atomic(const GemmArgs& a, void* con
 // a block is finished made the small calls 0.5-1 us slower: the code of a tail runs once, and every line of it is fetched.)
 //
 // A part that has not been given a compute unit yet (another kernel holds some) may be waiting for one of these.  So a part
-// waits for the others only where all of them have started, and for those that have not an eighth of its own time (at least
-// 0.5 us: a grid is not dispatched at once); a part that all others gave up on sums the tile alone, as if nothing were
+// waits for the others only where all of them have started, and for those that have not about an eighth of the time of its
+// main loop (sk_share, set on the host: nothing has to be kept through the main loop); a part that all others gave up on sums the tile alone, as if nothing were
 // shared.  Waiting for every part up to the bound stalled calls beside a kernel that holds compute units for as long (us per
 // call beside one that holds 4 / 32 / 128 units, every part waited for -> only started ones -> none ever: rs 64 x 2048 x 8192
 // 54 / 54 / 72 -> 26 / 26 / 29 -> 23 / 24 / 28, ag 8 x 3584 x 8192 30 / 59 / 73 -> 31 / 31 / 36 -> 28 / 29 / 34).  The start is
@@ -1090,13 +1091,12 @@ constexpr uint32_t SK_COUNT = 31u, SK_SEEN_AT = 5, SK_STARTED_AT = 10, SK_GAVE_U
 constexpr int SK_SHARE_MAX = 16;                      // parts of a tile whose shares fit the word
 static_assert(SK_SHARE_MAX <= 16, "a give-up bit per part, counts of up to 31");
 constexpr uint32_t SK_WAIT_TICKS = 10000;             // 100 us: longest wait for a part that has started
-constexpr uint32_t SK_START_TICKS = 50;               // 0.5 us: shortest wait for one that has not (a grid is being dispatched)
+constexpr uint32_t SK_START_TICKS = 50;               // 0.5 us: shortest wait for one that has not (a grid is not dispatched at once)
 
-// This part has its first operands and enters its main loop: counted in, and the time taken.
-__device__ __forceinline__ uint32_t part_started(const GemmArgs& a, int tile, int tid) {
+// This part has its first operands and enters its main loop.
+__device__ __forceinline__ void part_started(const GemmArgs& a, int tile, int tid) {
   if (tid == 0)
     __hip_atomic_fetch_add(a.sk_counters + sk_counter_index(tile - a.full_tiles), 1u << SK_STARTED_AT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return (uint32_t)wall_clock64();
 }
 
 template <class C, int EPI, bool EDGE, bool PF32, int NP>
@@ -1177,10 +1177,9 @@ struct SharedFinish {
     if (!EDGE || (m0 + row < a.M && n0 + col < a.N)) store_row8<EPI>(a, lds_outs, m0 + row, n0 + col, o);
   }
 
-  // Called by every part once its sums are parked and acknowledged.  `lds_misc`: two ints of the workgroup; `t_started`: what
-  // part_started returned.  False: all others gave up, the tile is this part's alone (the caller sums it up).
+  // Called by every part once its sums are parked and acknowledged.  `lds_misc`: two ints of the workgroup.  False: all others gave up, the tile is this part's alone (the caller sums it up).
   static __device__ __forceinline__ bool run(const GemmArgs& a, int* lds_misc, void* const* lds_outs, float* ep, int tile, int split,
-                                             int m0, int n0, int tid, int lane, int wave, uint32_t t_started) {
+                                             int m0, int n0, int tid, int lane, int wave) {
     const int st = tile - a.full_tiles, S = a.split_k;
     uint32_t* const word = a.sk_counters + sk_counter_index(st);
     constexpr int NW = C::NT / 64;
@@ -1206,9 +1205,7 @@ struct SharedFinish {
       } else {
         const uint32_t t0 = (uint32_t)wall_clock64();
         const uint32_t longest = a.timeout_ticks < SK_WAIT_TICKS ? (uint32_t)a.timeout_ticks : SK_WAIT_TICKS;
-        uint32_t unstarted = a.full_tiles > 0 ? longest : (t0 - t_started) / 8;
-        if (unstarted < SK_START_TICKS) unstarted = SK_START_TICKS;
-        if (unstarted > longest) unstarted = longest;
+        const uint32_t unstarted = (uint32_t)a.sk_share < longest ? (uint32_t)a.sk_share : longest;
         for (;;) {
           const uint32_t now = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           if ((now & SK_COUNT) == (uint32_t)S) break;
@@ -1253,7 +1250,7 @@ struct SharedFinish {
 template <class C, int EPI, bool EDGE>
 __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem, int* lds_misc, void* const* lds_outs,
                                           f32x4 (&acc)[C::MI][C::NI], int tile, int split, bool is_split,
-                                          int m0, int n0, int tid, int lane, int wave, int wm, int wn, uint32_t t_started, int vb = -1) {
+                                          int m0, int n0, int tid, int lane, int wave, int wm, int wn, int vb = -1) {
   trace_stamp(a, TRACE_MAIN_END, vb);
   // ---- split-K: all but the last-arriving workgroup of a tile park their partial sums ----
   if (is_split) {
@@ -1286,13 +1283,13 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
     if (a.sk_share) {                                     // (uniform)
       float* const ep = reinterpret_cast<float*>(smem) + wave * (32 * C::EP_STRIDE);
       bool finished;
-      if (EPI != EPI_RS || a.write_only) finished = SharedFinish<C, EPI, EDGE, false, 0>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave, t_started);
+      if (EPI != EPI_RS || a.write_only) finished = SharedFinish<C, EPI, EDGE, false, 0>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
       else if (a.R <= 8) {
-        if (a.partial_f32) finished = SharedFinish<C, EPI, EDGE, true, 7>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave, t_started);
-        else finished = SharedFinish<C, EPI, EDGE, false, 7>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave, t_started);
+        if (a.partial_f32) finished = SharedFinish<C, EPI, EDGE, true, 7>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
+        else finished = SharedFinish<C, EPI, EDGE, false, 7>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
       } else {
-        if (a.partial_f32) finished = SharedFinish<C, EPI, EDGE, true, 15>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave, t_started);
-        else finished = SharedFinish<C, EPI, EDGE, false, 15>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave, t_started);
+        if (a.partial_f32) finished = SharedFinish<C, EPI, EDGE, true, 15>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
+        else finished = SharedFinish<C, EPI, EDGE, false, 15>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
       }
       if (finished) {
         trace_stamp(a, TRACE_END, vb);
@@ -1829,7 +1826,7 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
       for (int e = 0; e < 4; ++e) acc[mi][ni][e] = 0.f;
 
   pipe.start(ld, a, pool, k_begin, KT, wave);
-  const uint32_t t_started = is_split && a.sk_share ? part_started(a, tile, tid) : 0u;
+  if (is_split && a.sk_share) part_started(a, tile, tid);
   int kt = 0;
   if constexpr (CARRY) {
     if (side.pending()) {
@@ -1876,7 +1873,7 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
   }
   pipe.run(ld, a, pool, k_begin, KT, kt, wave, acc);
   wait_vm0_and_barrier();        // the epilogue's staging area lies over stages other waves may still be reading
-  gemm_tail<C, EPI, EDGE>(a, pool, lds_misc, lds_outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, t_started);
+  gemm_tail<C, EPI, EDGE>(a, pool, lds_misc, lds_outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn);
 }
 
 // The same kernel as a grid of resident workgroups, one per compute unit, each walking the block
@@ -1930,10 +1927,10 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma_resident(const 
     MmaPipe<C, false, false> pipe;
     pipe.init(pool, wm, wn, lane);
     pipe.start(ld, a, pool, k_begin, KT, wave);
-    const uint32_t t_started = is_split && a.sk_share ? part_started(a, tile, tid) : 0u;
+    if (is_split && a.sk_share) part_started(a, tile, tid);
     pipe.run(ld, a, pool, k_begin, KT, 0, wave, acc);
     wait_vm0_and_barrier();
-    gemm_tail<C, EPI, false>(a, pool, lds_misc, lds_outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, t_started, vb);
+    gemm_tail<C, EPI, false>(a, pool, lds_misc, lds_outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, vb);
     __syncthreads();      // the staging area and lds_misc are the next block's
   }
 }
