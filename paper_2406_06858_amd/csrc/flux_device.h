@@ -228,18 +228,23 @@ __device__ __forceinline__ void trace_stamp(const GemmArgs& a, int point, int vb
 
 // ---- LDS swizzles ---------------------------------------------------------------------------
 // A tile: rows of BK bf16 = BK/8 slots of 16 B; slot s of row r is stored at slot s ^ fA(r).
-// With 128-byte rows, 8 (or 16) consecutive rows read the same logical slot in one
-// ds_read_b128 pass; fA spreads them over all banks for both a 128 B and a 256 B wide LDS.
+// LDS has 64 banks of 4 B and answers a ds_read_b128 in four passes of 16 lanes that are not consecutive: lanes 0-3,
+// 12-15 and 20-27 together, then 4-11, 16-19 and 28-31, and the same for the upper half (measured: which two lanes get in each
+// other's way).  A fragment's lanes are rows i = 0..15 of slot q, the next sixteen the same rows of slot q + 1 (q even), so a
+// pass holds every row once, half of them with the lowest slot bit flipped.  128-byte rows fill half of the banks: the eight
+// rows of one parity must land in eight different slots, and s ^ (row & 7) does that.  (With bit 3 of the row mixed in as
+// well, right for sixteen consecutive lanes, every read took two turns: 6.0 against 3.1 cycles per instruction.)
 template <int SLOTS>
 __device__ __forceinline__ int swz_a(int row) {
-  return ((row & 7) ^ ((row >> 3) & 1)) & (SLOTS - 1);
+  return row & (SLOTS - 1);
 }
-// B tile: rows of BN bf16 (one k each); the transposing read touches 4 consecutive k rows at
-// the same columns, so rows k..k+3 are pushed to different 64-byte (and 32-byte) bank groups.
+// B tile: rows of BN bf16 (one k each).  The transposing read answers 32 lanes per pass: 32 bytes of each of the rows k..k+3
+// and k+8..k+11, whose pitch is a multiple of all banks (or, 64 columns, half of it).  Bits 0, 1 and 3 of k pick the 32-byte bank
+// group.  (Without bit 3 the two sets of four rows got in each other's way: 3.1 against 2.1 cycles per instruction.)
 template <int SLOTS>
 __device__ __forceinline__ int swz_b(int k) {
   const int kk = k & 3;
-  return ((kk << 2) ^ (kk << 1)) & (SLOTS - 1);
+  return ((kk << 2) ^ (kk << 1) ^ ((k >> 2) & 2)) & (SLOTS - 1);
 }
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
@@ -252,13 +257,20 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 // Streaming (non-temporal) 16-byte accesses for data touched exactly once: peer partials and
 // outputs must not push the A/B panels, which are re-read many times, out of the L2.
+// All of them are addresses of device memory.  Where the type says so (global_u32x4) an access counts as one to memory alone; of a
+// pointer that was kept in LDS the compiler does not know it and makes flat accesses, which a wait for an LDS read then waits
+// for too.  st_out16 says where that is wanted.
+typedef __attribute__((address_space(1))) u32x4 global_u32x4;
+__device__ __forceinline__ u32x4 ld_stream(const void* p) { return __builtin_nontemporal_load((const global_u32x4*)p); }
 __device__ __forceinline__ uint4 ld_stream16(const void* p) {
-  const u32x4 v = __builtin_nontemporal_load(static_cast<const u32x4*>(p));
+  const u32x4 v = ld_stream(p);
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
+template <bool FLAT = false>
 __device__ __forceinline__ void st_stream16(void* p, const uint4& v) {
   const u32x4 d = {v.x, v.y, v.z, v.w};
-  __builtin_nontemporal_store(d, static_cast<u32x4*>(p));
+  if (FLAT) __builtin_nontemporal_store(d, static_cast<u32x4*>(p));
+  else __builtin_nontemporal_store(d, (global_u32x4*)p);
 }
 
 // 16-byte store at device scope: written through this die's L2, so that a reader on another
@@ -268,9 +280,13 @@ __device__ __forceinline__ void store_through(uint4* p, const u32x4& d) {
 }
 // Output vectors: streamed, or written through when a consumer may read the tile as soon as its ready
 // counter moves (`through`, uniform).
+// FLAT: a wave does not read on from LDS before its stores are out.  With 256x256 tiles and peers, where every unit reads and
+// writes all the memory gives, that is faster (us, flat / global: rs 8192x12288x1536 424 / 438, 4096x8192x3584 250 / 252); elsewhere
+// waiting costs (1496x5112x3400 89.1 / 86.5, the end of a 256x256 tile without peers 9.0 / 7.6).
+template <bool FLAT>
 __device__ __forceinline__ void st_out16(void* p, const uint4& v, bool through) {
   if (through) store_through(static_cast<uint4*>(p), u32x4{v.x, v.y, v.z, v.w});
-  else st_stream16(p, v);
+  else st_stream16<FLAT>(p, v);
 }
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -279,21 +295,40 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 // B_NK: B is given as [N,K] (row n holds the K values of output column n, the layout of a linear
 // layer's weight).  Its tile then sits in LDS like A's (rows of BK values, the same slot swizzle) and a
 // fragment is one 16-byte read per lane, as for A, instead of two transposing reads.
-template <int BM_, int BN_, int BK_, int WAVES_M_, int WAVES_N_, int NSTAGE_, int OCC_, bool B_NK_ = false>
+// NA, NB: slabs of A and of B that LDS holds; one of the two may have one more.
+template <int BM_, int BN_, int BK_, int WAVES_M_, int WAVES_N_, int NA_, int NB_, int OCC_, bool B_NK_ = false>
 struct TileCfg {
   static constexpr int BM = BM_, BN = BN_, BK = BK_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_;
-  static constexpr int NSTAGE = NSTAGE_, OCC = OCC_;
+  static constexpr int NA = NA_, NB = NB_, OCC = OCC_;
   static constexpr bool B_NK = B_NK_;
   static constexpr int NT = WAVES_M * WAVES_N * 64;
   static constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
   static constexpr int MI = WTM / 16, NI = WTN / 16;       // 16x16 blocks of a wave's tile
   static constexpr int A_SLOTS = BK / 8, B_SLOTS = BN / 8;
   static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BK * BN * 2;
-  static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
+  static constexpr int RING_BYTES = NA * A_BYTES + NB * B_BYTES;   // the A slabs, then the B slabs
   static constexpr int EP_STRIDE = WTN + 8;                       // floats; 4 rows apart = 128 B off
   static constexpr int EP_BYTES = WAVES_M * WAVES_N * 32 * EP_STRIDE * 4;
   static_assert(BM % (WAVES_M * 32) == 0 && BN % (WAVES_N * 32) == 0 && BK % 32 == 0, "tile shape");
   static_assert(B_SLOTS >= 8, "BN >= 64");
+  static_assert(NA >= 2 && NB >= 2 && NA <= NB + 1 && NB <= NA + 1, "the order of the loads (MmaPipe)");
+
+  // LDS of a workgroup: the ring, over it (once the main loop is done) the epilogue's staging area, and a few words that the
+  // workgroup shares (SharedWords).  Where the ring takes all of a compute unit's LDS the words lie over the slab that is asked
+  // for last, by the main loop, and behind the staging area after it.
+  static constexpr int LDS_MAX = 160 * 1024;
+  static constexpr int WORDS_BYTES = 256;
+  static constexpr int MAX_BYTES = RING_BYTES > EP_BYTES ? RING_BYTES : EP_BYTES;
+  static constexpr bool WORDS_IN_RING = MAX_BYTES + WORDS_BYTES > LDS_MAX / OCC;
+  static constexpr int POOL_BYTES = WORDS_IN_RING ? MAX_BYTES : MAX_BYTES + WORDS_BYTES;
+  static constexpr int WORDS_AT = !WORDS_IN_RING ? MAX_BYTES : NA > NB ? (NA - 1) * A_BYTES : RING_BYTES - B_BYTES;   // before and in the main loop
+  static constexpr int WORDS_AT_TAIL = WORDS_IN_RING ? MAX_BYTES - WORDS_BYTES : MAX_BYTES;   // after it
+  static_assert(!WORDS_IN_RING || (NA != NB && WORDS_AT_TAIL >= EP_BYTES), "room for the shared words");
+};
+
+struct SharedWords {
+  void* outs[FLUX_MAX_RANKS];       // output slices (reduce-scatter) or chunk sources (all-gather), by rank
+  int misc[4];
 };
 
 // MFMA shape: 16x16x32, the A fragment held over a row of MFMAs.  With random operands the chip runs at its power
@@ -319,7 +354,7 @@ __device__ __forceinline__ void mfma_results_settle(f32x4 (&acc)[MI][NI]) {
 
 // Store 8 consecutive output columns of one row into the owner's slice (GetOutput of Alg. 1) or
 // into C, converting once.
-template <int EPI>
+template <int EPI, bool FLAT>
 __device__ __forceinline__ void store_row8(const GemmArgs& a, void* const* lds_outs, int gm, int gn, const float (&v)[8]) {
   void* base;
   size_t o;
@@ -334,13 +369,13 @@ __device__ __forceinline__ void store_row8(const GemmArgs& a, void* const* lds_o
   }
   if (a.out_f32) {
     float* q = static_cast<float*>(base) + o;
-    st_out16(q, make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])), through);
-    st_out16(q + 4, make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])), through);
+    st_out16<FLAT>(q, make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])), through);
+    st_out16<FLAT>(q + 4, make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])), through);
   } else {
     uint4 w;
     w.x = pack_bf16x2(v[0], v[1]); w.y = pack_bf16x2(v[2], v[3]);
     w.z = pack_bf16x2(v[4], v[5]); w.w = pack_bf16x2(v[6], v[7]);
-    st_out16(static_cast<__bf16*>(base) + o, w, through);
+    st_out16<FLAT>(static_cast<__bf16*>(base) + o, w, through);
   }
 }
 
@@ -415,7 +450,7 @@ __device__ __forceinline__ void epilogue_block(const GemmArgs& a, void* const* l
           }
         }
       }
-      if (ok[b]) store_row8<EPI>(a, lds_outs, m0 + row_base + r, n0 + col_base + cc * 8, v);
+      if (ok[b]) store_row8<EPI, NP != 0 && C::BM * C::BN == 256 * 256>(a, lds_outs, m0 + row_base + r, n0 + col_base + cc * 8, v);
     }
     // one batch of peer loads in flight at a time: left alone, the scheduler hoists the loads of
     // later batches up here too and has to spill accumulators to make room for them
@@ -488,7 +523,7 @@ __device__ __forceinline__ void copy_piece_as(const uint4* __restrict__ src, uin
     u32x4 v[DEPTH];
 #pragma unroll
     for (int u = 0; u < DEPTH; ++u)
-      if (i + u * stride < tile_vec) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + i + u * stride));
+      if (i + u * stride < tile_vec) v[u] = ld_stream(src + i + u * stride);
 #pragma unroll
     for (int u = 0; u < DEPTH; ++u)
       if (i + u * stride < tile_vec) store_through(dst + agg_index<PITCHED>(g, i + u * stride), v[u]);
@@ -512,7 +547,7 @@ __device__ __forceinline__ void load_piece(const uint4* __restrict__ src, unsign
 #pragma unroll
   for (int u = 0; u < COPY_DEPTH; ++u) {
     v[u] = u32x4{0, 0, 0, 0};
-    if (i + u * stride < tile_vec) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + i + u * stride));
+    if (i + u * stride < tile_vec) v[u] = ld_stream(src + i + u * stride);
   }
 }
 template <bool PITCHED>
@@ -947,7 +982,7 @@ __device__ __forceinline__ bool wait_signals(const GemmArgs& a, int m0, int m1, 
           const int chunk = row / a.S;
           src[u] = static_cast<const uint4*>(lds_srcs[chunk]) + (unsigned long long)(row - chunk * a.S) * vec_per_row + col;
           dst[u] = reinterpret_cast<uint4*>(const_cast<__bf16*>(a.A)) + (unsigned long long)row * ((unsigned long long)a.lda / 8) + col;
-          if (vv < nvec) x[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src[u]));
+          if (vv < nvec) x[u] = ld_stream(src[u]);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -1174,7 +1209,7 @@ struct SharedFinish {
     }
     int row, col;
     place(u, lane, row, col);
-    if (!EDGE || (m0 + row < a.M && n0 + col < a.N)) store_row8<EPI>(a, lds_outs, m0 + row, n0 + col, o);
+    if (!EDGE || (m0 + row < a.M && n0 + col < a.N)) store_row8<EPI, false>(a, lds_outs, m0 + row, n0 + col, o);
   }
 
   // Called by every part once its sums are parked and acknowledged.  `lds_misc`: two ints of the workgroup.  False: all others gave up, the tile is this part's alone (the caller sums it up).
@@ -1396,7 +1431,8 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
 //   A: one instruction = 8 rows x 128 B; lane i fills physical slot i%8 of row i/8 and fetches
 //      logical slot (i%8) ^ swz_a(row);
 //   B: one instruction = 1 KiB / (2*BN) k-rows; lane i fills physical slot i%B_SLOTS and
-//      fetches logical slot (i%B_SLOTS) ^ swz_b(k).
+//      fetches logical slot (i%B_SLOTS) ^ swz_b(k).  Which rows are a wave's: those whose bits 0, 1 and 3, which swz_b looks
+//      at, are the same in all of its instructions (wave_row, instr_row).
 // Per K-slab only scalar offsets change (soffset), so the address arithmetic costs no vector
 // instructions.
 //
@@ -1409,6 +1445,13 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
 // ---------------------------------------------------------------------------------------------
 typedef __attribute__((address_space(3))) void lds_void_t;
 
+// A slab of A and one of B: where they start in K, and the matrices, or nothing in the place of a slab past the end (its
+// loads touch no memory).
+struct Slabs {
+  __amdgpu_buffer_rsrc_t ra, rb;
+  int ka, kb;
+};
+
 template <class C, bool EDGE>
 struct DmaLoader {
   static constexpr int NW = C::NT / 64;
@@ -1416,8 +1459,17 @@ struct DmaLoader {
   static constexpr int A_INSTR = C::BM / A_RPI / NW;           // per wave
   static constexpr int RPI = C::B_NK ? A_RPI : 512 / C::BN;    // B rows per instruction: k-rows of BN values, or ([N,K]) n-rows of BK
   static constexpr int B_INSTR = (C::B_NK ? C::BN : C::BK) / RPI / NW;   // per wave
+  // first row of the p-th of a wave's instructions for B: wave_row(wave) + instr_row(p)
+  static constexpr __device__ int wave_row(int wave) {
+    if (C::B_NK || RPI == 8) return RPI * wave;
+    return RPI == 4 ? 8 * (wave & 1) + 4 * (wave >> 1) : 2 * (wave & 1) + 8 * (wave >> 1);
+  }
+  static constexpr __device__ int instr_row(int p) {
+    if (C::B_NK || RPI == 8) return p * RPI * NW;
+    return RPI == 4 ? 16 * p : 4 * (p & 1) + 16 * (p >> 1);
+  }
   static_assert(C::BK == 64, "A rows must be 128 B");
-  static_assert(NW % 2 == 0 && (RPI * NW) % 4 == 0, "swizzle must not depend on the instruction index");
+  static_assert(NW == 4 && (RPI == 2 || RPI == 4 || RPI == 8), "the swizzle must not depend on the instruction index");
   static_assert(C::BM % (A_RPI * NW) == 0 && (C::B_NK ? C::BN : C::BK) % (RPI * NW) == 0 && 512 % C::BN == 0, "loader shape");
 
   // Offsets into A and B are unsigned 32-bit byte offsets (a matrix has fewer than 2^31 elements, so
@@ -1426,24 +1478,18 @@ struct DmaLoader {
   uint32_t voff_a, voff_b;
   uint32_t K2, N2;               // row pitches in bytes
   uint32_t bytes_a, bytes_b;     // extents
+  uint32_t lds_b;                // where this wave's rows of B begin in a slab in LDS
   // EDGE: how many of this lane's loads of A (and of an [N,K] B) have a row, the k of its vector in a slab, and the k of
   // its first vector of a [K,N] B (out of reach for a lane past the last column)
   int lim_a, lim_b, k_vec, k_row;
   static constexpr uint32_t OUTSIDE = 0xfffffff0u;      // a matrix has fewer than 2^31 elements
-
-  // The same loader, or one whose loads all lie outside its records: they touch no memory (a slab past the end).
-  __device__ __forceinline__ DmaLoader only_if(bool valid, const GemmArgs& a) const {
-    DmaLoader d = *this;
-    d.ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.A), 0, (int)(valid ? bytes_a : 0u), 0x00027000);
-    d.rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.B), 0, (int)(valid ? bytes_b : 0u), 0x00027000);
-    return d;
-  }
 
   __device__ __forceinline__ void init(const GemmArgs& a, int m0, int n0, int wave, int lane) {
     bytes_a = ((unsigned)(a.M - 1) * (unsigned)a.lda + (unsigned)a.K) * 2u;
     bytes_b = (C::B_NK ? (unsigned)(a.N - 1) * (unsigned)a.ldb + (unsigned)a.K : (unsigned)(a.K - 1) * (unsigned)a.ldb + (unsigned)a.N) * 2u;
     ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.A), 0, (int)bytes_a, 0x00027000);
     rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.B), 0, (int)bytes_b, 0x00027000);
+    lds_b = (uint32_t)(wave_row(wave) * (1024 / RPI));
     const int r_in = lane / C::A_SLOTS, sp = lane % C::A_SLOTS;
     const int row = A_RPI * wave + r_in;
     if (EDGE) {
@@ -1458,44 +1504,42 @@ struct DmaLoader {
       voff_b = (uint32_t)(n0 + row) * N2 + ((uint32_t)(sp ^ swz_a<C::A_SLOTS>(row)) << 4);      // as for A, rows of n
     } else {
       const int k_in = lane / C::B_SLOTS, spb = lane % C::B_SLOTS;
-      const int k = RPI * wave + k_in;
+      const int k = wave_row(wave) + k_in;
       voff_b = (uint32_t)k * N2 + (uint32_t)n0 * 2u + ((uint32_t)(spb ^ swz_b<C::B_SLOTS>(k)) << 4);
       if (EDGE) k_row = n0 + (spb ^ swz_b<C::B_SLOTS>(k)) * 8 < a.N ? k : 0x40000000;
     }
   }
   static constexpr int N_INSTR = A_INSTR + B_INSTR;
 
-  // load idx (constant after unrolling; A's first) of the slab that starts at k0, into LDS stage `stage`
-  __device__ __forceinline__ void issue_dyn(int idx, const GemmArgs& a, unsigned char* stage, int k0, int wave) const {
-    if (idx < A_INSTR) {
-      const uint32_t v = !EDGE || idx < (k_vec < a.K - k0 ? lim_a : 0) ? voff_a : OUTSIDE;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void_t*)(stage + (idx * NW + wave) * 1024), 16, (int)v,
-                                               (int)((uint32_t)k0 * 2u + (uint32_t)(idx * A_RPI * NW) * K2), 0, 0);
-    } else {
-      const int p = idx - A_INSTR;
-      const bool in = !EDGE || (C::B_NK ? p < (k_vec < a.K - k0 ? lim_b : 0) : k_row < a.K - k0 - p * RPI * NW);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void_t*)(stage + C::A_BYTES + (p * NW + wave) * 1024), 16, (int)(in ? voff_b : OUTSIDE),
-                                               (int)(C::B_NK ? (uint32_t)k0 * 2u + (uint32_t)(p * RPI * NW) * N2 : (uint32_t)(k0 + p * RPI * NW) * N2), 0, 0);
-    }
+  __device__ __forceinline__ Slabs slabs(const GemmArgs& a, bool there_a, int ka, bool there_b, int kb) const {
+    return Slabs{__builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.A), 0, (int)(there_a ? bytes_a : 0u), 0x00027000),
+                 __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.B), 0, (int)(there_b ? bytes_b : 0u), 0x00027000), ka, kb};
+  }
+
+  // the d-th (constant after unrolling) of this wave's loads of A / of B, into `slab` in LDS
+  __device__ __forceinline__ void load_a(int d, const GemmArgs& a, const Slabs& s, unsigned char* slab, int wave) const {
+    const uint32_t v = !EDGE || d < (k_vec < a.K - s.ka ? lim_a : 0) ? voff_a : OUTSIDE;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(s.ra, (lds_void_t*)(slab + (d * NW + wave) * 1024), 16, (int)v,
+                                             (int)((uint32_t)s.ka * 2u + (uint32_t)(d * A_RPI * NW) * K2), 0, 0);
+  }
+  __device__ __forceinline__ void load_b(int d, const GemmArgs& a, const Slabs& s, unsigned char* slab) const {
+    const bool in = !EDGE || (C::B_NK ? d < (k_vec < a.K - s.kb ? lim_b : 0) : k_row < a.K - s.kb - instr_row(d));
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(s.rb, (lds_void_t*)(slab + instr_row(d) * (1024 / RPI) + lds_b), 16, (int)(in ? voff_b : OUTSIDE),
+                                             (int)(C::B_NK ? (uint32_t)s.kb * 2u + (uint32_t)instr_row(d) * N2 : (uint32_t)(s.kb + instr_row(d)) * N2), 0, 0);
   }
 
   // this wave's loads of the A part / the B part of one K-slab
-  __device__ __forceinline__ void issue_a(const GemmArgs& a, unsigned char* stage, int k0, int wave) const {
+  __device__ __forceinline__ void issue_a(const GemmArgs& a, const Slabs& s, unsigned char* slab, int wave) const {
 #pragma unroll
-    for (int d = 0; d < A_INSTR; ++d) issue_dyn(d, a, stage, k0, wave);
+    for (int d = 0; d < A_INSTR; ++d) load_a(d, a, s, slab, wave);
     // keep the loads where they are written: scheduled late they would be issued just before
     // the wait for them, and nothing would overlap
     __builtin_amdgcn_sched_barrier(0);
   }
-  __device__ __forceinline__ void issue_b(const GemmArgs& a, unsigned char* stage, int k0, int wave) const {
+  __device__ __forceinline__ void issue_b(const GemmArgs& a, const Slabs& s, unsigned char* slab) const {
 #pragma unroll
-    for (int d = A_INSTR; d < N_INSTR; ++d) issue_dyn(d, a, stage, k0, wave);
+    for (int d = 0; d < B_INSTR; ++d) load_b(d, a, s, slab);
     __builtin_amdgcn_sched_barrier(0);
-  }
-  // all loads of one K-slab for this wave
-  __device__ __forceinline__ void issue(const GemmArgs& a, unsigned char* stage, int k0, int wave) const {
-    issue_a(a, stage, k0, wave);
-    issue_b(a, stage, k0, wave);
   }
 };
 
@@ -1556,21 +1600,31 @@ __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-// The main loop of every kernel: K-slabs out of an LDS ring of NSTAGE stages, every memory instruction placed
+// The main loop of every kernel: K-slabs out of an LDS ring of NA slabs of A and NB of B, every memory instruction placed
 // by hand between the MFMAs.  A wave issues in order and (with the large tile) has its SIMD to itself, so what it
 // issues in a burst or waits for is time its matrix core stands still:
 //   * a slab has two k-steps of 32; the fragments of the next k-step are read while the MFMAs of this one run,
 //     one read per few MFMAs, also across the slab's end: the last k-step reads the first fragments of the
-//     next stage;
+//     next slab;
 //   * the one barrier per slab therefore sits at the start of the last k-step: by then the next slab has landed
-//     (counter wait: loads land in issue order), and every wave has its last fragments of this stage in
-//     registers, so this stage is free for the slab NSTAGE ahead;
-//   * the wave's loads for that slab are dealt out from there on, over LOAD_SPAN MFMAs, and have the rest of the slab
-//     to land.
-// What bounds it: the chip's power limit for long K (8192^3, N(0,.) operands: 1.57 PFLOP/s, MFMAs alone 2.0).  Plain
-// GEMM kernels, us, against reading a k-step's fragments in one burst, waiting at the slab's end and 32x32x16 MFMAs:
-// 8192^3 699 against 799, 8192x12288x4608 611 against 691, 4096x3584x8192 171 against 195, 8192x12288x1536 233 against
-// 260.  Of that the placement gives 5-6 %, the MFMA shape 8-9 %.
+//     (counter wait: loads land in issue order), and every wave has its last fragments of this slab in
+//     registers, so this slab's place is free;
+//   * from there on the wave's loads are dealt out over SPAN MFMAs: B of the slab NB ahead, which the next barrier but NB - 2
+//     needs, and A of the slab NA ahead.
+// An operand that leads (the 256x256 tile, whose two slabs of 64 KB leave 32 KB of LDS: a third slab of A): with two slabs of
+// each nothing was in flight at the barrier, and a slab's 64 KB, asked for in one go, took 1.24 us to come out of an L2 without a
+// single MFMA beside them, longer than the 1.05 us of its MFMAs.  A third slab keeps 32 to 96 KB on their way.  Plain GEMM, us,
+// two slabs / three of A: 4096x4096x8192 on zeros (no power limit) 166 / 135, where the MFMAs and the LDS reads take 134 by
+// themselves; N(0,1), operands from memory: 4096x3584x8192 204 / 178, 8192x4608x12288 846 / 727 (B as [N,K] 918 / 770),
+// 8192x12288x4608 670 / 648; 4096x4096x12288 with one peer 334 / 293.
+// What bounds it now: with operands from a cache the chip's power limit (4096x4096x8192 182-200 us on N(0,1), 135 on zeros;
+// MFMAs alone 2.0 PFLOP/s), with a long K from memory the memory (8192x4608x12288: 740 us on zeros too).
+// Placing reads and loads between 16x16x32 MFMAs, against a burst per k-step, a wait at the slab's end and 32x32x16: 8192^3 699
+// against 799 us, 8192x12288x4608 611 / 691; of that the placement gives 5-6 %, the MFMA shape 8-9 %.
+// Measured, not kept: bringing the lines of a slab 4 to 32 ahead to the L2 with a load of one word per line and workgroup
+// (instead of the third slab: the same gain; with it, or with 256x128 tiles: slower, a line is a line for the unit's L1);
+// starting each die's walk over K elsewhere (dies share lines in the Infinity Cache only while they walk in step: 176 -> 185 us,
+// 3000 rows 185 -> 258); B's fourth slab of 256x128 tiles (147 / 168 us on zeros, nothing on the calls).
 // The fragment reads are instructions the compiler cannot look into.  For every LDS read it can see, it works
 // out by itself which of the direct-to-LDS loads in flight must land first, and gets that wrong on the safe side.
 // Their addresses are a few registers per lane plus an immediate.  They are waited for in the k-step that issued
@@ -1582,137 +1636,187 @@ __device__ __forceinline__ void static_for(F&& f) {
 template <class C, bool B_FIRST, bool EDGE>
 struct MmaPipe {
   typedef DmaLoader<C, EDGE> Ld;
-  static constexpr int NS = C::NSTAGE;
+  static constexpr int NA = C::NA, NB = C::NB;
+  static constexpr int N = NA < NB ? NA : NB;
+  static constexpr bool A_LEADS = NA > NB, B_LEADS = NB > NA;      // by one slab
+  static constexpr int U = NA == NB ? N : NA * NB;                   // slabs after which both rings are where they were
   static constexpr int KS = C::BK / 32;                              // k-steps per slab
   static_assert(KS == 2, "two fragment sets, one per k-step");
   static constexpr int G = C::MI * C::NI;                            // MFMAs per k-step
   static constexpr int NF = C::MI + C::NI;                           // fragments per k-step
-  static constexpr int L = Ld::N_INSTR;                    // loads per slab and wave
-  static constexpr int LA = Ld::A_INSTR;
+  static constexpr int LA = Ld::A_INSTR, LB = Ld::B_INSTR, L = LA + LB;   // loads per slab and wave
+  static constexpr int LX = A_LEADS ? LA : B_LEADS ? LB : 0;       // loads of the operand that is a slab further ahead
+  static constexpr int LXA = A_LEADS ? LA : 0;
   static constexpr int NBV = C::B_NK ? KS : C::NI;
-  static constexpr int NHI = (NS * C::STAGE_BYTES + 65535) / 65536;  // a read's immediate offset reaches 64 KB
-  // Placement, in MFMAs.  (8192^3, of G = 64: within 1 % for SPREAD 40 to 62, BAR_AT 1 to 12, SPAN 64 to 96; SPAN 118
-  // costs 3-6 %: the last loads have not landed at the wait.)
+  static constexpr int A_HI = (NA * C::A_BYTES + 65535) / 65536, B_HI = (NB * C::B_BYTES + 65535) / 65536;  // a read's immediate offset reaches 64 KB
+  // Placement, in MFMAs.  (8192^3, of G = 64: within 1 % for SPREAD 40 to 62, BAR_AT 1 to 12.  Without an operand that leads SPAN
+  // 64 to 96 are alike and 118 costs 3-6 %: the last loads have not landed at the wait.  With one they have a slab longer: 104 is
+  // 1 % ahead of 88.)
   static constexpr int BAR_AT = G / 8;                               // MFMAs of the last k-step ahead of the barrier
   static constexpr int SPREAD = (G * 15 + 15) / 16;                  // the reads go with the first SPREAD MFMAs of a k-step
-  static constexpr int SPAN = G * 11 / 8;                            // the loads with the first SPAN MFMAs from the last k-step on
-  static_assert(BAR_AT < SPREAD && SPREAD <= G && SPAN <= 2 * G, "placement");
-  // load d of a slab goes with slot load_slot(d), counted from the start of the last k-step of the slab NS before it
+  static constexpr int SPAN = G * (NA != NB ? 13 : 11) / 8;           // the loads with the first SPAN MFMAs from the last k-step on
+  static_assert(BAR_AT < SPREAD && SPREAD <= G && SPAN >= G && SPAN + LX <= 2 * G, "placement");
+  // the d-th load goes with slot load_slot(d), counted from the start of the last k-step
   static constexpr int load_slot(int d) { return BAR_AT + d * (SPAN - BAR_AT) / L; }
   static constexpr int loads_before(int slot) { int n = 0; while (n < L && load_slot(n) < slot) ++n; return n; }
   static constexpr int reads_before(int slot, int from) { int n = 0; while (n < NF && from + n * (SPREAD - from) / NF < slot) ++n; return n; }
-  static constexpr int L0 = loads_before(G);                         // loads of a slab that go with that last k-step
+  static constexpr int L0 = loads_before(G);                         // loads that go with that last k-step
 
-  uint32_t a[NHI][KS], b[NHI][NBV];
+  // What a step's loads are.  WHOLE_RING: as above.  TWO_SLABS (of a ring of three slabs of A and two of B): A no further ahead
+  // than B, in the first two places of A's ring.  SWITCH: the step after the last one of those.
+  enum Mode { WHOLE_RING, TWO_SLABS, SWITCH };
+
+  unsigned char* pool;
+  uint32_t a[A_HI][KS], b[B_HI][NBV];
   typedef std::conditional_t<C::B_NK, bf16x8, FragHalves> FragB;
   bf16x8 af[2][C::MI];
   FragB bf[2][C::NI];
 
-  __device__ __forceinline__ void init(const unsigned char* pool, int wm, int wn, int lane) {
-    const uint32_t base = lds_address(pool);
+  __device__ __forceinline__ unsigned char* slab_a(int i) const { return pool + i * C::A_BYTES; }
+  __device__ __forceinline__ unsigned char* slab_b(int i) const { return pool + NA * C::A_BYTES + i * C::B_BYTES; }
+
+  __device__ __forceinline__ void init(unsigned char* pool_, int wm, int wn, int lane) {
+    pool = pool_;
+    const uint32_t base_a = lds_address(pool), base_b = base_a + NA * C::A_BYTES;
     const int g = lane >> 4, i = lane & 15;
 #pragma unroll
-    for (int h = 0; h < NHI; ++h) {
-      const uint32_t bh = base + h * 65536u;
+    for (int ks = 0; ks < KS; ++ks) {
+      const int q = ks * 4 + g;
+      const int row = wm * C::WTM + i;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const int row = wm * C::WTM + i, q = ks * 4 + g;
-        a[h][ks] = bh + row * (C::BK * 2) + ((q ^ swz_a<C::A_SLOTS>(row)) << 4);
-        if constexpr (C::B_NK) {
-          const int rn = wn * C::WTN + i;
-          b[h][ks] = bh + rn * (C::BK * 2) + ((q ^ swz_a<C::A_SLOTS>(rn)) << 4);
-        }
+      for (int h = 0; h < A_HI; ++h) a[h][ks] = base_a + h * 65536u + row * (C::BK * 2) + ((q ^ swz_a<C::A_SLOTS>(row)) << 4);
+      if constexpr (C::B_NK) {
+        const int rn = wn * C::WTN + i;
+#pragma unroll
+        for (int h = 0; h < B_HI; ++h) b[h][ks] = base_b + h * 65536u + rn * (C::BK * 2) + ((q ^ swz_a<C::A_SLOTS>(rn)) << 4);
       }
-      if constexpr (!C::B_NK) {
+    }
+    if constexpr (!C::B_NK) {
 #pragma unroll
-        for (int ni = 0; ni < C::NI; ++ni) {
-          const int k = 8 * g + (i >> 2);
-          const int n = wn * C::WTN + ni * 16 + 4 * (i & 3);
-          b[h][ni] = bh + k * (C::BN * 2) + (((n >> 3) ^ swz_b<C::B_SLOTS>(k)) << 4) + ((n >> 2) & 1) * 8;
-        }
+      for (int ni = 0; ni < C::NI; ++ni) {
+        const int k = 8 * g + (i >> 2);
+        const int n = wn * C::WTN + ni * 16 + 4 * (i & 3);
+#pragma unroll
+        for (int h = 0; h < B_HI; ++h) b[h][ni] = base_b + h * 65536u + k * (C::BN * 2) + (((n >> 3) ^ swz_b<C::B_SLOTS>(k)) << 4) + ((n >> 2) & 1) * 8;
       }
     }
   }
 
   template <int OFF>
-  static __device__ __forceinline__ bf16x8 read16(const uint32_t (&base)[NHI]) {
+  static __device__ __forceinline__ bf16x8 read16(uint32_t base) {
     u32x4 v;
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(base[OFF / 65536]), "n"(OFF % 65536));
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(base), "n"(OFF));
     return __builtin_bit_cast(bf16x8, v);
   }
   template <int OFF>
-  static __device__ __forceinline__ FragHalves read_tr(const uint32_t (&base)[NHI]) {
-    constexpr int O2 = OFF + 4 * C::BN * 2;
-    FragHalves f;
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.lo) : "v"(base[OFF / 65536]), "n"(OFF % 65536));
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.hi) : "v"(base[O2 / 65536]), "n"(O2 % 65536));
-    return f;
+  static __device__ __forceinline__ u32x2 read_tr(uint32_t base) {
+    u32x2 v;
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(base), "n"(OFF));
+    return v;
   }
-  // fragment R (in the order the MFMAs want them) of k-step K out of stage S
-  template <int S, int K, int R>
+  // fragment R (in the order the MFMAs want them) of k-step K out of A's slab SA / B's slab SB in LDS
+  template <int SA, int SB, int K, int R>
   __device__ __forceinline__ void fetch() {
     constexpr bool IS_B = R >= 1 && R <= C::NI;
     constexpr int I = R == 0 ? 0 : (IS_B ? R - 1 : R - C::NI);
-    uint32_t base[NHI];
-#pragma unroll
-    for (int h = 0; h < NHI; ++h) base[h] = IS_B ? b[h][C::B_NK ? K : I] : a[h][K];
-    if constexpr (!IS_B) af[K][I] = read16<S * C::STAGE_BYTES + I * 16 * C::BK * 2>(base);
-    else if constexpr (C::B_NK) bf[K][I] = read16<S * C::STAGE_BYTES + C::A_BYTES + I * 16 * C::BK * 2>(base);
-    else bf[K][I] = read_tr<S * C::STAGE_BYTES + C::A_BYTES + K * 32 * C::BN * 2>(base);
+    if constexpr (!IS_B) {
+      constexpr int OFF = SA * C::A_BYTES + I * 16 * C::BK * 2;
+      af[K][I] = read16<OFF % 65536>(a[OFF / 65536][K]);
+    } else if constexpr (C::B_NK) {
+      constexpr int OFF = SB * C::B_BYTES + I * 16 * C::BK * 2;
+      bf[K][I] = read16<OFF % 65536>(b[OFF / 65536][K]);
+    } else {
+      constexpr int LO = SB * C::B_BYTES + K * 32 * C::BN * 2, HI = LO + 4 * C::BN * 2;
+      bf[K][I].lo = read_tr<LO % 65536>(b[LO / 65536][I]);
+      bf[K][I].hi = read_tr<HI % 65536>(b[HI / 65536][I]);
+    }
   }
 
-  // Fills the pipeline: slabs 0 .. NS-2 and the first loads of slab NS-1 requested, the fragments of the first k-step
-  // read.  Slabs past the end are loads outside the records everywhere (no memory access): every step issues the same
-  // number of loads, which keeps the counter waits constants and the loop one shape.
-  __device__ __forceinline__ void request_b(const Ld& ld, const GemmArgs& ga, unsigned char* pool, int k_begin, int KT, int wave) {
+  // Fills the pipeline: slabs 0 .. N-2 requested, and the operand that leads of slab N-1; then the first of the loads that a step
+  // "-1" would deal out; the fragments of the first k-step read.  Slabs past the end are loads outside the records everywhere
+  // (no memory access): every step issues the same number of loads, which keeps the counter waits constants and the loop
+  // one shape.
+  // (`two_slabs`: the steps that follow are of that mode.)
+  __device__ __forceinline__ void request_b(const Ld& ld, const GemmArgs& ga, int k_begin, int KT) {
     static_assert(B_FIRST);
 #pragma unroll
-    for (int j = 0; j < NS - 1; ++j) ld.only_if(j < KT, ga).issue_b(ga, pool + j * C::STAGE_BYTES, k_begin + j * C::BK, wave);
+    for (int j = 0; j < N - 1 + B_LEADS; ++j) ld.issue_b(ga, slab_pair(ld, ga, k_begin, j, j, KT), slab_b(j));
   }
-  __device__ __forceinline__ void start(const Ld& ld, const GemmArgs& ga, unsigned char* pool, int k_begin, int KT, int wave) {
+  __device__ __forceinline__ void start(const Ld& ld, const GemmArgs& ga, int k_begin, int KT, int wave, bool two_slabs) {
 #pragma unroll
-    for (int j = 0; j < NS - 1; ++j) {
-      const Ld l = ld.only_if(j < KT, ga);
-      if constexpr (B_FIRST) l.issue_a(ga, pool + j * C::STAGE_BYTES, k_begin + j * C::BK, wave);
-      else l.issue(ga, pool + j * C::STAGE_BYTES, k_begin + j * C::BK, wave);
+    for (int j = 0; j < N - 1; ++j) {
+      const auto s = slab_pair(ld, ga, k_begin, j, j, KT);
+      ld.issue_a(ga, s, slab_a(j), wave);
+      if constexpr (!B_FIRST) ld.issue_b(ga, s, slab_b(j));
     }
-    const Ld l = ld.only_if(NS - 1 < KT, ga);
+    const auto s = slab_pair(ld, ga, k_begin, N - 1, N - 1, KT);
+    if constexpr (B_LEADS && !B_FIRST) ld.issue_b(ga, s, slab_b(N - 1));
+    constexpr int BEHIND = (N - 2) * (B_FIRST ? LA : L) + L0;         // loads behind slab 0's, without the leading operand's
+    if (A_LEADS && two_slabs) {
+      const auto w = window<TWO_SLABS>(ld, ga, k_begin, -1, KT);
 #pragma unroll
-    for (int d = 0; d < L0; ++d) l.issue_dyn(d, ga, pool + (NS - 1) * C::STAGE_BYTES, k_begin + (NS - 1) * C::BK, wave);
-    wait_vm_at_most<(NS - 2) * (B_FIRST ? LA : L) + L0>();        // slab 0 is there
+      for (int d = 0; d < L0; ++d) load<TWO_SLABS>(ld, ga, w, d, NB - 1, wave);
+      wait_vm_at_most<BEHIND>();                                      // slab 0 is there
+    } else {
+      if constexpr (A_LEADS) ld.issue_a(ga, s, slab_a(N - 1), wave);
+      const auto w = window<WHOLE_RING>(ld, ga, k_begin, -1, KT);
+#pragma unroll
+      for (int d = 0; d < L0; ++d) load<WHOLE_RING>(ld, ga, w, d, U - 1, wave);
+      wait_vm_at_most<BEHIND + (B_FIRST ? LXA : LX)>();
+    }
     barrier_keeping_loads_in_flight();
-    static_for<NF>([&](auto r) { fetch<0, 0, decltype(r)::value>(); });
+    static_for<NF>([&](auto r) { fetch<0, 0, 0, decltype(r)::value>(); });
     wait_lds_reads(af[0], bf[0]);
   }
 
-  // Slab kt, which lies in stage S = kt % NS.  VM_EXTRA: that many younger memory operations, issued by before_wait(),
-  // may stay outstanding at the wait.
-  template <int S, int VM_EXTRA, class Hook>
-  __device__ __forceinline__ void step(const Ld& ld, const GemmArgs& ga, unsigned char* pool, int k_begin, int kt, int KT, int wave,
+  // slab ja of A and slab jb of B
+  __device__ __forceinline__ Slabs slab_pair(const Ld& ld, const GemmArgs& ga, int k_begin, int ja, int jb, int KT) const {
+    return ld.slabs(ga, ja < KT, k_begin + ja * C::BK, jb < KT, k_begin + jb * C::BK);
+  }
+  // What step kt (in place S of the unrolled loop) asks for from its barrier on, and the d-th of those loads: first the operand
+  // that the next barrier needs.
+  static constexpr Mode now(Mode m) { return m == TWO_SLABS ? TWO_SLABS : WHOLE_RING; }
+  static constexpr Mode before(Mode m) { return m == WHOLE_RING ? WHOLE_RING : TWO_SLABS; }     // of the step ahead of it
+  template <Mode MODE>
+  __device__ __forceinline__ Slabs window(const Ld& ld, const GemmArgs& ga, int k_begin, int kt, int KT) const {
+    return slab_pair(ld, ga, k_begin, kt + (MODE == TWO_SLABS ? NB : NA), kt + NB, KT);
+  }
+  template <Mode MODE>
+  __device__ __forceinline__ void load(const Ld& ld, const GemmArgs& ga, const Slabs& w, int d, int S, int wave) const {
+    const bool is_a = A_LEADS ? d >= LB : d < LA;
+    if (is_a) ld.load_a(A_LEADS ? d - LB : d, ga, w, slab_a(S % (MODE == TWO_SLABS ? NB : NA)), wave);
+    else ld.load_b(A_LEADS ? d : d - LA, ga, w, slab_b(S % NB));
+  }
+
+  // Slab kt, in place S of the unrolled loop: A in place S % NA (TWO_SLABS: S % NB) of its ring, B in S % NB.  VM_EXTRA: that
+  // many younger memory operations, issued by before_wait(), may stay outstanding at the wait.
+  template <int S, int VM_EXTRA, Mode MODE, class Hook>
+  __device__ __forceinline__ void step(const Ld& ld, const GemmArgs& ga, int k_begin, int kt, int KT, int wave,
                                        f32x4 (&acc)[C::MI][C::NI], Hook&& before_wait) {
-    unsigned char* const st_rest = pool + ((S + NS - 1) % NS) * C::STAGE_BYTES;
-    unsigned char* const st_cur = pool + S * C::STAGE_BYTES;
+    constexpr int RA = MODE == TWO_SLABS ? NB : NA;
+    constexpr int VM = (N - 2) * L + (MODE == TWO_SLABS ? 0 : LX) + VM_EXTRA;
     // (the slab's offset goes into the loads' scalar operand: should the compiler ever take the loop
     // counter for a value that may differ between lanes, it would wrap every load into a loop over lanes)
     kt = __builtin_amdgcn_readfirstlane(kt);
-    const Ld ld_rest = ld.only_if(kt + NS - 1 < KT, ga), ld_first = ld.only_if(kt + NS < KT, ga);
-    const int k_rest = k_begin + (kt + NS - 1) * C::BK, k_first = k_rest + C::BK;
+    const auto rest = window<before(MODE)>(ld, ga, k_begin, kt - 1, KT), first = window<now(MODE)>(ld, ga, k_begin, kt, KT);
     static_for<KS>([&](auto ks_) {
       constexpr int ks = decltype(ks_)::value;
       constexpr bool LAST = ks == KS - 1;
       if constexpr (LAST) before_wait();
       static_for<G>([&](auto g_) {
         constexpr int g = decltype(g_)::value;
-        constexpr int mi = g / C::NI, ni = g % C::NI;
+        // (with the large tile every second row of MFMAs goes backwards: it begins with the B fragment that the row before ended with,
+        // 1-2 % of 8192x4608x12288 and 8192x12288x4608 at the power limit; small tiles lose as much)
+        constexpr int mi = g / C::NI, ni = G < 64 || mi % 2 == 0 ? g % C::NI : C::NI - 1 - g % C::NI;
         if constexpr (LAST && g == BAR_AT) {
-          // slab kt+1 is there (this wave's part, then everyone's); stage S has been read by all
-          if constexpr (B_FIRST && S < NS - 2) {
-            // (slabs 0 .. NS-2 were requested as all of B, then all of A: behind slab kt+1's are the A parts of the
-            // later ones of those, and the slabs requested since)
-            if (kt == S) wait_vm_at_most<(NS - 3 - S) * LA + (S + 1) * L + VM_EXTRA>();
-            else wait_vm_at_most<(NS - 2) * L + VM_EXTRA>();
+          // slab kt+1 is there (this wave's part, then everyone's); this slab has been read by all
+          if constexpr (B_FIRST && S < N - 2) {
+            // (slabs 0 .. N-2 were requested as all of B, then all of A: behind slab kt+1's are the A parts of the
+            // later ones of those, and what was requested since)
+            if (kt == S) wait_vm_at_most<(N - 3 - S) * LA + LXA + (S + 1) * L + VM_EXTRA>();
+            else wait_vm_at_most<VM>();
           } else {
-            wait_vm_at_most<(NS - 2) * L + VM_EXTRA>();
+            wait_vm_at_most<VM>();
           }
           barrier_keeping_loads_in_flight();
         }
@@ -1721,14 +1825,15 @@ struct MmaPipe {
         constexpr int d0 = loads_before(LAST ? g : G + g), d1 = loads_before((LAST ? g : G + g) + 1);
 #pragma unroll
         for (int d = d0; d < d1; ++d) {
-          if constexpr (LAST) ld_first.issue_dyn(d, ga, st_cur, k_first, wave);
-          else ld_rest.issue_dyn(d, ga, st_rest, k_rest, wave);
+          if constexpr (LAST) load<now(MODE)>(ld, ga, first, d, S, wave);
+          else load<before(MODE)>(ld, ga, rest, d, S + U - 1, wave);
         }
+        if constexpr (MODE == SWITCH && !LAST && g >= SPAN - G && g < SPAN - G + LA) load<WHOLE_RING>(ld, ga, window<WHOLE_RING>(ld, ga, k_begin, kt - 1, KT), LB + g - (SPAN - G), S + U - 1, wave);
         constexpr int r0 = reads_before(g, LAST ? BAR_AT : 0), r1 = reads_before(g + 1, LAST ? BAR_AT : 0);
         static_for<r1 - r0>([&](auto r_) {
           constexpr int r = r0 + decltype(r_)::value;
-          if constexpr (LAST) fetch<(S + 1) % NS, 0, r>();
-          else fetch<S, ks + 1, r>();
+          if constexpr (LAST) fetch<(S + 1) % RA, (S + 1) % NB, 0, r>();
+          else fetch<S % RA, S % NB, ks + 1, r>();
         });
         __builtin_amdgcn_sched_barrier(0);
       });
@@ -1736,32 +1841,77 @@ struct MmaPipe {
     });
   }
 
-  // Slabs kt (a multiple of NS; 0 after start()) to the end.
-  __device__ __forceinline__ void run(const Ld& ld, const GemmArgs& ga, unsigned char* pool, int k_begin, int KT, int kt, int wave,
-                                      f32x4 (&acc)[C::MI][C::NI]) {
-    for (; kt + NS <= KT; kt += NS)
-      static_for<NS>([&](auto s_) {
+  // Slabs kt to the end: 0 after start(), or the next one after steps of TWO_SLABS (`two_slabs`), an even number of them.
+  __device__ __forceinline__ void run(const Ld& ld, const GemmArgs& ga, int k_begin, int KT, int kt, int wave,
+                                      f32x4 (&acc)[C::MI][C::NI], bool two_slabs) {
+    if constexpr (A_LEADS && B_FIRST) {
+      if (two_slabs) {
+        // the first step asks for A a slab further ahead; from there on as if K began here
+        if (kt < KT) step<0, 0, SWITCH>(ld, ga, k_begin, kt, KT, wave, acc, [] {});
+        static_for<U - 1>([&](auto s_) {
+          constexpr int S = decltype(s_)::value + 1;
+          if (kt + S < KT) step<S, 0, WHOLE_RING>(ld, ga, k_begin, kt + S, KT, wave, acc, [] {});
+        });
+        kt += U;
+      }
+    }
+    for (; kt + U <= KT; kt += U)
+      static_for<U>([&](auto s_) {
         constexpr int S = decltype(s_)::value;
-        step<S, 0>(ld, ga, pool, k_begin, kt + S, KT, wave, acc, [] {});
+        step<S, 0, WHOLE_RING>(ld, ga, k_begin, kt + S, KT, wave, acc, [] {});
       });
-    static_for<NS - 1>([&](auto s_) {
+    static_for<U - 1>([&](auto s_) {
       constexpr int S = decltype(s_)::value;
-      if (kt + S < KT) step<S, 0>(ld, ga, pool, k_begin, kt + S, KT, wave, acc, [] {});
+      if (kt + S < KT) step<S, 0, WHOLE_RING>(ld, ga, k_begin, kt + S, KT, wave, acc, [] {});
     });
     mfma_results_settle<C::MI, C::NI>(acc);
+  }
+};
+
+// All of A asked for once, ahead of the main loop, in the order it lies in memory: the grid's threads take its 128-byte lines
+// in turn, one word each, so that it is in the Infinity Cache when the slabs are loaded.  A slab is 128 bytes of every row, and
+// rows a multiple of 2 KB apart put those into few of the memory's channels, slab after slab: A of 6 MB out of memory cost a call
+// with 151 MB of weights as much as the weights did (512x12288x6144: 67 us with both in the cache, 82 with the weights
+// out of memory, 91 with A out of memory, 93 with both).
+// us per call without / with, 2 ranks: 512x8192x5120 68.7 / 63.5, 512x8192x6144 74.3 / 68.6, 1024x8192x7168 109.4 / 103.7, 256x8192x6144
+// 48.5 / 47.3; 8 ranks: 512x12288x6144 112.6 / 97.3.  Not taken (warm_a): other pitches (512x8192x3584 47.8 / 48.7, 1496x5112x3400
+// 67.0 / 68.2), a multiple of 16 KB (1024x8192x8192 134.9 / 137.7; 512x12288x8192 113.8 / 111.7), few slabs (512x12288x3072 47.0 /
+// 46.9), tiles other than 256x128 (64x8192x8192 33.9 / 34.6, 4096x8192x4096 224.7 / 228.6), and a gathered A, which has just been written.
+constexpr int WARM_LOADS = 8;      // per thread
+__device__ __forceinline__ bool warm_a(const GemmArgs& a, uint32_t lines) {
+  const uint32_t pitch = (uint32_t)a.lda * 2u;
+  return pitch % 2048u == 0u && pitch % 16384u != 0u && a.K >= 4096 && lines <= WARM_LOADS * gridDim.x * 256u;
+}
+struct WarmA {
+  uint32_t word[WARM_LOADS];
+  __device__ __forceinline__ void ask(const GemmArgs& a, uint32_t bytes_a, int tid) {
+    const uint32_t row_lines = ((uint32_t)a.K * 2u + 127u) / 128u, lines = (uint32_t)a.M * row_lines, at_once = gridDim.x * 256u;
+    const bool warm = warm_a(a, lines);
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.A), 0, (int)bytes_a, 0x00027000);
+#pragma unroll
+    for (int t = 0; t < WARM_LOADS; ++t) {
+      word[t] = 0u;
+      if (!warm || t * at_once >= lines) continue;         // (uniform)
+      const uint32_t i = t * at_once + blockIdx.x * 256u + (uint32_t)tid, row = i / row_lines;
+      const uint32_t off = i < lines ? row * ((uint32_t)a.lda * 2u) + (i - row * row_lines) * 128u : 0xfffffff0u;
+      word[t] = __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0);
+    }
+  }
+  __device__ __forceinline__ void drop() {
+#pragma unroll
+    for (int t = 0; t < WARM_LOADS; ++t) asm volatile("" : : "v"(word[t]));
   }
 };
 
 // EDGE: the tile does not divide M, N or K (see DmaLoader; the epilogue leaves rows and columns past the end out).
 template <class C, int EPI, bool WAIT, bool EDGE>
 __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs a) {
-  // the transfer inside the main loop (SideCopy) is asked of the two-stage kernel with one workgroup per unit
-  constexpr bool CARRY = WAIT && !EDGE && C::NSTAGE == 2 && C::OCC == 1;
-  // one pool: the stages, and over them (once the main loop is done) the epilogue's staging area
-  constexpr int POOL_BYTES = C::NSTAGE * C::STAGE_BYTES > C::EP_BYTES ? C::NSTAGE * C::STAGE_BYTES : C::EP_BYTES;
-  __shared__ __attribute__((aligned(1024))) unsigned char pool[POOL_BYTES];
-  __shared__ int lds_misc[4];
-  __shared__ void* lds_outs[FLUX_MAX_RANKS];
+  // the transfer inside the main loop (SideCopy) is asked of the kernel with two slabs of B and one workgroup per unit
+  constexpr bool CARRY = WAIT && !EDGE && C::NB == 2 && C::OCC == 1;
+  __shared__ __attribute__((aligned(1024))) unsigned char pool[C::POOL_BYTES];
+  SharedWords* const words = reinterpret_cast<SharedWords*>(pool + C::WORDS_AT);
+  int* const lds_misc = words->misc;
+  void** const lds_outs = words->outs;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
@@ -1774,16 +1924,15 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
   const int m0 = mt * C::BM, n0 = nt * C::BN;
   trace_begin(a, tile, mt, nt, split, is_split);
 
-  if (EPI == EPI_RS || WAIT) {      // output slices (reduce-scatter) or chunk sources (all-gather), by rank
-    fill_lds_outs(a, lds_outs, tid);
-  }
+  if (WAIT || (EPI == EPI_RS && !C::WORDS_IN_RING)) fill_lds_outs(a, lds_outs, tid);
   const int k_begin = is_split ? split * a.k_per_split : 0;
   const int k_end = (is_split && k_begin + a.k_per_split < a.K) ? k_begin + a.k_per_split : a.K;
   const int KT = (k_end - k_begin + C::BK - 1) / C::BK;
 
   DmaLoader<C, EDGE> ld;
   ld.init(a, m0, n0, wave, lane);
-  MmaPipe<C, WAIT, EDGE> pipe;
+  typedef MmaPipe<C, WAIT, EDGE> Pipe;
+  Pipe pipe;
   pipe.init(pool, wm, wn, lane);
   SideCopy side;
   if constexpr (WAIT) {
@@ -1803,7 +1952,7 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
     }
     // Then the weights, which do not depend on the gathered rows: their part of the first slabs is on its
     // way while the workgroup waits for its signals.
-    pipe.request_b(ld, a, pool, k_begin, KT, wave);
+    pipe.request_b(ld, a, k_begin, KT);
     if (!wait_signals(a, m0, m1, lds_misc, lds_outs)) {
       // given up (a workgroup only gets to its wait with pieces left if its signals were there, so this
       // is for safety): the pieces it claimed still have to be moved, or their tiles' signals never come
@@ -1825,11 +1974,17 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[mi][ni][e] = 0.f;
 
-  pipe.start(ld, a, pool, k_begin, KT, wave);
+  bool carries = false;
+  if constexpr (CARRY) carries = side.pending();      // (uniform)
+  constexpr bool WARM = !WAIT && C::BM == 256 && C::BN == 128;
+  WarmA warm;
+  if constexpr (WARM) warm.ask(a, ld.bytes_a, tid);
+  pipe.start(ld, a, k_begin, KT, wave, carries);
+  if constexpr (WARM) warm.drop();
   if (is_split && a.sk_share) part_started(a, tile, tid);
   int kt = 0;
   if constexpr (CARRY) {
-    if (side.pending()) {
+    if (carries) {
       // With the transfer aboard (a workgroup of the first round with pieces to move; everybody else
       // runs the plain loop below): per slab two stores (of the vectors loaded two slabs ago) ahead of
       // the slab's operand loads and two loads right before the slab's wait.  "All but the two youngest
@@ -1837,19 +1992,20 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
       // order, and those two are the youngest loads).  Thread 0 looks at the clock once per two slabs and
       // leaves word in LDS whether a tile is due to be counted in (a decision every wave must take
       // alike: finish() has barriers).  When the last tile is counted in, the plain loop takes over for the rest of K.
+      // (The loop leaves A's last slab in LDS alone: the workgroup's shared words may lie there.)
       u32x4 dA0 = side.load(a, lds_outs), dA1 = side.load(a, lds_outs);
       u32x4 dB0 = side.load(a, lds_outs), dB1 = side.load(a, lds_outs);
       for (; kt + 2 <= KT && side.pending(); kt += 2) {
         side.store(a, dA0);
         side.store(a, dA1);
-        pipe.template step<0, 2>(ld, a, pool, k_begin, kt, KT, wave, acc, [&] {
+        pipe.template step<0, 2, Pipe::TWO_SLABS>(ld, a, k_begin, kt, KT, wave, acc, [&] {
           dA0 = side.load(a, lds_outs);
           dA1 = side.load(a, lds_outs);
         });
         side.store(a, dB0);
         side.store(a, dB1);
         bool look = false;
-        pipe.template step<1, 2>(ld, a, pool, k_begin, kt + 1, KT, wave, acc, [&] {
+        pipe.template step<1, 2, Pipe::TWO_SLABS>(ld, a, k_begin, kt + 1, KT, wave, acc, [&] {
           look = side.may_be_due();       // (uniform)
           if (look) {
             if (tid == 0) *side.slot = side.due() ? 1 : 0;
@@ -1871,9 +2027,14 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
       }
     }
   }
-  pipe.run(ld, a, pool, k_begin, KT, kt, wave, acc);
-  wait_vm0_and_barrier();        // the epilogue's staging area lies over stages other waves may still be reading
-  gemm_tail<C, EPI, EDGE>(a, pool, lds_misc, lds_outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn);
+  pipe.run(ld, a, k_begin, KT, kt, wave, acc, carries);
+  wait_vm0_and_barrier();        // the epilogue's staging area lies over slabs other waves may still be reading
+  SharedWords* const tail_words = reinterpret_cast<SharedWords*>(pool + C::WORDS_AT_TAIL);
+  if (EPI == EPI_RS && C::WORDS_IN_RING) {
+    fill_lds_outs(a, tail_words->outs, tid);
+    __syncthreads();
+  }
+  gemm_tail<C, EPI, EDGE>(a, pool, tail_words->misc, tail_words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn);
 }
 
 // The same kernel as a grid of resident workgroups, one per compute unit, each walking the block
@@ -1881,11 +2042,8 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
 // instead of in dispatch).
 template <class C, int EPI>
 __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma_resident(const GemmArgs a_) {
-  constexpr int POOL_BYTES = 2 * C::STAGE_BYTES > C::EP_BYTES ? 2 * C::STAGE_BYTES : C::EP_BYTES;   // the stages; later the epilogue's staging area
-  __shared__ __attribute__((aligned(1024))) unsigned char pool[POOL_BYTES];
-  __shared__ int lds_misc[4];
-  __shared__ void* lds_outs[FLUX_MAX_RANKS];
-  if (EPI == EPI_RS) fill_lds_outs(a_, lds_outs, (int)threadIdx.x);
+  __shared__ __attribute__((aligned(1024))) unsigned char pool[C::POOL_BYTES];
+  SharedWords* const words = reinterpret_cast<SharedWords*>(pool + C::WORDS_AT_TAIL);
   if (a_.persist_delay_ticks != 0 && ((blockIdx.x >> 3) & 1)) {
     const uint64_t t0 = wall_clock64();
     while (wall_clock64() - t0 < a_.persist_delay_ticks) __builtin_amdgcn_s_sleep(32);
@@ -1926,12 +2084,16 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma_resident(const 
     ld.init(a, m0, n0, wave, lane);
     MmaPipe<C, false, false> pipe;
     pipe.init(pool, wm, wn, lane);
-    pipe.start(ld, a, pool, k_begin, KT, wave);
+    pipe.start(ld, a, k_begin, KT, wave, false);
     if (is_split && a.sk_share) part_started(a, tile, tid);
-    pipe.run(ld, a, pool, k_begin, KT, 0, wave, acc);
+    pipe.run(ld, a, k_begin, KT, 0, wave, acc, false);
     wait_vm0_and_barrier();
-    gemm_tail<C, EPI, false>(a, pool, lds_misc, lds_outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, vb);
-    __syncthreads();      // the staging area and lds_misc are the next block's
+    if (EPI == EPI_RS) {
+      fill_lds_outs(a, words->outs, tid);
+      __syncthreads();
+    }
+    gemm_tail<C, EPI, false>(a, pool, words->misc, words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, vb);
+    __syncthreads();      // the staging area and the shared words are the next block's
   }
 }
 

@@ -5,25 +5,25 @@
 namespace flux {
 
 #if FLUX_CFG_ID == 1
-#define FLUX_CFG_PARAMS 256, 256, 64, 2, 2, 2, 1   // 128x128 per wave, one workgroup per CU
+#define FLUX_CFG_PARAMS 256, 256, 64, 2, 2, 3, 2, 1   // 128x128 per wave, one workgroup per CU
 #elif FLUX_CFG_ID == 2
-#define FLUX_CFG_PARAMS 256, 128, 64, 2, 2, 3, 1   // 128x64 per wave: twice the tiles of 256x256; three LDS stages
+#define FLUX_CFG_PARAMS 256, 128, 64, 2, 2, 3, 3, 1   // 128x64 per wave: twice the tiles of 256x256; three LDS stages
 #elif FLUX_CFG_ID == 3
-#define FLUX_CFG_PARAMS 128, 128, 64, 2, 2, 2, 2   // 64x64 per wave
+#define FLUX_CFG_PARAMS 128, 128, 64, 2, 2, 2, 2, 2   // 64x64 per wave
 #elif FLUX_CFG_ID == 4
-#define FLUX_CFG_PARAMS 64, 64, 64, 2, 2, 2, 2     // 32x32 per wave, small problems
+#define FLUX_CFG_PARAMS 64, 64, 64, 2, 2, 2, 2, 2     // 32x32 per wave, small problems
 #elif FLUX_CFG_ID == 5
-#define FLUX_CFG_PARAMS 64, 128, 64, 2, 2, 2, 2    // decode, M <= 64
+#define FLUX_CFG_PARAMS 64, 128, 64, 2, 2, 2, 2, 2    // decode, M <= 64
 #elif FLUX_CFG_ID == 6
-#define FLUX_CFG_PARAMS 32, 128, 64, 1, 4, 2, 2    // decode, M <= 32
+#define FLUX_CFG_PARAMS 32, 128, 64, 1, 4, 2, 2, 2    // decode, M <= 32
 #elif FLUX_CFG_ID == 7
-#define FLUX_CFG_PARAMS 64, 64, 64, 2, 2, 6, 1     // decode, M <= 64: six LDS stages, one workgroup per CU
+#define FLUX_CFG_PARAMS 64, 64, 64, 2, 2, 6, 6, 1     // decode, M <= 64: six LDS stages, one workgroup per CU
 #elif FLUX_CFG_ID == 8
-#define FLUX_CFG_PARAMS 32, 128, 64, 1, 4, 6, 1    // decode, M <= 32: six LDS stages
+#define FLUX_CFG_PARAMS 32, 128, 64, 1, 4, 6, 6, 1    // decode, M <= 32: six LDS stages
 #elif FLUX_CFG_ID == 9
-#define FLUX_CFG_PARAMS 64, 128, 64, 2, 2, 4, 1    // M <= 256: four LDS stages
+#define FLUX_CFG_PARAMS 64, 128, 64, 2, 2, 4, 4, 1    // M <= 256: four LDS stages
 #elif FLUX_CFG_ID == 10
-#define FLUX_CFG_PARAMS 64, 128, 64, 2, 2, 3, 2    // few rows over a long K: 64x128, three stages, two workgroups per CU
+#define FLUX_CFG_PARAMS 64, 128, 64, 2, 2, 3, 3, 2    // few rows over a long K: 64x128, three stages, two workgroups per CU
 #else
 #error "FLUX_CFG_ID must be 1..10"
 #endif
@@ -33,7 +33,7 @@ typedef TileCfg<FLUX_CFG_PARAMS, true> CfgNK;    // B as [N,K]
 // `edge`: the tile does not divide the shape (masked loads and stores).
 template <class Cfg, int EPI, bool WAIT>
 static hipError_t launch_one(int edge, const GemmArgs& a, int grid, hipStream_t s) {
-  if constexpr (!WAIT && Cfg::NSTAGE == 2 && Cfg::OCC == 1) {
+  if constexpr (!WAIT && Cfg::NB == 2 && Cfg::OCC == 1) {
     if (a.persist_blocks > 0) {          // (only planned for shapes the tile divides)
       hipLaunchKernelGGL((gemm_kernel_dma_resident<Cfg, EPI>), dim3(grid), dim3(Cfg::NT), 0, s, a);
       return hipGetLastError();
