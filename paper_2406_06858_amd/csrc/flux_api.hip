@@ -401,6 +401,12 @@ static double plan_cost(const flux_problem_t* p, int cfg) {
   return rounds * (double)bm * (double)bn / rate;
 }
 
+// Many short 256x256 tiles: what a resident grid is for (see make_plan).
+static bool resident_shape(const flux_problem_t* p, const Plan& pl) {
+  return g_cfgs[pl.cfg].stages == 2 && g_cfgs[pl.cfg].occupancy == 1 && pl.edge == 0 &&
+         (long long)pl.full_tiles + (long long)pl.split_tiles * pl.split_k >= 4ll * N_CU && p->K <= 3072;
+}
+
 static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
   int st = validate_problem(op, p);
   if (st != FLUX_OK) return st;
@@ -528,8 +534,7 @@ static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
   pl->resident = 0;
   pl->resident_delay_ticks = 0;
   if (op == FLUX_OP_RS && !(p->flags & (FLUX_FLAG_RS_WRITE_ONLY | FLUX_FLAG_RS_ATOMIC | FLUX_FLAG_NO_RESIDENT_GRID)) &&
-      g_cfgs[cfg].stages == 2 && g_cfgs[cfg].occupancy == 1 && pl->edge == 0 &&
-      (long long)pl->full_tiles + (long long)pl->split_tiles * pl->split_k >= 4ll * N_CU && p->K <= 3072) {
+      resident_shape(p, *pl)) {
     pl->resident = 1;
     // half a period: (main loop + epilogue of a tile on a compute unit that shares the memory with
     // half of the others) / 2; 1.5 us per 64-deep K slab of a 256x256 tile, 33 GB/s per unit
@@ -641,7 +646,7 @@ static int check_arrival(const flux_problem_t* p, const int32_t* arrival, int* o
 // [local chunk, arrival order...], among the chunks the tile's rows touch.
 static void pack_order(TileMap* tm, const uint16_t* m_order) {
   tm->packed = tm->tiles_m <= 16;
-  tm->pad_ = 0;
+  tm->peers_first = 0;
   tm->order4 = 0;
   if (tm->packed)
     for (int t = 0; t < tm->tiles_m; ++t) tm->order4 |= (uint64_t)m_order[t] << (4 * t);
@@ -1080,6 +1085,13 @@ int gemm_rs_planned(const flux_problem_t* p, const Plan& pl, const void* A, cons
     if (!write_only && r != p->rank) a.peers[j++] = peer_partials[r];
   }
   build_tile_map(FLUX_OP_RS, p, pl, nullptr, &a.tm, a.m_order);
+  // Half of the tiles add their peers ahead of their main loop, so that one half of the chip reads while the other multiplies
+  // (sum_peers_first): whole tiles that are large, bf16 partials and results (which round to 8 bits whichever sum of fp32 comes
+  // first).  Not the many short tiles of a resident grid, or of one that FLUX_FLAG_NO_RESIDENT_GRID would keep from being one
+  // (results do not depend on that flag): 8192x12288x1536 427 us on a resident grid half of which
+  // starts late, 437 on one whose every second group takes its peers first.
+  a.tm.peers_first = !write_only && p->R > 1 && p->R <= PEERS_FIRST_RANKS && p->partial_dtype == FLUX_BF16 && p->out_dtype == FLUX_BF16 &&
+                     pl.bm * pl.bn >= PEERS_FIRST_AREA && !resident_shape(p, pl);
   return launch_gemm(pl, EPI_RS, 0, a, s);
 }
 

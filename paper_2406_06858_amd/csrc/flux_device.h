@@ -63,7 +63,8 @@ constexpr int MAX_COPY_PIECES = 256;       // pieces per communication tile = co
 // table (about a microsecond at the start of every workgroup).
 struct TileMap {
   int32_t tiles_m, tiles_n, band_h, n_xcd;
-  int32_t packed, pad_;
+  int32_t packed;
+  int32_t peers_first;       // reduce-scatter: every second group of eight tiles adds its peers ahead of its main loop (see sum_peers_first)
   uint64_t order4;
 };
 
@@ -280,9 +281,9 @@ __device__ __forceinline__ void store_through(uint4* p, const u32x4& d) {
 }
 // Output vectors: streamed, or written through when a consumer may read the tile as soon as its ready
 // counter moves (`through`, uniform).
-// FLAT: a wave does not read on from LDS before its stores are out.  With 256x256 tiles and peers, where every unit reads and
-// writes all the memory gives, that is faster (us, flat / global: rs 8192x12288x1536 424 / 438, 4096x8192x3584 250 / 252); elsewhere
-// waiting costs (1496x5112x3400 89.1 / 86.5, the end of a 256x256 tile without peers 9.0 / 7.6).
+// FLAT: a wave does not read on from LDS before its stores are out.  Behind reads of peers, where every unit reads and writes all
+// the memory gives, that is faster (us, flat / global: rs 8192x12288x1536 424 / 438, 512x8192x1024 37.9 / 39.6, 1024x4096x2048 44.4 / 46.3;
+// the other side: 1496x5112x3400 86.1 / 85.2); without peers waiting costs (the end of a 256x256 tile 9.0 / 7.6).
 template <bool FLAT>
 __device__ __forceinline__ void st_out16(void* p, const uint4& v, bool through) {
   if (through) store_through(static_cast<uint4*>(p), u32x4{v.x, v.y, v.z, v.w});
@@ -403,7 +404,7 @@ __device__ __forceinline__ void make_peer_bufs(const GemmArgs& a, int m0, int n0
 // columns of a row per pass.  With the reduce-scatter epilogue the peer loads of BATCH passes are
 // issued together before any of them is used (PF32: fp32 partials, two 16-byte loads per peer);
 // the peers are added in ascending rank order.
-template <class C, int EPI, bool EDGE, bool PF32, int BATCH, int NP>
+template <class C, int EPI, bool EDGE, bool PF32, int BATCH, int NP, bool RESIDENT>
 __device__ __forceinline__ void epilogue_block(const GemmArgs& a, void* const* lds_outs, const float* ep, const PeerBufs& pb,
                                                int row_base, int col_base, int m0, int n0, int lane) {
   constexpr int CH = C::WTN / 8;          // 8-column pieces per row of the wave tile
@@ -414,7 +415,11 @@ __device__ __forceinline__ void epilogue_block(const GemmArgs& a, void* const* l
   constexpr int NT_HINT = 2;              // cache policy: streamed once, do not keep
   static_assert(NIT % B == 0, "batch must divide the passes");
   const int cc = lane % CH, rl = lane / CH;
-#pragma unroll
+  // (A loop in the code too: unrolled, the ends of a 256x256 tile are 50 KB of instructions, and with the main loop they no longer fit
+  // the instruction cache of 64 KB that two units share: us, unrolled / not, 4096x8192x3584 251 / 242.  On a resident grid, whose units are
+  // out of step, unrolled is faster: 8192x12288x1536 428 / 436; and so is it with small tiles, whose code fits: 128x256x256 fp32 5.9 / 6.1.)
+  constexpr int UNROLL = RESIDENT || C::BM * C::BN < 128 * 128 ? NIT / B : 1;
+#pragma unroll UNROLL
   for (int it0 = 0; it0 < NIT; it0 += B) {
     u32x4 w[B][NP > 0 ? NP : 1][LPP];
     bool ok[B];
@@ -450,7 +455,7 @@ __device__ __forceinline__ void epilogue_block(const GemmArgs& a, void* const* l
           }
         }
       }
-      if (ok[b]) store_row8<EPI, NP != 0 && C::BM * C::BN == 256 * 256>(a, lds_outs, m0 + row_base + r, n0 + col_base + cc * 8, v);
+      if (ok[b]) store_row8<EPI, NP != 0>(a, lds_outs, m0 + row_base + r, n0 + col_base + cc * 8, v);
     }
     // one batch of peer loads in flight at a time: left alone, the scheduler hoists the loads of
     // later batches up here too and has to spill accumulators to make room for them
@@ -473,7 +478,7 @@ __device__ __forceinline__ void stage_rows32(float* ep, const f32x4 (&acc)[C::MI
 }
 
 // The whole epilogue of one wave: its accumulators pass through LDS 32 rows at a time.
-template <class C, int EPI, bool EDGE, bool PF32, int BATCH, int NP>
+template <class C, int EPI, bool EDGE, bool PF32, int BATCH, int NP, bool RESIDENT>
 __device__ __forceinline__ void epilogue_all(const GemmArgs& a, void* const* lds_outs, float* ep, f32x4 (&acc)[C::MI][C::NI],
                                              int m0, int n0, int lane, int wm, int wn) {
   PeerBufs pb;
@@ -481,9 +486,67 @@ __device__ __forceinline__ void epilogue_all(const GemmArgs& a, void* const* lds
 #pragma unroll
   for (int mb = 0; mb < C::WTM / 32; ++mb) {
     stage_rows32<C>(ep, acc, mb, lane);
-    epilogue_block<C, EPI, EDGE, PF32, BATCH, NP>(a, lds_outs, ep, pb, wm * C::WTM + mb * 32, wn * C::WTN, m0, n0, lane);
+    epilogue_block<C, EPI, EDGE, PF32, BATCH, NP, RESIDENT>(a, lds_outs, ep, pb, wm * C::WTM + mb * 32, wn * C::WTN, m0, n0, lane);
     __builtin_amdgcn_wave_barrier();
   }
+}
+
+// The peers' rows ahead of the main loop: their sum (fp32, ascending rank) is what the accumulators start from, and the end
+// of the tile only stores.  The way of epilogue_all backwards: 8 columns per lane -> LDS -> registers.
+//
+constexpr int PEERS_FIRST_AREA = 128 * 128, PEERS_FIRST_RANKS = 8;      // smallest tile, most ranks
+// Why: reading the peers takes a unit 32 us per 256x256 tile and 7 peers when half of the units do it, 44-50 when all do, and
+// the workgroups of a grid all reach the end of their tiles at about the same time.  With every second group of eight
+// (peers_first) reading its peers first, one half reads while the other multiplies, from the first tile on and whatever the number of
+// rounds.  us per call, 8 ranks, every tile's peers behind its main loop / half of them ahead: 4096x8192x3584 250 / 228, 4096x8192x1536
+// 166 / 143, 2048x8192x1024 73 / 61, 1024x8192x1024 41 / 34, 4096x12288x4608 444 / 414, 8192x12288x4608 846 / 834, 1496x5112x3400 87.4 / 85.5.
+// (Four passes' loads in flight instead of two: the same.)
+template <class C, bool EDGE, int NP>
+__device__ __forceinline__ void sum_peers_first(const GemmArgs& a, float* ep, f32x4 (&acc)[C::MI][C::NI], int m0, int n0, int lane, int wm, int wn) {
+  constexpr int CH = C::WTN / 8, RPP = 64 / CH, NIT = 32 / RPP, B = 2;
+  static_assert(NIT % B == 0);
+  PeerBufs pb;
+  make_peer_bufs(a, m0, n0, pb);
+  const int cc = lane % CH, rl = lane / CH;
+#pragma unroll
+  for (int mb = 0; mb < C::WTM / 32; ++mb) {
+#pragma unroll 1
+    for (int it0 = 0; it0 < NIT; it0 += B) {
+      u32x4 w[B][NP];
+#pragma unroll
+      for (int b = 0; b < B; ++b) {
+        const int row = wm * C::WTM + mb * 32 + (it0 + b) * RPP + rl, col = wn * C::WTN + cc * 8;
+        const bool ok = !EDGE || (m0 + row < a.M && n0 + col < a.N);
+        const int voff = ok ? (int)(((uint32_t)row * (uint32_t)a.N + (uint32_t)col) * 2u) : (int)0x80000000;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) w[b][j] = __builtin_amdgcn_raw_buffer_load_b128(pb.r[j], voff, 0, 2);
+      }
+#pragma unroll
+      for (int b = 0; b < B; ++b) {
+        float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < NP; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { v[2 * e] += bf16_lo(w[b][j][e]); v[2 * e + 1] += bf16_hi(w[b][j][e]); }
+        float* const to = ep + ((it0 + b) * RPP + rl) * C::EP_STRIDE + cc * 8;
+        *reinterpret_cast<float4*>(to) = make_float4(v[0], v[1], v[2], v[3]);
+        *reinterpret_cast<float4*>(to + 4) = make_float4(v[4], v[5], v[6], v[7]);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int ni = 0; ni < C::NI; ++ni)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          acc[2 * mb + s][ni][e] = ep[(16 * s + 4 * (lane >> 4) + e) * C::EP_STRIDE + ni * 16 + (lane & 15)];
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+template <class C, int EPI>
+__device__ __forceinline__ bool takes_peers_first(const GemmArgs& a, int tile, bool is_split) {
+  return EPI == EPI_RS && C::BM * C::BN >= PEERS_FIRST_AREA && a.tm.peers_first && !is_split && ((tile >> 3) & 1);
 }
 
 // ---- AllGather copy pieces --------------------------------------------------------------------
@@ -1282,10 +1345,10 @@ struct SharedFinish {
 // a tile park their partial sums, the last one adds them up) and the epilogue, in which the
 // accumulators pass through LDS once (per wave, 32 rows at a time) so that every lane ends up
 // with 8 consecutive columns of one row.  `smem` must hold C::EP_BYTES and is free to reuse.
-template <class C, int EPI, bool EDGE>
+template <class C, int EPI, bool EDGE, bool RESIDENT>
 __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem, int* lds_misc, void* const* lds_outs,
                                           f32x4 (&acc)[C::MI][C::NI], int tile, int split, bool is_split,
-                                          int m0, int n0, int tid, int lane, int wave, int wm, int wn, int vb = -1) {
+                                          int m0, int n0, int tid, int lane, int wave, int wm, int wn, bool peers_added, int vb = -1) {
   trace_stamp(a, TRACE_MAIN_END, vb);
   // ---- split-K: all but the last-arriving workgroup of a tile park their partial sums ----
   if (is_split) {
@@ -1402,14 +1465,14 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
   constexpr int NP_ALL = FLUX_MAX_RANKS - 1, NP_8 = 7;
   if (EPI == EPI_RS && a.write_only == 2) {
     epilogue_all_atomic<C, EDGE>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
-  } else if (EPI != EPI_RS || a.write_only) {
-    epilogue_all<C, EPI, EDGE, false, 2, 0>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
+  } else if (EPI != EPI_RS || a.write_only || peers_added) {
+    epilogue_all<C, EPI, EDGE, false, 2, 0, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
   } else if (a.R <= NP_8 + 1) {
-    if (a.partial_f32) epilogue_all<C, EPI, EDGE, true, 1, NP_8>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
-    else epilogue_all<C, EPI, EDGE, false, 2, NP_8>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
+    if (a.partial_f32) epilogue_all<C, EPI, EDGE, true, 1, NP_8, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
+    else epilogue_all<C, EPI, EDGE, false, 2, NP_8, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
   } else {
-    if (a.partial_f32) epilogue_all<C, EPI, EDGE, true, 1, NP_ALL>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
-    else epilogue_all<C, EPI, EDGE, false, 1, NP_ALL>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
+    if (a.partial_f32) epilogue_all<C, EPI, EDGE, true, 1, NP_ALL, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
+    else epilogue_all<C, EPI, EDGE, false, 1, NP_ALL, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
   }
   if (EPI == EPI_RS && a.tile_ready != nullptr) {
     // Producer side of the tile-ready handshake (Sec. 4.2, "Reduce", second form): the tile was written
@@ -1973,6 +2036,13 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
     for (int ni = 0; ni < C::NI; ++ni)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[mi][ni][e] = 0.f;
+  const bool added = takes_peers_first<C, EPI>(a, tile, is_split);       // (uniform)
+  if constexpr (EPI == EPI_RS && C::BM * C::BN >= PEERS_FIRST_AREA) {
+    if (added) {
+      sum_peers_first<C, EDGE, PEERS_FIRST_RANKS - 1>(a, reinterpret_cast<float*>(pool) + wave * (32 * C::EP_STRIDE), acc, m0, n0, lane, wm, wn);
+      __syncthreads();      // (the ring takes the place of other waves' staging areas)
+    }
+  }
 
   bool carries = false;
   if constexpr (CARRY) carries = side.pending();      // (uniform)
@@ -2034,7 +2104,7 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
     fill_lds_outs(a, tail_words->outs, tid);
     __syncthreads();
   }
-  gemm_tail<C, EPI, EDGE>(a, pool, tail_words->misc, tail_words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn);
+  gemm_tail<C, EPI, EDGE, false>(a, pool, tail_words->misc, tail_words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, added);
 }
 
 // The same kernel as a grid of resident workgroups, one per compute unit, each walking the block
@@ -2092,7 +2162,7 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma_resident(const 
       fill_lds_outs(a, words->outs, tid);
       __syncthreads();
     }
-    gemm_tail<C, EPI, false>(a, pool, words->misc, words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, vb);
+    gemm_tail<C, EPI, false, true>(a, pool, words->misc, words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, false, vb);
     __syncthreads();      // the staging area and the shared words are the next block's
   }
 }
