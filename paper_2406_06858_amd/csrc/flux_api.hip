@@ -396,7 +396,10 @@ static double plan_cost(const flux_problem_t* p, int cfg) {
   double rounds;
   if (split > 1 && split_tiles < tiles) rounds = (double)((tiles - split_tiles) / slots) + part * (double)((split_tiles * split + slots - 1) / slots);
   else rounds = part * (double)((tiles * split + slots - 1) / slots);
-  double rate = cfg == 0 ? 1.0 : cfg == 1 ? 0.84 : 0.8 / g_cfgs[cfg].occupancy;
+  // (128x128 tiles that have a CU each, whole: us, 256x128 / 128x128, rs 512x4608x288 27.2 / 17.0, 608x448x768 36.9 / 22.0, 852x3584x872
+  // 29.4 / 20.9, 1074x3584x3584 51.8 / 46.1, ag 3872x472x912 35.5 / 28.1, 592x6144x1536 28.8 / 24.7, 520x6144x3016 50.5 / 44.7, write-only
+  // 632x6144x3584 47.8 / 45.5, 512x8192x672 22.7 / 20.0; with the rate of two per CU all of these went to 256x128)
+  double rate = cfg == 0 ? 1.0 : cfg == 1 ? 0.84 : split == 1 && tiles <= N_CU ? 0.5 : 0.8 / g_cfgs[cfg].occupancy;
   if (p->M % bm != 0 || p->N % bn != 0 || p->K % bk != 0) rate *= 0.7;
   return rounds * (double)bm * (double)bn / rate;
 }
@@ -488,12 +491,20 @@ static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
     else {
       // Large tiles: 256x256 moves the least operand data per flop but needs a grid that fills the
       // chip round by round; 256x128 and 128x128 give two and four times the tiles.  Take the one
-      // with the least estimated time.  256x256 with a uniform K split is never worth it.
+      // with the least estimated time.  Fewer than 128 tiles of 256x256 have to be cut along K: that pays over a long K, into three
+      // parts or more or where the rows are as many as the columns (us, what else is taken / 256x256: 6592x408x9704 145 / 101,
+      // 2168x2648x12288 232 / 196, 768x6144x8192 106 / 93, ag 3600x1536x9432 206 / 167, write-only 320x4608x9336 78 / 63, 576x6520x8192
+      // 122 / 96, 386x6144x7720 88 / 65; the other side, a shorter K: ag 504x12288x4608 67 / 80, 528x6144x6144 71 / 76; two
+      // parts of wide matrices: 576x8192x12288 166 / 197, ag 1216x3584x8192 101 / 127).
       cfg = 2;
       double best = plan_cost(p, 2);
       const double c1 = plan_cost(p, 1);
       if (c1 < best) { best = c1; cfg = 1; }
-      if ((long long)((p->M + 255) / 256) * ((p->N + 255) / 256) >= 128) {
+      const long long tiles0 = (long long)((p->M + 255) / 256) * ((p->N + 255) / 256);
+      int split0;
+      long long cut0;
+      plan_split(p, 0, tiles0, (p->K + 63) / 64, &split0, &cut0);
+      if (tiles0 >= 128 || (p->K >= 7168 && (split0 >= 3 || (split0 == 2 && 5ll * p->M >= 4ll * p->N)))) {
         const double c0 = plan_cost(p, 0);
         if (c0 <= best) { best = c0; cfg = 0; }
       }
