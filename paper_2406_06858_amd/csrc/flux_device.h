@@ -494,12 +494,13 @@ __device__ __forceinline__ void epilogue_all(const GemmArgs& a, void* const* lds
 // The peers' rows ahead of the main loop: their sum (fp32, ascending rank) is what the accumulators start from, and the end
 // of the tile only stores.  The way of epilogue_all backwards: 8 columns per lane -> LDS -> registers.
 //
-constexpr int PEERS_FIRST_AREA = 128 * 128, PEERS_FIRST_RANKS = 8;      // smallest tile, most ranks
+constexpr int PEERS_FIRST_AREA = 128 * 128;      // smallest tile
 // Why: reading the peers takes a unit 32 us per 256x256 tile and 7 peers when half of the units do it, 44-50 when all do, and
 // the workgroups of a grid all reach the end of their tiles at about the same time.  With every second group of eight
 // (peers_first) reading its peers first, one half reads while the other multiplies, from the first tile on and whatever the number of
 // rounds.  us per call, 8 ranks, every tile's peers behind its main loop / half of them ahead: 4096x8192x3584 250 / 228, 4096x8192x1536
 // 166 / 143, 2048x8192x1024 73 / 61, 1024x8192x1024 41 / 34, 4096x12288x4608 444 / 414, 8192x12288x4608 846 / 834, 1496x5112x3400 87.4 / 85.5.
+// 16 ranks: 2048x8192x3584 172 / 144, 1024x8192x1536 71 / 56, 4096x8192x1536 261 / 209, 4096x4608x3584 233 / 219, 832x4608x1448 44 / 40.
 // (Four passes' loads in flight instead of two: the same.)
 template <class C, bool EDGE, int NP>
 __device__ __forceinline__ void sum_peers_first(const GemmArgs& a, float* ep, f32x4 (&acc)[C::MI][C::NI], int m0, int n0, int lane, int wm, int wn) {
@@ -2039,7 +2040,9 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
   const bool added = takes_peers_first<C, EPI>(a, tile, is_split);       // (uniform)
   if constexpr (EPI == EPI_RS && C::BM * C::BN >= PEERS_FIRST_AREA) {
     if (added) {
-      sum_peers_first<C, EDGE, PEERS_FIRST_RANKS - 1>(a, reinterpret_cast<float*>(pool) + wave * (32 * C::EP_STRIDE), acc, m0, n0, lane, wm, wn);
+      float* const ep = reinterpret_cast<float*>(pool) + wave * (32 * C::EP_STRIDE);
+      if (a.R <= 8) sum_peers_first<C, EDGE, 7>(a, ep, acc, m0, n0, lane, wm, wn);
+      else sum_peers_first<C, EDGE, FLUX_MAX_RANKS - 1>(a, ep, acc, m0, n0, lane, wm, wn);
       __syncthreads();      // (the ring takes the place of other waves' staging areas)
     }
   }

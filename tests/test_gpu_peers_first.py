@@ -1,5 +1,5 @@
 """Reduce-scatter tiles that add their peers ahead of the main loop (every second group of eight large tiles), and A asked for
-ahead of it: whole and ragged tiles, as many ranks as the rule takes and one more, both dtypes, both layouts of B, row pitches.
+ahead of it: whole and ragged tiles, up to eight ranks and more, both dtypes, both layouts of B, row pitches.
 Integer inputs whose sums stay below 2^24: any order of an fp32 sum gives the same, and the comparison is bit for bit."""
 import pytest
 
@@ -23,7 +23,7 @@ def _check(M, N, K, R, dtype, cfg, nk, pads, rank):
         gh.assert_bits_equal(outs[r][1], want[r], f"{(M, N, K, R)} slice {r}")
 
 
-@pytest.mark.parametrize("R,dtype", [(2, "bf16"), (5, "bf16"), (8, "bf16"), (9, "bf16"), (8, "f32")])
+@pytest.mark.parametrize("R,dtype", [(2, "bf16"), (5, "bf16"), (8, "bf16"), (9, "bf16"), (16, "bf16"), (8, "f32")])
 @pytest.mark.parametrize("cfg", [1, 2, 3])
 def test_half_of_the_tiles_add_their_peers_first(cfg, R, dtype):
     bm, bn, _ = fb.flux_tile_config_info(cfg)
