@@ -10,7 +10,7 @@ namespace flux {
 struct CfgInfo {
   int bm, bn, bk;
   int occupancy;   // workgroups per CU the kernel is built for
-  int stages;      // LDS stages of the direct-to-LDS kernel (more than two: the deep pipeline)
+  int stages;      // slabs of B in LDS (more than two: the deep pipeline; the 256x256 tile holds one more of A)
   hipError_t (*launch)(int epi, int wait, int edge, const GemmArgs& a, int grid, hipStream_t s);
 };
 
