@@ -410,7 +410,9 @@ static bool resident_shape(const flux_problem_t* p, const Plan& pl) {
          (long long)pl.full_tiles + (long long)pl.split_tiles * pl.split_k >= 4ll * N_CU && p->K <= 3072;
 }
 
-static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
+// `scratch`: the most workspace there is (flux_gemm_rs_static; the planner's other cuts are not sized for it, a call whose
+// parts do not fit is refused as ever).
+static int make_plan(int op, const flux_problem_t* p, Plan* pl, size_t scratch = SIZE_MAX) {
   int st = validate_problem(op, p);
   if (st != FLUX_OK) return st;
   int cfg;
@@ -504,7 +506,8 @@ static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
       int split0;
       long long cut0;
       plan_split(p, 0, tiles0, (p->K + 63) / 64, &split0, &cut0);
-      if (tiles0 >= 128 || (p->K >= 7168 && (split0 >= 3 || (split0 == 2 && 5ll * p->M >= 4ll * p->N)))) {
+      const bool fits = WS_HEADER_BYTES + (size_t)split0 * (size_t)tiles0 * (256 * 256 * sizeof(float)) <= scratch;
+      if (tiles0 >= 128 || (fits && p->K >= 7168 && (split0 >= 3 || (split0 == 2 && 5ll * p->M >= 4ll * p->N)))) {
         const double c0 = plan_cost(p, 0);
         if (c0 <= best) { best = c0; cfg = 0; }
       }
@@ -1044,7 +1047,7 @@ int flux_gemm_rs(const flux_problem_t* p, const void* A, const void* B, const vo
 int flux_gemm_rs_static(const flux_problem_t* p, const void* A, const void* B, const void* const* peer_partials,
                         void* const* out_slices, void* stream) {
   Plan pl;
-  int st = make_plan(FLUX_OP_RS, p, &pl);
+  int st = make_plan(FLUX_OP_RS, p, &pl, (size_t)FLUX_STATIC_SCRATCH_BYTES);
   if (st != FLUX_OK) return st;
   const size_t need = pl.split_k > 1 ? workspace_need(pl) : 0;
   if (need > (size_t)FLUX_STATIC_SCRATCH_BYTES) return FLUX_ERR_WORKSPACE;
