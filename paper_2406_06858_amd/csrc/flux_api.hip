@@ -410,9 +410,7 @@ static bool resident_shape(const flux_problem_t* p, const Plan& pl) {
          (long long)pl.full_tiles + (long long)pl.split_tiles * pl.split_k >= 4ll * N_CU && p->K <= 3072;
 }
 
-// `scratch`: the most workspace there is (flux_gemm_rs_static; the planner's other cuts are not sized for it, a call whose
-// parts do not fit is refused as ever).
-static int make_plan(int op, const flux_problem_t* p, Plan* pl, size_t scratch = SIZE_MAX) {
+static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
   int st = validate_problem(op, p);
   if (st != FLUX_OK) return st;
   int cfg;
@@ -493,21 +491,33 @@ static int make_plan(int op, const flux_problem_t* p, Plan* pl, size_t scratch =
     else {
       // Large tiles: 256x256 moves the least operand data per flop but needs a grid that fills the
       // chip round by round; 256x128 and 128x128 give two and four times the tiles.  Take the one
-      // with the least estimated time.  Fewer than 128 tiles of 256x256 have to be cut along K: that pays over a long K, into three
-      // parts or more or where the rows are as many as the columns (us, what else is taken / 256x256: 6592x408x9704 145 / 101,
-      // 2168x2648x12288 232 / 196, 768x6144x8192 106 / 93, ag 3600x1536x9432 206 / 167, write-only 320x4608x9336 78 / 63, 576x6520x8192
-      // 122 / 96, 386x6144x7720 88 / 65; the other side, a shorter K: ag 504x12288x4608 67 / 80, 528x6144x6144 71 / 76; two
-      // parts of wide matrices: 576x8192x12288 166 / 197, ag 1216x3584x8192 101 / 127).
+      // with the least estimated time.
       cfg = 2;
       double best = plan_cost(p, 2);
       const double c1 = plan_cost(p, 1);
       if (c1 < best) { best = c1; cfg = 1; }
+      // Fewer than 128 tiles of 256x256 have to be cut along K.  AllGather calls over a long K: that pays where their parts fill more
+      // of the chip than 256x128 tiles would, and instead of 128x128 tiles (us, what else is taken / 256x256: ag 768x6144x8192 109 /
+      // 98, 656x6064x11480 209 / 125, 448x6144x9248 103 / 78, 320x4608x9552 74 / 68, 384x6144x8408 77 / 77, 640x6144x8272 115 / 101,
+      // 1064x3584x12288 127 / 124); where both fill it alike the hand-over of twice the sums costs as much as the operands save or
+      // more (the other side: 320x4608x8192 54 / 59, 240x8192x8192 56 / 64, 272x3584x8416 46 / 50, 3072x1480x8192 116 / 136,
+      // 960x3584x12288 114 / 121, 576x3584x12288 87 / 90; 512x4608x12288 91 / 83), but for two parts of tall matrices over K
+      // beyond 9216 (2880x1536x9576 146 / 148, 3600x1536x9432 206 / 167, 4864x1536x9552 210 / 177, 3344x1536x12288 218 / 181).
+      // Not reduce-scatter calls: the parts are 64 MiB, which the entry point without a workspace does not have, and it has the plan
+      // of the one with a workspace.
       const long long tiles0 = (long long)((p->M + 255) / 256) * ((p->N + 255) / 256);
-      int split0;
-      long long cut0;
-      plan_split(p, 0, tiles0, (p->K + 63) / 64, &split0, &cut0);
-      const bool fits = WS_HEADER_BYTES + (size_t)split0 * (size_t)tiles0 * (256 * 256 * sizeof(float)) <= scratch;
-      if (tiles0 >= 128 || (fits && p->K >= 7168 && (split0 >= 3 || (split0 == 2 && 5ll * p->M >= 4ll * p->N)))) {
+      bool take = tiles0 >= 128;
+      if (!take && op == FLUX_OP_AG && p->split_k <= 0 && p->K >= 7168) {
+        const long long tiles1 = (long long)((p->M + 255) / 256) * ((p->N + 127) / 128);
+        const int kt = (p->K + 63) / 64;
+        int parts0, parts1;
+        long long cut;
+        plan_split(p, 0, tiles0, kt, &parts0, &cut);
+        plan_split(p, 1, tiles1, kt, &parts1, &cut);
+        const bool fills_more = parts0 >= 3 && (cfg == 2 || 20ll * parts0 * tiles0 >= 23ll * parts1 * tiles1);
+        take = fills_more || (parts0 == 2 && p->K > 9216 && 5ll * p->M >= 4ll * p->N);
+      }
+      if (take) {
         const double c0 = plan_cost(p, 0);
         if (c0 <= best) { best = c0; cfg = 0; }
       }
@@ -1047,7 +1057,7 @@ int flux_gemm_rs(const flux_problem_t* p, const void* A, const void* B, const vo
 int flux_gemm_rs_static(const flux_problem_t* p, const void* A, const void* B, const void* const* peer_partials,
                         void* const* out_slices, void* stream) {
   Plan pl;
-  int st = make_plan(FLUX_OP_RS, p, &pl, (size_t)FLUX_STATIC_SCRATCH_BYTES);
+  int st = make_plan(FLUX_OP_RS, p, &pl);
   if (st != FLUX_OK) return st;
   const size_t need = pl.split_k > 1 ? workspace_need(pl) : 0;
   if (need > (size_t)FLUX_STATIC_SCRATCH_BYTES) return FLUX_ERR_WORKSPACE;

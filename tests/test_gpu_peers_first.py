@@ -12,13 +12,13 @@ from test_gpu_strides import _rs_call, _say
 pytestmark = pytest.mark.gpu
 
 
-def _check(M, N, K, R, dtype, cfg, nk, pads, rank, static=False):
+def _check(M, N, K, R, dtype, cfg, nk, pads, rank):
     w = fi.Workload("peers_first", "rs", M, N, K, R, partial_dtype=dtype, out_dtype=dtype, a_dist=("int", 2), b_dist=("int", 2),
                     peer_dist=("int", 8), seed=M + N + K + R)
     A, B, peers = fi.make_rs_inputs(w, rank)
     _, want = gh.oracle_rs(w, rank, A, B, peers)
     _say("peers first", (M, N, K, R), dtype, "cfg", cfg, "nk", nk)
-    _, outs = _rs_call(w, rank, A, B, peers, pads, tile_config=cfg, nk=nk, static=static)
+    _, outs = _rs_call(w, rank, A, B, peers, pads, tile_config=cfg, nk=nk)
     for r in range(R):
         gh.assert_bits_equal(outs[r][1], want[r], f"{(M, N, K, R)} slice {r}")
 
@@ -36,12 +36,3 @@ def test_half_of_the_tiles_add_their_peers_first(cfg, R, dtype):
 def test_a_asked_for_ahead_of_the_main_loop(K, pad, nk):
     """Rows of A a multiple of 2 KB apart, 256x128 tiles: rows and K that no batch of lines divides."""
     _check(264, 392, K, 2, "bf16", 2, nk, (pad, 0, 0), 1)
-
-
-@pytest.mark.parametrize("M,N,K", [(272, 4608, 7752), (192, 6144, 7472)])
-def test_static_scratch_holds_what_a_larger_workspace_would_cut_more(M, N, K):
-    """Shapes whose K the library cuts into more than the 32 MiB of the entry point without a workspace: taken there too, cut
-    less."""
-    p = fb.problem(M, N, K, 2, 1)
-    assert fb.flux_workspace_bytes(fb.FLUX_OP_RS, p) > 32 << 20
-    _check(M, N, K, 2, "bf16", 0, False, (0, 0, 0), 1, static=True)

@@ -389,3 +389,26 @@ def test_tile_of_65_to_127_rows_over_a_long_k(M, N, K, tile):
 def test_k_parts_of_few_rows_and_columns(M, N, K, parts):
     p = fb.problem(M, N, K, 8, 0)
     assert fb.flux_split_plan(fb.FLUX_OP_RS, p) == (0, M // 64 * (N // 128), parts)
+
+
+@pytest.mark.parametrize("M,N,K", [(272, 4608, 7752), (192, 6144, 7472), (768, 6144, 8192), (352, 6144, 12288), (1216, 3584, 12288), (3312, 576, 12288),
+                                   (2960, 1536, 8192), (7020, 920, 8192)])
+def test_a_long_k_is_cut_into_what_the_static_scratch_holds(M, N, K):
+    """Reduce-scatter grids of fewer than 128 tiles of 256x256 over a long K: the plan is one for both entry points, the one
+    with a workspace and the one without, and so are the queries."""
+    for flags in (0, fb.FLUX_FLAG_RS_WRITE_ONLY):
+        for R in (1, 2):
+            p = fb.problem(M, N, K, R, 0, flags=flags)
+            assert fb.flux_workspace_bytes(fb.FLUX_OP_RS, p) <= fb.FLUX_STATIC_SCRATCH_BYTES
+            assert (fb.flux_tile_shape(fb.FLUX_OP_RS, p).tile_m, fb.flux_tile_shape(fb.FLUX_OP_RS, p).tile_n) != (256, 256)
+
+
+@pytest.mark.parametrize("M,N,K,tile,plan", [
+    (768, 6144, 8192, (256, 256), (0, 72, 3)), (384, 6144, 8408, (256, 256), (0, 48, 5)), (640, 6144, 8272, (256, 256), (0, 72, 3)),    # fill more
+    (768, 6144, 7104, (256, 128), (0, 144, 1)), (320, 4608, 8192, (256, 128), (0, 72, 3)), (240, 8192, 8192, (256, 128), (0, 64, 4)),  # a shorter K; alike
+    (512, 4608, 12288, (256, 128), (0, 72, 3)), (960, 3584, 12288, (256, 128), (0, 112, 2)),
+    (3344, 1536, 12288, (256, 256), (0, 84, 2)), (3344, 1536, 9208, (256, 128), (0, 168, 1)), (1216, 3584, 8192, (256, 128), (0, 140, 1))])   # two parts
+def test_large_tiles_of_all_gather_calls_over_a_long_k(M, N, K, tile, plan):
+    p = fb.problem(M, N, K, 8, 0)
+    got = fb.flux_tile_shape(fb.FLUX_OP_AG, p)
+    assert (got.tile_m, got.tile_n) == tile and fb.flux_split_plan(fb.FLUX_OP_AG, p) == plan

@@ -102,3 +102,25 @@ def test_static_scratch_rejects_what_does_not_fit():
     with pytest.raises(fb.FluxError) as e:
         fb.flux_gemm_rs_static(p, dummy, dummy, [dummy] * 8, [dummy] * 8)
     assert e.value.status == fb.FLUX_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("M,N,K", [(272, 4608, 7752), (192, 6144, 7472)])
+def test_static_form_runs_the_plan_that_the_queries_give(M, N, K):
+    """Few large tiles over a long K: the call fits, gives the results of the call with a workspace bit for bit (sums in the same
+    order), and its trace has the grid and the tiles that the queries say."""
+    w = fi.Workload("rs_static_plan", "rs", M, N, K, 2, seed=97)
+    p, A, B, peers, want, got = _both(w, 1)
+    full, cut, parts = fb.flux_split_plan(fb.FLUX_OP_RS, p)
+    assert parts > 1 and fb.flux_workspace_bytes(fb.FLUX_OP_RS, p) <= fb.FLUX_STATIC_SCRATCH_BYTES
+    grid = full + cut * parts
+    trace = torch.zeros((grid, 8), dtype=torch.int64, device=gh.DEV)
+    print("static call, traced:", M, N, K, (full, cut, parts), flush=True)
+    fb.flux_trace_next_call(trace)
+    fb.flux_gemm_rs_static(p, A, B, peers, got)
+    torch.cuda.synchronize()
+    for r in range(w.R):
+        assert torch.equal(got[r].view(torch.int16), want[r].view(torch.int16)), f"slice {r}"
+    rec = trace.cpu().numpy().view(np.uint32).reshape(grid, 16)
+    assert np.array_equal(rec[:, 0], np.arange(grid))
+    for b in range(0, grid, 7):
+        assert (int(rec[b, 1]), int(rec[b, 2])) == fb.flux_tile_coord(fb.FLUX_OP_RS, p, None, int(rec[b, 6]))
