@@ -160,6 +160,12 @@ typedef struct flux_problem {
  *                   written (every element exactly once; with FLUX_FLAG_RS_ATOMIC: added to).
  *   workspace       device, >= flux_workspace_bytes(FLUX_OP_RS, p) bytes (may be NULL if 0),
  *                   initialised once with flux_init_buffers.
+ * Sums are fp32 and converted once.  An element's order of summation: the product (ascending K; the K parts of a cut tile
+ * in ascending order), then the peers in ascending rank.  With bf16 partials and slices, half of the uncut tiles of 128x128
+ * or more (every second row or column of them, by where a tile lies in [M,N]; none of a grid that FLUX_FLAG_NO_RESIDENT_GRID is
+ * about) start from the sum of the peers, in ascending rank, and add the product to it.  The order follows from M, N, K, R, the
+ * data types, the tile configuration and which tiles are cut along K: same problem and rank, same bits.  With no tile or every
+ * tile cut, rank and the flags that change the order of visits change nothing; of a last round cut along K they choose the tiles.
  */
 int flux_gemm_rs(const flux_problem_t* p, const void* A, const void* B,
                  const void* const* peer_partials, void* const* out_slices,

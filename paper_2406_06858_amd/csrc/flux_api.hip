@@ -1113,9 +1113,10 @@ int gemm_rs_planned(const flux_problem_t* p, const Plan& pl, const void* A, cons
   // (sum_peers_first): whole tiles that are large, bf16 partials and results (which round to 8 bits whichever sum of fp32 comes
   // first).  Not the many short tiles of a resident grid, or of one that FLUX_FLAG_NO_RESIDENT_GRID would keep from being one
   // (results do not depend on that flag): 8192x12288x1536 427 us on a resident grid half of which
-  // starts late, 437 on one whose every second group takes its peers first.
-  a.tm.peers_first = !write_only && p->R > 1 && p->partial_dtype == FLUX_BF16 && p->out_dtype == FLUX_BF16 &&
-                     pl.bm * pl.bn >= PEERS_FIRST_AREA && !resident_shape(p, pl);
+  // starts late, 437 on one half of which takes its peers first.
+  if (!write_only && p->R > 1 && p->partial_dtype == FLUX_BF16 && p->out_dtype == FLUX_BF16 && pl.bm * pl.bn >= PEERS_FIRST_AREA &&
+      !resident_shape(p, pl))
+    a.tm.peers_first = a.S % pl.bm == 0 && a.S >= 2 * pl.bm ? 2 : 1;
   return launch_gemm(pl, EPI_RS, 0, a, s);
 }
 

@@ -64,7 +64,7 @@ constexpr int MAX_COPY_PIECES = 256;       // pieces per communication tile = co
 struct TileMap {
   int32_t tiles_m, tiles_n, band_h, n_xcd;
   int32_t packed;
-  int32_t peers_first;       // reduce-scatter: every second group of eight tiles adds its peers ahead of its main loop (see sum_peers_first)
+  int32_t peers_first;       // reduce-scatter: every second column (1) or row (2) of tiles adds its peers ahead of its main loop (see sum_peers_first)
   uint64_t order4;
 };
 
@@ -496,8 +496,8 @@ __device__ __forceinline__ void epilogue_all(const GemmArgs& a, void* const* lds
 //
 constexpr int PEERS_FIRST_AREA = 128 * 128;      // smallest tile
 // Why: reading the peers takes a unit 32 us per 256x256 tile and 7 peers when half of the units do it, 44-50 when all do, and
-// the workgroups of a grid all reach the end of their tiles at about the same time.  With every second group of eight
-// (peers_first) reading its peers first, one half reads while the other multiplies, from the first tile on and whatever the number of
+// the workgroups of a grid all reach the end of their tiles at about the same time.  With half of the tiles
+// (peers_first) reading their peers first, one half reads while the other multiplies, from the first tile on and whatever the number of
 // rounds.  us per call, 8 ranks, every tile's peers behind its main loop / half of them ahead: 4096x8192x3584 250 / 228, 4096x8192x1536
 // 166 / 143, 2048x8192x1024 73 / 61, 1024x8192x1024 41 / 34, 4096x12288x4608 444 / 414, 8192x12288x4608 846 / 834, 1496x5112x3400 87.4 / 85.5.
 // 16 ranks: 2048x8192x3584 172 / 144, 1024x8192x1536 71 / 56, 4096x8192x1536 261 / 209, 4096x4608x3584 233 / 219, 832x4608x1448 44 / 40.
@@ -545,9 +545,17 @@ __device__ __forceinline__ void sum_peers_first(const GemmArgs& a, float* ep, f3
     __builtin_amdgcn_wave_barrier();
   }
 }
+// Which half follows from where a tile lies in the result, not from when it is visited: the bits of a result depend neither on the
+// rank nor on the flags that change the order of visits.  Every second column of tiles, or, where a slice is two tiles high or more
+// (a die then walks down the rows of a slice), every second row.  us, columns / rows: 1024x8192x1024 33.5 / 35.7, 16 ranks 1024x8192x1536
+// 55.9 / 60.9, 1152x12288x2048 87.8 / 93.6, 768x12288x2048 66.4 / 72.1, but 1496x5112x3400 85.0 / 81.7; the other side, slices of two tiles
+// or more: 4096x8192x3584 229.8 / 227.1, 8192x3584x1536 147.2 / 136.8, 8192x1536x6144 221.7 / 204.2, 4 ranks 4096x1536x4608 77.4 / 66.4.
+// (Neighbours in both directions in turn is behind one of the two everywhere: tiles that share a panel of B or A part company.  By place in
+// the order of visits, every second group of eight tiles: the same times where a slice's tiles fill the dies evenly, 3-10 % behind
+// where they do not: 3000x3584x5120 150.4 / 137.4, 1280x4608x1536 39.2 / 35.7, 6144x3072x2048 133.5 / 123.9.)
 template <class C, int EPI>
-__device__ __forceinline__ bool takes_peers_first(const GemmArgs& a, int tile, bool is_split) {
-  return EPI == EPI_RS && C::BM * C::BN >= PEERS_FIRST_AREA && a.tm.peers_first && !is_split && ((tile >> 3) & 1);
+__device__ __forceinline__ bool takes_peers_first(const GemmArgs& a, int mt, int nt, bool is_split) {
+  return EPI == EPI_RS && C::BM * C::BN >= PEERS_FIRST_AREA && a.tm.peers_first && !is_split && ((a.tm.peers_first == 2 ? mt : nt) & 1);
 }
 
 // ---- AllGather copy pieces --------------------------------------------------------------------
@@ -2037,7 +2045,7 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
     for (int ni = 0; ni < C::NI; ++ni)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[mi][ni][e] = 0.f;
-  const bool added = takes_peers_first<C, EPI>(a, tile, is_split);       // (uniform)
+  const bool added = takes_peers_first<C, EPI>(a, mt, nt, is_split);       // (uniform)
   if constexpr (EPI == EPI_RS && C::BM * C::BN >= PEERS_FIRST_AREA) {
     if (added) {
       float* const ep = reinterpret_cast<float*>(pool) + wave * (32 * C::EP_STRIDE);
