@@ -1940,25 +1940,30 @@ struct MmaPipe {
   }
 };
 
-// All of A asked for once, ahead of the main loop, in the order it lies in memory: the grid's threads take its 128-byte lines
-// in turn, one word each, so that it is in the Infinity Cache when the slabs are loaded.  A slab is 128 bytes of every row, and
+// All of A asked for once, ahead of the main loop, in the order it lies in memory: the threads of the first round's workgroups take its
+// 128-byte lines in turn, one word each, so that it is in the Infinity Cache when the slabs are loaded.  A slab is 128 bytes of every row, and
 // rows a multiple of 2 KB apart put those into few of the memory's channels, slab after slab: A of 6 MB out of memory cost a call
 // with 151 MB of weights as much as the weights did (512x12288x6144: 67 us with both in the cache, 82 with the weights
 // out of memory, 91 with A out of memory, 93 with both).
-// us per call without / with, 2 ranks: 512x8192x5120 68.7 / 63.5, 512x8192x6144 74.3 / 68.6, 1024x8192x7168 109.4 / 103.7, 256x8192x6144
-// 48.5 / 47.3; 8 ranks: 512x12288x6144 112.6 / 97.3.  Not taken (warm_a): other pitches (512x8192x3584 47.8 / 48.7, 1496x5112x3400
-// 67.0 / 68.2), a multiple of 16 KB (1024x8192x8192 134.9 / 137.7; 512x12288x8192 113.8 / 111.7), few slabs (512x12288x3072 47.0 /
-// 46.9), tiles other than 256x128 (64x8192x8192 33.9 / 34.6, 4096x8192x4096 224.7 / 228.6), and a gathered A, which has just been written.
+// us in the kernel without / with, A in memory: 2 ranks 512x8192x5120 87.0 / 77.3, 1024x8192x7168 130.5 / 120.3, 256x8192x6144 64.3 / 59.7, 8 ranks
+// 512x12288x6144 136.2 / 120.0; several rounds, 8 ranks 3000x3584x5120 182.9 / 164.3, 1400x8192x5120 194.9 / 166.5, 2048x4608x5120 148.8 / 137.1 (shared
+// out over all workgroups, of which the later ones ask when A has gone by: 168.5, 170.0, 147.2).  An A that is in a cache, written by the
+// kernel before, gains nothing and costs the requests: 76.6 / 77.3, 116.7 / 118.2, 58.4 / 59.5, 119.5 / 119.9; 156.9 / 159.5, 161.9 / 163.5, 132.0 / 133.0.
+// Not taken (warm_a): other pitches (512x8192x3584 47.8 / 48.7, 1496x5112x3400 67.0 / 68.2), a multiple of 16 KB (1024x8192x8192
+// 134.9 / 137.7; 512x12288x8192 113.8 / 111.7), few slabs (512x12288x3072 47.0 / 46.9), tiles other than 256x128 (64x8192x8192 33.9 / 34.6,
+// 4096x8192x4096 224.7 / 228.6), and the fused call's gathered A, which the same grid has just written.
 constexpr int WARM_LOADS = 8;      // per thread
-__device__ __forceinline__ bool warm_a(const GemmArgs& a, uint32_t lines) {
+constexpr uint32_t WARM_BLOCKS = 256;   // workgroups of one round: one per compute unit
+__device__ __forceinline__ bool warm_a(const GemmArgs& a, uint32_t lines, uint32_t at_once) {
   const uint32_t pitch = (uint32_t)a.lda * 2u;
-  return pitch % 2048u == 0u && pitch % 16384u != 0u && a.K >= 4096 && lines <= WARM_LOADS * gridDim.x * 256u;
+  return blockIdx.x < WARM_BLOCKS && pitch % 2048u == 0u && pitch % 16384u != 0u && a.K >= 4096 && lines <= WARM_LOADS * at_once;
 }
 struct WarmA {
   uint32_t word[WARM_LOADS];
   __device__ __forceinline__ void ask(const GemmArgs& a, uint32_t bytes_a, int tid) {
-    const uint32_t row_lines = ((uint32_t)a.K * 2u + 127u) / 128u, lines = (uint32_t)a.M * row_lines, at_once = gridDim.x * 256u;
-    const bool warm = warm_a(a, lines);
+    const uint32_t row_lines = ((uint32_t)a.K * 2u + 127u) / 128u, lines = (uint32_t)a.M * row_lines;
+    const uint32_t at_once = (gridDim.x < WARM_BLOCKS ? gridDim.x : WARM_BLOCKS) * 256u;
+    const bool warm = warm_a(a, lines, at_once);
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.A), 0, (int)bytes_a, 0x00027000);
 #pragma unroll
     for (int t = 0; t < WARM_LOADS; ++t) {

@@ -40,6 +40,14 @@ def test_a_asked_for_ahead_of_the_main_loop(K, pad, nk):
     _check(264, 392, K, 2, "bf16", 2, nk, (pad, 0, 0), 1)
 
 
+def test_a_asked_for_by_the_first_round_of_several():
+    """Two rounds of 256x128 tiles, the second cut along K: 256 workgroups ask for all of A, the others for nothing."""
+    p = fb.problem(2304, 4096, 5120, 2, 1, tile_config=2)
+    full, cut, parts = fb.flux_split_plan(fb.FLUX_OP_RS, p)
+    assert full == 256 and cut * parts > 0
+    _check(2304, 4096, 5120, 2, "bf16", 2, False, (0, 0, 0), 1)
+
+
 def _run(M, N, K, R, rank, cfg, A, B, others, flags=0):
     """The whole [M,N] result for `others`, the R-1 peers' partials in ascending rank."""
     p = fb.problem(M, N, K, R, rank, "bf16", "bf16", cfg, 1, flags)
