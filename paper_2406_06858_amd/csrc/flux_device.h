@@ -296,7 +296,7 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 // B_NK: B is given as [N,K] (row n holds the K values of output column n, the layout of a linear
 // layer's weight).  Its tile then sits in LDS like A's (rows of BK values, the same slot swizzle) and a
 // fragment is one 16-byte read per lane, as for A, instead of two transposing reads.
-// NA, NB: slabs of A and of B that LDS holds; one of the two may have one more.
+// NA, NB: slabs of A and of B that LDS holds; A may have one more.
 template <int BM_, int BN_, int BK_, int WAVES_M_, int WAVES_N_, int NA_, int NB_, int OCC_, bool B_NK_ = false>
 struct TileCfg {
   static constexpr int BM = BM_, BN = BN_, BK = BK_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_;
@@ -312,7 +312,7 @@ struct TileCfg {
   static constexpr int EP_BYTES = WAVES_M * WAVES_N * 32 * EP_STRIDE * 4;
   static_assert(BM % (WAVES_M * 32) == 0 && BN % (WAVES_N * 32) == 0 && BK % 32 == 0, "tile shape");
   static_assert(B_SLOTS >= 8, "BN >= 64");
-  static_assert(NA >= 2 && NB >= 2 && NA <= NB + 1 && NB <= NA + 1, "the order of the loads (MmaPipe)");
+  static_assert(NB >= 2 && (NA == NB || NA == NB + 1), "the order of the loads (MmaPipe)");
 
   // LDS of a workgroup: the ring, over it (once the main loop is done) the epilogue's staging area, and a few words that the
   // workgroup shares (SharedWords).  Where the ring takes all of a compute unit's LDS the words lie over the slab that is asked
@@ -322,9 +322,9 @@ struct TileCfg {
   static constexpr int MAX_BYTES = RING_BYTES > EP_BYTES ? RING_BYTES : EP_BYTES;
   static constexpr bool WORDS_IN_RING = MAX_BYTES + WORDS_BYTES > LDS_MAX / OCC;
   static constexpr int POOL_BYTES = WORDS_IN_RING ? MAX_BYTES : MAX_BYTES + WORDS_BYTES;
-  static constexpr int WORDS_AT = !WORDS_IN_RING ? MAX_BYTES : NA > NB ? (NA - 1) * A_BYTES : RING_BYTES - B_BYTES;   // before and in the main loop
+  static constexpr int WORDS_AT = WORDS_IN_RING ? (NA - 1) * A_BYTES : MAX_BYTES;   // before and in the main loop
   static constexpr int WORDS_AT_TAIL = WORDS_IN_RING ? MAX_BYTES - WORDS_BYTES : MAX_BYTES;   // after it
-  static_assert(!WORDS_IN_RING || (NA != NB && WORDS_AT_TAIL >= EP_BYTES), "room for the shared words");
+  static_assert(!WORDS_IN_RING || (NA > NB && WORDS_AT_TAIL >= EP_BYTES), "room for the shared words");
 };
 
 struct SharedWords {
@@ -1546,7 +1546,6 @@ struct DmaLoader {
 
   // Offsets into A and B are unsigned 32-bit byte offsets (a matrix has fewer than 2^31 elements, so
   // fewer than 2^32 bytes); the hardware adds the vector and the scalar part as unsigned numbers.
-  __amdgpu_buffer_rsrc_t ra, rb;
   uint32_t voff_a, voff_b;
   uint32_t K2, N2;               // row pitches in bytes
   uint32_t bytes_a, bytes_b;     // extents
@@ -1559,8 +1558,6 @@ struct DmaLoader {
   __device__ __forceinline__ void init(const GemmArgs& a, int m0, int n0, int wave, int lane) {
     bytes_a = ((unsigned)(a.M - 1) * (unsigned)a.lda + (unsigned)a.K) * 2u;
     bytes_b = (C::B_NK ? (unsigned)(a.N - 1) * (unsigned)a.ldb + (unsigned)a.K : (unsigned)(a.K - 1) * (unsigned)a.ldb + (unsigned)a.N) * 2u;
-    ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.A), 0, (int)bytes_a, 0x00027000);
-    rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.B), 0, (int)bytes_b, 0x00027000);
     lds_b = (uint32_t)(wave_row(wave) * (1024 / RPI));
     const int r_in = lane / C::A_SLOTS, sp = lane % C::A_SLOTS;
     const int row = A_RPI * wave + r_in;
@@ -1581,7 +1578,6 @@ struct DmaLoader {
       if (EDGE) k_row = n0 + (spb ^ swz_b<C::B_SLOTS>(k)) * 8 < a.N ? k : 0x40000000;
     }
   }
-  static constexpr int N_INSTR = A_INSTR + B_INSTR;
 
   __device__ __forceinline__ Slabs slabs(const GemmArgs& a, bool there_a, int ka, bool there_b, int kb) const {
     return Slabs{__builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.A), 0, (int)(there_a ? bytes_a : 0u), 0x00027000),
@@ -1709,16 +1705,14 @@ template <class C, bool B_FIRST, bool EDGE>
 struct MmaPipe {
   typedef DmaLoader<C, EDGE> Ld;
   static constexpr int NA = C::NA, NB = C::NB;
-  static constexpr int N = NA < NB ? NA : NB;
-  static constexpr bool A_LEADS = NA > NB, B_LEADS = NB > NA;      // by one slab
-  static constexpr int U = NA == NB ? N : NA * NB;                   // slabs after which both rings are where they were
+  static constexpr bool A_LEADS = NA > NB;                           // by one slab
+  static constexpr int U = NA == NB ? NB : NA * NB;                   // slabs after which both rings are where they were
   static constexpr int KS = C::BK / 32;                              // k-steps per slab
   static_assert(KS == 2, "two fragment sets, one per k-step");
   static constexpr int G = C::MI * C::NI;                            // MFMAs per k-step
   static constexpr int NF = C::MI + C::NI;                           // fragments per k-step
   static constexpr int LA = Ld::A_INSTR, LB = Ld::B_INSTR, L = LA + LB;   // loads per slab and wave
-  static constexpr int LX = A_LEADS ? LA : B_LEADS ? LB : 0;       // loads of the operand that is a slab further ahead
-  static constexpr int LXA = A_LEADS ? LA : 0;
+  static constexpr int LX = A_LEADS ? LA : 0;                        // loads of A where it is a slab further ahead
   static constexpr int NBV = C::B_NK ? KS : C::NI;
   static constexpr int A_HI = (NA * C::A_BYTES + 65535) / 65536, B_HI = (NB * C::B_BYTES + 65535) / 65536;  // a read's immediate offset reaches 64 KB
   // Placement, in MFMAs.  (8192^3, of G = 64: within 1 % for SPREAD 40 to 62, BAR_AT 1 to 12.  Without an operand that leads SPAN
@@ -1804,7 +1798,7 @@ struct MmaPipe {
     }
   }
 
-  // Fills the pipeline: slabs 0 .. N-2 requested, and the operand that leads of slab N-1; then the first of the loads that a step
+  // Fills the pipeline: slabs 0 .. NB-2 requested, and A of slab NB-1 where it leads; then the first of the loads that a step
   // "-1" would deal out; the fragments of the first k-step read.  Slabs past the end are loads outside the records everywhere
   // (no memory access): every step issues the same number of loads, which keeps the counter waits constants and the loop
   // one shape.
@@ -1812,29 +1806,28 @@ struct MmaPipe {
   __device__ __forceinline__ void request_b(const Ld& ld, const GemmArgs& ga, int k_begin, int KT) {
     static_assert(B_FIRST);
 #pragma unroll
-    for (int j = 0; j < N - 1 + B_LEADS; ++j) ld.issue_b(ga, slab_pair(ld, ga, k_begin, j, j, KT), slab_b(j));
+    for (int j = 0; j < NB - 1; ++j) ld.issue_b(ga, slab_pair(ld, ga, k_begin, j, j, KT), slab_b(j));
   }
   __device__ __forceinline__ void start(const Ld& ld, const GemmArgs& ga, int k_begin, int KT, int wave, bool two_slabs) {
 #pragma unroll
-    for (int j = 0; j < N - 1; ++j) {
+    for (int j = 0; j < NB - 1; ++j) {
       const auto s = slab_pair(ld, ga, k_begin, j, j, KT);
       ld.issue_a(ga, s, slab_a(j), wave);
       if constexpr (!B_FIRST) ld.issue_b(ga, s, slab_b(j));
     }
-    const auto s = slab_pair(ld, ga, k_begin, N - 1, N - 1, KT);
-    if constexpr (B_LEADS && !B_FIRST) ld.issue_b(ga, s, slab_b(N - 1));
-    constexpr int BEHIND = (N - 2) * (B_FIRST ? LA : L) + L0;         // loads behind slab 0's, without the leading operand's
+    const auto s = slab_pair(ld, ga, k_begin, NB - 1, NB - 1, KT);
+    constexpr int BEHIND = (NB - 2) * (B_FIRST ? LA : L) + L0;         // loads behind slab 0's, without the A that leads
     if (A_LEADS && two_slabs) {
       const auto w = window<TWO_SLABS>(ld, ga, k_begin, -1, KT);
 #pragma unroll
       for (int d = 0; d < L0; ++d) load<TWO_SLABS>(ld, ga, w, d, NB - 1, wave);
       wait_vm_at_most<BEHIND>();                                      // slab 0 is there
     } else {
-      if constexpr (A_LEADS) ld.issue_a(ga, s, slab_a(N - 1), wave);
+      if constexpr (A_LEADS) ld.issue_a(ga, s, slab_a(NB - 1), wave);
       const auto w = window<WHOLE_RING>(ld, ga, k_begin, -1, KT);
 #pragma unroll
       for (int d = 0; d < L0; ++d) load<WHOLE_RING>(ld, ga, w, d, U - 1, wave);
-      wait_vm_at_most<BEHIND + (B_FIRST ? LXA : LX)>();
+      wait_vm_at_most<BEHIND + LX>();
     }
     barrier_keeping_loads_in_flight();
     static_for<NF>([&](auto r) { fetch<0, 0, 0, decltype(r)::value>(); });
@@ -1866,7 +1859,7 @@ struct MmaPipe {
   __device__ __forceinline__ void step(const Ld& ld, const GemmArgs& ga, int k_begin, int kt, int KT, int wave,
                                        f32x4 (&acc)[C::MI][C::NI], Hook&& before_wait) {
     constexpr int RA = MODE == TWO_SLABS ? NB : NA;
-    constexpr int VM = (N - 2) * L + (MODE == TWO_SLABS ? 0 : LX) + VM_EXTRA;
+    constexpr int VM = (NB - 2) * L + (MODE == TWO_SLABS ? 0 : LX) + VM_EXTRA;
     // (the slab's offset goes into the loads' scalar operand: should the compiler ever take the loop
     // counter for a value that may differ between lanes, it would wrap every load into a loop over lanes)
     kt = __builtin_amdgcn_readfirstlane(kt);
@@ -1882,10 +1875,10 @@ struct MmaPipe {
         constexpr int mi = g / C::NI, ni = G < 64 || mi % 2 == 0 ? g % C::NI : C::NI - 1 - g % C::NI;
         if constexpr (LAST && g == BAR_AT) {
           // slab kt+1 is there (this wave's part, then everyone's); this slab has been read by all
-          if constexpr (B_FIRST && S < N - 2) {
-            // (slabs 0 .. N-2 were requested as all of B, then all of A: behind slab kt+1's are the A parts of the
+          if constexpr (B_FIRST && S < NB - 2) {
+            // (slabs 0 .. NB-2 were requested as all of B, then all of A: behind slab kt+1's are the A parts of the
             // later ones of those, and what was requested since)
-            if (kt == S) wait_vm_at_most<(N - 3 - S) * LA + LXA + (S + 1) * L + VM_EXTRA>();
+            if (kt == S) wait_vm_at_most<(NB - 3 - S) * LA + LX + (S + 1) * L + VM_EXTRA>();
             else wait_vm_at_most<VM>();
           } else {
             wait_vm_at_most<VM>();
@@ -2123,10 +2116,10 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
   gemm_tail<C, EPI, EDGE, false>(a, pool, tail_words->misc, tail_words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, added);
 }
 
-// The same kernel as a grid of resident workgroups, one per compute unit, each walking the block
+// The same kernel for reduce-scatter calls as a grid of resident workgroups, one per compute unit, each walking the block
 // sequence with the grid's stride (block b, b + grid, ...: the order of Sec. 4.1 is kept, in time
 // instead of in dispatch).
-template <class C, int EPI>
+template <class C>
 __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma_resident(const GemmArgs a_) {
   __shared__ __attribute__((aligned(1024))) unsigned char pool[C::POOL_BYTES];
   SharedWords* const words = reinterpret_cast<SharedWords*>(pool + C::WORDS_AT_TAIL);
@@ -2174,11 +2167,9 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma_resident(const 
     if (is_split && a.sk_share) part_started(a, tile, tid);
     pipe.run(ld, a, k_begin, KT, 0, wave, acc, false);
     wait_vm0_and_barrier();
-    if (EPI == EPI_RS) {
-      fill_lds_outs(a, words->outs, tid);
-      __syncthreads();
-    }
-    gemm_tail<C, EPI, false, true>(a, pool, words->misc, words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, false, vb);
+    fill_lds_outs(a, words->outs, tid);
+    __syncthreads();
+    gemm_tail<C, EPI_RS, false, true>(a, pool, words->misc, words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, false, vb);
     __syncthreads();      // the staging area and the shared words are the next block's
   }
 }

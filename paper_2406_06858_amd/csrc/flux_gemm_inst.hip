@@ -33,9 +33,9 @@ typedef TileCfg<FLUX_CFG_PARAMS, true> CfgNK;    // B as [N,K]
 // `edge`: the tile does not divide the shape (masked loads and stores).
 template <class Cfg, int EPI, bool WAIT>
 static hipError_t launch_one(int edge, const GemmArgs& a, int grid, hipStream_t s) {
-  if constexpr (!WAIT && Cfg::NB == 2 && Cfg::OCC == 1) {
+  if constexpr (EPI == EPI_RS && Cfg::NB == 2 && Cfg::OCC == 1) {
     if (a.persist_blocks > 0) {          // (only planned for shapes the tile divides)
-      hipLaunchKernelGGL((gemm_kernel_dma_resident<Cfg, EPI>), dim3(grid), dim3(Cfg::NT), 0, s, a);
+      hipLaunchKernelGGL(gemm_kernel_dma_resident<Cfg>, dim3(grid), dim3(Cfg::NT), 0, s, a);
       return hipGetLastError();
     }
   }
