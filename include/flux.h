@@ -460,7 +460,8 @@ typedef struct flux_trace_record {
   uint32_t reserved;
   uint64_t t_start;     /* kernel entry                                                          */
   uint64_t t_ready;     /* past the signal wait (AllGather; equals t_start otherwise)            */
-  uint64_t t_main_end;  /* main loop done                                                        */
+  uint64_t t_main_end;  /* main loop done; from t_ready, so with the reads of the peers in a tile of
+                           flux_gemm_rs that starts from their sum                               */
   uint64_t t_end;       /* epilogue (or K-part hand-over) done, stores acknowledged              */
 } flux_trace_record_t;
 int flux_trace_next_call(void* records, size_t bytes);

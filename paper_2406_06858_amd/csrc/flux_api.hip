@@ -379,7 +379,7 @@ static void plan_split(const flux_problem_t* p, int cfg, long long tiles, int kt
 // Estimated time of the GEMM under configuration `cfg`, in arbitrary units: rounds of the grid
 // over the chip's workgroup slots, times the tile's area, over the configuration's rate per slot
 // (from measurements of full grids: 256x256 = 1, 256x128 on three stages 0.84, 128x128 two per
-// CU 0.8 per CU).  A shape that the tile does not divide counts 0.7 of that.  Masked loads cost less (ag 4096x3584x8192 with 8
+// CU 0.8 per CU; with two slabs of A of 256x256, which have become faster since).  A shape that the tile does not divide counts 0.7 of that.  Masked loads cost less (ag 4096x3584x8192 with 8
 // rows, columns or K values less: 256x256 5 %, 256x128 7-15 %, 128x128 4-16 %), but with 0.93 in its place five of twelve drawn
 // shapes whose tile then changes are slower (1920x12288x3584 209 -> 237 us, 3456x6144x3584 204 -> 217) and four faster
 // (3968x8192x4608 263 -> 237, ag 5248x8192x1536 158 -> 143, ag 4224x3584x8192 246 -> 215): it stands in for what the
@@ -561,7 +561,8 @@ static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
       resident_shape(p, *pl)) {
     pl->resident = 1;
     // half a period: (main loop + epilogue of a tile on a compute unit that shares the memory with
-    // half of the others) / 2; 1.5 us per 64-deep K slab of a 256x256 tile, 33 GB/s per unit
+    // half of the others) / 2; 1.5 us per 64-deep K slab of a 256x256 tile (with two slabs of A in LDS; 1.05-1.2 with three, the delay
+    // not measured again), 33 GB/s per unit
     const double main_ticks = 150.0 * (double)kt;
     const double tile_bytes = (double)pl->bm * pl->bn *
         ((p->R - 1) * (p->partial_dtype == FLUX_F32 ? 4.0 : 2.0) + (p->out_dtype == FLUX_F32 ? 4.0 : 2.0));

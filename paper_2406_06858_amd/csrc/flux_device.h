@@ -498,9 +498,9 @@ constexpr int PEERS_FIRST_AREA = 128 * 128;      // smallest tile
 // Why: reading the peers takes a unit 32 us per 256x256 tile and 7 peers when half of the units do it, 44-50 when all do, and
 // the workgroups of a grid all reach the end of their tiles at about the same time.  With half of the tiles
 // (peers_first) reading their peers first, one half reads while the other multiplies, from the first tile on and whatever the number of
-// rounds.  us per call, 8 ranks, every tile's peers behind its main loop / half of them ahead: 4096x8192x3584 250 / 228, 4096x8192x1536
-// 166 / 143, 2048x8192x1024 73 / 61, 1024x8192x1024 41 / 34, 4096x12288x4608 444 / 414, 8192x12288x4608 846 / 834, 1496x5112x3400 87.4 / 85.5.
-// 16 ranks: 2048x8192x3584 172 / 144, 1024x8192x1536 71 / 56, 4096x8192x1536 261 / 209, 4096x4608x3584 233 / 219, 832x4608x1448 44 / 40.
+// rounds.  us per call, 8 ranks, every tile's peers behind its main loop / half of them ahead: 4096x8192x3584 256 / 224, 4096x8192x1536
+// 167 / 142, 2048x8192x1024 74 / 61, 1024x8192x1024 42 / 33, 4096x12288x4608 435 / 401, 8192x12288x4608 833 / 797, 1496x5112x3400 85.1 / 84.4.
+// 16 ranks: 2048x8192x3584 172 / 144, 1024x8192x1536 71 / 56, 4096x8192x1536 257 / 208, 4096x4608x3584 233 / 201, 832x4608x1448 44 / 38.
 // (Four passes' loads in flight instead of two: the same.)
 template <class C, bool EDGE, int NP>
 __device__ __forceinline__ void sum_peers_first(const GemmArgs& a, float* ep, f32x4 (&acc)[C::MI][C::NI], int m0, int n0, int lane, int wm, int wn) {
