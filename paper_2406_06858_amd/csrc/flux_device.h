@@ -417,7 +417,9 @@ __device__ __forceinline__ void epilogue_block(const GemmArgs& a, void* const* l
   const int cc = lane % CH, rl = lane / CH;
   // (A loop in the code too: unrolled, the ends of a 256x256 tile are 50 KB of instructions, and with the main loop they no longer fit
   // the instruction cache of 64 KB that two units share: us, unrolled / not, 4096x8192x3584 251 / 242.  On a resident grid, whose units are
-  // out of step, unrolled is faster: 8192x12288x1536 428 / 436; and so is it with small tiles, whose code fits: 128x256x256 fp32 5.9 / 6.1.)
+  // out of step, unrolled is faster: 8192x12288x1536 428 / 436; and so is it with small tiles, whose code fits: 128x256x256 fp32 5.9 / 6.1.
+  // Without peers to read: unrolled ahead in one round of tiles (ag 768x8192x1536 25.9 / 26.1, write-only 768x8192x1536 27.4 / 27.6), behind
+  // in several (write-only 5440x8192x1536 156 / 145, 5336x4608x6144 277 / 272).)
   constexpr int UNROLL = RESIDENT || C::BM * C::BN < 128 * 128 ? NIT / B : 1;
 #pragma unroll UNROLL
   for (int it0 = 0; it0 < NIT; it0 += B) {
