@@ -91,10 +91,12 @@ typedef enum { FLUX_OP_RS = 0, FLUX_OP_AG = 1 } flux_op_t;
                                         owner that never runs and is taken over by a workgroup that waits for
                                         it.  For tests of that take-over; costs time, never correctness. */
 
-#define FLUX_FLAG_AG_COPY_UPFRONT 0x200u /* flux_ag_gemm without a copy kernel: move every remote chunk before the
-                                        signal wait.  Without the flag a grid of several rounds moves only
-                                        the chunks its first round needs up front and carries the others
-                                        inside the first round's main loops (see flux_ag_deferred_tiles). */
+#define FLUX_FLAG_AG_COPY_UPFRONT 0x200u /* flux_ag_gemm without a copy kernel: move every remote chunk into A_agg before
+                                        the signal wait, each source being read once, and read A from there.
+                                        Without the flag most grids read A from the chunk sources, and of those
+                                        that do not, one of several rounds moves only the chunks its first
+                                        round needs up front and carries the others inside the first round's
+                                        main loops (see flux_ag_gemm, flux_ag_deferred_tiles). */
 
 #define FLUX_FLAG_NO_RESIDENT_GRID 0x100u /* flux_gemm_rs: always one workgroup per tile, dispatched by the hardware.
                                         Without the flag a grid of at least four rounds of 256x256 tiles with
@@ -192,7 +194,13 @@ int flux_gemm_rs_static(const flux_problem_t* p, const void* A, const void* B,
  * Who moves the remote chunks (communication tile by communication tile in `arrival_order`,
  * setting each tile's signal when it is complete) depends on the problem:
  *   - link_gbps == 0, copy_workgroups == 0, no FLUX_FLAG_COPY_MEMCPY (the default): no copy kernel
- *     is launched and copy_stream stays unused.  The first workgroups of the GEMM grid (as many as
+ *     is launched and copy_stream stays unused.  Every tile reads its rows of A from the chunk sources
+ *     and stores a share of them into A_agg on the way; nothing waits and the signals stay as they are
+ *     (a tile's rows have arrived when its loads have).  A source is read by every tile that needs it:
+ *     right for sources in this GPU's memory.
+ *     With FLUX_FLAG_AG_COPY_UPFRONT or FLUX_FLAG_AG_ABSENT_OWNERS, where a chunk (other than the local one in
+ *     its place) overlaps A_agg or C, and for tiles whose row of tiles is too short to share its rows out (fewer
+ *     than tile height / 32 tiles), A is gathered first.  The first workgroups of the GEMM grid (as many as
  *     run at once) share the pieces of the tiles out among themselves by index and move them
  *     before they look at their own signals; in a grid of several rounds they move only the chunks
  *     the first round reads that way and carry the others inside their main loops (see
@@ -409,8 +417,8 @@ int flux_split_plan(int op, const flux_problem_t* p, int32_t* full_tiles, int32_
 int32_t flux_rs_resident_grid(const flux_problem_t* p, uint32_t* delay_ticks);
 
 /*
- * How many of the (R-1) * comm_tiles_per_chunk remote communication tiles flux_ag_gemm (forms without a
- * copy kernel) has its first round of workgroups carry themselves instead of moving them before the
+ * How many of the (R-1) * comm_tiles_per_chunk remote communication tiles flux_ag_gemm, where it gathers A
+ * first and without a copy kernel, has its first round of workgroups carry themselves instead of moving them before the
  * signal wait (Sec. 3.2: tiles whose data has arrived compute while the rest is on its way): the last
  * that many tiles of the transfer order; all of them when link_gbps > 0.  0: everything is moved up
  * front, or a copy kernel moves it.  Host function.

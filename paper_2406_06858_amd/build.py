@@ -34,9 +34,10 @@ def _run(cmd):
 def build(verbose: bool = False, jobs: int | None = None) -> str:
     os.makedirs(OBJ, exist_ok=True)
     units = [(os.path.join(CSRC, "flux_api.hip"), os.path.join(OBJ, "flux_api.o"), [])]
-    for i in range(1, N_CFGS + 1):
-        units.append((os.path.join(CSRC, "flux_gemm_inst.hip"), os.path.join(OBJ, f"flux_gemm_cfg{i}.o"),
-                      [f"-DFLUX_CFG_ID={i}"]))
+    for i in range(1, N_CFGS + 1):           # (the largest tiles take longest and come first)
+        for nk in (0, 1):
+            units.append((os.path.join(CSRC, "flux_gemm_inst.hip"), os.path.join(OBJ, f"flux_gemm_cfg{i}_nk{nk}.o"),
+                          [f"-DFLUX_CFG_ID={i}", f"-DFLUX_B_NK={nk}"]))
     jobs = jobs or min(8, os.cpu_count() or 1, len(units))
 
     def compile_one(u):

@@ -12,10 +12,10 @@ namespace flux {
 
 // (not const: a const table of host function pointers would also be emitted for the device)
 CfgInfo g_cfgs[NUM_CFGS] = {
-    {256, 256, 64, 1, 2, launch_cfg1}, {256, 128, 64, 1, 3, launch_cfg2}, {128, 128, 64, 2, 2, launch_cfg3},
-    {64, 64, 64, 2, 2, launch_cfg4},   {64, 128, 64, 2, 2, launch_cfg5},  {32, 128, 64, 2, 2, launch_cfg6},
-    {64, 64, 64, 1, 6, launch_cfg7},   {32, 128, 64, 1, 6, launch_cfg8},  {64, 128, 64, 1, 4, launch_cfg9},
-    {64, 128, 64, 2, 3, launch_cfg10},
+    {256, 256, 64, 1, 2, {launch_cfg1_nk0, launch_cfg1_nk1}}, {256, 128, 64, 1, 3, {launch_cfg2_nk0, launch_cfg2_nk1}}, {128, 128, 64, 2, 2, {launch_cfg3_nk0, launch_cfg3_nk1}},
+    {64, 64, 64, 2, 2, {launch_cfg4_nk0, launch_cfg4_nk1}},   {64, 128, 64, 2, 2, {launch_cfg5_nk0, launch_cfg5_nk1}},  {32, 128, 64, 2, 2, {launch_cfg6_nk0, launch_cfg6_nk1}},
+    {64, 64, 64, 1, 6, {launch_cfg7_nk0, launch_cfg7_nk1}},   {32, 128, 64, 1, 6, {launch_cfg8_nk0, launch_cfg8_nk1}},  {64, 128, 64, 1, 4, {launch_cfg9_nk0, launch_cfg9_nk1}},
+    {64, 128, 64, 2, 3, {launch_cfg10_nk0, launch_cfg10_nk1}},
 };
 
 constexpr int N_CU = 256;                      // compute units of an MI355X
@@ -772,7 +772,7 @@ static int take_trace(const Plan& pl, flux_trace_record_t** out) {
 }
 
 // Fills in what depends on how the grid is launched.
-static int launch_gemm(const Plan& pl, int epi, int wait, GemmArgs& a, hipStream_t s) {
+static int launch_gemm(const Plan& pl, int epi, int pro, GemmArgs& a, hipStream_t s) {
   const int grid = pl.full_tiles + pl.split_tiles * pl.split_k;
   hipEvent_t e0 = g_prof_start, e1 = g_prof_stop;
   g_prof_start = g_prof_stop = nullptr;
@@ -791,12 +791,12 @@ static int launch_gemm(const Plan& pl, int epi, int wait, GemmArgs& a, hipStream
   const long long eighth = (long long)(pl.k_per_split / pl.bk) * pl.bm * pl.bn * 5 / (64 * 128);
   a.sk_share = !share ? 0 : pl.full_tiles > 0 ? (int32_t)SK_WAIT_TICKS : (int32_t)std::min<long long>(std::max<long long>(eighth, SK_START_TICKS), SK_WAIT_TICKS);
   if (e0) FLUX_HIP(hipEventRecord(e0, s));
-  if (pl.resident && epi == EPI_RS && !wait && a.write_only == 0) {
+  if (pl.resident && epi == EPI_RS && a.write_only == 0) {
     a.persist_blocks = grid;
     a.persist_delay_ticks = pl.resident_delay_ticks;
-    FLUX_HIP(g_cfgs[pl.cfg].launch(epi, wait, pl.edge, a, N_CU, s));
+    FLUX_HIP(g_cfgs[pl.cfg].launch[a.b_is_nk](epi, pro, pl.edge, a, N_CU, s));
   } else {
-    FLUX_HIP(g_cfgs[pl.cfg].launch(epi, wait, pl.edge, a, grid, s));
+    FLUX_HIP(g_cfgs[pl.cfg].launch[a.b_is_nk](epi, pro, pl.edge, a, grid, s));
   }
   if (e1) FLUX_HIP(hipEventRecord(e1, s));
   return FLUX_OK;
@@ -1118,7 +1118,7 @@ int gemm_rs_planned(const flux_problem_t* p, const Plan& pl, const void* A, cons
   if (!write_only && p->R > 1 && p->partial_dtype == FLUX_BF16 && p->out_dtype == FLUX_BF16 && pl.bm * pl.bn >= PEERS_FIRST_AREA &&
       !resident_shape(p, pl))
     a.tm.peers_first = a.S % pl.bm == 0 && a.S >= 2 * pl.bm ? 2 : 1;
-  return launch_gemm(pl, EPI_RS, 0, a, s);
+  return launch_gemm(pl, EPI_RS, PRO_NONE, a, s);
 }
 
 }  // namespace flux
@@ -1231,6 +1231,13 @@ int flux_ag_gemm(const flux_problem_t* p, const void* const* A_chunks, void* A_a
   const bool local_in_grid = local_away && pl.copy_self && pl.pace_ticks == 0 && p->R > 1 && !(all_cut && chunk_elems * 2 > (6u << 20)) &&
                              !overlap(A_chunks[p->rank], chunk_elems * 2, A_agg, agg_bytes) &&
                              !overlap(A_chunks[p->rank], chunk_elems * 2, C, c_bytes);
+  // Nothing has to wait for the gathered matrix where the grid can read A from the chunk sources (GatherOut: 7-25 % of a call): nobody asks
+  // for another transfer, a row of tiles is long enough to store its rows, and no source lies in what the grid writes while it reads.
+  bool from_chunks = pl.copy_self && pl.pace_ticks == 0 && p->R > 1 && gather_fits(pl.bm, pl.tiles_n) &&
+                     !(p->flags & (FLUX_FLAG_AG_ABSENT_OWNERS | FLUX_FLAG_AG_COPY_UPFRONT));
+  for (int r = 0; r < p->R && from_chunks; ++r)
+    if (r != p->rank || local_away)
+      from_chunks = !overlap(A_chunks[r], chunk_elems * 2, A_agg, agg_bytes) && !overlap(A_chunks[r], chunk_elems * 2, C, c_bytes);
   if (pl.copy_help && p->R > 1) {
     a.copy_pieces = pl.copy_pieces;
     a.copy_driver_wgs = pl.copy_self ? 0 : pl.copy_wgs;
@@ -1273,6 +1280,10 @@ int flux_ag_gemm(const flux_problem_t* p, const void* const* A_chunks, void* A_a
     if (st != FLUX_OK) return st;
   }
 
+  if (from_chunks) {
+    a.gather_local = local_away;
+    return launch_gemm(pl, EPI_PLAIN, PRO_CHUNKS, a, cs);
+  }
   // local chunk (its signal is preset, so it must be in place before the kernel starts)
   if (local_away && !local_in_grid) {
     int self = p->rank;
@@ -1281,7 +1292,7 @@ int flux_ag_gemm(const flux_problem_t* p, const void* const* A_chunks, void* A_a
   }
   if (!driver_form) {
     // nothing runs beside the GEMM grid: no fork, no join
-    return launch_gemm(pl, EPI_PLAIN, 1, a, cs);
+    return launch_gemm(pl, EPI_PLAIN, PRO_WAIT, a, cs);
   }
   // fork: the copy driver may start once everything queued so far on compute_stream is done
   FLUX_HIP(hipEventRecord(ev_fork, cs));
@@ -1303,7 +1314,7 @@ int flux_ag_gemm(const flux_problem_t* p, const void* const* A_chunks, void* A_a
     st = launch_copy(p, pl, A_chunks, A_agg, order, p->R - 1, true, signals, workspace, call_id, xs);
     if (st != FLUX_OK) return st;
   }
-  st = launch_gemm(pl, EPI_PLAIN, 1, a, cs);
+  st = launch_gemm(pl, EPI_PLAIN, PRO_WAIT, a, cs);
   if (st != FLUX_OK) return st;
   // join: compute_stream continues only after the copy driver has finished too (the signals
   // were already put back by the last workgroup past its wait)
@@ -1358,7 +1369,7 @@ int flux_gemm_ref_unfused(int op, int phases, const flux_problem_t* p, const voi
     if (do_gemm) {
       if (!A || !aligned16(A)) return FLUX_ERR_INVALID_ARG;
       a.A = static_cast<const __bf16*>(A);
-      st = launch_gemm(pl, EPI_PLAIN, 0, a, s);
+      st = launch_gemm(pl, EPI_PLAIN, PRO_NONE, a, s);
       if (st != FLUX_OK) return st;
     }
     if (do_comm) {
@@ -1402,7 +1413,7 @@ int flux_gemm_ref_unfused(int op, int phases, const flux_problem_t* p, const voi
   }
   if (do_gemm) {
     a.A = static_cast<const __bf16*>(A_agg);
-    st = launch_gemm(pl, EPI_PLAIN, 0, a, s);
+    st = launch_gemm(pl, EPI_PLAIN, PRO_NONE, a, s);
     if (st != FLUX_OK) return st;
   }
   return FLUX_OK;
@@ -1505,7 +1516,7 @@ int flux_gemm_ref_chunked(int op, const flux_problem_t* p, const void* A, const 
       const int slice = (p->rank + d) % R;
       g.A = static_cast<const __bf16*>(A) + (size_t)slice * S * pitch_a(p);
       g.C = static_cast<unsigned char*>(C) + (size_t)slice * S * pitch_c(p) * out_size;
-      st = launch_gemm(plq, EPI_PLAIN, 0, g, cs);
+      st = launch_gemm(plq, EPI_PLAIN, PRO_NONE, g, cs);
       if (st != FLUX_OK) return st;
       FLUX_HIP(hipEventRecord(ev[slice], cs));
       FLUX_HIP(hipStreamWaitEvent(xs, ev[slice], 0));
@@ -1549,7 +1560,7 @@ int flux_gemm_ref_chunked(int op, const flux_problem_t* p, const void* A, const 
     if (i >= 0) FLUX_HIP(hipStreamWaitEvent(cs, ev[c], 0));
     g.A = agg + (size_t)c * S * pitch_a(p);
     g.C = static_cast<unsigned char*>(C) + (size_t)c * S * pitch_c(p) * out_size;
-    st = launch_gemm(plq, EPI_PLAIN, 0, g, cs);
+    st = launch_gemm(plq, EPI_PLAIN, PRO_NONE, g, cs);
     if (st != FLUX_OK) return st;
   }
   return FLUX_OK;

@@ -80,6 +80,9 @@ __host__ __device__ inline void tile_coord(const TileMap& tm, const uint16_t* m_
 }
 
 enum : int { EPI_PLAIN = 0, EPI_RS = 1 };
+// What a kernel does about A ahead of its main loop: nothing; wait for the signals of its rows of the gathered matrix (Alg. 2);
+// or read A from the chunk sources themselves, and move the chunks into the gathered matrix beside its products.
+enum : int { PRO_NONE = 0, PRO_WAIT = 1, PRO_CHUNKS = 2 };
 
 // Kernel arguments.  A workgroup's first fetches from the argument block miss the scalar cache one
 // 64-byte line after the other, a quarter of a microsecond each, before its first load can be
@@ -150,6 +153,7 @@ struct GemmArgs {
   // ... and with copy_pace_ticks != 0 they stand for a link: the i-th tile of the transfer order is
   // counted in no earlier than (i + 1) * copy_pace_ticks (100 MHz ticks) after the kernel started
   unsigned long long copy_pace_ticks;
+  int32_t gather_local;      // A read from the chunk sources (see GatherOut): the rank's own chunk, too, lies in a buffer of its own
   // ---- split-K hand-over, reduce-scatter epilogue ----
   float* sk_partials;             // [split_k][split_tiles][BM*BN] fp32
   uint32_t* sk_counters;          // [tiles]
@@ -1526,7 +1530,12 @@ struct Slabs {
   int ka, kb;
 };
 
-template <class C, bool EDGE>
+// CHUNKS: row i of A is row i % S of chunk source i / S, so every lane has a pointer per load of a slab (its rows of a tile lie in
+// different chunks); a lane with nothing to fetch reads zero_vec instead.  Two additions per load, between the MFMAs: the main loop
+// alone takes what it takes on a gathered matrix through buffer loads (4096x3584x8192 170 us, plain GEMM 173; with masks, 3000 rows, 166 / 160).
+static __device__ const uint4 zero_vec = {0u, 0u, 0u, 0u};
+
+template <class C, bool EDGE, bool CHUNKS = false>
 struct DmaLoader {
   static constexpr int NW = C::NT / 64;
   static constexpr int A_RPI = 8;                              // A rows per instruction (1 KiB of 128-byte rows)
@@ -1555,6 +1564,7 @@ struct DmaLoader {
   // EDGE: how many of this lane's loads of A (and of an [N,K] B) have a row, the k of its vector in a slab, and the k of
   // its first vector of a [K,N] B (out of reach for a lane past the last column)
   int lim_a, lim_b, k_vec, k_row;
+  uint64_t rows[CHUNKS ? A_INSTR : 1];
   static constexpr uint32_t OUTSIDE = 0xfffffff0u;      // a matrix has fewer than 2^31 elements
 
   __device__ __forceinline__ void init(const GemmArgs& a, int m0, int n0, int wave, int lane) {
@@ -1581,6 +1591,26 @@ struct DmaLoader {
     }
   }
 
+  // The lane's pointers into the chunk sources: `src` holds the one of chunk j in lane j.
+  __device__ __forceinline__ void init_rows(const GemmArgs& a, uint64_t src, int m0, int wave, int lane) {
+    static_assert(CHUNKS);
+    const int sp = lane % C::A_SLOTS;
+    const int chunk0 = m0 / a.S, in0 = m0 - chunk0 * a.S;              // (uniform)
+    const float per_row = __builtin_amdgcn_rcpf((float)a.S);
+#pragma unroll
+    for (int d = 0; d < A_INSTR; ++d) {
+      const int row = A_RPI * wave + lane / C::A_SLOTS + d * A_RPI * NW;
+      const int x = in0 + row;
+      // x / S: a tile touches one or two chunks, or x is below 2 * BM (exact in fp32: x + 1/2 is no closer than 1/2 to a multiple of S)
+      const int q = a.S >= C::BM ? (x >= a.S ? 1 : 0) : (int)(((float)x + 0.5f) * per_row);
+      const int chunk = chunk0 + q < a.R ? chunk0 + q : a.R - 1;        // (rows past the last are not loaded)
+      const uint64_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(chunk * 4, (int)(uint32_t)src);
+      const uint64_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(chunk * 4, (int)(uint32_t)(src >> 32));
+      const uint32_t pitch = !a.gather_local && chunk == a.rank ? K2 : (uint32_t)a.K * 2u;       // (in place: the gathered matrix's)
+      rows[d] = (lo | hi << 32) + (uint64_t)(uint32_t)(x - q * a.S) * pitch + ((uint32_t)(sp ^ swz_a<C::A_SLOTS>(row)) << 4);
+    }
+  }
+
   __device__ __forceinline__ Slabs slabs(const GemmArgs& a, bool there_a, int ka, bool there_b, int kb) const {
     return Slabs{__builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.A), 0, (int)(there_a ? bytes_a : 0u), 0x00027000),
                  __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.B), 0, (int)(there_b ? bytes_b : 0u), 0x00027000), ka, kb};
@@ -1588,6 +1618,15 @@ struct DmaLoader {
 
   // the d-th (constant after unrolling) of this wave's loads of A / of B, into `slab` in LDS
   __device__ __forceinline__ void load_a(int d, const GemmArgs& a, const Slabs& s, unsigned char* slab, int wave) const {
+    if constexpr (CHUNKS) {
+      // (a slab past the end of K: the last one again, into a place that nobody reads)
+      const int ka = !EDGE && s.ka > a.K - C::BK ? a.K - C::BK : s.ka;
+      uint64_t p = rows[d] + (uint32_t)ka * 2u;
+      if (EDGE && !(d < (k_vec < a.K - s.ka ? lim_a : 0))) p = reinterpret_cast<uint64_t>(&zero_vec);
+      typedef const __attribute__((address_space(1))) void* global_ptr;
+      __builtin_amdgcn_global_load_lds((global_ptr)p, (lds_void_t*)(slab + (d * NW + wave) * 1024), 16, 0, 0);
+      return;
+    }
     const uint32_t v = !EDGE || d < (k_vec < a.K - s.ka ? lim_a : 0) ? voff_a : OUTSIDE;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(s.ra, (lds_void_t*)(slab + (d * NW + wave) * 1024), 16, (int)v,
                                              (int)((uint32_t)s.ka * 2u + (uint32_t)(d * A_RPI * NW) * K2), 0, 0);
@@ -1670,6 +1709,48 @@ __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
+// The gathered matrix of a grid that reads A from the chunk sources: nothing waits for it, it is a result like C, and it is stored
+// out of the slabs of A that lie in LDS for the products.  The tiles of a row of tiles share its rows out among themselves: the nt-th
+// stores rows [nt * share, (nt + 1) * share) of every slab, one vector per thread (gather_fits; the parts of a tile cut along K each
+// their slabs).
+// us per pass, gathered first and waited for / read from the sources: 4 layers of 8x3584x8192 86.0 / 70.0 (the wait was 6.5 of a call's
+// 17.6 us in the kernel), 4 of 200x3584x8192 150 / 119, 4096x3584x8192 192 / 177, 3000x3584x8192 180 / 173, 8192x4608x12288 694 / 657.  The stores
+// are 2-3 % of that (left out: 70.0 / 68.9, 183 / 179, 175.5 / 170, 676 / 664 on a slower box); moving the chunks through registers, a load and a
+// store per slab, costs 7 % (a load that goes to memory holds up the operand loads behind it: 184, 175, 680).
+constexpr int GATHER_ROWS = 32;      // rows of a slab that 256 threads store
+__host__ __device__ constexpr bool gather_fits(int bm, int tiles_n) { return (long long)GATHER_ROWS * tiles_n >= bm; }
+template <class C, bool EDGE>
+struct GatherOut {
+  __amdgpu_buffer_rsrc_t r;
+  uint32_t from, to;                 // this lane's vector: in a slab in LDS, in the gathered matrix
+  int k_vec;
+  u32x4 v;
+  static_assert(C::NT == 256 && C::A_SLOTS == 8, "32 rows of 8 vectors");
+  static constexpr uint32_t OUTSIDE = 0xfffffff0u;
+
+  __device__ __forceinline__ void init(const GemmArgs& a, const unsigned char* slab0, int m0, int nt, int tid) {
+    const int share = (C::BM + a.tm.tiles_n - 1) / a.tm.tiles_n;
+    const int slot = tid % C::A_SLOTS, row = nt * share + tid / C::A_SLOTS, gm = m0 + row;
+    const bool in_place = !a.gather_local && gm >= a.rank * a.S && gm < (a.rank + 1) * a.S;
+    const bool mine = tid / C::A_SLOTS < share && row < C::BM && gm < a.M && !in_place;
+    from = lds_address(slab0) + (uint32_t)(row & (C::BM - 1)) * (C::BK * 2) + ((uint32_t)(slot ^ swz_a<C::A_SLOTS>(row)) << 4);
+    to = mine ? (uint32_t)gm * ((uint32_t)a.lda * 2u) + (uint32_t)slot * 16u : OUTSIDE;
+    k_vec = slot * 8;
+    const unsigned bytes = ((unsigned)(a.M - 1) * (unsigned)a.lda + (unsigned)a.K) * 2u;
+    r = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(a.A), 0, (int)bytes, 0x00027000);
+  }
+  template <int SLAB>
+  __device__ __forceinline__ void read() {
+    constexpr int OFF = SLAB * C::A_BYTES;
+    const uint32_t at = OFF >= 65536 ? from + 65536u : from;
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(at), "n"(OFF % 65536));
+  }
+  __device__ __forceinline__ void settle() { asm volatile("" : "+v"(v)); }
+  __device__ __forceinline__ void write(const GemmArgs& a, int k) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)(!EDGE || k_vec < a.K - k ? to : OUTSIDE), k * 2, 2);
+  }
+};
+
 // The main loop of every kernel: K-slabs out of an LDS ring of NA slabs of A and NB of B, every memory instruction placed
 // by hand between the MFMAs.  A wave issues in order and (with the large tile) has its SIMD to itself, so what it
 // issues in a burst or waits for is time its matrix core stands still:
@@ -1703,9 +1784,9 @@ __device__ __forceinline__ void static_for(F&& f) {
 // B_FIRST (signal wait): B, which does not depend on a gathered A, is requested before the wait for all of the first
 // slabs, A after it.  Without, the first slabs are requested one after the other, so that slab 0 does not have to
 // wait for the B of the others (64 x 8192 x 3584: 0.5 us of 23).
-template <class C, bool B_FIRST, bool EDGE>
+template <class C, bool B_FIRST, bool EDGE, bool CHUNKS = false>
 struct MmaPipe {
-  typedef DmaLoader<C, EDGE> Ld;
+  typedef DmaLoader<C, EDGE, CHUNKS> Ld;
   static constexpr int NA = C::NA, NB = C::NB;
   static constexpr bool A_LEADS = NA > NB;                           // by one slab
   static constexpr int U = NA == NB ? NB : NA * NB;                   // slabs after which both rings are where they were
@@ -1739,6 +1820,7 @@ struct MmaPipe {
   typedef std::conditional_t<C::B_NK, bf16x8, FragHalves> FragB;
   bf16x8 af[2][C::MI];
   FragB bf[2][C::NI];
+  GatherOut<C, EDGE> out;            // CHUNKS
 
   __device__ __forceinline__ unsigned char* slab_a(int i) const { return pool + i * C::A_BYTES; }
   __device__ __forceinline__ unsigned char* slab_b(int i) const { return pool + NA * C::A_BYTES + i * C::B_BYTES; }
@@ -1870,6 +1952,7 @@ struct MmaPipe {
       constexpr int ks = decltype(ks_)::value;
       constexpr bool LAST = ks == KS - 1;
       if constexpr (LAST) before_wait();
+      if constexpr (CHUNKS && !LAST) out.template read<S % RA>();
       static_for<G>([&](auto g_) {
         constexpr int g = decltype(g_)::value;
         // (with the large tile every second row of MFMAs goes backwards: it begins with the B fragment that the row before ended with,
@@ -1888,6 +1971,8 @@ struct MmaPipe {
           barrier_keeping_loads_in_flight();
         }
         mfma_in_place(acc[mi][ni], af[ks][mi], frag_value(bf[ks][ni]));
+        // (behind the barrier: a store is acknowledged in any order with loads, so the next wait must not find it too young)
+        if constexpr (CHUNKS && LAST && g == BAR_AT) out.write(ga, k_begin + kt * C::BK);
         // this MFMA's loads [d0, d1) and fragment reads [r0, r1)
         constexpr int d0 = loads_before(LAST ? g : G + g), d1 = loads_before((LAST ? g : G + g) + 1);
 #pragma unroll
@@ -1905,6 +1990,7 @@ struct MmaPipe {
         __builtin_amdgcn_sched_barrier(0);
       });
       wait_lds_reads(af[1 - ks], bf[1 - ks]);
+      if constexpr (CHUNKS && !LAST) out.settle();
     });
   }
 
@@ -1976,8 +2062,9 @@ struct WarmA {
 };
 
 // EDGE: the tile does not divide M, N or K (see DmaLoader; the epilogue leaves rows and columns past the end out).
-template <class C, int EPI, bool WAIT, bool EDGE>
+template <class C, int EPI, int PRO, bool EDGE>
 __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs a) {
+  constexpr bool WAIT = PRO == PRO_WAIT, CHUNKS = PRO == PRO_CHUNKS;
   // the transfer inside the main loop (SideCopy) is asked of the kernel with two slabs of B and one workgroup per unit
   constexpr bool CARRY = WAIT && !EDGE && C::NB == 2 && C::OCC == 1;
   __shared__ __attribute__((aligned(1024))) unsigned char pool[C::POOL_BYTES];
@@ -1987,6 +2074,12 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
+  uint64_t src = 0;
+  if constexpr (CHUNKS) {
+    // the chunk sources, one per lane: asked for at once, beside the fetch of everything else (the struct is the kernel's only argument)
+    typedef const uint64_t __attribute__((address_space(4))) * SrcPtr;
+    src = reinterpret_cast<const uint64_t*>((const unsigned char*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(GemmArgs, outs))[lane & (FLUX_MAX_RANKS - 1)];
+  }
 
   int tile, split;
   bool is_split;
@@ -2001,11 +2094,15 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
   const int k_end = (is_split && k_begin + a.k_per_split < a.K) ? k_begin + a.k_per_split : a.K;
   const int KT = (k_end - k_begin + C::BK - 1) / C::BK;
 
-  DmaLoader<C, EDGE> ld;
+  typedef MmaPipe<C, WAIT, EDGE, CHUNKS> Pipe;
+  typename Pipe::Ld ld;
   ld.init(a, m0, n0, wave, lane);
-  typedef MmaPipe<C, WAIT, EDGE> Pipe;
   Pipe pipe;
   pipe.init(pool, wm, wn, lane);
+  if constexpr (CHUNKS) {
+    ld.init_rows(a, src, m0, wave, lane);
+    pipe.out.init(a, pipe.slab_a(0), m0, nt, tid);
+  }
   SideCopy side;
   if constexpr (WAIT) {
     const int m1 = (!EDGE || m0 + C::BM < a.M) ? m0 + C::BM : a.M;
@@ -2057,7 +2154,7 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
 
   bool carries = false;
   if constexpr (CARRY) carries = side.pending();      // (uniform)
-  constexpr bool WARM = !WAIT && C::BM == 256 && C::BN == 128;
+  constexpr bool WARM = PRO == PRO_NONE && C::BM == 256 && C::BN == 128;
   WarmA warm;
   if constexpr (WARM) warm.ask(a, ld.bytes_a, tid);
   pipe.start(ld, a, k_begin, KT, wave, carries);

@@ -1,5 +1,5 @@
-// Instantiates the GEMM kernel family for ONE tile configuration; compiled once per
-// configuration with -DFLUX_CFG_ID=<id> so the configurations build in parallel.
+// Instantiates the GEMM kernel family for ONE tile configuration and layout of B; compiled once for each
+// with -DFLUX_CFG_ID=<id> -DFLUX_B_NK=<0|1> so that they build in parallel.
 #include "flux_internal.h"
 
 namespace flux {
@@ -27,11 +27,10 @@ namespace flux {
 #else
 #error "FLUX_CFG_ID must be 1..10"
 #endif
-typedef TileCfg<FLUX_CFG_PARAMS> Cfg;            // B as [K,N]
-typedef TileCfg<FLUX_CFG_PARAMS, true> CfgNK;    // B as [N,K]
+typedef TileCfg<FLUX_CFG_PARAMS, FLUX_B_NK> Cfg;     // B as [K,N] / [N,K]
 
 // `edge`: the tile does not divide the shape (masked loads and stores).
-template <class Cfg, int EPI, bool WAIT>
+template <int EPI, int PRO>
 static hipError_t launch_one(int edge, const GemmArgs& a, int grid, hipStream_t s) {
   if constexpr (EPI == EPI_RS && Cfg::NB == 2 && Cfg::OCC == 1) {
     if (a.persist_blocks > 0) {          // (only planned for shapes the tile divides)
@@ -39,29 +38,19 @@ static hipError_t launch_one(int edge, const GemmArgs& a, int grid, hipStream_t 
       return hipGetLastError();
     }
   }
-  if (edge) hipLaunchKernelGGL((gemm_kernel_dma<Cfg, EPI, WAIT, true>), dim3(grid), dim3(Cfg::NT), 0, s, a);
-  else hipLaunchKernelGGL((gemm_kernel_dma<Cfg, EPI, WAIT, false>), dim3(grid), dim3(Cfg::NT), 0, s, a);
+  if (edge) hipLaunchKernelGGL((gemm_kernel_dma<Cfg, EPI, PRO, true>), dim3(grid), dim3(Cfg::NT), 0, s, a);
+  else hipLaunchKernelGGL((gemm_kernel_dma<Cfg, EPI, PRO, false>), dim3(grid), dim3(Cfg::NT), 0, s, a);
   return hipGetLastError();
 }
 
-template <class Cfg>
-static hipError_t launch_layout(int epi, int wait, int edge, const GemmArgs& a, int grid, hipStream_t s) {
-  if (epi == EPI_RS) return launch_one<Cfg, EPI_RS, false>(edge, a, grid, s);
-  if (wait) return launch_one<Cfg, EPI_PLAIN, true>(edge, a, grid, s);
-  return launch_one<Cfg, EPI_PLAIN, false>(edge, a, grid, s);
-}
+#define FLUX_CAT2(a, b, c, d) a##b##c##d
+#define FLUX_CAT(a, b, c, d) FLUX_CAT2(a, b, c, d)
 
-#define FLUX_CAT2(a, b) a##b
-#define FLUX_CAT(a, b) FLUX_CAT2(a, b)
-
-hipError_t FLUX_CAT(launch_cfg, FLUX_CFG_ID)(int epi, int wait, int edge, const GemmArgs& a, int grid, hipStream_t s) {
-  // one set of kernels per layout of B
-  if (a.b_is_nk) return launch_layout<CfgNK>(epi, wait, edge, a, grid, s);
-  return launch_layout<Cfg>(epi, wait, edge, a, grid, s);
-}
-
-void FLUX_CAT(info_cfg, FLUX_CFG_ID)(int* bm, int* bn, int* bk) {
-  *bm = Cfg::BM; *bn = Cfg::BN; *bk = Cfg::BK;
+hipError_t FLUX_CAT(launch_cfg, FLUX_CFG_ID, _nk, FLUX_B_NK)(int epi, int pro, int edge, const GemmArgs& a, int grid, hipStream_t s) {
+  if (epi == EPI_RS) return launch_one<EPI_RS, PRO_NONE>(edge, a, grid, s);
+  if (pro == PRO_WAIT) return launch_one<EPI_PLAIN, PRO_WAIT>(edge, a, grid, s);
+  if (pro == PRO_CHUNKS) return launch_one<EPI_PLAIN, PRO_CHUNKS>(edge, a, grid, s);
+  return launch_one<EPI_PLAIN, PRO_NONE>(edge, a, grid, s);
 }
 
 }  // namespace flux
