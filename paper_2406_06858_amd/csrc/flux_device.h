@@ -336,6 +336,16 @@ struct SharedWords {
   int misc[4];
 };
 
+// f(0), f(1), ... f(N-1) with the index as a compile-time constant.
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
 // MFMA shape: 16x16x32, the A fragment held over a row of MFMAs.  With random operands the chip runs at its power
 // limit, and this form takes less power than 32x32x16: MFMAs alone 2.0 against 1.75-1.8 PFLOP/s (2.4 for both on
 // zeros).  Holding B instead and changing A every time costs 25 % of the rate even on zeros.
@@ -404,13 +414,63 @@ __device__ __forceinline__ void make_peer_bufs(const GemmArgs& a, int m0, int n0
   }
 }
 
+// The peers' rows of a small whole tile, asked for ahead of its main loop and held in registers until its end: a small call is a
+// chain of memory round trips, and this one does not depend on the products.  NP peers (1, 3 or 7; absent ones read nothing, but cost
+// an issue slot each), where they fit ROOM vectors (with 14 instead of 6 the kernels of two workgroups per unit spill: 5.9 us -> 6.6).
+// us per call, peers behind the main loop / ahead of it: fp32, 2 ranks: 128x256x256 5.92 / 5.09, 64x512x512 8.21 / 6.69, 512x1024x256 9.00 /
+// 6.85; bf16: 2 ranks 2048x2048x1024 18.7 / 16.3, 4 ranks 512x3584x1536 14.7 / 13.7, 8 ranks 2048x1024x512 13.5 / 13.0; the other side:
+// 64x512x512 7.8 / 8.0, 2048x1024x2048 20.5 / 20.8.
+template <class C>
+struct EarlyPeers {
+  static constexpr int RPP = 512 / C::WTN;                 // rows per pass (see epilogue_block)
+  static constexpr int PASSES = C::WTM / RPP;
+  static constexpr bool SMALL = C::BM * C::BN < 128 * 128;
+  static constexpr int ROOM = C::OCC == 1 ? 28 : 6;        // 112 or 24 registers
+  u32x4 w[SMALL ? ROOM : 1];                               // pass by pass, peer by peer
+  template <int NP, bool PF32>
+  static constexpr __device__ int at(int pass, int j, int l) { return (pass * NP + j) * (PF32 ? 2 : 1) + l; }
+  template <int NP, bool PF32>
+  static constexpr bool fits() { return SMALL && PASSES * NP * (PF32 ? 2 : 1) <= ROOM; }
+
+  template <bool EDGE, int NP, bool PF32>
+  __device__ __forceinline__ int ask_as(const GemmArgs& a, int m0, int n0, int lane, int wm, int wn) {
+    if constexpr (fits<NP, PF32>()) {
+      PeerBufs pb;
+      make_peer_bufs(a, m0, n0, pb);
+      const int cc = lane % (C::WTN / 8), rl = lane / (C::WTN / 8);
+#pragma unroll
+      for (int t = 0; t < PASSES; ++t) {
+        const int row = wm * C::WTM + t * RPP + rl, col = wn * C::WTN + cc * 8;
+        const bool ok = !EDGE || (m0 + row < a.M && n0 + col < a.N);
+        const int voff = ok ? (int)(((uint32_t)row * (uint32_t)a.N + (uint32_t)col) * (PF32 ? 4u : 2u)) : (int)0x80000000;
+#pragma unroll
+        for (int j = 0; j < NP; ++j)
+#pragma unroll
+          for (int l = 0; l < (PF32 ? 2 : 1); ++l) w[at<NP, PF32>(t, j, l)] = __builtin_amdgcn_raw_buffer_load_b128(pb.r[j], voff + 16 * l, 0, 2);
+      }
+      return NP;
+    }
+    return 0;
+  }
+  // Peers asked for: 1, 3, 7 or none.  (Uniform.)
+  template <bool EDGE>
+  __device__ __forceinline__ int ask(const GemmArgs& a, bool is_split, int m0, int n0, int lane, int wm, int wn) {
+    if (is_split || a.write_only) return 0;
+    if (a.R == 2) return a.partial_f32 ? ask_as<EDGE, 1, true>(a, m0, n0, lane, wm, wn) : ask_as<EDGE, 1, false>(a, m0, n0, lane, wm, wn);
+    if (a.R <= 4) return a.partial_f32 ? ask_as<EDGE, 3, true>(a, m0, n0, lane, wm, wn) : ask_as<EDGE, 3, false>(a, m0, n0, lane, wm, wn);
+    if (a.R <= 8) return a.partial_f32 ? ask_as<EDGE, 7, true>(a, m0, n0, lane, wm, wn) : ask_as<EDGE, 7, false>(a, m0, n0, lane, wm, wn);
+    return 0;
+  }
+};
+
 // One 32-row block of a wave's tile, already transposed into `ep`: every lane takes 8 consecutive
 // columns of a row per pass.  With the reduce-scatter epilogue the peer loads of BATCH passes are
 // issued together before any of them is used (PF32: fp32 partials, two 16-byte loads per peer);
 // the peers are added in ascending rank order.
-template <class C, int EPI, bool EDGE, bool PF32, int BATCH, int NP, bool RESIDENT>
+// EARLY: they are in `early` already, from pass `pass0` on.
+template <class C, int EPI, bool EDGE, bool PF32, int BATCH, int NP, bool RESIDENT, bool EARLY>
 __device__ __forceinline__ void epilogue_block(const GemmArgs& a, void* const* lds_outs, const float* ep, const PeerBufs& pb,
-                                               int row_base, int col_base, int m0, int n0, int lane) {
+                                               int row_base, int col_base, int m0, int n0, int lane, const EarlyPeers<C>& early, int pass0) {
   constexpr int CH = C::WTN / 8;          // 8-column pieces per row of the wave tile
   constexpr int RPP = 64 / CH;            // rows per pass
   constexpr int NIT = 32 / RPP;
@@ -440,7 +500,10 @@ __device__ __forceinline__ void epilogue_block(const GemmArgs& a, void* const* l
 #pragma unroll
         for (int j = 0; j < NP; ++j)
 #pragma unroll
-          for (int l = 0; l < LPP; ++l) w[b][j][l] = __builtin_amdgcn_raw_buffer_load_b128(pb.r[j], voff + 16 * l, 0, NT_HINT);
+          for (int l = 0; l < LPP; ++l) {
+            if constexpr (EARLY) w[b][j][l] = early.w[EarlyPeers<C>::template at<NP, PF32>(pass0 + it0 + b, j, l)];
+            else w[b][j][l] = __builtin_amdgcn_raw_buffer_load_b128(pb.r[j], voff + 16 * l, 0, NT_HINT);
+          }
       }
     }
 #pragma unroll
@@ -484,15 +547,16 @@ __device__ __forceinline__ void stage_rows32(float* ep, const f32x4 (&acc)[C::MI
 }
 
 // The whole epilogue of one wave: its accumulators pass through LDS 32 rows at a time.
-template <class C, int EPI, bool EDGE, bool PF32, int BATCH, int NP, bool RESIDENT>
+template <class C, int EPI, bool EDGE, bool PF32, int BATCH, int NP, bool RESIDENT, bool EARLY = false>
 __device__ __forceinline__ void epilogue_all(const GemmArgs& a, void* const* lds_outs, float* ep, f32x4 (&acc)[C::MI][C::NI],
-                                             int m0, int n0, int lane, int wm, int wn) {
+                                             int m0, int n0, int lane, int wm, int wn, const EarlyPeers<C>& early = {}) {
   PeerBufs pb;
-  if (EPI == EPI_RS) make_peer_bufs(a, m0, n0, pb);
+  if (EPI == EPI_RS && NP > 0 && !EARLY) make_peer_bufs(a, m0, n0, pb);
 #pragma unroll
   for (int mb = 0; mb < C::WTM / 32; ++mb) {
     stage_rows32<C>(ep, acc, mb, lane);
-    epilogue_block<C, EPI, EDGE, PF32, BATCH, NP, RESIDENT>(a, lds_outs, ep, pb, wm * C::WTM + mb * 32, wn * C::WTN, m0, n0, lane);
+    epilogue_block<C, EPI, EDGE, PF32, BATCH, NP, RESIDENT, EARLY>(a, lds_outs, ep, pb, wm * C::WTM + mb * 32, wn * C::WTN, m0, n0, lane,
+                                                                   early, mb * (32 / EarlyPeers<C>::RPP));
     __builtin_amdgcn_wave_barrier();
   }
 }
@@ -510,7 +574,7 @@ constexpr int PEERS_FIRST_AREA = 128 * 128;      // smallest tile
 // (Four passes' loads in flight instead of two: the same.)
 template <class C, bool EDGE, int NP>
 __device__ __forceinline__ void sum_peers_first(const GemmArgs& a, float* ep, f32x4 (&acc)[C::MI][C::NI], int m0, int n0, int lane, int wm, int wn) {
-  constexpr int CH = C::WTN / 8, RPP = 64 / CH, NIT = 32 / RPP, B = 2;
+  constexpr int CH = C::WTN / 8, RPP = 64 / CH, NIT = 32 / RPP, B = NP <= 3 ? 4 : 2;
   static_assert(NIT % B == 0);
   PeerBufs pb;
   make_peer_bufs(a, m0, n0, pb);
@@ -1360,10 +1424,13 @@ struct SharedFinish {
 // a tile park their partial sums, the last one adds them up) and the epilogue, in which the
 // accumulators pass through LDS once (per wave, 32 rows at a time) so that every lane ends up
 // with 8 consecutive columns of one row.  `smem` must hold C::EP_BYTES and is free to reuse.
-template <class C, int EPI, bool EDGE, bool RESIDENT>
+// MAX_NP: most peers there can be (a resident kernel is built for up to 4 ranks or for more: with the code of both in one kernel
+// 8192x12288x1536 of 8 ranks took 439 us instead of 422).
+template <class C, int EPI, bool EDGE, bool RESIDENT, int MAX_NP = FLUX_MAX_RANKS - 1>
 __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem, int* lds_misc, void* const* lds_outs,
                                           f32x4 (&acc)[C::MI][C::NI], int tile, int split, bool is_split,
-                                          int m0, int n0, int tid, int lane, int wave, int wm, int wn, bool peers_added, int vb = -1) {
+                                          int m0, int n0, int tid, int lane, int wave, int wm, int wn, bool peers_added,
+                                          const EarlyPeers<C>& early, int n_early, int vb = -1) {
   trace_stamp(a, TRACE_MAIN_END, vb);
   // ---- split-K: all but the last-arriving workgroup of a tile park their partial sums ----
   if (is_split) {
@@ -1397,7 +1464,10 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
       float* const ep = reinterpret_cast<float*>(smem) + wave * (32 * C::EP_STRIDE);
       bool finished;
       if (EPI != EPI_RS || a.write_only) finished = SharedFinish<C, EPI, EDGE, false, 0>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
-      else if (a.R <= 8) {
+      else if (a.R <= 4) {
+        if (a.partial_f32) finished = SharedFinish<C, EPI, EDGE, true, 3>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
+        else finished = SharedFinish<C, EPI, EDGE, false, 3>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
+      } else if (a.R <= 8) {
         if (a.partial_f32) finished = SharedFinish<C, EPI, EDGE, true, 7>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
         else finished = SharedFinish<C, EPI, EDGE, false, 7>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
       } else {
@@ -1475,13 +1545,32 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
   // ---- epilogue: registers -> LDS (per wave, 32 rows at a time) -> 8 columns per lane ----
   float* ep = reinterpret_cast<float*>(smem) + wave * (32 * C::EP_STRIDE);
   // (the dtype and rank-count tests stay outside the loop over blocks: inside it, the accumulators
-  // would no longer be kept in registers.  Up to 8 ranks, 7 peer loads per piece are issued, else 15:
-  // loads from absent peers return zeros but still cost an issue slot and four registers each.)
-  constexpr int NP_ALL = FLUX_MAX_RANKS - 1, NP_8 = 7;
+  // would no longer be kept in registers.  Up to 4 ranks, 3 peer loads per piece are issued, up to 8, 7, else 15:
+  // loads from absent peers return zeros but still cost an issue slot and four registers each: us, 7 / 3 of them, 2 ranks 4096x8192x1536
+  // 111.9 / 98.6, 4096x8192x3584 195 / 180, 1024x8192x1024 27.1 / 23.9, 512x12288x6144 92.2 / 87.7, 4 ranks 4096x8192x3584 211 / 189,
+  // 8192x12288x1536 351 / 317, 1496x5112x3400 72.5 / 70.5; fp32 partials 2 ranks 4096x8192x3584 225 / 218, 4 ranks 1496x5112x3400
+  // 84.7 / 83.8; the other side: fp32, 4 ranks 4096x8192x1536 187 / 192.)
+  constexpr int NP_ALL = FLUX_MAX_RANKS - 1, NP_8 = 7, NP_4 = 3;
   if (EPI == EPI_RS && a.write_only == 2) {
     epilogue_all_atomic<C, EDGE>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
   } else if (EPI != EPI_RS || a.write_only || peers_added) {
     epilogue_all<C, EPI, EDGE, false, 2, 0, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
+  } else if (EarlyPeers<C>::SMALL && n_early != 0) {
+    auto finish = [&](auto np_, auto pf32_) {
+      constexpr int NP = decltype(np_)::value;
+      constexpr bool PF32 = decltype(pf32_)::value;
+      if constexpr (EarlyPeers<C>::template fits<NP, PF32>())
+        if (n_early == NP && (a.partial_f32 != 0) == PF32) epilogue_all<C, EPI, EDGE, PF32, PF32 ? 1 : 2, NP, RESIDENT, true>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn, early);
+    };
+    static_for<2>([&](auto pf32_) {
+      constexpr std::bool_constant<decltype(pf32_)::value != 0> PF32;
+      finish(std::integral_constant<int, 1>{}, PF32);
+      finish(std::integral_constant<int, 3>{}, PF32);
+      finish(std::integral_constant<int, 7>{}, PF32);
+    });
+  } else if (RESIDENT ? MAX_NP == NP_4 : a.R <= NP_4 + 1) {
+    if (a.partial_f32) epilogue_all<C, EPI, EDGE, true, 1, NP_4, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
+    else epilogue_all<C, EPI, EDGE, false, 4, NP_4, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
   } else if (a.R <= NP_8 + 1) {
     if (a.partial_f32) epilogue_all<C, EPI, EDGE, true, 1, NP_8, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
     else epilogue_all<C, EPI, EDGE, false, 2, NP_8, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
@@ -1697,16 +1786,6 @@ __device__ __forceinline__ void barrier_keeping_loads_in_flight() {
 __device__ __forceinline__ void wait_vm0_and_barrier() {
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's LDS-bound loads have landed
   __syncthreads();
-}
-
-// f(0), f(1), ... f(N-1) with the index as a compile-time constant.
-template <class F, int... I>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
 // The gathered matrix of a grid that reads A from the chunk sources: nothing waits for it, it is a result like C, and it is stored
@@ -2146,11 +2225,16 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
   if constexpr (EPI == EPI_RS && C::BM * C::BN >= PEERS_FIRST_AREA) {
     if (added) {
       float* const ep = reinterpret_cast<float*>(pool) + wave * (32 * C::EP_STRIDE);
-      if (a.R <= 8) sum_peers_first<C, EDGE, 7>(a, ep, acc, m0, n0, lane, wm, wn);
+      if (a.R <= 4) sum_peers_first<C, EDGE, 3>(a, ep, acc, m0, n0, lane, wm, wn);
+      else if (a.R <= 8) sum_peers_first<C, EDGE, 7>(a, ep, acc, m0, n0, lane, wm, wn);
       else sum_peers_first<C, EDGE, FLUX_MAX_RANKS - 1>(a, ep, acc, m0, n0, lane, wm, wn);
       __syncthreads();      // (the ring takes the place of other waves' staging areas)
     }
   }
+
+  EarlyPeers<C> early;
+  int n_early = 0;
+  if constexpr (EPI == EPI_RS && EarlyPeers<C>::SMALL) n_early = early.template ask<EDGE>(a, is_split, m0, n0, lane, wm, wn);
 
   bool carries = false;
   if constexpr (CARRY) carries = side.pending();      // (uniform)
@@ -2212,13 +2296,13 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
     fill_lds_outs(a, tail_words->outs, tid);
     __syncthreads();
   }
-  gemm_tail<C, EPI, EDGE, false>(a, pool, tail_words->misc, tail_words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, added);
+  gemm_tail<C, EPI, EDGE, false>(a, pool, tail_words->misc, tail_words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, added, early, n_early);
 }
 
 // The same kernel for reduce-scatter calls as a grid of resident workgroups, one per compute unit, each walking the block
 // sequence with the grid's stride (block b, b + grid, ...: the order of Sec. 4.1 is kept, in time
 // instead of in dispatch).
-template <class C>
+template <class C, int MAX_NP>
 __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma_resident(const GemmArgs a_) {
   __shared__ __attribute__((aligned(1024))) unsigned char pool[C::POOL_BYTES];
   SharedWords* const words = reinterpret_cast<SharedWords*>(pool + C::WORDS_AT_TAIL);
@@ -2268,7 +2352,7 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma_resident(const 
     wait_vm0_and_barrier();
     fill_lds_outs(a, words->outs, tid);
     __syncthreads();
-    gemm_tail<C, EPI_RS, false, true>(a, pool, words->misc, words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, false, vb);
+    gemm_tail<C, EPI_RS, false, true, MAX_NP>(a, pool, words->misc, words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, false, {}, 0, vb);
     __syncthreads();      // the staging area and the shared words are the next block's
   }
 }

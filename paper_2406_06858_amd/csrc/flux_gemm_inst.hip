@@ -34,7 +34,8 @@ template <int EPI, int PRO>
 static hipError_t launch_one(int edge, const GemmArgs& a, int grid, hipStream_t s) {
   if constexpr (EPI == EPI_RS && Cfg::NB == 2 && Cfg::OCC == 1) {
     if (a.persist_blocks > 0) {          // (only planned for shapes the tile divides)
-      hipLaunchKernelGGL(gemm_kernel_dma_resident<Cfg>, dim3(grid), dim3(Cfg::NT), 0, s, a);
+      if (a.R <= 4) hipLaunchKernelGGL((gemm_kernel_dma_resident<Cfg, 3>), dim3(grid), dim3(Cfg::NT), 0, s, a);
+      else hipLaunchKernelGGL((gemm_kernel_dma_resident<Cfg, FLUX_MAX_RANKS - 1>), dim3(grid), dim3(Cfg::NT), 0, s, a);
       return hipGetLastError();
     }
   }
