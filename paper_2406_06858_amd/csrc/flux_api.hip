@@ -19,7 +19,8 @@ CfgInfo g_cfgs[NUM_CFGS] = {
 };
 
 constexpr int N_CU = 256;                      // compute units of an MI355X
-constexpr int N_XCD = 8;                       // accelerator dies of an MI355X, one L2 each
+constexpr int N_XCD = 8;                       // accelerator dies of an MI355X, one L2 each ...
+constexpr unsigned long long L2_BYTES = 4ull << 20;      // ... of 4 MB
 constexpr unsigned long long DEFAULT_TIMEOUT_TICKS = 1000000000ull;   // 10 s at 100 MHz
 
 static thread_local int g_last_hip_error = 0;
@@ -790,13 +791,24 @@ static int launch_gemm(const Plan& pl, int epi, int pro, GemmArgs& a, hipStream_
   // (an eighth of a main loop: about 0.4 us per slab of a 64x128 tile; the parts of a last round start one by one)
   const long long eighth = (long long)(pl.k_per_split / pl.bk) * pl.bm * pl.bn * 5 / (64 * 128);
   a.sk_share = !share ? 0 : pl.full_tiles > 0 ? (int32_t)SK_WAIT_TICKS : (int32_t)std::min<long long>(std::max<long long>(eighth, SK_START_TICKS), SK_WAIT_TICKS);
+  // B is streamed (a non-temporal load) where the tiles of a column read it at about the same time through one L2: one row of tiles, or two
+  // whose columns go to the same die (TileCoord deals runs of a band to the dies).  us per pass, kept / streamed, one row: 4 layers of ag
+  // 8x3584x8192 69.6 / 66.0, ag 200x3584x8192 116.1 / 112.9, rs 64x8192x3584 81.7 / 78.8, 2 layers of rs 256x12288x6144 144.3 / 140.6; two:
+  // 4 layers of rs 128x8192x3584 107.0 / 100.6, rs 400x8192x8192 85.5 / 80.5, ag 512x6144x12288 96.6 / 91.2, rs 512x12288x6144 97.0 / 95.3, rs
+  // 512x8192x3584 53.7 / 53.9; the other side, two rows on different dies: 4 layers of ag 128x3584x8192 115.0 / 125.5, more rows: rs
+  // 512x3584x1536 16.6 / 21.9, 4 layers of rs 200x8192x3584 (64x128 tiles) 118.8 / 142.5, rs 2048x4608x1536 57.9 / 64.2.
+  // Not where neighbouring tiles share lines (rows of B that are no whole lines: rs 24x880x8592 52.9 / 63.3), nor a B that the L2s hold from
+  // one call to the next (64x256x4608 46.0 / 50.0).
+  const bool b_lines = reinterpret_cast<uintptr_t>(a.B) % 128 == 0 && (size_t)a.ldb * 2 % 128 == 0;
+  const bool b_large = (unsigned long long)a.N * a.K * 2 > (unsigned long long)N_XCD * L2_BYTES;
+  const int b_once = b_lines && b_large && (pl.tiles_m == 1 || (pl.tiles_m == 2 && pl.n_xcd > 1 && pl.tiles_n % pl.n_xcd == 0));
   if (e0) FLUX_HIP(hipEventRecord(e0, s));
   if (pl.resident && epi == EPI_RS && a.write_only == 0) {
     a.persist_blocks = grid;
     a.persist_delay_ticks = pl.resident_delay_ticks;
-    FLUX_HIP(g_cfgs[pl.cfg].launch[a.b_is_nk](epi, pro, pl.edge, a, N_CU, s));
+    FLUX_HIP(g_cfgs[pl.cfg].launch[a.b_is_nk](epi, pro, pl.edge, b_once, a, N_CU, s));
   } else {
-    FLUX_HIP(g_cfgs[pl.cfg].launch[a.b_is_nk](epi, pro, pl.edge, a, grid, s));
+    FLUX_HIP(g_cfgs[pl.cfg].launch[a.b_is_nk](epi, pro, pl.edge, b_once, a, grid, s));
   }
   if (e1) FLUX_HIP(hipEventRecord(e1, s));
   return FLUX_OK;

@@ -394,6 +394,37 @@ __device__ __forceinline__ void store_row8(const GemmArgs& a, void* const* lds_o
   }
 }
 
+// ... and 4 of them (fp32 partials: see piece_col).
+template <int EPI, bool FLAT>
+__device__ __forceinline__ void store_row4(const GemmArgs& a, void* const* lds_outs, int gm, int gn, const float* v) {
+  const bool through = EPI == EPI_RS && a.tile_ready != nullptr;
+  void* base = a.C;
+  size_t o = (size_t)gm * a.ldc + gn;
+  if (EPI == EPI_RS) {
+    const int r = gm / a.S;
+    base = lds_outs[r];
+    o = (size_t)(gm - r * a.S) * a.ldc + gn;
+  }
+  if (a.out_f32) {
+    st_out16<FLAT>(static_cast<float*>(base) + o, make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])), through);
+  } else {
+    // (fp32 partials are never asked for with counted-in tiles, whose peers are not read: no write-through form)
+    typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_;
+    typedef __attribute__((address_space(1))) u32x2_ global_u32x2;
+    const u32x2_ d = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+    __builtin_nontemporal_store(d, (global_u32x2*)(static_cast<__bf16*>(base) + o));
+  }
+}
+
+// A lane's 8 columns of a row of a wave's tile: 8 in a row; of fp32 partials twice 4, so that an instruction reads (and writes) 16 bytes a
+// lane without gaps: whole lines of 64 columns or more.  With 8 in a row an instruction takes every second 16 bytes of twice as many lines, and
+// streamed lines were fetched twice: us, 8 in a row / twice 4, fp32, 8 ranks 512x1024x256 14.2 / 11.0, 512x12288x6144 126 / 113, 1496x5112x3400
+// 124 / 115, 4096x4608x1536 189 / 176, 16 ranks 4096x4608x3584 386 / 344, 2 ranks 8192x6144x1536 203 / 181.
+template <class C, bool PF32>
+__device__ __forceinline__ int piece_col(int cc, int half) {
+  return PF32 ? (half * (C::WTN / 8) + cc) * 4 : cc * 8 + half * 4;
+}
+
 // The peer partials of one tile as buffer resources based at the tile's origin (Reduce of Alg. 1
 // reads them).  `a.peers` holds the R-1 peers in ascending rank order; a resource past that has no
 // records, so its loads return zeros and every lane runs the same straight-line code: seven loads
@@ -416,7 +447,7 @@ __device__ __forceinline__ void make_peer_bufs(const GemmArgs& a, int m0, int n0
 
 // The peers' rows of a small whole tile, asked for ahead of its main loop and held in registers until its end: a small call is a
 // chain of memory round trips, and this one does not depend on the products.  NP peers (1, 3 or 7; absent ones read nothing, but cost
-// an issue slot each), where they fit ROOM vectors (with 14 instead of 6 the kernels of two workgroups per unit spill: 5.9 us -> 6.6).
+// an issue slot each; not streamed: half a line each, us, streamed / kept, 8 ranks 512x1024x256 9.0 / 7.6, 32x8192x384 9.4 / 7.9), where they fit ROOM vectors (with 14 instead of 6 the kernels of two workgroups per unit spill: 5.9 us -> 6.6).
 // us per call, peers behind the main loop / ahead of it: fp32, 2 ranks: 128x256x256 5.92 / 5.09, 64x512x512 8.21 / 6.69, 512x1024x256 9.00 /
 // 6.85; bf16: 2 ranks 2048x2048x1024 18.7 / 16.3, 4 ranks 512x3584x1536 14.7 / 13.7, 8 ranks 2048x1024x512 13.5 / 13.0; the other side:
 // 64x512x512 7.8 / 8.0, 2048x1024x2048 20.5 / 20.8.
@@ -440,13 +471,15 @@ struct EarlyPeers {
       const int cc = lane % (C::WTN / 8), rl = lane / (C::WTN / 8);
 #pragma unroll
       for (int t = 0; t < PASSES; ++t) {
-        const int row = wm * C::WTM + t * RPP + rl, col = wn * C::WTN + cc * 8;
-        const bool ok = !EDGE || (m0 + row < a.M && n0 + col < a.N);
-        const int voff = ok ? (int)(((uint32_t)row * (uint32_t)a.N + (uint32_t)col) * (PF32 ? 4u : 2u)) : (int)0x80000000;
+        const int row = wm * C::WTM + t * RPP + rl;
 #pragma unroll
-        for (int j = 0; j < NP; ++j)
+        for (int l = 0; l < (PF32 ? 2 : 1); ++l) {
+          const int col = wn * C::WTN + piece_col<C, PF32>(cc, l);
+          const bool ok = !EDGE || (m0 + row < a.M && n0 + col < a.N);
+          const int voff = ok ? (int)(((uint32_t)row * (uint32_t)a.N + (uint32_t)col) * (PF32 ? 4u : 2u)) : (int)0x80000000;
 #pragma unroll
-          for (int l = 0; l < (PF32 ? 2 : 1); ++l) w[at<NP, PF32>(t, j, l)] = __builtin_amdgcn_raw_buffer_load_b128(pb.r[j], voff + 16 * l, 0, 2);
+          for (int j = 0; j < NP; ++j) w[at<NP, PF32>(t, j, l)] = __builtin_amdgcn_raw_buffer_load_b128(pb.r[j], voff, 0, 0);
+        }
       }
       return NP;
     }
@@ -476,7 +509,8 @@ __device__ __forceinline__ void epilogue_block(const GemmArgs& a, void* const* l
   constexpr int NIT = 32 / RPP;
   constexpr int B = BATCH < NIT ? BATCH : NIT;
   constexpr int LPP = PF32 ? 2 : 1;
-  constexpr int NT_HINT = 2;              // cache policy: streamed once, do not keep
+  // cache policy: streamed, not kept; but where an instruction reads half a line of a row, another wave has the other half
+  constexpr int CACHE = C::WTN < 64 ? 0 : 2;
   static_assert(NIT % B == 0, "batch must divide the passes");
   const int cc = lane % CH, rl = lane / CH;
   // (A loop in the code too: unrolled, the ends of a 256x256 tile are 50 KB of instructions, and with the main loop they no longer fit
@@ -488,29 +522,30 @@ __device__ __forceinline__ void epilogue_block(const GemmArgs& a, void* const* l
 #pragma unroll UNROLL
   for (int it0 = 0; it0 < NIT; it0 += B) {
     u32x4 w[B][NP > 0 ? NP : 1][LPP];
-    bool ok[B];
+    bool ok[B][LPP];
 #pragma unroll
     for (int b = 0; b < B; ++b) {
-      const int row = row_base + (it0 + b) * RPP + rl, col = col_base + cc * 8;
-      ok[b] = !EDGE || (m0 + row < a.M && n0 + col < a.N);
-      if (EPI == EPI_RS) {
+      const int row = row_base + (it0 + b) * RPP + rl;
+#pragma unroll
+      for (int l = 0; l < LPP; ++l) {
+        const int col = col_base + piece_col<C, PF32>(cc, l);
+        ok[b][l] = !EDGE || (m0 + row < a.M && n0 + col < a.N);
+        if (EPI != EPI_RS) continue;
         // a lane outside the matrix gets an offset past the records: zeros, no memory access
         // (tile-relative: row < BM <= 256 and N < 2^21, so the byte offset stays below 2^31)
-        const int voff = ok[b] ? (int)(((uint32_t)row * (uint32_t)a.N + (uint32_t)col) * (PF32 ? 4u : 2u)) : (int)0x80000000;
+        const int voff = ok[b][l] ? (int)(((uint32_t)row * (uint32_t)a.N + (uint32_t)col) * (PF32 ? 4u : 2u)) : (int)0x80000000;
 #pragma unroll
-        for (int j = 0; j < NP; ++j)
-#pragma unroll
-          for (int l = 0; l < LPP; ++l) {
-            if constexpr (EARLY) w[b][j][l] = early.w[EarlyPeers<C>::template at<NP, PF32>(pass0 + it0 + b, j, l)];
-            else w[b][j][l] = __builtin_amdgcn_raw_buffer_load_b128(pb.r[j], voff + 16 * l, 0, NT_HINT);
-          }
+        for (int j = 0; j < NP; ++j) {
+          if constexpr (EARLY) w[b][j][l] = early.w[EarlyPeers<C>::template at<NP, PF32>(pass0 + it0 + b, j, l)];
+          else w[b][j][l] = __builtin_amdgcn_raw_buffer_load_b128(pb.r[j], voff, 0, CACHE);
+        }
       }
     }
 #pragma unroll
     for (int b = 0; b < B; ++b) {
       const int r = (it0 + b) * RPP + rl;
-      const float4 x = *reinterpret_cast<const float4*>(ep + r * C::EP_STRIDE + cc * 8);
-      const float4 y = *reinterpret_cast<const float4*>(ep + r * C::EP_STRIDE + cc * 8 + 4);
+      const float4 x = *reinterpret_cast<const float4*>(ep + r * C::EP_STRIDE + piece_col<C, PF32>(cc, 0));
+      const float4 y = *reinterpret_cast<const float4*>(ep + r * C::EP_STRIDE + piece_col<C, PF32>(cc, 1));
       float v[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
       if (EPI == EPI_RS) {
 #pragma unroll
@@ -524,7 +559,13 @@ __device__ __forceinline__ void epilogue_block(const GemmArgs& a, void* const* l
           }
         }
       }
-      if (ok[b]) store_row8<EPI, NP != 0>(a, lds_outs, m0 + row_base + r, n0 + col_base + cc * 8, v);
+      if constexpr (PF32) {
+#pragma unroll
+        for (int l = 0; l < LPP; ++l)
+          if (ok[b][l]) store_row4<EPI, NP != 0>(a, lds_outs, m0 + row_base + r, n0 + col_base + piece_col<C, PF32>(cc, l), v + 4 * l);
+      } else if (ok[b][0]) {
+        store_row8<EPI, NP != 0>(a, lds_outs, m0 + row_base + r, n0 + col_base + cc * 8, v);
+      }
     }
     // one batch of peer loads in flight at a time: left alone, the scheduler hoists the loads of
     // later batches up here too and has to spill accumulators to make room for them
@@ -1291,6 +1332,8 @@ struct SharedFinish {
     row = (w / C::WAVES_N) * C::WTM + (v / (C::NI / 2)) * 16 + lane / 4;
     col = (w % C::WAVES_N) * C::WTN + (v % (C::NI / 2)) * 32 + (lane % 4) * 8;
   }
+  // (Not streamed: a block's rows are 64 bytes of bf16, half a line, and another wave takes the other half.  us, streamed / kept: 4
+  // layers of 64x8192x3584 with 7 peers 78.8 / 74.5.)
   static __device__ __forceinline__ void load_peers(const GemmArgs& a, const PeerBufs& pb, int u, int m0, int n0, int lane, u32x4 (&w)[NPA][LPP]) {
     int row, col;
     place(u, lane, row, col);
@@ -1299,7 +1342,7 @@ struct SharedFinish {
 #pragma unroll
     for (int j = 0; j < NP; ++j)
 #pragma unroll
-      for (int l = 0; l < LPP; ++l) w[j][l] = __builtin_amdgcn_raw_buffer_load_b128(pb.r[j], voff + 16 * l, 0, 2);
+      for (int l = 0; l < LPP; ++l) w[j][l] = __builtin_amdgcn_raw_buffer_load_b128(pb.r[j], voff + 16 * l, 0, 0);
   }
   static __device__ __forceinline__ void block(const GemmArgs& a, void* const* lds_outs, float* ep, int u, int st, int m0, int n0, int lane,
                                                const u32x4 (&w)[NPA][LPP]) {
@@ -1424,14 +1467,15 @@ struct SharedFinish {
 // a tile park their partial sums, the last one adds them up) and the epilogue, in which the
 // accumulators pass through LDS once (per wave, 32 rows at a time) so that every lane ends up
 // with 8 consecutive columns of one row.  `smem` must hold C::EP_BYTES and is free to reuse.
-// MAX_NP: most peers there can be (a resident kernel is built for up to 4 ranks or for more: with the code of both in one kernel
+// MAX_NP: most peers there can be; PARTIALS: their type, 0 bf16, 1 fp32, -1 either (a resident kernel is built for up to 4 ranks or for more, and a type: with the code of both in one kernel
 // 8192x12288x1536 of 8 ranks took 439 us instead of 422).
-template <class C, int EPI, bool EDGE, bool RESIDENT, int MAX_NP = FLUX_MAX_RANKS - 1>
+template <class C, int EPI, bool EDGE, bool RESIDENT, int MAX_NP = FLUX_MAX_RANKS - 1, int PARTIALS = -1>
 __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem, int* lds_misc, void* const* lds_outs,
                                           f32x4 (&acc)[C::MI][C::NI], int tile, int split, bool is_split,
                                           int m0, int n0, int tid, int lane, int wave, int wm, int wn, bool peers_added,
                                           const EarlyPeers<C>& early, int n_early, int vb = -1) {
   trace_stamp(a, TRACE_MAIN_END, vb);
+  const bool partial_f32 = PARTIALS < 0 ? a.partial_f32 != 0 : PARTIALS != 0;
   // ---- split-K: all but the last-arriving workgroup of a tile park their partial sums ----
   if (is_split) {
     const int st = tile - a.full_tiles;            // index among the split tiles
@@ -1465,13 +1509,13 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
       bool finished;
       if (EPI != EPI_RS || a.write_only) finished = SharedFinish<C, EPI, EDGE, false, 0>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
       else if (a.R <= 4) {
-        if (a.partial_f32) finished = SharedFinish<C, EPI, EDGE, true, 3>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
+        if (partial_f32) finished = SharedFinish<C, EPI, EDGE, true, 3>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
         else finished = SharedFinish<C, EPI, EDGE, false, 3>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
       } else if (a.R <= 8) {
-        if (a.partial_f32) finished = SharedFinish<C, EPI, EDGE, true, 7>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
+        if (partial_f32) finished = SharedFinish<C, EPI, EDGE, true, 7>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
         else finished = SharedFinish<C, EPI, EDGE, false, 7>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
       } else {
-        if (a.partial_f32) finished = SharedFinish<C, EPI, EDGE, true, 15>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
+        if (partial_f32) finished = SharedFinish<C, EPI, EDGE, true, 15>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
         else finished = SharedFinish<C, EPI, EDGE, false, 15>::run(a, lds_misc, lds_outs, ep, tile, split, m0, n0, tid, lane, wave);
       }
       if (finished) {
@@ -1548,8 +1592,8 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
   // would no longer be kept in registers.  Up to 4 ranks, 3 peer loads per piece are issued, up to 8, 7, else 15:
   // loads from absent peers return zeros but still cost an issue slot and four registers each: us, 7 / 3 of them, 2 ranks 4096x8192x1536
   // 111.9 / 98.6, 4096x8192x3584 195 / 180, 1024x8192x1024 27.1 / 23.9, 512x12288x6144 92.2 / 87.7, 4 ranks 4096x8192x3584 211 / 189,
-  // 8192x12288x1536 351 / 317, 1496x5112x3400 72.5 / 70.5; fp32 partials 2 ranks 4096x8192x3584 225 / 218, 4 ranks 1496x5112x3400
-  // 84.7 / 83.8; the other side: fp32, 4 ranks 4096x8192x1536 187 / 192.)
+  // 8192x12288x1536 351 / 317, 1496x5112x3400 72.5 / 70.5; fp32 partials 2 ranks 4096x8192x3584 225 / 218.
+  // Of 3 peers four passes' loads are out together: fp32, 2 ranks 8192x6144x1536 220 / 186 / 181 us with one / two / four.)
   constexpr int NP_ALL = FLUX_MAX_RANKS - 1, NP_8 = 7, NP_4 = 3;
   if (EPI == EPI_RS && a.write_only == 2) {
     epilogue_all_atomic<C, EDGE>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
@@ -1560,7 +1604,7 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
       constexpr int NP = decltype(np_)::value;
       constexpr bool PF32 = decltype(pf32_)::value;
       if constexpr (EarlyPeers<C>::template fits<NP, PF32>())
-        if (n_early == NP && (a.partial_f32 != 0) == PF32) epilogue_all<C, EPI, EDGE, PF32, PF32 ? 1 : 2, NP, RESIDENT, true>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn, early);
+        if (n_early == NP && partial_f32 == PF32) epilogue_all<C, EPI, EDGE, PF32, PF32 ? 1 : 2, NP, RESIDENT, true>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn, early);
     };
     static_for<2>([&](auto pf32_) {
       constexpr std::bool_constant<decltype(pf32_)::value != 0> PF32;
@@ -1569,13 +1613,13 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
       finish(std::integral_constant<int, 7>{}, PF32);
     });
   } else if (RESIDENT ? MAX_NP == NP_4 : a.R <= NP_4 + 1) {
-    if (a.partial_f32) epilogue_all<C, EPI, EDGE, true, 1, NP_4, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
+    if (partial_f32) epilogue_all<C, EPI, EDGE, true, 4, NP_4, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
     else epilogue_all<C, EPI, EDGE, false, 4, NP_4, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
   } else if (a.R <= NP_8 + 1) {
-    if (a.partial_f32) epilogue_all<C, EPI, EDGE, true, 1, NP_8, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
+    if (partial_f32) epilogue_all<C, EPI, EDGE, true, 1, NP_8, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
     else epilogue_all<C, EPI, EDGE, false, 2, NP_8, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
   } else {
-    if (a.partial_f32) epilogue_all<C, EPI, EDGE, true, 1, NP_ALL, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
+    if (partial_f32) epilogue_all<C, EPI, EDGE, true, 1, NP_ALL, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
     else epilogue_all<C, EPI, EDGE, false, 1, NP_ALL, RESIDENT>(a, lds_outs, ep, acc, m0, n0, lane, wm, wn);
   }
   if (EPI == EPI_RS && a.tile_ready != nullptr) {
@@ -1624,7 +1668,8 @@ struct Slabs {
 // alone takes what it takes on a gathered matrix through buffer loads (4096x3584x8192 170 us, plain GEMM 173; with masks, 3000 rows, 166 / 160).
 static __device__ const uint4 zero_vec = {0u, 0u, 0u, 0u};
 
-template <class C, bool EDGE, bool CHUNKS = false>
+// B_ONCE: B is streamed (see b_once in the host's plan).
+template <class C, bool EDGE, bool CHUNKS = false, bool B_ONCE = false>
 struct DmaLoader {
   static constexpr int NW = C::NT / 64;
   static constexpr int A_RPI = 8;                              // A rows per instruction (1 KiB of 128-byte rows)
@@ -1722,8 +1767,11 @@ struct DmaLoader {
   }
   __device__ __forceinline__ void load_b(int d, const GemmArgs& a, const Slabs& s, unsigned char* slab) const {
     const bool in = !EDGE || (C::B_NK ? d < (k_vec < a.K - s.kb ? lim_b : 0) : k_row < a.K - s.kb - instr_row(d));
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(s.rb, (lds_void_t*)(slab + instr_row(d) * (1024 / RPI) + lds_b), 16, (int)(in ? voff_b : OUTSIDE),
-                                             (int)(C::B_NK ? (uint32_t)s.kb * 2u + (uint32_t)instr_row(d) * N2 : (uint32_t)(s.kb + instr_row(d)) * N2), 0, 0);
+    lds_void_t* const to = (lds_void_t*)(slab + instr_row(d) * (1024 / RPI) + lds_b);
+    const int v = (int)(in ? voff_b : OUTSIDE);
+    const int from = (int)(C::B_NK ? (uint32_t)s.kb * 2u + (uint32_t)instr_row(d) * N2 : (uint32_t)(s.kb + instr_row(d)) * N2);
+    if constexpr (B_ONCE) __builtin_amdgcn_raw_ptr_buffer_load_lds(s.rb, to, 16, v, from, 0, 2);
+    else __builtin_amdgcn_raw_ptr_buffer_load_lds(s.rb, to, 16, v, from, 0, 0);
   }
 
   // this wave's loads of the A part / the B part of one K-slab
@@ -1863,9 +1911,9 @@ struct GatherOut {
 // B_FIRST (signal wait): B, which does not depend on a gathered A, is requested before the wait for all of the first
 // slabs, A after it.  Without, the first slabs are requested one after the other, so that slab 0 does not have to
 // wait for the B of the others (64 x 8192 x 3584: 0.5 us of 23).
-template <class C, bool B_FIRST, bool EDGE, bool CHUNKS = false>
+template <class C, bool B_FIRST, bool EDGE, bool CHUNKS = false, bool B_ONCE = false>
 struct MmaPipe {
-  typedef DmaLoader<C, EDGE, CHUNKS> Ld;
+  typedef DmaLoader<C, EDGE, CHUNKS, B_ONCE> Ld;
   static constexpr int NA = C::NA, NB = C::NB;
   static constexpr bool A_LEADS = NA > NB;                           // by one slab
   static constexpr int U = NA == NB ? NB : NA * NB;                   // slabs after which both rings are where they were
@@ -2141,7 +2189,7 @@ struct WarmA {
 };
 
 // EDGE: the tile does not divide M, N or K (see DmaLoader; the epilogue leaves rows and columns past the end out).
-template <class C, int EPI, int PRO, bool EDGE>
+template <class C, int EPI, int PRO, bool EDGE, bool B_ONCE>
 __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs a) {
   constexpr bool WAIT = PRO == PRO_WAIT, CHUNKS = PRO == PRO_CHUNKS;
   // the transfer inside the main loop (SideCopy) is asked of the kernel with two slabs of B and one workgroup per unit
@@ -2173,7 +2221,7 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
   const int k_end = (is_split && k_begin + a.k_per_split < a.K) ? k_begin + a.k_per_split : a.K;
   const int KT = (k_end - k_begin + C::BK - 1) / C::BK;
 
-  typedef MmaPipe<C, WAIT, EDGE, CHUNKS> Pipe;
+  typedef MmaPipe<C, WAIT, EDGE, CHUNKS, B_ONCE> Pipe;
   typename Pipe::Ld ld;
   ld.init(a, m0, n0, wave, lane);
   Pipe pipe;
@@ -2302,7 +2350,7 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
 // The same kernel for reduce-scatter calls as a grid of resident workgroups, one per compute unit, each walking the block
 // sequence with the grid's stride (block b, b + grid, ...: the order of Sec. 4.1 is kept, in time
 // instead of in dispatch).
-template <class C, int MAX_NP>
+template <class C, int MAX_NP, int PARTIALS>
 __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma_resident(const GemmArgs a_) {
   __shared__ __attribute__((aligned(1024))) unsigned char pool[C::POOL_BYTES];
   SharedWords* const words = reinterpret_cast<SharedWords*>(pool + C::WORDS_AT_TAIL);
@@ -2352,7 +2400,7 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma_resident(const 
     wait_vm0_and_barrier();
     fill_lds_outs(a, words->outs, tid);
     __syncthreads();
-    gemm_tail<C, EPI_RS, false, true, MAX_NP>(a, pool, words->misc, words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, false, {}, 0, vb);
+    gemm_tail<C, EPI_RS, false, true, MAX_NP, PARTIALS>(a, pool, words->misc, words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, false, {}, 0, vb);
     __syncthreads();      // the staging area and the shared words are the next block's
   }
 }

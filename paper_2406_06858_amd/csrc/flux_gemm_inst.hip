@@ -29,29 +29,45 @@ namespace flux {
 #endif
 typedef TileCfg<FLUX_CFG_PARAMS, FLUX_B_NK> Cfg;     // B as [K,N] / [N,K]
 
+// Tiles that few rows over large weights take have a second set of kernels, which stream B.
+constexpr bool MAYBE_ONCE = FLUX_CFG_ID == 2 || FLUX_CFG_ID == 7 || FLUX_CFG_ID == 8 || FLUX_CFG_ID == 9;
+
+template <int EPI, int PRO, bool B_ONCE>
+static hipError_t launch_two(int edge, const GemmArgs& a, int grid, hipStream_t s) {
+  if (edge) hipLaunchKernelGGL((gemm_kernel_dma<Cfg, EPI, PRO, true, B_ONCE>), dim3(grid), dim3(Cfg::NT), 0, s, a);
+  else hipLaunchKernelGGL((gemm_kernel_dma<Cfg, EPI, PRO, false, B_ONCE>), dim3(grid), dim3(Cfg::NT), 0, s, a);
+  return hipGetLastError();
+}
+
+template <int PARTIALS>
+static hipError_t launch_resident(const GemmArgs& a, int grid, hipStream_t s) {
+  if (a.R <= 4) hipLaunchKernelGGL((gemm_kernel_dma_resident<Cfg, 3, PARTIALS>), dim3(grid), dim3(Cfg::NT), 0, s, a);
+  else hipLaunchKernelGGL((gemm_kernel_dma_resident<Cfg, FLUX_MAX_RANKS - 1, PARTIALS>), dim3(grid), dim3(Cfg::NT), 0, s, a);
+  return hipGetLastError();
+}
+
 // `edge`: the tile does not divide the shape (masked loads and stores).
 template <int EPI, int PRO>
-static hipError_t launch_one(int edge, const GemmArgs& a, int grid, hipStream_t s) {
+static hipError_t launch_one(int edge, int b_once, const GemmArgs& a, int grid, hipStream_t s) {
   if constexpr (EPI == EPI_RS && Cfg::NB == 2 && Cfg::OCC == 1) {
     if (a.persist_blocks > 0) {          // (only planned for shapes the tile divides)
-      if (a.R <= 4) hipLaunchKernelGGL((gemm_kernel_dma_resident<Cfg, 3>), dim3(grid), dim3(Cfg::NT), 0, s, a);
-      else hipLaunchKernelGGL((gemm_kernel_dma_resident<Cfg, FLUX_MAX_RANKS - 1>), dim3(grid), dim3(Cfg::NT), 0, s, a);
-      return hipGetLastError();
+      if (a.partial_f32) return launch_resident<1>(a, grid, s);
+      return launch_resident<0>(a, grid, s);
     }
   }
-  if (edge) hipLaunchKernelGGL((gemm_kernel_dma<Cfg, EPI, PRO, true>), dim3(grid), dim3(Cfg::NT), 0, s, a);
-  else hipLaunchKernelGGL((gemm_kernel_dma<Cfg, EPI, PRO, false>), dim3(grid), dim3(Cfg::NT), 0, s, a);
-  return hipGetLastError();
+  if constexpr (MAYBE_ONCE && (EPI == EPI_RS || PRO == PRO_CHUNKS))
+    if (b_once) return launch_two<EPI, PRO, true>(edge, a, grid, s);
+  return launch_two<EPI, PRO, false>(edge, a, grid, s);
 }
 
 #define FLUX_CAT2(a, b, c, d) a##b##c##d
 #define FLUX_CAT(a, b, c, d) FLUX_CAT2(a, b, c, d)
 
-hipError_t FLUX_CAT(launch_cfg, FLUX_CFG_ID, _nk, FLUX_B_NK)(int epi, int pro, int edge, const GemmArgs& a, int grid, hipStream_t s) {
-  if (epi == EPI_RS) return launch_one<EPI_RS, PRO_NONE>(edge, a, grid, s);
-  if (pro == PRO_WAIT) return launch_one<EPI_PLAIN, PRO_WAIT>(edge, a, grid, s);
-  if (pro == PRO_CHUNKS) return launch_one<EPI_PLAIN, PRO_CHUNKS>(edge, a, grid, s);
-  return launch_one<EPI_PLAIN, PRO_NONE>(edge, a, grid, s);
+hipError_t FLUX_CAT(launch_cfg, FLUX_CFG_ID, _nk, FLUX_B_NK)(int epi, int pro, int edge, int b_once, const GemmArgs& a, int grid, hipStream_t s) {
+  if (epi == EPI_RS) return launch_one<EPI_RS, PRO_NONE>(edge, b_once, a, grid, s);
+  if (pro == PRO_WAIT) return launch_one<EPI_PLAIN, PRO_WAIT>(edge, b_once, a, grid, s);
+  if (pro == PRO_CHUNKS) return launch_one<EPI_PLAIN, PRO_CHUNKS>(edge, b_once, a, grid, s);
+  return launch_one<EPI_PLAIN, PRO_NONE>(edge, b_once, a, grid, s);
 }
 
 }  // namespace flux
