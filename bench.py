@@ -293,7 +293,6 @@ def main() -> int:
         if t_atomic is not None:
             more["ms_atomic_reduce_f32"] = round(t_atomic, 4)
         if hasattr(op, "copy_upfront") and op.p.flags == 0 and op.p.link_gbps == 0 and fb.flux_ag_deferred_tiles(op.p) > 0:
-            more["chunks_moved_inside_main_loops"] = fb.flux_ag_deferred_tiles(op.p)
             more["ms_fused_all_chunks_up_front"] = round(time_calls(op.copy_upfront, reps, warm), 4)
         if hasattr(op, "one_workgroup_per_tile") and fb.flux_rs_resident_grid(op.p)[0] > 0:
             more["resident_grid"] = dict(zip(("workgroups", "late_start_ticks_100MHz"), fb.flux_rs_resident_grid(op.p)))
