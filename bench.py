@@ -25,7 +25,7 @@ if ROOT not in sys.path:
 
 MFMA_BF16_PEAK_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
 # bytes per launch behind the L2 of the two kernels of the timed step (rocprofv3 FETCH_SIZE + WRITE_SIZE)
-TRAFFIC_BYTES = {"rs": 2170.8e6 + 201.6e6, "ag": 2809.9e6 + 324.4e6}     # profiles/bench_c4_pmc_traffic.txt
+TRAFFIC_BYTES = {"rs": 2205.2e6 + 203.2e6, "ag": 2509.9e6 + 324.2e6}     # profiles/bench_c4_pmc_traffic.txt
 HBM_PEAK_GBS = 8000.0
 TIMEOUT_TICKS = 500_000_000        # 5 s: a lost signal ends the run with an error, not a hang
 
@@ -411,7 +411,7 @@ def main() -> int:
 
     # Traffic behind the L2 per launch, from two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE) of
     # `bench.py --serial-kernels 5`, each scaled by what the same counter reads for the 176.2 MB chunk
-    # copy of the same run (1.9987 and 1.0000 KiB per count); profiles/bench_c4_pmc_traffic.txt.
+    # copy of the same run (1.9985 and 1.0000 KiB per count); profiles/bench_c4_pmc_traffic.txt.
     traffic = TRAFFIC_BYTES
     alg = {"rs": rs.alg_bytes(), "ag": ag.alg_bytes()}
 
