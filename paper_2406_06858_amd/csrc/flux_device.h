@@ -1842,7 +1842,7 @@ __device__ __forceinline__ void wait_vm0_and_barrier() {
 // their slabs).
 // us per pass, gathered first and waited for / read from the sources: 4 layers of 8x3584x8192 86.0 / 70.0 (the wait was 6.5 of a call's
 // 17.6 us in the kernel), 4 of 200x3584x8192 150 / 119, 4096x3584x8192 192 / 177, 3000x3584x8192 180 / 173, 8192x4608x12288 694 / 657.  The stores
-// are 2-3 % of that (left out: 70.0 / 68.9, 183 / 179, 175.5 / 170, 676 / 664 on a slower box); moving the chunks through registers, a load and a
+// are 2-3 % of that (left out: 70.0 / 68.9, 183 / 179, 175.5 / 170, 676 / 664 on a slower chip); moving the chunks through registers, a load and a
 // store per slab, costs 7 % (a load that goes to memory holds up the operand loads behind it: 184, 175, 680).
 constexpr int GATHER_ROWS = 32;      // rows of a slab that 256 threads store
 __host__ __device__ constexpr bool gather_fits(int bm, int tiles_n) { return (long long)GATHER_ROWS * tiles_n >= bm; }
