@@ -463,6 +463,15 @@ struct EarlyPeers {
   template <int NP, bool PF32>
   static constexpr bool fits() { return SMALL && PASSES * NP * (PF32 ? 2 : 1) <= ROOM; }
 
+  // K-cut tiles never ask.  The compiler does not know it, and kept these registers through their hand-over, which then spilled in the kernels of
+  // two workgroups per unit (8 to 28 bytes of scratch a lane; us, spilled / not: 128x256x256 fp32, 2 ranks, 5.16 / 5.12, 8 ranks 40x1000x2008
+  // 9.33 / 9.09, 8x1000x1024 8.56 / 8.45, 136x1536x1536 [N,K] 9.03 / 8.92; the other side 72x1536x1536 8.22 / 8.29).  Called where a hand-over ends.
+  __device__ __forceinline__ void forget() {
+    if constexpr (SMALL)
+#pragma unroll
+      for (int i = 0; i < ROOM; ++i) asm volatile("" : "=v"(w[i]));
+  }
+
   template <bool EDGE, int NP, bool PF32>
   __device__ __forceinline__ int ask_as(const GemmArgs& a, int m0, int n0, int lane, int wm, int wn) {
     if constexpr (fits<NP, PF32>()) {
@@ -1473,7 +1482,7 @@ template <class C, int EPI, bool EDGE, bool RESIDENT, int MAX_NP = FLUX_MAX_RANK
 __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem, int* lds_misc, void* const* lds_outs,
                                           f32x4 (&acc)[C::MI][C::NI], int tile, int split, bool is_split,
                                           int m0, int n0, int tid, int lane, int wave, int wm, int wn, bool peers_added,
-                                          const EarlyPeers<C>& early, int n_early, int vb = -1) {
+                                          EarlyPeers<C>& early, int n_early, int vb = -1) {
   trace_stamp(a, TRACE_MAIN_END, vb);
   const bool partial_f32 = PARTIALS < 0 ? a.partial_f32 != 0 : PARTIALS != 0;
   // ---- split-K: all but the last-arriving workgroup of a tile park their partial sums ----
@@ -1584,6 +1593,7 @@ __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem
       }
     }
     __syncthreads();
+    early.forget();
   }
 
   // ---- epilogue: registers -> LDS (per wave, 32 rows at a time) -> 8 columns per lane ----
@@ -2400,7 +2410,8 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma_resident(const 
     wait_vm0_and_barrier();
     fill_lds_outs(a, words->outs, tid);
     __syncthreads();
-    gemm_tail<C, EPI_RS, false, true, MAX_NP, PARTIALS>(a, pool, words->misc, words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, false, {}, 0, vb);
+    EarlyPeers<C> none;
+    gemm_tail<C, EPI_RS, false, true, MAX_NP, PARTIALS>(a, pool, words->misc, words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, false, none, 0, vb);
     __syncthreads();      // the staging area and the shared words are the next block's
   }
 }
