@@ -417,11 +417,12 @@ int flux_split_plan(int op, const flux_problem_t* p, int32_t* full_tiles, int32_
 int32_t flux_rs_resident_grid(const flux_problem_t* p, uint32_t* delay_ticks);
 
 /*
- * How many of the (R-1) * comm_tiles_per_chunk remote communication tiles flux_ag_gemm, where it gathers A
- * first and without a copy kernel, has its first round of workgroups carry themselves instead of moving them before the
- * signal wait (Sec. 3.2: tiles whose data has arrived compute while the rest is on its way): the last
- * that many tiles of the transfer order; all of them when link_gbps > 0.  0: everything is moved up
- * front, or a copy kernel moves it.  Host function.
+ * How many of the (R-1) * comm_tiles_per_chunk remote communication tiles flux_ag_gemm has its first round of
+ * workgroups carry themselves instead of moving them before the signal wait (Sec. 3.2: tiles whose data has
+ * arrived compute while the rest is on its way): the last that many tiles of the transfer order; all of
+ * them when link_gbps > 0.  0: A is read from the chunk sources, everything is moved up front, or a copy kernel
+ * moves it.  (For sources outside A_agg and C: with one inside, a call that would read A from the sources gathers first
+ * and may carry tiles too.)  Host function.
  */
 int32_t flux_ag_deferred_tiles(const flux_problem_t* p);
 

@@ -272,6 +272,7 @@ struct Plan {
   int copy_pieces;          // pieces per communication tile (the unit a workgroup claims and moves)
   int copy_help;            // waiting GEMM workgroups may take pieces
   int copy_self;            // no copy kernel at all: the GEMM grid moves everything
+  int from_chunks;          // ... reading A from the chunk sources as it goes, unless one lies in what the call writes; otherwise:
   int copy_owners;          // ... its first copy_owners workgroups sharing the pieces out by index
   int defer_tiles;          // ... the last defer_tiles remote communication tiles carried inside the first round's main loops,
   int defer_steps;          //     defer_steps vectors per thread and tile
@@ -571,7 +572,7 @@ static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
     pl->resident_delay_ticks = (uint32_t)std::min(20000.0, (main_ticks + epi_ticks) / 2);
   }
   pl->ctpc = p->comm_tiles_per_chunk <= 0 ? 1 : p->comm_tiles_per_chunk;
-  pl->copy_wgs = 0; pl->copy_pieces = 0; pl->copy_help = 0; pl->copy_self = 0; pl->copy_owners = 0; pl->claim_bytes = 0; pl->defer_tiles = 0; pl->defer_steps = 0; pl->pace_ticks = 0;
+  pl->copy_wgs = 0; pl->copy_pieces = 0; pl->copy_help = 0; pl->copy_self = 0; pl->from_chunks = 0; pl->copy_owners = 0; pl->claim_bytes = 0; pl->defer_tiles = 0; pl->defer_steps = 0; pl->pace_ticks = 0;
   if (op == FLUX_OP_AG) {
     // Driver: one piece of every communication tile per workgroup.  A small driver: it keeps the
     // later chunks coming in the background while waiting GEMM workgroups pull what they need now;
@@ -620,6 +621,9 @@ static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
       pl->defer_steps = (int)((tile_vec + (unsigned long long)pl->copy_pieces * 256 - 1) / ((unsigned long long)pl->copy_pieces * 256));
       pl->pace_ticks = std::max<unsigned long long>(1, (unsigned long long)((double)tile_vec * 16.0 / (double)p->link_gbps / 10.0));
     } else if (pl->copy_self) {
+      // Nothing has to wait for the gathered matrix where the grid can read A from the chunk sources (see GatherOut for both sides):
+      // nobody asks for another transfer, and a row of tiles is long enough to store its rows.
+      pl->from_chunks = p->R > 1 && gather_fits(pl->bm, pl->tiles_n) && !(p->flags & (FLUX_FLAG_AG_ABSENT_OWNERS | FLUX_FLAG_AG_COPY_UPFRONT));
       // the first workgroups of the grid, as many as surely run at once, own the pieces
       pl->copy_wgs = 0;
       // pieces of 16 KiB or more, as many as the claim table allows
@@ -1019,7 +1023,7 @@ int flux_split_plan(int op, const flux_problem_t* p, int32_t* full_tiles, int32_
 int32_t flux_ag_deferred_tiles(const flux_problem_t* p) {
   Plan pl;
   if (p == nullptr || make_plan(FLUX_OP_AG, p, &pl) != FLUX_OK) return 0;
-  return pl.defer_tiles;
+  return pl.from_chunks ? 0 : pl.defer_tiles;
 }
 
 int32_t flux_rs_resident_grid(const flux_problem_t* p, uint32_t* delay_ticks) {
@@ -1243,10 +1247,8 @@ int flux_ag_gemm(const flux_problem_t* p, const void* const* A_chunks, void* A_a
   const bool local_in_grid = local_away && pl.copy_self && pl.pace_ticks == 0 && p->R > 1 && !(all_cut && chunk_elems * 2 > (6u << 20)) &&
                              !overlap(A_chunks[p->rank], chunk_elems * 2, A_agg, agg_bytes) &&
                              !overlap(A_chunks[p->rank], chunk_elems * 2, C, c_bytes);
-  // Nothing has to wait for the gathered matrix where the grid can read A from the chunk sources (GatherOut: 7-25 % of a call): nobody asks
-  // for another transfer, a row of tiles is long enough to store its rows, and no source lies in what the grid writes while it reads.
-  bool from_chunks = pl.copy_self && pl.pace_ticks == 0 && p->R > 1 && gather_fits(pl.bm, pl.tiles_n) &&
-                     !(p->flags & (FLUX_FLAG_AG_ABSENT_OWNERS | FLUX_FLAG_AG_COPY_UPFRONT));
+  // A from the chunk sources: if none lies in what the grid writes while it reads
+  bool from_chunks = pl.from_chunks;
   for (int r = 0; r < p->R && from_chunks; ++r)
     if (r != p->rank || local_away)
       from_chunks = !overlap(A_chunks[r], chunk_elems * 2, A_agg, agg_bytes) && !overlap(A_chunks[r], chunk_elems * 2, C, c_bytes);
