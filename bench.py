@@ -132,8 +132,8 @@ def main() -> int:
                                      compute_stream=compute, comm_stream=copy)
 
         def copy_upfront(self):
-            # the same fused call with every remote chunk moved before the signal wait (only differs where
-            # the library would carry the later chunks inside the first round's main loops)
+            # the same fused call with every remote chunk moved before a signal wait, instead of A read from the chunk
+            # sources (or, with few columns of tiles, the later chunks carried inside the first round's main loops)
             if not hasattr(self, "p_up"):
                 w = self.w
                 self.p_up = fb.problem(w.M, w.N, w.K, w.R, self.rank, "bf16", w.out_dtype, spin_timeout_ticks=TIMEOUT_TICKS,
@@ -150,9 +150,9 @@ def main() -> int:
             fb.flux_ag_gemm(self.p_nk, self.chunks, self.A_agg, self.B_nk, self.C, self.signals, self.arrival,
                             self.ws, compute, copy)
 
-        def alg_bytes(self):     # fused kernel: A_agg + B read once, C written once; the default call has no
-            w = self.w           # copy kernel, so the R-1 remote chunks are read and written by this kernel too
-            return 2.0 * (w.M * w.K + w.K * w.N + w.M * w.N) + 2 * 2.0 * (w.R - 1) * w.S * w.K
+        def alg_bytes(self):     # fused call: the chunks and B read once, C and the remote rows of A_agg written once
+            w = self.w
+            return 2.0 * (w.M * w.K + w.K * w.N + w.M * w.N) + 2.0 * (w.R - 1) * w.S * w.K
 
     class RS(RotatingB):
         def __init__(self, w, rank, **kw):
@@ -292,7 +292,7 @@ def main() -> int:
             more["ms_fused_graph_replay"] = round(t_graph, 4)
         if t_atomic is not None:
             more["ms_atomic_reduce_f32"] = round(t_atomic, 4)
-        if hasattr(op, "copy_upfront") and op.p.flags == 0 and op.p.link_gbps == 0 and fb.flux_ag_deferred_tiles(op.p) > 0:
+        if hasattr(op, "copy_upfront") and op.p.flags == 0 and op.p.link_gbps == 0 and op.p.copy_workgroups == 0:
             more["ms_fused_all_chunks_up_front"] = round(time_calls(op.copy_upfront, reps, warm), 4)
         if hasattr(op, "one_workgroup_per_tile") and fb.flux_rs_resident_grid(op.p)[0] > 0:
             more["resident_grid"] = dict(zip(("workgroups", "late_start_ticks_100MHz"), fb.flux_rs_resident_grid(op.p)))
@@ -432,7 +432,7 @@ def main() -> int:
         return line
 
     # The roofline line is for the kernel of the step that takes longer, each against the roof that
-    # binds it: the AllGather-GEMM (927.7 GFLOP over 390 MB + 352 MB gathered: MFMA), the
+    # binds it: the AllGather-GEMM (927.7 GFLOP over 390 MB + 176 MB gathered: MFMA), the
     # GEMM-ReduceScatter of this shape (309 GFLOP over 1673.5 MB: 123 us of MFMA work against
     # 209 us of memory traffic at peak: HBM).  The other one follows as "second_kernel".
     lines = [kernel_line("GEMM kernel <ReduceScatter epilogue> on c4_rs", "rs", rs.w, rs_ms, "hbm"),

@@ -1603,9 +1603,9 @@ std::vector<Candidate> tune_candidates(int op, const flux_problem_t* p) {
     if (make_plan(op, &q, &pl) != FLUX_OK) continue;
     out.push_back({cfg, 1, 0});
     // the forms of prologue and epilogue the plan would pick by rule are knobs too (Sec. 4.4): all chunks
-    // moved before the first main loop instead of carried inside it; one workgroup per tile instead of
-    // a resident grid
-    if (op == FLUX_OP_AG && pl.defer_tiles > 0 && pl.pace_ticks == 0) out.push_back({cfg, 1, 0, FLUX_FLAG_AG_COPY_UPFRONT});
+    // moved before the first main loop instead of A read from the sources, or some carried inside it; one
+    // workgroup per tile instead of a resident grid
+    if (op == FLUX_OP_AG && (pl.from_chunks || (pl.defer_tiles > 0 && pl.pace_ticks == 0))) out.push_back({cfg, 1, 0, FLUX_FLAG_AG_COPY_UPFRONT});
     if (op == FLUX_OP_RS && pl.resident) out.push_back({cfg, 1, 0, FLUX_FLAG_NO_RESIDENT_GRID});
     // few rows: how K is cut decides how well the grid fills the chip and what the hand-over costs;
     // half and twice the library's number of parts are candidates too
