@@ -83,7 +83,7 @@ RS_SHAPES = {
 
 @pytest.mark.parametrize("pads", [(8, 16, 24), (64, 0, 0), (0, 128, 0), (0, 0, 8)])
 @pytest.mark.parametrize("shape", list(RS_SHAPES))
-@pytest.mark.parametrize("pd,od", [("bf16", "bf16"), ("f32", "f32")])
+@pytest.mark.parametrize("pd,od", [("bf16", "bf16"), ("f32", "f32"), ("f32", "bf16")])
 def test_rs_with_row_pitches(shape, pads, pd, od):
     w = fi.scaled(RS_SHAPES[shape], partial_dtype=pd, out_dtype=od)
     rank = w.R - 2
