@@ -13,10 +13,11 @@
  *
  *   AllGather-GEMM      (paper Alg. 2 + Alg. 3 pull form, Sec. 3.2, Sec. 4.1, Sec. 4.3)
  *       C = A_agg B,  A_agg = rows of chunk 0, chunk 1, ... chunk R-1.
- *       A copy driver on `copy_stream` moves the remote chunks into A_agg in `arrival_order`
- *       and sets one 32-bit signal per communication tile; the GEMM kernel on
- *       `compute_stream` visits tiles in the same order and spins on the signals of the rows
- *       a tile needs before touching them (WaitSignal in the prologue).
+ *       The GEMM kernel on `compute_stream` visits tiles in `arrival_order`.  By default every tile reads
+ *       its rows from the chunks where they lie and A_agg is stored on the way; otherwise the remote
+ *       chunks are moved into A_agg in that order (by the grid, or by a copy driver on `copy_stream`), one
+ *       32-bit signal per communication tile is set, and a tile spins on the signals of the rows it
+ *       needs before touching them (WaitSignal in the prologue).  See flux_ag_gemm.
  *
  * plus the non-overlapped baseline used for the overlap-efficiency metric (Sec. 2.3, Eq. 1-2).
  *
@@ -196,8 +197,9 @@ int flux_gemm_rs_static(const flux_problem_t* p, const void* A, const void* B,
  *   - link_gbps == 0, copy_workgroups == 0, no FLUX_FLAG_COPY_MEMCPY (the default): no copy kernel
  *     is launched and copy_stream stays unused.  Every tile reads its rows of A from the chunk sources
  *     and stores a share of them into A_agg on the way; nothing waits and the signals stay as they are
- *     (a tile's rows have arrived when its loads have).  A source is read by every tile that needs it:
- *     right for sources in this GPU's memory.
+ *     (a tile's rows have arrived when its loads have).  A source is read by every column of tiles that needs it:
+ *     right for sources in this GPU's memory, which is what these pointers are.  For memory behind a link
+ *     FLUX_FLAG_AG_COPY_UPFRONT reads each source once; nothing here detects that case.
  *     With FLUX_FLAG_AG_COPY_UPFRONT or FLUX_FLAG_AG_ABSENT_OWNERS, where a chunk (other than the local one in
  *     its place) overlaps A_agg or C, and for tiles whose row of tiles is too short to share its rows out (fewer
  *     than tile height / 32 tiles), A is gathered first.  The first workgroups of the GEMM grid (as many as
@@ -229,8 +231,8 @@ int flux_gemm_rs_static(const flux_problem_t* p, const void* A, const void* B,
  * that waits takes over unclaimed pieces of the tiles it waits for, so a mover that has not been
  * given a compute unit yet cannot stall the grid.
  * Stream capture: in the default form the call is one kernel launch on compute_stream, which also
- * moves a local chunk that is not in place yet (R = 1, a local chunk that lies inside A_agg or C, or
- * one above 6 MiB where all tiles are cut along K: a copy ahead of it), and everything that changes
+ * gathers a local chunk that is not in place yet (R = 1, a local chunk that lies inside A_agg or C, or, where A is
+ * gathered first, one above 6 MiB with all tiles cut along K: a copy ahead of it), and everything that changes
  * from call to call lives in the workspace, so it may be recorded in a HIP graph and replayed.  The
  * forms with a driver take a fresh claim id from the host on every call: under stream capture they
  * return FLUX_ERR_UNSUPPORTED.

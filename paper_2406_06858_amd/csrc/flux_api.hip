@@ -803,6 +803,12 @@ static int launch_gemm(const Plan& pl, int epi, int pro, GemmArgs& a, hipStream_
   // 512x3584x1536 16.6 / 21.9, 4 layers of rs 200x8192x3584 (64x128 tiles) 118.8 / 142.5, rs 2048x4608x1536 57.9 / 64.2.
   // Not where neighbouring tiles share lines (rows of B that are no whole lines: rs 24x880x8592 52.9 / 63.3), nor a B that the L2s hold from
   // one call to the next (64x256x4608 46.0 / 50.0).
+  // The price: streamed lines do not stay in the Infinity Cache.  A B of up to 256 MB that is called again and again by itself stays there if it is
+  // kept.  us per call, kept / streamed, by itself and in turn with 600 to 900 MB of others: rs, 8 ranks, 64x12288x6144 33.4 / 40.1 and 42.4 / 40.4,
+  // 512x12288x6144 81.2 / 95.3 and 96.9 / 95.2, 2 ranks 8x12288x6144 28.4 / 30.2 and 35.0 / 33.4, 64x5120x6144 18.4 / 21.8 and 25.9 / 24.4, 64x18432x6144
+  // 42.0 / 56.0 and 68.8 / 65.6, 512x9216x6144 74.6 / 84.3 and 91.4 / 85.0, 8x3072x6144 12.7 / 11.7 and 14.8 / 14.0, 8x24576x6144 (302 MB) 59.5 / 53.3 and
+  // 62.5 / 58.2.  In turn it gains 3-8 % at all 13 widths from 3072 to 24576, and that is the use: between two uses of a matrix this large a
+  // program goes through its other layers'.
   const bool b_lines = reinterpret_cast<uintptr_t>(a.B) % 128 == 0 && (size_t)a.ldb * 2 % 128 == 0;
   const bool b_large = (unsigned long long)a.N * a.K * 2 > (unsigned long long)N_XCD * L2_BYTES;
   const int b_once = b_lines && b_large && (pl.tiles_m == 1 || (pl.tiles_m == 2 && pl.n_xcd > 1 && pl.tiles_n % pl.n_xcd == 0));
@@ -1231,10 +1237,10 @@ int flux_ag_gemm(const flux_problem_t* p, const void* const* A_chunks, void* A_a
   // communication tile
   a.acquire_l2 = (reinterpret_cast<uintptr_t>(A_agg) % 128 != 0) || (((size_t)pitch_a(p) * 2) % 128 != 0);
   const uint32_t call_id = next_call_id();
-  // A local chunk that is not in place yet is moved by the grid like the remote ones, ahead of them, where the grid moves
-  // everything; a grid that keeps a link's schedule (whose tiles are counted from the first remote one), a driver, or R = 1
-  // has it copied by a kernel of its own ahead of the grid.  So does a chunk handed over inside the gathered matrix (in
-  // another chunk's rows, say) or inside C: the grid writes both while it would still be reading the chunk.  And so does a large
+  // A local chunk that is not in place yet is read where it lies, like the remote ones, where A comes from the chunk sources.  Where A is gathered
+  // first and the grid moves everything, it moves this chunk too, ahead of the remote ones; a grid that keeps a link's schedule (whose tiles are
+  // counted from the first remote one), a driver, or R = 1 has it copied by a kernel of its own ahead of the grid.  So does a chunk handed over inside
+  // the gathered matrix (in another chunk's rows, say) or inside C: the grid writes both while it would still be reading the chunk.  And so does a large
   // chunk of a grid whose every tile is cut along K: no part can start before the grid has moved everything, and the copy
   // kernel moves it faster (us, grid / copy ahead: 2 ranks 1088x1408x12288, 13 MB, 113 / 98, 1352x2800x10608 148 / 143, 4 ranks
   // 7 MB 141 / 137, 2 ranks 2000x1536x6144 71.9 / 70.2; the other side: 2 ranks 512x3584x8192, 4 MB, 52.4 / 54.0, 8 ranks

@@ -1,8 +1,9 @@
 // Device-side building blocks of the fused tensor-parallel GEMM kernels (gfx950 / CDNA4).
 //
 // One templated kernel serves the three entry points; what differs is the prologue
-// (AllGather-GEMM waits on signals, paper Alg. 2) and the epilogue (GEMM-ReduceScatter adds
-// the peer partial tiles and writes each row into its owner's slice, paper Alg. 1).
+// (AllGather-GEMM reads A from the chunk sources and stores the gathered matrix on the way, or waits on
+// signals, paper Alg. 2) and the epilogue (GEMM-ReduceScatter adds the peer partial tiles and writes
+// each row into its owner's slice, paper Alg. 1).
 //
 // Mapping to the hardware:
 //   * bf16 inputs, v_mfma_f32_16x16x32_bf16, fp32 accumulators kept in registers;
@@ -11,8 +12,8 @@
 //     needs 8 consecutive k of one column) with the transposing ds_read_b64_tr_b16;
 //   * direct global-to-LDS loads of the slabs ahead while this one is multiplied;
 //   * the accumulators go through LDS once in the epilogue so that every lane owns 8
-//     consecutive columns of a row: peer partials are read and outputs written 16 B (bf16)
-//     or 32 B (fp32) per lane, 128..512 B contiguous per row.
+//     consecutive columns of a row (of fp32 partials twice 4): peer partials are read and outputs
+//     written 16 B per lane and instruction, 128..512 B contiguous per row.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stddef.h>
@@ -447,8 +448,9 @@ __device__ __forceinline__ void make_peer_bufs(const GemmArgs& a, int m0, int n0
 
 // The peers' rows of a small whole tile, asked for ahead of its main loop and held in registers until its end: a small call is a
 // chain of memory round trips, and this one does not depend on the products.  NP peers (1, 3 or 7; absent ones read nothing, but cost
-// an issue slot each; not streamed: half a line each, us, streamed / kept, 8 ranks 512x1024x256 9.0 / 7.6, 32x8192x384 9.4 / 7.9), where they fit ROOM vectors (with 14 instead of 6 the kernels of two workgroups per unit spill: 5.9 us -> 6.6).
-// us per call, peers behind the main loop / ahead of it: fp32, 2 ranks: 128x256x256 5.92 / 5.09, 64x512x512 8.21 / 6.69, 512x1024x256 9.00 /
+// an issue slot each; not streamed: half a line each, us, streamed / kept, 8 ranks 512x1024x256 9.0 / 7.6, 32x8192x384 9.4 / 7.9), where they fit ROOM
+// vectors (with 14 instead of 6, and kept through a hand-over, the kernels of two workgroups per unit spilled: 5.9 us -> 6.6).
+// us per call, peers behind the main loop / ahead of it: fp32, 2 ranks: 128x256x256 5.92 / 5.09 (5.1 to 5.8 on other boxes, 4 to 10 % gained), 64x512x512 8.21 / 6.69, 512x1024x256 9.00 /
 // 6.85; bf16: 2 ranks 2048x2048x1024 18.7 / 16.3, 4 ranks 512x3584x1536 14.7 / 13.7, 8 ranks 2048x1024x512 13.5 / 13.0; the other side:
 // 64x512x512 7.8 / 8.0, 2048x1024x2048 20.5 / 20.8.
 template <class C>
@@ -518,7 +520,9 @@ __device__ __forceinline__ void epilogue_block(const GemmArgs& a, void* const* l
   constexpr int NIT = 32 / RPP;
   constexpr int B = BATCH < NIT ? BATCH : NIT;
   constexpr int LPP = PF32 ? 2 : 1;
-  // cache policy: streamed, not kept; but where an instruction reads half a line of a row, another wave has the other half
+  // cache policy: streamed, not kept; but where an instruction reads half a line of a row, another wave has the other half.  (By the tile's
+  // width alone: rows of peers or results that are no whole lines, N * size not a multiple of 128 bytes, share lines between
+  // instructions and are streamed all the same.)
   constexpr int CACHE = C::WTN < 64 ? 0 : 2;
   static_assert(NIT % B == 0, "batch must divide the passes");
   const int cc = lane % CH, rl = lane / CH;
@@ -1763,7 +1767,9 @@ struct DmaLoader {
   // the d-th (constant after unrolling) of this wave's loads of A / of B, into `slab` in LDS
   __device__ __forceinline__ void load_a(int d, const GemmArgs& a, const Slabs& s, unsigned char* slab, int wave) const {
     if constexpr (CHUNKS) {
-      // (a slab past the end of K: the last one again, into a place that nobody reads)
+      // (Slabs past the end, into places that nobody reads: of K, the last one again, or zeros; of a part of K, the next part's.  With the
+      // part's own last slab there, whose lines the unit has just had, the same times: us, next part's / own, 8x3584x8192 16.68 / 16.75, 200x3584x8192
+      // [N,K] 30.58 / 30.61, 512x3584x8192 44.35 / 44.11, 512x6144x12288 90.6 / 91.4.)
       const int ka = !EDGE && s.ka > a.K - C::BK ? a.K - C::BK : s.ka;
       uint64_t p = rows[d] + (uint32_t)ka * 2u;
       if (EDGE && !(d < (k_vec < a.K - s.ka ? lim_a : 0))) p = reinterpret_cast<uint64_t>(&zero_vec);
@@ -1851,7 +1857,10 @@ __device__ __forceinline__ void wait_vm0_and_barrier() {
 // stores rows [nt * share, (nt + 1) * share) of every slab, one vector per thread (gather_fits; the parts of a tile cut along K each
 // their slabs).
 // us per pass, gathered first and waited for / read from the sources: 4 layers of 8x3584x8192 86.0 / 70.0 (the wait was 6.5 of a call's
-// 17.6 us in the kernel), 4 of 200x3584x8192 150 / 119, 4096x3584x8192 192 / 177, 3000x3584x8192 180 / 173, 8192x4608x12288 694 / 657.  The stores
+// 17.6 us in the kernel), 4 of 200x3584x8192 150 / 119, 4096x3584x8192 192 / 177, 3000x3584x8192 180 / 173, 8192x4608x12288 694 / 657.  With sources,
+// weights and results out of memory (buffers of 1.2 GB in turn), per call: 8x3584x8192 21.6 / 16.7, 200x3584x8192 [N,K] 37.3 / 29.1, 512x6144x12288 106.7 / 92.5,
+// 1024x8192x7168, 2 ranks, 107.9 / 102.1, 2048x6144x6144, 4 ranks, 154.4 / 149.5, 4096x3584x5120 140.6 / 114.7, 3000x3584x8192 188.9 / 174.8, 5000x4608x3400
+// 188.7 / 161.3, 8192x4608x12288 738 / 655; the other side, weights of 151 MB out of the Infinity Cache: 512x6144x12288 88.2 / 89.7.  The stores
 // are 2-3 % of that (left out: 70.0 / 68.9, 183 / 179, 175.5 / 170, 676 / 664 on a slower chip); moving the chunks through registers, a load and a
 // store per slab, costs 7 % (a load that goes to memory holds up the operand loads behind it: 184, 175, 680).
 constexpr int GATHER_ROWS = 32;      // rows of a slab that 256 threads store
@@ -2021,8 +2030,8 @@ struct MmaPipe {
 
   // Fills the pipeline: slabs 0 .. NB-2 requested, and A of slab NB-1 where it leads; then the first of the loads that a step
   // "-1" would deal out; the fragments of the first k-step read.  Slabs past the end are loads outside the records everywhere
-  // (no memory access): every step issues the same number of loads, which keeps the counter waits constants and the loop
-  // one shape.
+  // (no memory access; A from the chunk sources has addresses instead: see load_a): every step issues the same number of loads,
+  // which keeps the counter waits constants and the loop one shape.
   // (`two_slabs`: the steps that follow are of that mode.)
   __device__ __forceinline__ void request_b(const Ld& ld, const GemmArgs& ga, int k_begin, int KT) {
     static_assert(B_FIRST);
@@ -2169,7 +2178,8 @@ struct MmaPipe {
 // kernel before, gains nothing and costs the requests: 76.6 / 77.3, 116.7 / 118.2, 58.4 / 59.5, 119.5 / 119.9; 156.9 / 159.5, 161.9 / 163.5, 132.0 / 133.0.
 // Not taken (warm_a): other pitches (512x8192x3584 47.8 / 48.7, 1496x5112x3400 67.0 / 68.2), a multiple of 16 KB (1024x8192x8192
 // 134.9 / 137.7; 512x12288x8192 113.8 / 111.7), few slabs (512x12288x3072 47.0 / 46.9), tiles other than 256x128 (64x8192x8192 33.9 / 34.6,
-// 4096x8192x4096 224.7 / 228.6), and the fused call's gathered A, which the same grid has just written.
+// 4096x8192x4096 224.7 / 228.6), a gathered A, which the same grid has just written, and an A read from the chunk sources (not measured:
+// its rows are packed in up to 16 buffers).
 constexpr int WARM_LOADS = 8;      // per thread
 constexpr uint32_t WARM_BLOCKS = 256;   // workgroups of one round: one per compute unit
 __device__ __forceinline__ bool warm_a(const GemmArgs& a, uint32_t lines, uint32_t at_once) {
