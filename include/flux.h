@@ -419,12 +419,13 @@ int flux_split_plan(int op, const flux_problem_t* p, int32_t* full_tiles, int32_
 int32_t flux_rs_resident_grid(const flux_problem_t* p, uint32_t* delay_ticks);
 
 /*
- * How many of the (R-1) * comm_tiles_per_chunk remote communication tiles flux_ag_gemm has its first round of
- * workgroups carry themselves instead of moving them before the signal wait (Sec. 3.2: tiles whose data has
- * arrived compute while the rest is on its way): the last that many tiles of the transfer order; all of
- * them when link_gbps > 0.  0: A is read from the chunk sources, everything is moved up front, or a copy kernel
- * moves it.  (For sources outside A_agg and C: with one inside, a call that would read A from the sources gathers first
- * and may carry tiles too.)  Host function.
+ * How many of the (R-1) * comm_tiles_per_chunk remote communication tiles flux_ag_gemm, where it gathers A
+ * first and without a copy kernel, has its first round of workgroups carry themselves instead of moving them before the
+ * signal wait (Sec. 3.2: tiles whose data has arrived compute while the rest is on its way): the last
+ * that many tiles of the transfer order; all of them when link_gbps > 0.  0: everything is moved up
+ * front, or a copy kernel moves it.  This is a number of the form that gathers A first, whether or not the call comes to
+ * it: a default call whose tiles read A from the chunk sources (32 * ceil(N / tile_n) >= tile_m of flux_tile_shape and no
+ * chunk inside what it writes, see flux_ag_gemm) carries nothing.  Host function.
  */
 int32_t flux_ag_deferred_tiles(const flux_problem_t* p);
 

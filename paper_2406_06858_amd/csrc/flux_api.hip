@@ -1029,7 +1029,7 @@ int flux_split_plan(int op, const flux_problem_t* p, int32_t* full_tiles, int32_
 int32_t flux_ag_deferred_tiles(const flux_problem_t* p) {
   Plan pl;
   if (p == nullptr || make_plan(FLUX_OP_AG, p, &pl) != FLUX_OK) return 0;
-  return pl.from_chunks ? 0 : pl.defer_tiles;
+  return pl.defer_tiles;
 }
 
 int32_t flux_rs_resident_grid(const flux_problem_t* p, uint32_t* delay_ticks) {

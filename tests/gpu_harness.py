@@ -67,10 +67,9 @@ def run_rs(w: fi.Workload, rank: int, A, B, peers, tile_config=0, split_k=0, fla
 
 def run_ag(w: fi.Workload, rank: int, chunks, B, arrival, tile_config=0, split_k=0, flags=0,
            comm_tiles_per_chunk=0, copy_workgroups=0, local_in_place=False, delay_copy_cycles=0,
-           timeout_ticks=TEST_TIMEOUT_TICKS, repeat=1, link_gbps=0, copy_stream=None, agg_offset_elems=0, gathers_first=None):
+           timeout_ticks=TEST_TIMEOUT_TICKS, repeat=1, link_gbps=0, copy_stream=None, agg_offset_elems=0):
     """Fused AllGather-GEMM through the C ABI.  A_agg starts NaN-poisoned so a tile that reads
-    rows before their signal shows up in C.  Returns (C, A_agg, signals, status).  gathers_first: the
-    form that has to run, one that waits for the gathered matrix or one that reads the chunk sources."""
+    rows before their signal shows up in C.  Returns (C, A_agg, signals, status)."""
     p = fb.problem(w.M, w.N, w.K, w.R, rank, "bf16", w.out_dtype, tile_config, split_k, flags,
                    comm_tiles_per_chunk, copy_workgroups, timeout_ticks, link_gbps)
     dB = B.to(DEV)
@@ -95,7 +94,6 @@ def run_ag(w: fi.Workload, rank: int, chunks, B, arrival, tile_config=0, split_k
         with torch.cuda.stream(copy):
             torch.cuda._sleep(int(delay_copy_cycles))
     results = []
-    trace = None if gathers_first is None else trace_next_call(fb.FLUX_OP_AG, p)
     for _ in range(repeat):      # later calls rely on the state the previous call left behind
         if results:
             A_agg[:rank * w.S].fill_(float("nan"))
@@ -104,23 +102,8 @@ def run_ag(w: fi.Workload, rank: int, chunks, B, arrival, tile_config=0, split_k
         fb.flux_ag_gemm(p, dchunks, A_agg, dB, Cout, signals, arrival, ws, compute, copy)
         torch.cuda.synchronize()
         results.append(fb.flux_query_status(ws))
-    if trace is not None:
-        assert waited(trace) == gathers_first
     status = results[-1] if all(r == results[0] for r in results) else results
     return Cout, A_agg, signals, status
-
-
-def trace_next_call(op, p) -> torch.Tensor:
-    full, cut, k = fb.flux_split_plan(op, p)
-    trace = torch.zeros((full + cut * k, 8), dtype=torch.int64, device=DEV)
-    fb.flux_trace_next_call(trace)
-    return trace
-
-
-def waited(trace) -> bool:
-    """Whether the traced AllGather call's tiles waited for signals: they leave the time at which they were past
-    their wait, a kernel without one leaves its start's."""
-    return bool((trace[:, 5] > trace[:, 4]).any())
 
 
 def oracle_rs(w, rank, A, B, peers):

@@ -1,4 +1,4 @@
-"""A local chunk in a buffer of its own: read there by the tiles, moved by the GEMM grid ahead of the remote chunks, or copied ahead of it; and the
+"""A local chunk in a buffer of its own is moved by the GEMM grid, ahead of the remote chunks, or copied ahead of it; and the
 slice reduction for every number of partials.  Integer inputs whose sums stay below 2^24: bit for bit."""
 import pytest
 import torch
@@ -20,8 +20,7 @@ pytestmark = pytest.mark.gpu
     (512, 512, 512, 16, 2, 4, 0),         # the largest number of ranks: all sixteen places of the transfer order taken
     (64, 128, 256, 2, 1, 7, 0),
     (4096, 1280, 4096, 8, 1, 3, 0),       # several rounds of tiles, many pieces per owner
-    (8192, 2560, 1536, 8, 1, 1, 0),
-    (16384, 1792, 1536, 8, 1, 1, 0),      # too few columns of tiles to read A from the chunk sources: the last chunks carried inside the main loops
+    (8192, 2560, 1536, 8, 1, 1, 0),       # the last chunks carried inside the main loops
     (768, 384, 8192, 2, 1, 3, 0),         # K-cut tiles, a chunk of 6 MiB: by the grid ...
     (770, 384, 8192, 2, 1, 3, 8),         # ... and above: a copy ahead of the grid
 ])
@@ -36,36 +35,28 @@ def test_local_chunk_moved_by_the_grid(M, N, K, R, ctpc, cfg, pitch):
     store = torch.full((M, K + pitch), float("nan"), dtype=torch.bfloat16, device=gh.DEV)
     A_agg = store[:, :K]
     C = torch.empty((M, N), dtype=torch.bfloat16, device=gh.DEV)
-    p, up = (fb.problem(M, N, K, R, rank, "bf16", "bf16", cfg, flags=flags, comm_tiles_per_chunk=ctpc, spin_timeout_ticks=gh.TEST_TIMEOUT_TICKS,
-                        lda=K + pitch if pitch else 0) for flags in (0, fb.FLUX_FLAG_AG_COPY_UPFRONT))
-    assert fb.flux_ag_deferred_tiles(p) == (3 if M == 16384 else 0)
+    p = fb.problem(M, N, K, R, rank, "bf16", "bf16", cfg, comm_tiles_per_chunk=ctpc, spin_timeout_ticks=gh.TEST_TIMEOUT_TICKS,
+                   lda=K + pitch if pitch else 0)
     signals = torch.zeros(R * ctpc, dtype=torch.int32, device=gh.DEV)
     ws = gh.workspace_for(fb.FLUX_OP_AG, p)
     ws.fill_(-1)
     fb.flux_init_buffers(fb.FLUX_OP_AG, p, ws, signals)
     preset = signals.clone()
     copy = torch.cuda.Stream()
-    sh = fb.flux_tile_shape(fb.FLUX_OP_AG, p)
-    few_columns = 32 * -(-N // sh.tile_n) < sh.tile_m
-    # the third and the sixth with the chunk in place, the last two gathered first: all forms on one workspace
-    for call, q in enumerate((p, p, p, p, up, up)):
+    for call in range(4):                 # the third with the chunk in place: both forms on one workspace
         _say("local chunk", (M, N, K), "R", R, "cfg", cfg, "call", call)
         store.fill_(float("nan"))
         C.fill_(float("nan"))
         given = list(dchunks)
-        if call in (2, 5):
+        if call == 2:
             given[rank] = A_agg[rank * w.S:(rank + 1) * w.S]
             given[rank].copy_(dchunks[rank])
-        if call in (0, 4):
-            trace = gh.trace_next_call(fb.FLUX_OP_AG, q)
-        fb.flux_ag_gemm(q, given, A_agg, dB, C, signals, arrival, ws, torch.cuda.current_stream(), copy)
+        fb.flux_ag_gemm(p, given, A_agg, dB, C, signals, arrival, ws, torch.cuda.current_stream(), copy)
         torch.cuda.synchronize()
         assert fb.flux_query_status(ws) == (fb.FLUX_OK, 0)
         assert torch.equal(A_agg, gathered)
         assert torch.equal(signals, preset)
         assert torch.equal(C, want), f"call {call}"
-        if call in (0, 4):
-            assert gh.waited(trace) == (call == 4 or few_columns)
 
 
 @pytest.mark.parametrize("where", ["agg", "agg_across", "c"])

@@ -322,7 +322,7 @@ AG_SMALL = fi.scaled(W["c2_ag"], M=2048, N=512, K=512)
 
 
 @pytest.mark.parametrize("order", ["ring", "reversed", "random"])
-@pytest.mark.parametrize("flags", [0, fb.FLUX_FLAG_COPY_MEMCPY, fb.FLUX_FLAG_NO_SWIZZLE, fb.FLUX_FLAG_AG_COPY_UPFRONT])
+@pytest.mark.parametrize("flags", [0, fb.FLUX_FLAG_COPY_MEMCPY, fb.FLUX_FLAG_NO_SWIZZLE])
 def test_ag_arrival_orders_and_copy_engines(order, flags):
     w = AG_SMALL
     rank = 5
@@ -333,8 +333,8 @@ def test_ag_arrival_orders_and_copy_engines(order, flags):
         arrival = list(reversed(fo.default_order(rank, w.R)))
     _say("ag order", order, "flags", flags)
     C64, _ = gh.oracle_ag(w, chunks, B)
-    # copy_workgroups = 0 lets the library choose: no copy kernel (A read from the chunk sources, or moved by the
-    # grid where everything is asked for up front); a number asks for the copy kernel on the copy stream
+    # copy_workgroups = 0 lets the library choose: for a transfer this small, no copy kernel at all
+    # (the waiting workgroups pull the tiles); a number asks for the copy kernel on the copy stream
     for ctpc, cw in ((0, 0), (2, 0), (4, 0), (0, 48), (2, 48), (4, 7)):
         Cg, _, signals, status = gh.run_ag(w, rank, chunks, B, arrival, flags=flags, comm_tiles_per_chunk=ctpc,
                                            tile_config=3, copy_workgroups=cw)
@@ -399,19 +399,19 @@ def test_ag_waiting_workgroups_move_the_data_themselves():
 @pytest.mark.parametrize("shape", [dict(M=4096, N=2048, K=512), dict(M=2048, N=1024, K=1024), dict(M=64, N=1024, K=2048)])
 @pytest.mark.parametrize("ctpc", [1, 4])
 def test_ag_without_copy_kernel(shape, ctpc):
-    """No copy kernel (a grid of several rounds, one that leaves compute units free, a decode shape).  The default reads
-    A from the chunk sources.  With FLUX_FLAG_AG_COPY_UPFRONT the first workgroups of the GEMM grid share the pieces out
-    by index; with FLUX_FLAG_AG_ABSENT_OWNERS every second piece belongs to a workgroup that never runs, so the
+    """The default: no copy kernel, the first workgroups of the GEMM grid share the pieces out by index
+    (a grid of several rounds, one that leaves compute units free, a decode shape).  With
+    FLUX_FLAG_AG_ABSENT_OWNERS every second piece belongs to a workgroup that never runs, so the
     workgroups that wait for it have to take it over through the claim table.  Two calls in a row:
     the second relies on the counters, claims and signals the first left behind."""
     w = fi.scaled(W["c2_ag"], **shape)
     rank = 6
     chunks, B, arrival = fi.make_ag_inputs(w, rank)
     C64, _ = gh.oracle_ag(w, chunks, B)
-    for flags in (0, fb.FLUX_FLAG_AG_COPY_UPFRONT, fb.FLUX_FLAG_AG_ABSENT_OWNERS, fb.FLUX_FLAG_AG_ABSENT_OWNERS | fb.FLUX_FLAG_NO_SWIZZLE):
+    for flags in (0, fb.FLUX_FLAG_AG_ABSENT_OWNERS, fb.FLUX_FLAG_AG_ABSENT_OWNERS | fb.FLUX_FLAG_NO_SWIZZLE):
         _say("no copy kernel", shape, "ctpc", ctpc, "flags", flags)
         Cg, A_agg, signals, status = gh.run_ag(w, rank, chunks, B, arrival, flags=flags, comm_tiles_per_chunk=ctpc,
-                                               repeat=2, gathers_first=flags != 0)
+                                               repeat=2)
         assert status == (fb.FLUX_OK, 0)
         gh.assert_close(Cg, C64, w.out_dtype)
         gh.assert_bits_equal(A_agg, np.concatenate([fi.to_numpy(c) for c in chunks]), "A_agg")
@@ -471,8 +471,8 @@ def test_ag_r1_needs_no_copy():
     assert signals.cpu().tolist() == [1]
 
 
-@pytest.mark.parametrize("cw,flags", [(0, 0), (0, fb.FLUX_FLAG_AG_COPY_UPFRONT), (16, 0)])
-def test_ag_gathered_matrix_not_line_aligned(cw, flags):
+@pytest.mark.parametrize("cw", [0, 16])
+def test_ag_gathered_matrix_not_line_aligned(cw):
     """A gathered matrix whose rows do not start on cache line boundaries (base 16 bytes into a
     line): rows of two communication tiles can then share a line, and the wait ends with the
     acquire that also drops stale lines from the die's L2 (the cheaper one is only taken when
@@ -483,9 +483,9 @@ def test_ag_gathered_matrix_not_line_aligned(cw, flags):
     chunks, B, arrival = fi.make_ag_inputs(w, rank)
     C64, _ = gh.oracle_ag(w, chunks, B)
     for ctpc in (1, 2):
-        _say("unaligned gathered matrix, copy workgroups", cw, "flags", flags, "ctpc", ctpc)
-        Cg, A_agg, _, status = gh.run_ag(w, rank, chunks, B, arrival, copy_workgroups=cw, flags=flags, comm_tiles_per_chunk=ctpc,
-                                         repeat=2, agg_offset_elems=8, gathers_first=bool(cw or flags))
+        _say("unaligned gathered matrix, copy workgroups", cw, "ctpc", ctpc)
+        Cg, A_agg, _, status = gh.run_ag(w, rank, chunks, B, arrival, copy_workgroups=cw, comm_tiles_per_chunk=ctpc,
+                                         repeat=2, agg_offset_elems=8)
         assert status == (fb.FLUX_OK, 0)
         assert A_agg.data_ptr() % 128 == 16
         gh.assert_close(Cg, C64, w.out_dtype)
@@ -494,26 +494,24 @@ def test_ag_gathered_matrix_not_line_aligned(cw, flags):
 
 
 AG_TWO_ROUNDS = fi.Workload("int_ag_two_rounds", "ag", 8192, 4608, 2048, 8, a_dist=("int", 2), b_dist=("int", 2), seed=84)
-# ... of seven columns of 256x256 tiles, too few to store a tile's rows on the way (eight would read A from the chunk sources)
-AG_TWO_ROUNDS_NARROW = fi.Workload("int_ag_two_rounds_narrow", "ag", 16384, 1792, 2048, 8, a_dist=("int", 2), b_dist=("int", 2), seed=84)
 
 
 @pytest.mark.parametrize("order", ["ring", "random"])
 def test_ag_later_chunks_travel_inside_the_main_loops(order):
-    """A grid of more than one round that gathers A moves only the chunks its first round needs before the signal
+    """A grid of more than one round moves only the chunks its first round needs before the signal
     wait; the others are carried inside the first round's main loops (Sec. 3.2: compute on what has
     arrived while the rest is on its way).  Same bits as with everything moved up front, and as the
     oracle's; the gathered matrix is complete; the second call finds the state the first one left."""
-    w, rank = AG_TWO_ROUNDS_NARROW, 5
+    w, rank = AG_TWO_ROUNDS, 5
     chunks, B, arrival = fi.make_ag_inputs(w, rank)
     if order == "ring":
         arrival = fo.default_order(rank, w.R)
     p = fb.problem(w.M, w.N, w.K, w.R, rank)
     q = fb.problem(w.M, w.N, w.K, w.R, rank, flags=fb.FLUX_FLAG_AG_COPY_UPFRONT)
-    assert fb.flux_ag_deferred_tiles(p) == 3 and fb.flux_ag_deferred_tiles(q) == 0
+    assert fb.flux_ag_deferred_tiles(p) == 4 and fb.flux_ag_deferred_tiles(q) == 0
     _say("ag deferred transfer", order, "plan", fb.flux_split_plan(fb.FLUX_OP_AG, p))
     _, want = gh.oracle_ag(w, chunks, B)
-    Cd, A_agg, signals, status = gh.run_ag(w, rank, chunks, B, arrival, repeat=2, gathers_first=True)
+    Cd, A_agg, signals, status = gh.run_ag(w, rank, chunks, B, arrival, repeat=2)
     assert status == (fb.FLUX_OK, 0)
     gh.assert_bits_equal(Cd, want, "C, later chunks inside the main loops")
     gh.assert_bits_equal(A_agg, np.concatenate([fi.to_numpy(c) for c in chunks]), "A_agg")
@@ -523,48 +521,20 @@ def test_ag_later_chunks_travel_inside_the_main_loops(order):
     gh.assert_bits_equal(Cu, want, "C, everything up front")
 
 
-def test_ag_deferred_transfer_of_a_source_in_its_own_rows():
-    """Eight columns of tiles and more gather A all the same where a chunk lies in what the call writes: the later chunks travel
-    inside the main loops, that one onto itself."""
-    w, rank = AG_TWO_ROUNDS, 2
-    chunks, B, arrival = fi.make_ag_inputs(w, rank)
-    _, want = gh.oracle_ag(w, chunks, B)
-    p = fb.problem(w.M, w.N, w.K, w.R, rank, spin_timeout_ticks=gh.TEST_TIMEOUT_TICKS)
-    dchunks, dB = [c.to(gh.DEV) for c in chunks], B.to(gh.DEV)
-    signals = torch.zeros(w.R, dtype=torch.int32, device=gh.DEV)
-    ws = gh.workspace_for(fb.FLUX_OP_AG, p)
-    fb.flux_init_buffers(fb.FLUX_OP_AG, p, ws, signals)
-    for far in (arrival[0], arrival[-1]):            # a chunk that is moved up front, one that is carried
-        A_agg = torch.full((w.M, w.K), float("nan"), dtype=torch.bfloat16, device=gh.DEV)
-        C = torch.full((w.M, w.N), float("nan"), dtype=torch.bfloat16, device=gh.DEV)
-        there = A_agg[far * w.S:(far + 1) * w.S]
-        there.copy_(dchunks[far])
-        _say("ag deferred transfer, chunk in its own rows", far)
-        trace = gh.trace_next_call(fb.FLUX_OP_AG, p)
-        fb.flux_ag_gemm(p, dchunks[:far] + [there] + dchunks[far + 1:], A_agg, dB, C, signals, arrival, ws, torch.cuda.current_stream(),
-                        torch.cuda.Stream())
-        torch.cuda.synchronize()
-        assert fb.flux_query_status(ws) == (fb.FLUX_OK, 0) and gh.waited(trace)
-        gh.assert_bits_equal(C, want, "C")
-        gh.assert_bits_equal(A_agg, np.concatenate([fi.to_numpy(c) for c in chunks]), "A_agg")
-        assert signals.tolist() == [1 if r == rank else 0 for r in range(w.R)]
-
-
-@pytest.mark.parametrize("R,gbps,M,N,K,carried", [(2, 0, 20480, 1792, 2048, 1), (16, 0, 12288, 1792, 1408, 3), (16, 800, 8192, 4608, 2048, 15),
-                                                  (4, 0, 16384, 1792, 2048, 1)])
-def test_ag_carried_transfer_with_other_rank_counts(R, gbps, M, N, K, carried):
+@pytest.mark.parametrize("R,gbps", [(2, 0), (16, 0), (16, 800), (4, 0)])
+def test_ag_carried_transfer_with_other_rank_counts(R, gbps):
     """Two ranks: the first round is all local tiles and the one remote chunk travels inside its main
-    loops, nothing is moved up front.  Sixteen ranks: about half as many pieces per chunk as the first round
+    loops, nothing is moved up front.  Sixteen ranks: half as many pieces per chunk as the first round
     has workgroups, so half of them carry nothing."""
-    w = fi.Workload(f"int_ag_two_rounds_r{R}", "ag", M, N, K, R, a_dist=("int", 2), b_dist=("int", 2), seed=86 + R)
+    w = fi.Workload(f"int_ag_two_rounds_r{R}", "ag", 8192, 4608, 2048, R, a_dist=("int", 2), b_dist=("int", 2), seed=86 + R)
     rank = R - 1
     chunks, B, arrival = fi.make_ag_inputs(w, rank)
     p = fb.problem(w.M, w.N, w.K, w.R, rank, link_gbps=gbps)
     deferred = fb.flux_ag_deferred_tiles(p)
     _say("ag carried transfer, ranks", R, "link", gbps, "tiles carried", deferred)
-    assert deferred == carried
+    assert deferred == (R - 1 if gbps else {2: 1, 4: 2, 16: 8}[R])
     _, want = gh.oracle_ag(w, chunks, B)
-    Cg, A_agg, signals, status = gh.run_ag(w, rank, chunks, B, arrival, link_gbps=gbps, repeat=2, gathers_first=True)
+    Cg, A_agg, signals, status = gh.run_ag(w, rank, chunks, B, arrival, link_gbps=gbps, repeat=2)
     assert status == (fb.FLUX_OK, 0)
     gh.assert_bits_equal(Cg, want, "C")
     gh.assert_bits_equal(A_agg, np.concatenate([fi.to_numpy(c) for c in chunks]), "A_agg")
@@ -635,10 +605,10 @@ def test_ag_carried_pieces_are_moved_whatever_happens_to_the_tiles(gbps):
     rounds start when the first has finished); either way the kernel exits, the status block is
     consistent with the result, and the gathered matrix is complete: the workgroups that carry the
     pieces move all of them and count them in on schedule, whether or not anybody still waits."""
-    w, rank = AG_TWO_ROUNDS if gbps else AG_TWO_ROUNDS_NARROW, 1
+    w, rank = AG_TWO_ROUNDS, 1
     chunks, B, arrival = fi.make_ag_inputs(w, rank)
-    assert fb.flux_ag_deferred_tiles(fb.problem(w.M, w.N, w.K, w.R, rank, link_gbps=gbps)) == (7 if gbps else 3)
-    Cg, A_agg, signals, status = gh.run_ag(w, rank, chunks, B, arrival, timeout_ticks=1, link_gbps=gbps, gathers_first=True)
+    assert fb.flux_ag_deferred_tiles(fb.problem(w.M, w.N, w.K, w.R, rank, link_gbps=gbps)) == (7 if gbps else 4)
+    Cg, A_agg, signals, status = gh.run_ag(w, rank, chunks, B, arrival, timeout_ticks=1, link_gbps=gbps)
     code, detail = status
     _, want = gh.oracle_ag(w, chunks, B)
     gh.assert_bits_equal(A_agg, np.concatenate([fi.to_numpy(c) for c in chunks]), "A_agg")

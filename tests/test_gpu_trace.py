@@ -113,22 +113,19 @@ def test_rs_trace_matches_oracle_tile_coord(cfg, flags):
     assert (trace == 0).all()
 
 
-@pytest.mark.parametrize("order", ["ring", "random", "no_swizzle", "random_ctpc2", "random_upfront"])
+@pytest.mark.parametrize("order", ["ring", "random", "no_swizzle", "random_ctpc2"])
 @pytest.mark.parametrize("cfg", [0, 1])
 def test_ag_trace_matches_oracle_tile_coord(order, cfg):
     w = fi.Workload("ag_trace", "ag", 4096, 5120, 512, 8, seed=92)
     rank = 2
     chunks, B, arrival = fi.make_ag_inputs(w, rank)
-    swizzle = order != "no_swizzle"
-    flags = 0 if swizzle else fb.FLUX_FLAG_NO_SWIZZLE
-    if order == "random_upfront":                       # gathered first; else every tile reads the chunk sources
-        flags = fb.FLUX_FLAG_AG_COPY_UPFRONT
+    flags = fb.FLUX_FLAG_NO_SWIZZLE if order == "no_swizzle" else 0
     ctpc = 2 if order == "random_ctpc2" else 1          # two signals per chunk: a band is one communication tile
     if order == "ring":
         arrival = fo.default_order(rank, w.R)
     p = fb.problem(w.M, w.N, w.K, w.R, rank, tile_config=cfg, flags=flags, comm_tiles_per_chunk=ctpc,
                    spin_timeout_ticks=gh.TEST_TIMEOUT_TICKS)
-    grid, tile, part, coords, sh, split_k = _expected_tiles("ag", p, w, rank, arrival, 8 if swizzle else 1, ctpc)
+    grid, tile, part, coords, sh, split_k = _expected_tiles("ag", p, w, rank, arrival, 1 if flags else 8, ctpc)
     _say("ag trace", order, "cfg", cfg, "tile", sh.tile_m, sh.tile_n, "grid", grid, "split_k", split_k)
     dchunks = [c.to(gh.DEV) for c in chunks]
     A_agg = torch.full((w.M, w.K), float("nan"), dtype=torch.bfloat16, device=gh.DEV)
@@ -144,7 +141,7 @@ def test_ag_trace_matches_oracle_tile_coord(order, cfg):
     rec = _records(trace, grid)
     assert np.array_equal(rec["block"], np.arange(grid))
     assert np.array_equal(rec["tile"], tile)
-    if not swizzle:
+    if flags:
         tiles_n = -(-w.N // sh.tile_n)
         want = np.stack([tile // tiles_n, tile % tiles_n], axis=1)
     else:
@@ -152,8 +149,7 @@ def test_ag_trace_matches_oracle_tile_coord(order, cfg):
     assert np.array_equal(np.stack([rec["m_tile"], rec["n_tile"]], axis=1), want)
     assert (rec["t_start"] <= rec["t_ready"]).all() and (rec["t_ready"] <= rec["t_main_end"]).all()
     assert (rec["t_main_end"] <= rec["t_end"]).all()
-    assert gh.waited(trace) == (order == "random_upfront")
-    if swizzle:
+    if not flags:
         _check_dispatch_order(rec, tile, sh, w, "ag")
         # the tiles of the local chunk (the first band) need no transfer of their own rows: none of
         # them can be past its wait later than the last tile of the last chunk to arrive

@@ -291,12 +291,12 @@ def test_row_pitches_are_validated(bad, status):
 def test_row_pitches_in_planning():
     """A pitch equal to the row length is the packed layout; a gathered matrix with a longer pitch is
     moved before the signal wait (its communication tiles are not single runs of memory)."""
-    packed = fb.problem(16384, 1792, 2048, 8, 1)
-    same = fb.problem(16384, 1792, 2048, 8, 1, lda=2048, ldb=1792, ldc=1792)
+    packed = fb.problem(8192, 4608, 2048, 8, 1)
+    same = fb.problem(8192, 4608, 2048, 8, 1, lda=2048, ldb=4608, ldc=4608)
     assert fb.flux_ag_deferred_tiles(packed) == fb.flux_ag_deferred_tiles(same) > 0
-    assert fb.flux_ag_deferred_tiles(fb.problem(16384, 1792, 2048, 8, 1, lda=2048 + 64)) == 0
-    assert fb.flux_ag_deferred_tiles(fb.problem(16384, 1792, 2048, 8, 1, lda=2048 + 64, link_gbps=400)) == 0
-    assert fb.flux_ag_deferred_tiles(fb.problem(16384, 1792, 2048, 8, 1, ldb=1792 + 64, ldc=1792 + 8)) > 0
+    assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 2048, 8, 1, lda=2048 + 64)) == 0
+    assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 2048, 8, 1, lda=2048 + 64, link_gbps=400)) == 0
+    assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 2048, 8, 1, ldb=4608 + 64, ldc=4608 + 8)) > 0
     # the largest pitch that keeps the last element's index below 2^31
     assert fb.flux_tile_shape(fb.FLUX_OP_RS, fb.problem(128, 256, 256, 8, 0, lda=(2 ** 31 - 256) // 127 // 8 * 8)).tile_m > 0
 
@@ -331,28 +331,23 @@ def test_resident_grid_is_planned_for_many_short_reduce_scatter_tiles():
 
 def test_deferred_transfer_is_planned_for_grids_of_several_rounds():
     """flux_ag_deferred_tiles: the chunks the first round of workgroups does not touch, when every condition holds."""
-    narrow = (16384, 1792, 12288, 8, 2)              # 1.75 rounds of seven columns of tiles; the first covers 5 bands of 56
-    assert fb.flux_ag_deferred_tiles(fb.problem(*narrow)) == 3
-    assert fb.flux_ag_deferred_tiles(fb.problem(12288, 1792, 12288, 8, 2)) == 1       # bands of 42 tiles
-    assert fb.flux_ag_deferred_tiles(fb.problem(*narrow, flags=fb.FLUX_FLAG_AG_COPY_UPFRONT)) == 0
-    assert fb.flux_ag_deferred_tiles(fb.problem(*narrow, flags=fb.FLUX_FLAG_NO_SWIZZLE)) == 0
-    assert fb.flux_ag_deferred_tiles(fb.problem(*narrow, comm_tiles_per_chunk=2)) == 0
-    assert fb.flux_ag_deferred_tiles(fb.problem(*narrow, copy_workgroups=16)) == 0    # a copy kernel moves the data
-    assert fb.flux_ag_deferred_tiles(fb.problem(9216, 1792, 12288, 8, 2, tile_config=1)) == 0     # one round: every chunk is needed at once
-    assert fb.flux_ag_deferred_tiles(fb.problem(16384, 1792, 12288, 2, 0)) == 0       # the first round touches every chunk
-    assert fb.flux_ag_deferred_tiles(fb.problem(16384, 1792, 512, 8, 2)) == 0         # K too short to carry the vectors
-    assert fb.flux_ag_deferred_tiles(fb.problem(*narrow, tile_config=2)) == 0         # other kernel
-    assert fb.flux_ag_deferred_tiles(fb.problem(16384, 1792, 12288, 1, 0)) == 0
-    # eight columns of tiles and more: nothing is deferred, A is read from the chunk sources (2.25 and 3 rounds)
-    assert fb.flux_ag_deferred_tiles(fb.problem(16384, 2048, 12288, 8, 2)) == 0
-    assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 12288, 8, 2)) == 0
-    assert fb.flux_ag_deferred_tiles(fb.problem(8192, 6144, 12288, 8, 2)) == 0
+    assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 12288, 8, 2)) == 4        # 2.25 rounds; the first covers 4 bands of 72 tiles
+    assert fb.flux_ag_deferred_tiles(fb.problem(8192, 6144, 12288, 8, 2)) == 5        # three rounds, bands of 96 tiles
+    assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 12288, 8, 2, flags=fb.FLUX_FLAG_AG_COPY_UPFRONT)) == 0
+    assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 12288, 8, 2, flags=fb.FLUX_FLAG_NO_SWIZZLE)) == 0
+    assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 12288, 8, 2, comm_tiles_per_chunk=2)) == 0
+    assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 12288, 8, 2, copy_workgroups=16)) == 0   # a copy kernel moves the data
     # a transfer that stands for a link and has no driver of its own is carried whole, on the link's schedule
     assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 12288, 8, 2, link_gbps=400)) == 7
     assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 12288, 8, 2, link_gbps=400, comm_tiles_per_chunk=4)) == 28
     assert fb.flux_ag_deferred_tiles(fb.problem(4096, 3584, 8192, 8, 2, link_gbps=400)) == 7
     assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 12288, 8, 2, link_gbps=400, copy_workgroups=20)) == 0
     assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 12288, 8, 2, link_gbps=400, flags=fb.FLUX_FLAG_COPY_MEMCPY)) == 0
+    assert fb.flux_ag_deferred_tiles(fb.problem(4096, 3584, 8192, 8, 2)) == 0         # one round: every chunk is needed at once
+    assert fb.flux_ag_deferred_tiles(fb.problem(2048, 6144, 12288, 8, 2)) == 0        # the first round touches every chunk
+    assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 512, 8, 2)) == 0          # K too short to carry the vectors
+    assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 12288, 8, 2, tile_config=2)) == 0   # other kernel
+    assert fb.flux_ag_deferred_tiles(fb.problem(8192, 4608, 12288, 1, 0)) == 0
 
 
 @pytest.mark.parametrize("op,M,N,K,cfg", [("rs", 976, 264, 12288, 4), ("rs", 48, 12288, 1536, 5), ("rs", 8, 12288, 1648, 6), ("rs", 1040, 1416, 6144, 3),
