@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 def test_every_number_of_peers(R, cfg):
     for M, N, K in ((16 * R, 136, 200), (256 * R, 256, 128)):        # edges in every direction; tiles that divide it
         for split in (1, 3):
-            for pd, od in (("bf16", "bf16"), ("f32", "f32"), ("bf16", "f32"), ("f32", "bf16")):
+            for pd, od in (("bf16", "bf16"), ("f32", "f32"), ("bf16", "f32")):
                 w = fi.Workload("few_peers", "rs", M, N, K, R, pd, od, a_dist=("int", 2), b_dist=("int", 2), peer_dist=("int", 4), seed=M + R + cfg)
                 rank = (cfg + M) % R
                 A, B, peers = fi.make_rs_inputs(w, rank)
@@ -45,21 +45,3 @@ def test_many_short_tiles_of_few_ranks():
             if t is not None:
                 want += t.to(gh.DEV).float()
         assert torch.equal(torch.cat(outs), want.to(outs[0].dtype))
-
-
-@pytest.mark.parametrize("R,pd,od", [(2, "f32", "f32"), (4, "f32", "bf16"), (8, "f32", "f32"), (8, "f32", "bf16"), (16, "f32", "f32"), (16, "bf16", "f32")])
-def test_many_short_tiles_by_type_of_the_partials(R, pd, od):
-    """... and for a type of the partials each."""
-    w = fi.Workload("few_peers_resident", "rs", 8192, 8192, 192, R, pd, od)
-    assert fb.flux_rs_resident_grid(fb.problem(w.M, w.N, w.K, R, 1, pd, od))[0] == 256
-    gen = torch.Generator(device=gh.DEV).manual_seed(R)
-    draw = lambda shape, top, dt: torch.randint(-top, top + 1, shape, generator=gen, device=gh.DEV, dtype=torch.int32).to(dt)
-    A, B = draw((w.M, w.K), 2, torch.bfloat16), draw((w.K, w.N), 2, torch.bfloat16)
-    peers = [None if r == 1 else draw((w.M, w.N), 4, torch.float32 if pd == "f32" else torch.bfloat16) for r in range(R)]
-    _say("resident, ranks", R, pd, od)
-    outs = gh.run_rs(w, 1, A, B, peers)
-    want = A.float() @ B.float()
-    for t in peers:
-        if t is not None:
-            want += t.float()
-    assert torch.equal(torch.cat(outs), want.to(outs[0].dtype))
