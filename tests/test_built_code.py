@@ -2,7 +2,7 @@
 its distance from the others: what it places between them is checked here, in the code that was built.  In every block that
 holds MFMAs: no register of an LDS read is touched before the read has been waited for, operands of an MFMA come from an LDS
 read and nowhere else (a copy in between would need wait states), and nothing but an MFMA touches an accumulator within the
-18 wait states an MFMA may take.  And no kernel but the largest tile's uses scratch memory."""
+18 wait states an MFMA may take."""
 import os
 import re
 import subprocess
@@ -12,8 +12,6 @@ import pytest
 from paper_2406_06858_amd import build
 
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
-READELF = "/opt/rocm/llvm/bin/llvm-readelf"
-SCRATCH_256 = 72                  # bytes a lane
 MFMA_WAIT_STATES = 18
 _REG = re.compile(r"\b([va])(?:(\d+)|\[(\d+):(\d+)\])")
 
@@ -81,32 +79,15 @@ def _blocks(text):
         yield block
 
 
-def _objects(tmp_path):
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
+def test_nothing_between_the_written_out_instructions(tmp_path):
     lib = tmp_path / "lib.so"
     lib.symlink_to(build.LIB)
     subprocess.run([OBJDUMP, "--offloading", str(lib)], cwd=tmp_path, check=True, capture_output=True)
     objects = [p for p in tmp_path.iterdir() if "gfx950" in p.name]
     assert objects
-    return objects
-
-
-@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
-def test_registers_do_not_spill(tmp_path):
-    """Scratch memory of every GEMM kernel: none, but for the 256x256 tile, whose accumulators and fragments take all registers and
-    which keeps a few values of a lane there across its main loop."""
-    found = []
-    for o in _objects(tmp_path):
-        notes = subprocess.run([READELF, "--notes", str(o)], check=True, capture_output=True, text=True).stdout
-        found += re.findall(r"\.name:\s+(_ZN4flux\d+gemm_kernel\S+)\s+\.private_segment_fixed_size:\s+(\d+)", notes)
-    assert len(found) >= 10 * build.N_CFGS
-    for name, scratch in found:
-        assert int(scratch) <= (SCRATCH_256 if "TileCfgILi256ELi256E" in name else 0), name
-
-
-@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
-def test_nothing_between_the_written_out_instructions(tmp_path):
     with_mfma = 0
-    for o in _objects(tmp_path):
+    for o in objects:
         text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", str(o)], check=True, capture_output=True, text=True).stdout
         for block in _blocks(text):
             if any(i.startswith("v_mfma") for i in block):
