@@ -801,6 +801,10 @@ static int launch_gemm(const Plan& pl, int epi, int pro, GemmArgs& a, hipStream_
   // 4 layers of rs 128x8192x3584 107.0 / 100.6, rs 400x8192x8192 85.5 / 80.5, ag 512x6144x12288 96.6 / 91.2, rs 512x12288x6144 97.0 / 95.3, rs
   // 512x8192x3584 53.7 / 53.9; the other side, two rows on different dies: 4 layers of ag 128x3584x8192 115.0 / 125.5, more rows: rs
   // 512x3584x1536 16.6 / 21.9, 4 layers of rs 200x8192x3584 (64x128 tiles) 118.8 / 142.5, rs 2048x4608x1536 57.9 / 64.2.
+  // Of two rows of tiles, the second at least seven eighths full: with fewer rows it runs ahead, and the first finds the lines gone.  2 layers, 8 ranks, in turn
+  // with two other sets of buffers: rs 72x12288x6144 105.0 / 134.2, 104x12288x6144 116.7 / 127.1, 112x12288x6144 [N,K] 119.9 / 126.0, 304x4096x12288 113.1 / 128.5,
+  // 384x4096x12288 119.5 / 136.4, ag 304x8192x3584 71.4 / 78.1, write-only 80x6144x6144 [N,K] 72.5 / 79.7; nearer full it gains: rs 120x12288x6144 122.4 / 120.0,
+  // 480x8192x3584 117.4 / 113.9, ag 480x12288x6144 [N,K] 182.8 / 169.8 (all 48 at 120, 128, 480 and 512 rows: 0-8 %); what is given up: rs 400x8192x8192 166.8 / 159.4.
   // Not where neighbouring tiles share lines (rows of B that are no whole lines: rs 24x880x8592 52.9 / 63.3), nor a B that the L2s hold from
   // one call to the next (64x256x4608 46.0 / 50.0).
   // The price: streamed lines do not stay in the Infinity Cache.  A B of up to 256 MB that is called again and again by itself stays there if it is
@@ -811,7 +815,7 @@ static int launch_gemm(const Plan& pl, int epi, int pro, GemmArgs& a, hipStream_
   // program goes through its other layers'.
   const bool b_lines = reinterpret_cast<uintptr_t>(a.B) % 128 == 0 && (size_t)a.ldb * 2 % 128 == 0;
   const bool b_large = (unsigned long long)a.N * a.K * 2 > (unsigned long long)N_XCD * L2_BYTES;
-  const int b_once = b_lines && b_large && (pl.tiles_m == 1 || (pl.tiles_m == 2 && pl.n_xcd > 1 && pl.tiles_n % pl.n_xcd == 0));
+  const int b_once = b_lines && b_large && (pl.tiles_m == 1 || (pl.tiles_m == 2 && a.M * 8ll >= pl.bm * 15ll && pl.n_xcd > 1 && pl.tiles_n % pl.n_xcd == 0));
   if (e0) FLUX_HIP(hipEventRecord(e0, s));
   if (pl.resident && epi == EPI_RS && a.write_only == 0) {
     a.persist_blocks = grid;

@@ -1,6 +1,6 @@
 """Weights larger than all L2s under one or two rows of tiles are streamed by kernels of their own: every configuration that has them, both
 layouts of B, both operations, whole and K-cut tiles, edges in rows and in K; and what keeps to the other kernels (rows of B that are no
-whole lines, three rows of tiles).  Integer inputs whose sums stay below 2^24: bit for bit."""
+whole lines, a second row of tiles that is far from full, three rows of tiles).  Integer inputs whose sums stay below 2^24: bit for bit."""
 import pytest
 import torch
 
@@ -17,7 +17,7 @@ def _ints(gen, shape, top=2):
 
 
 @pytest.mark.parametrize("nk", [0, 1])
-@pytest.mark.parametrize("M,cfg", [(8, 8), (32, 8), (48, 8), (64, 7), (128, 7), (40, 9), (64, 9), (128, 9), (192, 9), (200, 2), (304, 2)])
+@pytest.mark.parametrize("M,cfg", [(8, 8), (32, 8), (48, 8), (64, 7), (128, 7), (40, 9), (64, 9), (128, 9), (192, 9), (200, 2), (304, 2), (496, 2)])
 def test_streamed_weights(M, cfg, nk):
     R, rank = 8, 3
     for N, K in ((8192, 2304), (8192, 2312), (8200, 2304)):
