@@ -201,8 +201,9 @@ int flux_gemm_rs_static(const flux_problem_t* p, const void* A, const void* B,
  *     right for sources in this GPU's memory, which is what these pointers are.  For memory behind a link
  *     FLUX_FLAG_AG_COPY_UPFRONT reads each source once; nothing here detects that case.
  *     With FLUX_FLAG_AG_COPY_UPFRONT or FLUX_FLAG_AG_ABSENT_OWNERS, where a chunk (other than the local one in
- *     its place) overlaps A_agg or C, and for tiles whose row of tiles is too short to share its rows out (fewer
- *     than tile height / 32 tiles), A is gathered first.  The first workgroups of the GEMM grid (as many as
+ *     its place) overlaps A_agg or C, for tiles whose row of tiles is too short to share its rows out (fewer
+ *     than tile height / 32 tiles), and for a gathered matrix of 32 MB or more whose rows are no whole lines of 128 bytes (base
+ *     and pitch) with N <= 3584, A is gathered first.  The first workgroups of the GEMM grid (as many as
  *     run at once) share the pieces of the tiles out among themselves by index and move them
  *     before they look at their own signals; in a grid of several rounds they move only the chunks
  *     the first round reads that way and carry the others inside their main loops (see
@@ -424,8 +425,8 @@ int32_t flux_rs_resident_grid(const flux_problem_t* p, uint32_t* delay_ticks);
  * signal wait (Sec. 3.2: tiles whose data has arrived compute while the rest is on its way): the last
  * that many tiles of the transfer order; all of them when link_gbps > 0.  0: everything is moved up
  * front, or a copy kernel moves it.  This is a number of the form that gathers A first, whether or not the call comes to
- * it: a default call whose tiles read A from the chunk sources (32 * ceil(N / tile_n) >= tile_m of flux_tile_shape and no
- * chunk inside what it writes, see flux_ag_gemm) carries nothing.  Host function.
+ * it: a default call whose tiles read A from the chunk sources (32 * ceil(N / tile_n) >= tile_m of flux_tile_shape, no
+ * chunk inside what it writes, no large matrix of partial lines: see flux_ag_gemm) carries nothing.  Host function.
  */
 int32_t flux_ag_deferred_tiles(const flux_problem_t* p);
 

@@ -412,6 +412,15 @@ static bool resident_shape(const flux_problem_t* p, const Plan& pl) {
          (long long)pl.full_tiles + (long long)pl.split_tiles * pl.split_k >= 4ll * N_CU && p->K <= 3072;
 }
 
+// A gathered matrix whose rows are no whole lines is stored in parts of lines where A is read from the chunk sources (GatherOut: a slab's 128 bytes of a
+// row are parts of two lines, streamed out one after the other).  Large ones go to memory like that, and few columns of products do not
+// hide it.  us per call, 8 ranks, sources, weights and results of three sets in turn, gathered first / from the sources: 8192x1536x8568 305.6 / 325.1,
+// 8192x1536x5000 187.3 / 203.7, 8192x1536x3400 138.5 / 145.2, 8192x2304x8568 309.1 / 321.5, 4096x1536x8568 163.0 / 197.5, 2 ranks 2048x1152x8568 76.7 / 82.8;
+// the other side: 1024x1536x8568 60.0 / 49.2, 4096x1536x3400 75.8 / 58.5, 8192x4608x8568 552.7 / 541.1, 8192x6144x5000 423.4 / 402.2, whole lines:
+// 8192x1536x8512 251.7 / 229.7; given up: 3000x1536x8568 154.7 / 125.5, and one set by itself, most of it in the Infinity Cache: 8192x1536x8568
+// 258.8 / 237.6, 8192x3584x8568 452.7 / 408.2.
+static bool gather_parts_cost(const flux_problem_t* p) { return (long long)p->M * p->K * 2 >= (32ll << 20) && p->N <= 3584; }
+
 static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
   int st = validate_problem(op, p);
   if (st != FLUX_OK) return st;
@@ -622,8 +631,9 @@ static int make_plan(int op, const flux_problem_t* p, Plan* pl) {
       pl->pace_ticks = std::max<unsigned long long>(1, (unsigned long long)((double)tile_vec * 16.0 / (double)p->link_gbps / 10.0));
     } else if (pl->copy_self) {
       // Nothing has to wait for the gathered matrix where the grid can read A from the chunk sources (see GatherOut for both sides):
-      // nobody asks for another transfer, and a row of tiles is long enough to store its rows.
-      pl->from_chunks = p->R > 1 && gather_fits(pl->bm, pl->tiles_n) && !(p->flags & (FLUX_FLAG_AG_ABSENT_OWNERS | FLUX_FLAG_AG_COPY_UPFRONT));
+      // nobody asks for another transfer, a row of tiles is long enough to store its rows, and they are stored in whole lines or come cheap.
+      pl->from_chunks = p->R > 1 && gather_fits(pl->bm, pl->tiles_n) && !(p->flags & (FLUX_FLAG_AG_ABSENT_OWNERS | FLUX_FLAG_AG_COPY_UPFRONT)) &&
+                        (pitch_a(p) * 2 % 128 == 0 || !gather_parts_cost(p));
       // the first workgroups of the grid, as many as surely run at once, own the pieces
       pl->copy_wgs = 0;
       // pieces of 16 KiB or more, as many as the claim table allows
@@ -1257,8 +1267,8 @@ int flux_ag_gemm(const flux_problem_t* p, const void* const* A_chunks, void* A_a
   const bool local_in_grid = local_away && pl.copy_self && pl.pace_ticks == 0 && p->R > 1 && !(all_cut && chunk_elems * 2 > (6u << 20)) &&
                              !overlap(A_chunks[p->rank], chunk_elems * 2, A_agg, agg_bytes) &&
                              !overlap(A_chunks[p->rank], chunk_elems * 2, C, c_bytes);
-  // A from the chunk sources: if none lies in what the grid writes while it reads
-  bool from_chunks = pl.from_chunks;
+  // A from the chunk sources: if none lies in what the grid writes while it reads (and the gathered rows' base, too, is a line's)
+  bool from_chunks = pl.from_chunks && (reinterpret_cast<uintptr_t>(A_agg) % 128 == 0 || !gather_parts_cost(p));
   for (int r = 0; r < p->R && from_chunks; ++r)
     if (r != p->rank || local_away)
       from_chunks = !overlap(A_chunks[r], chunk_elems * 2, A_agg, agg_bytes) && !overlap(A_chunks[r], chunk_elems * 2, C, c_bytes);

@@ -106,6 +106,36 @@ def test_up_front_into_rows_that_are_not_line_aligned(ctpc):
     gh.assert_bits_equal(A_agg, np.concatenate([fi.to_numpy(c) for c in chunks]), "A_agg")
 
 
+@pytest.mark.parametrize("K,pitch,offset,N,waits", [
+    (4104, 0, 0, 2048, True), (4104, 56, 0, 2048, False),                        # rows in parts of lines, a pitch of whole lines
+    (4160, 0, 0, 2048, False), (4160, 8, 0, 2048, True), (4160, 0, 8, 2048, True),      # whole lines, a pitch of none, a base inside one
+    (4104, 0, 0, 3592, False), (4088, 0, 0, 2048, False),                        # enough columns to hide it; below 32 MB
+])
+def test_large_gathered_matrix_of_partial_lines(K, pitch, offset, N, waits):
+    w, rank = _ints(4096, N, K, 8), 5
+    chunks, B, arrival = fi.make_ag_inputs(w, rank)
+    dchunks, dB = [c.to(gh.DEV) for c in chunks], B.to(gh.DEV)
+    gathered = torch.cat(dchunks)
+    want = (gathered.float() @ dB.float()).to(torch.bfloat16)
+    p = fb.problem(w.M, N, K, w.R, rank, tile_config=2, lda=K + pitch if pitch else 0, spin_timeout_ticks=gh.TEST_TIMEOUT_TICKS)
+    store = torch.full((w.M * (K + pitch) + offset,), float("nan"), dtype=torch.bfloat16, device=gh.DEV)
+    A_agg = store[offset:].view(w.M, K + pitch)[:, :K]
+    C = torch.full((w.M, N), float("nan"), dtype=torch.bfloat16, device=gh.DEV)
+    signals = torch.zeros(w.R, dtype=torch.int32, device=gh.DEV)
+    ws = gh.workspace_for(fb.FLUX_OP_AG, p)
+    fb.flux_init_buffers(fb.FLUX_OP_AG, p, ws, signals)
+    for _ in range(2):
+        store.fill_(float("nan"))
+        C.fill_(float("nan"))
+        _say("partial lines", (w.M, N, K), "pitch", pitch, "offset", offset)
+        trace = _trace(p)
+        fb.flux_ag_gemm(p, dchunks, A_agg, dB, C, signals, arrival, ws, torch.cuda.current_stream(), torch.cuda.Stream())
+        torch.cuda.synchronize()
+        assert fb.flux_query_status(ws) == (fb.FLUX_OK, 0)
+        assert _waited(trace) == waits
+        assert torch.equal(C, want) and torch.equal(A_agg, gathered)
+
+
 def test_a_source_in_its_own_rows():
     """Eighteen columns of tiles, but a chunk lies in its own rows of the gathered matrix: A is gathered first, the later chunks travel inside the
     main loops, that one onto itself."""
