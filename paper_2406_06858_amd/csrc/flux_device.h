@@ -1480,8 +1480,10 @@ struct SharedFinish {
 // a tile park their partial sums, the last one adds them up) and the epilogue, in which the
 // accumulators pass through LDS once (per wave, 32 rows at a time) so that every lane ends up
 // with 8 consecutive columns of one row.  `smem` must hold C::EP_BYTES and is free to reuse.
-// MAX_NP: most peers there can be; PARTIALS: their type, 0 bf16, 1 fp32, -1 either (a resident kernel is built for up to 4 ranks or for more, and a type: with the code of both in one kernel
-// 8192x12288x1536 of 8 ranks took 439 us instead of 422).
+// MAX_NP: most peers there can be; PARTIALS: their type, 0 bf16, 1 fp32, -1 either.  (A resident kernel is built for up to 4 ranks or for more, and a type:
+// with the code of both in one kernel 8192x12288x1536 of 8 ranks took 439 us instead of 422.  The other kernels of 256x256 tiles are built for a type, too, since
+// their lanes have other columns for each; us, one kernel / by type, 8 ranks, bf16, masked edges: 4000x8192x1536 162.2 / 156.3, 3000x8192x3584 232.2 / 225.0, 2000x12288x6144
+// 326.7 / 324.5; the other side: fp32 3000x8192x3584 316.9 / 319.3, tiles that divide 4096x8192x3584 the same.)
 template <class C, int EPI, bool EDGE, bool RESIDENT, int MAX_NP = FLUX_MAX_RANKS - 1, int PARTIALS = -1>
 __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem, int* lds_misc, void* const* lds_outs,
                                           f32x4 (&acc)[C::MI][C::NI], int tile, int split, bool is_split,
@@ -2209,7 +2211,7 @@ struct WarmA {
 };
 
 // EDGE: the tile does not divide M, N or K (see DmaLoader; the epilogue leaves rows and columns past the end out).
-template <class C, int EPI, int PRO, bool EDGE, bool B_ONCE>
+template <class C, int EPI, int PRO, bool EDGE, bool B_ONCE, int PARTIALS>
 __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs a) {
   constexpr bool WAIT = PRO == PRO_WAIT, CHUNKS = PRO == PRO_CHUNKS;
   // the transfer inside the main loop (SideCopy) is asked of the kernel with two slabs of B and one workgroup per unit
@@ -2364,7 +2366,7 @@ __global__ void __launch_bounds__(C::NT, C::OCC) gemm_kernel_dma(const GemmArgs 
     fill_lds_outs(a, tail_words->outs, tid);
     __syncthreads();
   }
-  gemm_tail<C, EPI, EDGE, false>(a, pool, tail_words->misc, tail_words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, added, early, n_early);
+  gemm_tail<C, EPI, EDGE, false, FLUX_MAX_RANKS - 1, PARTIALS>(a, pool, tail_words->misc, tail_words->outs, acc, tile, split, is_split, m0, n0, tid, lane, wave, wm, wn, added, early, n_early);
 }
 
 // The same kernel for reduce-scatter calls as a grid of resident workgroups, one per compute unit, each walking the block

@@ -32,10 +32,10 @@ typedef TileCfg<FLUX_CFG_PARAMS, FLUX_B_NK> Cfg;     // B as [K,N] / [N,K]
 // Tiles that few rows over large weights take have a second set of kernels, which stream B.
 constexpr bool MAYBE_ONCE = FLUX_CFG_ID == 2 || FLUX_CFG_ID == 7 || FLUX_CFG_ID == 8 || FLUX_CFG_ID == 9;
 
-template <int EPI, int PRO, bool B_ONCE>
+template <int EPI, int PRO, bool B_ONCE, int PARTIALS>
 static hipError_t launch_two(int edge, const GemmArgs& a, int grid, hipStream_t s) {
-  if (edge) hipLaunchKernelGGL((gemm_kernel_dma<Cfg, EPI, PRO, true, B_ONCE>), dim3(grid), dim3(Cfg::NT), 0, s, a);
-  else hipLaunchKernelGGL((gemm_kernel_dma<Cfg, EPI, PRO, false, B_ONCE>), dim3(grid), dim3(Cfg::NT), 0, s, a);
+  if (edge) hipLaunchKernelGGL((gemm_kernel_dma<Cfg, EPI, PRO, true, B_ONCE, PARTIALS>), dim3(grid), dim3(Cfg::NT), 0, s, a);
+  else hipLaunchKernelGGL((gemm_kernel_dma<Cfg, EPI, PRO, false, B_ONCE, PARTIALS>), dim3(grid), dim3(Cfg::NT), 0, s, a);
   return hipGetLastError();
 }
 
@@ -55,9 +55,13 @@ static hipError_t launch_one(int edge, int b_once, const GemmArgs& a, int grid, 
       return launch_resident<0>(a, grid, s);
     }
   }
-  if constexpr (MAYBE_ONCE && (EPI == EPI_RS || PRO == PRO_CHUNKS))
-    if (b_once) return launch_two<EPI, PRO, true>(edge, a, grid, s);
-  return launch_two<EPI, PRO, false>(edge, a, grid, s);
+  if constexpr (EPI == EPI_RS && Cfg::BM * Cfg::BN >= 256 * 256) {          // (see gemm_tail)
+    return a.partial_f32 ? launch_two<EPI, PRO, false, 1>(edge, a, grid, s) : launch_two<EPI, PRO, false, 0>(edge, a, grid, s);
+  } else {
+    if constexpr (MAYBE_ONCE && (EPI == EPI_RS || PRO == PRO_CHUNKS))
+      if (b_once) return launch_two<EPI, PRO, true, -1>(edge, a, grid, s);
+    return launch_two<EPI, PRO, false, -1>(edge, a, grid, s);
+  }
 }
 
 #define FLUX_CAT2(a, b, c, d) a##b##c##d
