@@ -808,7 +808,7 @@ static int launch_gemm(const Plan& pl, int epi, int pro, GemmArgs& a, hipStream_
   // B is streamed (a non-temporal load) where the tiles of a column read it at about the same time through one L2: one row of tiles, or two
   // whose columns go to the same die (TileCoord deals runs of a band to the dies).  us per pass, kept / streamed, one row: 4 layers of ag
   // 8x3584x8192 69.6 / 66.0, ag 200x3584x8192 116.1 / 112.9, rs 64x8192x3584 81.7 / 78.8, 2 layers of rs 256x12288x6144 144.3 / 140.6; two:
-  // 4 layers of rs 128x8192x3584 107.0 / 100.6, rs 400x8192x8192 85.5 / 80.5, ag 512x6144x12288 96.6 / 91.2, rs 512x12288x6144 97.0 / 95.3, rs
+  // 4 layers of rs 128x8192x3584 107.0 / 100.6, ag 512x6144x12288 96.6 / 91.2, rs 512x12288x6144 97.0 / 95.3, rs
   // 512x8192x3584 53.7 / 53.9; the other side, two rows on different dies: 4 layers of ag 128x3584x8192 115.0 / 125.5, more rows: rs
   // 512x3584x1536 16.6 / 21.9, 4 layers of rs 200x8192x3584 (64x128 tiles) 118.8 / 142.5, rs 2048x4608x1536 57.9 / 64.2.
   // Of two rows of tiles, the second at least seven eighths full: with fewer rows it runs ahead, and the first finds the lines gone.  2 layers, 8 ranks, in turn
