@@ -450,7 +450,7 @@ __device__ __forceinline__ void make_peer_bufs(const GemmArgs& a, int m0, int n0
 // chain of memory round trips, and this one does not depend on the products.  NP peers (1, 3 or 7; absent ones read nothing, but cost
 // an issue slot each; not streamed: half a line each, us, streamed / kept, 8 ranks 512x1024x256 9.0 / 7.6, 32x8192x384 9.4 / 7.9), where they fit ROOM
 // vectors (with 14 instead of 6, and kept through a hand-over, the kernels of two workgroups per unit spilled: 5.9 us -> 6.6).
-// us per call, peers behind the main loop / ahead of it: fp32, 2 ranks: 128x256x256 5.92 / 5.09 (5.1 to 5.8 on other boxes, 4 to 10 % gained), 64x512x512 8.21 / 6.69, 512x1024x256 9.00 /
+// us per call, peers behind the main loop / ahead of it: fp32, 2 ranks: 128x256x256 5.92 / 5.09 (5.1 to 5.8 on other machines, 4 to 10 % gained), 64x512x512 8.21 / 6.69, 512x1024x256 9.00 /
 // 6.85; bf16: 2 ranks 2048x2048x1024 18.7 / 16.3, 4 ranks 512x3584x1536 14.7 / 13.7, 8 ranks 2048x1024x512 13.5 / 13.0; the other side:
 // 64x512x512 7.8 / 8.0, 2048x1024x2048 20.5 / 20.8.
 template <class C>
@@ -1483,7 +1483,8 @@ struct SharedFinish {
 // MAX_NP: most peers there can be; PARTIALS: their type, 0 bf16, 1 fp32, -1 either.  (A resident kernel is built for up to 4 ranks or for more, and a type:
 // with the code of both in one kernel 8192x12288x1536 of 8 ranks took 439 us instead of 422.  The other kernels of 256x256 tiles are built for a type, too, since
 // their lanes have other columns for each; us, one kernel / by type, 8 ranks, bf16, masked edges: 4000x8192x1536 162.2 / 156.3, 3000x8192x3584 232.2 / 225.0, 2000x12288x6144
-// 326.7 / 324.5; the other side: fp32 3000x8192x3584 316.9 / 319.3, tiles that divide 4096x8192x3584 the same.)
+// 326.7 / 324.5; the other side: fp32 3000x8192x3584 316.9 / 319.3, tiles that divide 4096x8192x3584 the same; not 256x128 and 128x128 tiles: 760x8192x1000
+// 35.3 / 38.2, 1104x4608x272 28.7 / 31.0, 552x4608x272 16.7 / 16.4.)
 template <class C, int EPI, bool EDGE, bool RESIDENT, int MAX_NP = FLUX_MAX_RANKS - 1, int PARTIALS = -1>
 __device__ __forceinline__ void gemm_tail(const GemmArgs& a, unsigned char* smem, int* lds_misc, void* const* lds_outs,
                                           f32x4 (&acc)[C::MI][C::NI], int tile, int split, bool is_split,
